@@ -202,6 +202,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* 
     lds_barrier();
     compute(I0{}, std::false_type{}, I0{});
   }
+  if (lead == total_steps) lds_barrier();  // fewer steps than a trip: the caller is about to reuse the LDS
   if (lead < total_steps) {
     // local step t = step - lead uses register stage t % DIST and LDS buffer t & 1
     [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {

@@ -7,14 +7,13 @@
 // device-scope release fence in every workgroup; on this GPU that is an L2 write-back per workgroup
 // and costs far more than the launch of a second kernel.)
 //
-// Three producers of the 128 x columns logit block exist:
+// Two producers of the 128 x columns logit block exist:
 //   * lmhead_bf16_mfma_kernel  - bf16 operands, v_mfma_f32_16x16x32_bf16, HBM-streaming design: a wavefront
 //                                streams 16 rows, the hidden states of all columns sit in LDS (up to 11
 //                                columns at D = 4096)
-//   * lmhead_bf16_tile_kernel  - bf16, more columns than that: the 128 x 64 tile loop of gemm_tile.h, both
-//                                operands stepping through LDS
-//   * lmhead_generic_kernel    - any dtype/shape within the limits, plain fp32 FMA
-// All hand the block over in LDS to the same epilogue.
+//   * lmhead_tile_kernel       - everything else (more columns, other hidden sizes, float operands): the tile
+//                                loop of gemm_tile.h, both operands stepping through LDS
+// Both hand the block over in LDS to the same epilogue.
 #include <mutex>
 #include <type_traits>
 #include <utility>
@@ -178,31 +177,6 @@ __global__ __launch_bounds__(64) void lmhead_merge_kernel(LmHeadParams p) {
   }
 }
 
-// ---- generic producer ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void lmhead_generic_kernel(LmHeadParams p) {
-  __shared__ float zbuf[kMaxCols * kZStride];
-  const int tid = threadIdx.x;
-  const int row_base = blockIdx.x * kRowsPerBlock;
-  const T* hidden = (const T*)p.hidden;
-  const T* w = (const T*)p.w;
-  for (int idx = tid; idx < p.BT * kRowsPerBlock; idx += 256) {
-    int m = idx / kRowsPerBlock, r = idx % kRowsPerBlock;
-    int row = row_base + r;
-    float z = -INFINITY;
-    if (row < p.Vp1) {
-      const T* hp = hidden + (size_t)m * p.D;
-      const T* wp = w + (size_t)row * p.D;
-      float acc = 0.f;
-      for (int d = 0; d < p.D; ++d) acc = fmaf(load_as_float(hp + d), load_as_float(wp + d), acc);
-      z = acc + (p.bias ? p.bias[row] : 0.f);
-    }
-    zbuf[m * kZStride + r] = z;
-  }
-  __syncthreads();
-  lmhead_block_epilogue(p, zbuf);
-}
-
 // ---- bf16 MFMA streaming producer -----------------------------------------------------------------
 // 8 waves; wave w owns the 16 rows [block*128 + 16w, +16) over the whole hidden dimension.
 // Per step of 256 hidden elements a wave issues 8 coalesced 16-byte loads (each instruction covers
@@ -352,50 +326,72 @@ __global__ __launch_bounds__(64 * kMfmaWaves) void lmhead_bf16_mfma_kernel(LmHea
   lmhead_block_epilogue(p, zbuf);
 }
 
-// ---- bf16 MFMA producer for many columns (more than fit in LDS over the whole hidden dimension) -----------------
-// The 128 x 64 tile loop shared with the base-model head: both operands staged through LDS step by step, the
-// weights still read exactly once.  Then the same block epilogue as the other producers.
+// ---- tile producer: any hidden size and type --------------------------------------------------------------------
+// The tile loop shared with the base-model head, 128 rows x 16, 32 or 64 columns: both operands staged through LDS
+// step by step, the weights still read exactly once.  Then the same block epilogue as the other producer.
 constexpr int kLmTileDist = 4;
-template <int CT>
-__global__ __launch_bounds__(64 * kTileWaves) void lmhead_bf16_tile_kernel(LmHeadParams p) {
+template <typename SH, typename EL, bool ROWS16>
+__global__ __launch_bounds__(64 * kTileWaves) void lmhead_tile_kernel(LmHeadParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  static_assert(SH::CTW == 1 && SH::ROWS == kRowsPerBlock, "one column tile per wavefront");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wr = wave >> 2, wc = wave & 3;
+  const int wr = wave / SH::WC, wc = wave % SH::WC;
   const int c = lane & 15, g = lane >> 4;
   const int row_base = blockIdx.x * kRowsPerBlock;
   GemmTileArgs t;
   t.w = p.w; t.hidden = p.hidden; t.zeros = p.zeros; t.D = p.D; t.V = p.Vp1; t.cols = p.BT; t.row_base = row_base;
-  f32x4 acc[4][CT];
-  static_assert(CT == 1, "the 128 x 64 tile");
-  gemm_tile<kLmTileDist, Tile128x64>(t, smem, acc);
+  f32x4 acc[SH::RT][1];
+  gemm_tile<kLmTileDist, SH, EL, ROWS16>(t, smem, acc);
   // (the loop's last barrier has every wavefront done with the LDS tiles)
   float* zbuf = (float*)smem;
+  const int col = wc * 16 + c;
+  if (col < p.BT) {
 #pragma unroll
-  for (int rt = 0; rt < 4; ++rt)
+    for (int rt = 0; rt < SH::RT; ++rt) {
+      f32x4 z;
+      const int r0 = (wr * SH::RT + rt) * 16 + g * 4;
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      const int col = wc * 16 * CT + ct * 16 + c;
-      if (col < p.BT) {
-        f32x4 z;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = row_base + wr * 64 + rt * 16 + g * 4 + i;
-          z[i] = row < p.Vp1 ? acc[rt][ct][i] + (p.bias ? p.bias[row] : 0.f) : -INFINITY;
-        }
-        *(f32x4*)(zbuf + col * kZStride + wr * 64 + rt * 16 + g * 4) = z;
+      for (int i = 0; i < 4; ++i) {
+        const int row = row_base + r0 + i;
+        z[i] = row < p.Vp1 ? acc[rt][0][i] + (p.bias ? p.bias[row] : 0.f) : -INFINITY;
       }
+      *(f32x4*)(zbuf + col * kZStride + r0) = z;
     }
+  }
   __syncthreads();
-  unsigned char* part = smem + kMaxCols * kZStride * 4;
-  if (p.BT <= 16) lmhead_block_epilogue(p, zbuf);  // a wavefront per column, at most two in turn
-  else if (p.k <= 1) lmhead_block_epilogue_wide<1>(p, zbuf, part);
-  else if (p.k <= 2) lmhead_block_epilogue_wide<2>(p, zbuf, part);
-  else if (p.k <= 4) lmhead_block_epilogue_wide<4>(p, zbuf, part);
-  else lmhead_block_epilogue_wide<8>(p, zbuf, part);
+  if constexpr (SH::COLS <= 16) {
+    lmhead_block_epilogue(p, zbuf);  // a wavefront per column, at most two in turn
+  } else {
+    unsigned char* part = smem + kMaxCols * kZStride * 4;
+    if (p.k <= 1) lmhead_block_epilogue_wide<1>(p, zbuf, part);
+    else if (p.k <= 2) lmhead_block_epilogue_wide<2>(p, zbuf, part);
+    else if (p.k <= 4) lmhead_block_epilogue_wide<4>(p, zbuf, part);
+    else lmhead_block_epilogue_wide<8>(p, zbuf, part);
+  }
 }
-static_assert(kMaxCols <= 64 && kMaxCols * kZStride * 4 + kMfmaWaves * kMaxCols * (8 + 8 * kMaxTopk) <= Tile128x64::LDS_BYTES,
-              "one 64-column tile holds every column and the epilogue's partials");
+constexpr int kLmEpilogueBytes = kMaxCols * kZStride * 4 + kMfmaWaves * kMaxCols * (8 + 8 * kMaxTopk);
+static_assert(kMaxCols <= 64 && kLmEpilogueBytes <= Tile128x64::LDS_BYTES && kLmEpilogueBytes <= Tile128x32::LDS_BYTES &&
+                  16 * kZStride * 4 <= Tile128x16::LDS_BYTES,
+              "one tile holds every column and the epilogue's partials");
+
+template <typename SH, typename EL, bool ROWS16>
+static hipError_t launch_tile_shape(const LmHeadParams& p, hipStream_t stream) {
+  hipLaunchKernelGGL((lmhead_tile_kernel<SH, EL, ROWS16>), dim3(p.n_blocks), dim3(64 * kTileWaves), SH::LDS_BYTES, stream, p);
+  return hipGetLastError();
+}
+template <typename EL, bool ROWS16>
+static hipError_t launch_tile_rows(const LmHeadParams& p, hipStream_t stream) {
+  // the narrowest tile that holds the columns: a wavefront without live columns would contract for nothing, which
+  // float operands (a sixteenth of the bf16 matrix rate) cannot afford
+  if (p.BT <= 16) return launch_tile_shape<Tile128x16, EL, ROWS16>(p, stream);
+  if (p.BT <= 32) return launch_tile_shape<Tile128x32, EL, ROWS16>(p, stream);
+  return launch_tile_shape<Tile128x64, EL, ROWS16>(p, stream);
+}
+template <typename EL>
+static hipError_t launch_tile(const LmHeadParams& p, hipStream_t stream) {
+  return tile_rows16(p.D, EL::ELEM) ? launch_tile_rows<EL, true>(p, stream) : launch_tile_rows<EL, false>(p, stream);
+}
 
 static void launch_merge(const LmHeadParams& p, hipStream_t stream) {
   if (p.k <= 1) hipLaunchKernelGGL(lmhead_merge_kernel<1>, dim3(p.BT), dim3(64), 0, stream, p);
@@ -447,6 +443,19 @@ static hipError_t allow_mfma_lds() {
                              hipFuncAttributeMaxDynamicSharedMemorySize, kMfmaLdsLimit);
 }
 
+template <typename EL, bool ROWS16>
+static hipError_t allow_tile_lds() {
+  hipError_t e = hipFuncSetAttribute((const void*)lmhead_tile_kernel<Tile128x16, EL, ROWS16>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, Tile128x16::LDS_BYTES);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void*)lmhead_tile_kernel<Tile128x32, EL, ROWS16>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, Tile128x32::LDS_BYTES);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void*)lmhead_tile_kernel<Tile128x64, EL, ROWS16>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, Tile128x64::LDS_BYTES);
+  return e;
+}
+
 // dynamic LDS limits of this file's kernels, on the current device
 static hipError_t allow_large_lds() {
   hipError_t e = allow_mfma_lds<1, 4>();
@@ -457,9 +466,10 @@ static hipError_t allow_large_lds() {
   if (e == hipSuccess) e = allow_mfma_lds<2, 2>();
   if (e == hipSuccess) e = allow_mfma_lds<3, 2>();
   if (e == hipSuccess) e = allow_mfma_lds<4, 2>();
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)lmhead_bf16_tile_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            Tile128x64::LDS_BYTES);
+  if (e == hipSuccess) e = allow_tile_lds<TileBf16, true>();
+  if (e == hipSuccess) e = allow_tile_lds<TileBf16, false>();
+  if (e == hipSuccess) e = allow_tile_lds<TileF32, true>();
+  if (e == hipSuccess) e = allow_tile_lds<TileF32, false>();
   return e;
 }
 
@@ -588,23 +598,14 @@ static int draft_topk_launch(ctcspec_ctx* err, hipStream_t stream, const LmScrat
       if (timing && timed) *timed = 1;
       return finish();
     }
-    if (D % kTileStepK == 0 && p.BT <= 64 && (long long)Vp1 * D * 2 < (1LL << 32)) {
-      // more columns than that: both operands step through LDS
-      if (timing) CTCSPEC_HIP(err, hipEventRecord(ev0, stream));
-      hipLaunchKernelGGL(lmhead_bf16_tile_kernel<1>, dim3(p.n_blocks), dim3(64 * kTileWaves), Tile128x64::LDS_BYTES,
-                         stream, p);
-      CTCSPEC_HIP(err, hipGetLastError());
-      if (timing) {
-        CTCSPEC_HIP(err, hipEventRecord(ev1, stream));
-        if (timed) *timed = 1;
-      }
-      return finish();
-    }
-    hipLaunchKernelGGL(lmhead_generic_kernel<unsigned short>, dim3(p.n_blocks), dim3(256), 0, stream, p);
-  } else {
-    hipLaunchKernelGGL(lmhead_generic_kernel<float>, dim3(p.n_blocks), dim3(256), 0, stream, p);
   }
-  CTCSPEC_HIP(err, hipGetLastError());
+  // every other shape: both operands step through LDS
+  if (timing) CTCSPEC_HIP(err, hipEventRecord(ev0, stream));
+  CTCSPEC_HIP(err, dt == CTCSPEC_BF16 ? launch_tile<TileBf16>(p, stream) : launch_tile<TileF32>(p, stream));
+  if (timing) {
+    CTCSPEC_HIP(err, hipEventRecord(ev1, stream));
+    if (timed) *timed = 1;
+  }
   return finish();
 }
 

@@ -1,21 +1,25 @@
-// A tile of a [V, D] x [cols, D]^T product, bf16 operands, fp32 accumulators: the main loop shared by the
-// base-model head (verify_head_argmax) and the draft head with many columns.
+// A tile of a [V, D] x [cols, D]^T product, bf16 or float operands, fp32 accumulators: the main loop shared by the
+// base-model head (verify_head_argmax) and the draft head.
 //
-// 8 wavefronts in a WR x WC grid (WR * WC = 8): wavefront (wr, wc) owns weight rows [64 wr, +64) x columns
-// [16 CTW wc, +16 CTW) - 4 x CTW MFMA tiles.  Shapes in use (rows x columns, step): 128 x 64 and 128 x 128 with steps
-// of 128 hidden elements (2 x 4 wavefronts, 64 x 16 or 64 x 32 per wavefront), and 256 x 128 with steps of 64
-// (4 x 2 wavefronts, 64 x 64 per wavefront) for products with several column blocks: per flop it reads two thirds
-// of the fragments from LDS and fetches half of the hidden-state tiles from L2.
+// 8 wavefronts in a WR x WC grid (WR * WC = 8): wavefront (wr, wc) owns weight rows [16 RT wr, +16 RT) x columns
+// [16 CTW wc, +16 CTW) - RT x CTW MFMA tiles.  Shapes in use (rows x columns, bytes of a row per step): 128 x 16,
+// x 32, x 64 and x 128 with steps of 256 bytes, and 256 x 128 with steps of 128 (4 x 2 wavefronts, 64 x 64 per
+// wavefront) for products with several column blocks: per flop it reads two thirds of the fragments from LDS and
+// fetches half of the hidden-state tiles from L2.
 // Per step both operands go through LDS: the W tile (nontemporal, the A operand) and the hidden states of the step
 // (the B operand) are fetched by all threads together with coalesced 16-byte loads, DIST steps ahead, into
 // rotating register stages (the VGPR file, 512 KB per compute unit, is the deep staging buffer), and written to
 // one of two LDS buffers while the other one is computed from: one barrier per step.  Within a step the fragment
-// reads of the next 32 k and the tile writes are issued in front of the MFMAs of the current 32 k and run under them.
+// reads of the next k-block and the tile writes are issued in front of the MFMAs of the current one and run under them.
 // What bounds it (measured, one compute unit): b128 fragment reads at 128 B per clock, b128 writes at 79 B per
 // clock - at 128 x 128, per step 192 KB read + 64 KB written = 2300 clocks against 1024 clocks of MFMA and 1.35 us
 // (3200 clocks) for the 32 KB of W at the HBM rate, so the LDS work fits under the stream only if nothing
 // serialises.  All loads are unconditional and counted (indices clamped; a request past the last step reads a
 // block of zeros), so the waits name the loads that stay in flight.
+// Hidden sizes that are no whole number of steps: what is left of every row goes first, unpipelined, padded with
+// zeros.  Rows that start at any element take the same loads at that alignment.  (One thread per logit with a dot
+// product over uncoalesced rows, which these shapes and float operands took before: 16 float columns x 32001 x 2048
+// in 2.12 ms against 53 us = 4.9 TB/s here, bound by HBM; 128 columns x 100 x 64 in 542 against 7 us.)
 #pragma once
 
 #include <type_traits>
@@ -26,62 +30,91 @@
 namespace ctcspec {
 
 constexpr int kTileWaves = 8;
-constexpr int kTileStepK = 128;  // hidden elements per step of the 128-row shapes
 
-template <int WR_, int CTW_, int STEPK_>
+template <int WR_, int CTW_, int STEPB_, int RT_ = 4>
 struct TileShape {
   static constexpr int WR = WR_, WC = kTileWaves / WR_;  // wavefront grid
-  static constexpr int CTW = CTW_;                       // 16-column MFMA tiles per wavefront
-  static constexpr int STEPK = STEPK_;                   // hidden elements per step
-  static constexpr int ROWS = 64 * WR, COLS = 16 * CTW * WC;
-  static constexpr int CPR = STEPK * 2 / 16;             // 16-byte chunks per staged row
+  static constexpr int CTW = CTW_, RT = RT_;             // 16-column and 16-row MFMA tiles per wavefront
+  static constexpr int STEPB = STEPB_;                   // bytes of a row per step
+  static constexpr int ROWS = 16 * RT * WR, COLS = 16 * CTW * WC;
+  static constexpr int CPR = STEPB / 16;                 // 16-byte chunks per staged row
   // bytes per staged row: the step's elements + 32.  A 16-byte LDS access of a wavefront is served 16 lanes per
   // clock, lanes {l .. l+7} together with {l+16 .. l+23} (what the conflict counter shows: a fragment read - lane =
   // row c, chunk g - is conflict-free when rows c .. c+7 at chunks g and g+1 fall on 16 different groups of 4
   // banks, i.e. when the pitch is 32 mod 64 bytes; at 128 + 16 bytes every read took one extra clock in four)
-  static constexpr int PITCH = STEPK * 2 + 32;
+  static constexpr int PITCH = STEPB + 32;
   static constexpr int RPP = 64 * kTileWaves / CPR;      // rows that one 16-byte piece per thread covers
-  static constexpr int WP = ROWS / RPP, HP = COLS / RPP;  // pieces per thread: W tile, hidden-state tile
-  static constexpr int KK = STEPK / 32;                  // MFMA k-blocks per step
-  static constexpr int HS_BYTES = COLS * PITCH, BUF_BYTES = (COLS + ROWS) * PITCH;
+  static constexpr int WP = ROWS / RPP, HP = (COLS + RPP - 1) / RPP;  // pieces per thread: W tile, hidden-state tile
+  static constexpr int KK = STEPB / 64;                  // k-blocks of 64 bytes per step
+  static constexpr int HS_BYTES = HP * RPP * PITCH, BUF_BYTES = HS_BYTES + ROWS * PITCH;
   static constexpr int LDS_BYTES = 2 * BUF_BYTES;
-  static_assert(WR * WC == kTileWaves && ROWS % RPP == 0 && COLS % RPP == 0 && WP % KK == 0, "tile shape");
+  static_assert(WR * WC == kTileWaves && ROWS % RPP == 0 && WP % KK == 0, "tile shape");
 };
-using Tile128x64 = TileShape<2, 1, 128>;
-using Tile128x128 = TileShape<2, 2, 128>;
-using Tile256x128 = TileShape<4, 4, 64>;
+using Tile128x16 = TileShape<8, 1, 256, 1>;
+using Tile128x32 = TileShape<4, 1, 256, 2>;
+using Tile128x64 = TileShape<2, 1, 256>;
+using Tile128x128 = TileShape<2, 2, 256>;
+using Tile256x128 = TileShape<4, 4, 128>;
+
+// One 64-byte k-block of a 16 x 16 tile: the operands' 16-byte fragments hold row (or column) lane & 15, chunk
+// lane >> 4.  bf16: 32 k in one instruction.  float: 16 k in four, instruction i contracting elements i of the four
+// chunks - both operands are cut the same way, so the order of k inside the block does not matter.
+struct TileBf16 {
+  static constexpr int ELEM = 2;
+  static __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  }
+};
+struct TileF32 {
+  static constexpr int ELEM = 4;
+  static __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c) {
+    const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[i], c, 0, 0, 0);
+    return c;
+  }
+};
 
 struct GemmTileArgs {
-  const void* w;       // [V][D] bf16
-  const void* hidden;  // [cols][D] bf16, first column of the tile
+  const void* w;       // [V][D]
+  const void* hidden;  // [cols][D], first column of the tile
   const void* zeros;   // 256 bytes of zeros
-  int D, V;            // D a multiple of the shape's step; both matrices smaller than 4 GB (32-bit byte offsets)
+  int D, V;
   int cols;            // live columns, 1 .. COLS
   int row_base;        // first weight row of the tile
 };
 
 typedef __attribute__((address_space(1))) u32x4 GlobalU32x4;  // a pointer made from an integer is generic otherwise
 
-// acc[rt][ct][i]: row row_base + 64 wr + 16 rt + 4 (lane >> 4) + i, column 16 CTW wc + 16 ct + (lane & 15),
+// How rows are read.  ROWS16: rows start at multiples of 16 bytes (the row size is one) and the rows of a tile lie
+// within 4 GB of the first, so a thread's place is a 32-bit offset.  Otherwise rows start at any element: the same
+// 16-byte loads, declared with the element's alignment, and 64-bit offsets.
+inline bool tile_rows16(int D, int elem) { return ((long long)D * elem) % 16 == 0 && (long long)D * elem * 256 < (1LL << 32); }
+
+// acc[rt][ct][i]: row row_base + 16 (RT wr + rt) + 4 (lane >> 4) + i, column 16 CTW wc + 16 ct + (lane & 15),
 // wr = wave / WC, wc = wave % WC.
 // Every wavefront of the workgroup (8) must call it; it ends with a barrier after the last read of LDS.
-template <int DIST, typename SH>
-__device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* smem, f32x4 (&acc)[4][SH::CTW]) {
-  constexpr int CTW = SH::CTW, STEPK = SH::STEPK, PITCH = SH::PITCH, CPR = SH::CPR, RPP = SH::RPP;
+template <int DIST, typename SH, typename EL, bool ROWS16>
+__device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* smem, f32x4 (&acc)[SH::RT][SH::CTW]) {
+  constexpr int CTW = SH::CTW, RT = SH::RT, STEPB = SH::STEPB, PITCH = SH::PITCH, CPR = SH::CPR, RPP = SH::RPP;
   constexpr int WP = SH::WP, HP = SH::HP, KK = SH::KK;
-  constexpr int WPK = WP / KK, HPK = (HP + KK - 1) / KK;  // pieces written to LDS per 32 k of the step before
+  constexpr int WPK = WP / KK, HPK = (HP + KK - 1) / KK;  // pieces written to LDS per k-block of the step before
   constexpr int HS_BYTES = SH::HS_BYTES, BUF_BYTES = SH::BUF_BYTES;
+  using Offset = std::conditional_t<ROWS16, unsigned int, size_t>;
+  struct Packed16 { u32x4 v; } __attribute__((packed, aligned(EL::ELEM)));  // 16 bytes at an element's alignment
+  typedef __attribute__((address_space(1))) Packed16 GlobalPacked16;
   constexpr int TRIP = DIST % 2 == 0 ? DIST : 2 * DIST;    // steps per loop trip: stage and buffer static
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave / SH::WC, wc = wave % SH::WC;
   const int c = lane & 15, g = lane >> 4;
   const int row_base = t.row_base;
-  const int total_steps = t.D / STEPK;
+  const size_t row_bytes = (size_t)t.D * EL::ELEM;
+  const int total_steps = (int)(row_bytes / STEPB);
   // LDS: buffer b = hidden-state tile (COLS rows) then W tile (ROWS rows)
 
-  // piece u of a thread: tile row prow + RPP u, 16-byte chunk pchunk; byte offsets in 32 bits (the host checks
-  // that the matrices are smaller than 4 GB).  A wavefront covers whole rows (4 of 256 bytes or 8 of 128), and
+  // piece u of a thread: tile row prow + RPP u, 16-byte chunk pchunk, as a byte offset from the tile's first row.
+  // A wavefront covers whole rows (4 of 256 bytes or 8 of 128), and
   // the lanes are dealt so that the 16 lanes the LDS serves together write 256 bytes that cover every bank once:
   // both halves of one 256-byte row, or two 128-byte rows 4 apart (4 x 160 bytes = 32 banks further on).
   int prow, pchunk;
@@ -95,21 +128,20 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* 
     pchunk = lane & 7;
   }
   const unsigned int lane_off = pchunk * 16;
-  const uintptr_t w_addr = (uintptr_t)t.w, h_addr = (uintptr_t)t.hidden;
+  const uintptr_t w_addr = (uintptr_t)t.w + (size_t)row_base * row_bytes, h_addr = (uintptr_t)t.hidden;
   const uintptr_t z_addr = (uintptr_t)t.zeros;
-  unsigned int woff[WP], hoff[HP];
+  Offset woff[WP], hoff[HP];
   const int dst0 = prow * PITCH + pchunk * 16;
 #pragma unroll
   for (int u = 0; u < WP; ++u) {
-    int row = row_base + prow + RPP * u;
-    row = row < t.V ? row : t.V - 1;            // the ragged last block re-reads the last row
-    woff[u] = (unsigned int)row * (unsigned int)(t.D * 2);
+    const int r = prow + RPP * u, last = t.V - 1 - row_base;
+    woff[u] = (Offset)(r < last ? r : last) * (Offset)row_bytes;  // the ragged last block re-reads the last row
   }
 #pragma unroll
   for (int u = 0; u < HP; ++u) {
     const int r = prow + RPP * u;
     const int col = r < t.cols ? r : t.cols - 1;  // columns past the end repeat the last one (never read back)
-    hoff[u] = (unsigned int)col * (unsigned int)(t.D * 2);
+    hoff[u] = (Offset)col * (Offset)row_bytes;
   }
   // A request past the last step still issues its loads, so that every wait counts the same loads: it reads
   // a 256-byte block of zeros (in L2, no HBM traffic) and nothing computes from the result.
@@ -118,16 +150,50 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* 
     constexpr int S = decltype(stage)::value;
     // address arithmetic in integers: a select between pointers would become a branch around each load
     const bool valid = step < total_steps;
-    const unsigned int mask = valid ? ~0u : 0u;
-    const unsigned int st = ((unsigned int)step * (unsigned int)(2 * STEPK)) & mask;
+    const Offset mask = valid ? ~(Offset)0 : (Offset)0;
+    const Offset st = ((Offset)step * (Offset)STEPB) & mask;
     const uintptr_t hb = (valid ? h_addr : z_addr) + st, wb = (valid ? w_addr : z_addr) + st;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < HP; ++u) hreg[S][u] = *(const GlobalU32x4*)(hb + ((hoff[u] & mask) + lane_off));
+    for (int u = 0; u < HP; ++u) {
+      const uintptr_t a = hb + ((hoff[u] & mask) + lane_off);
+      if constexpr (ROWS16) hreg[S][u] = *(const GlobalU32x4*)a;
+      else hreg[S][u] = ((const GlobalPacked16*)a)->v;
+    }
 #pragma unroll
-    for (int u = 0; u < WP; ++u)
-      wreg[S][u] = __builtin_nontemporal_load((const GlobalU32x4*)(wb + ((woff[u] & mask) + lane_off)));
+    for (int u = 0; u < WP; ++u) {
+      const uintptr_t a = wb + ((woff[u] & mask) + lane_off);
+      if constexpr (ROWS16) wreg[S][u] = __builtin_nontemporal_load((const GlobalU32x4*)a);
+      else wreg[S][u] = ((const GlobalPacked16*)a)->v;
+    }
     __builtin_amdgcn_sched_barrier(0);
+  };
+  // the elements of a row behind its last whole step (tail_bytes of them), zeros behind those: every load reads an
+  // element of the row (indices clamped) and what lies past its end is replaced
+  const int tail_bytes = (int)(row_bytes - (size_t)total_steps * STEPB);
+  auto tail_piece = [&](uintptr_t row) __attribute__((always_inline)) -> u32x4 {
+    const uintptr_t start = row + (size_t)total_steps * STEPB;
+    if constexpr (ROWS16) {  // whole chunks
+      const u32x4 v = *(const GlobalU32x4*)(start + (pchunk * 16 < tail_bytes ? pchunk * 16 : 0));
+      return pchunk * 16 < tail_bytes ? v : u32x4{0u, 0u, 0u, 0u};
+    } else {
+      using E = std::conditional_t<EL::ELEM == 2, unsigned short, unsigned int>;
+      constexpr int PER = 4 / EL::ELEM;  // elements per word
+      typedef __attribute__((address_space(1))) E GlobalE;
+      u32x4 v;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        unsigned int word = 0u;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+          const int at = pchunk * 16 + q * 4 + e * EL::ELEM;
+          const unsigned int x = *(const GlobalE*)(start + (at < tail_bytes ? at : 0));
+          word |= at < tail_bytes ? x << (8 * EL::ELEM * e) : 0u;
+        }
+        v[q] = word;
+      }
+      return v;
+    }
   };
   auto commit = [&](auto stage, auto buffer) __attribute__((always_inline)) {
     constexpr int S = decltype(stage)::value, BUF = decltype(buffer)::value;
@@ -139,12 +205,12 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* 
     for (int u = 0; u < WP; ++u) *(u32x4*)(ws + (dst0 + u * RPP * PITCH)) = wreg[S][u];
   };
 #pragma unroll
-  for (int rt = 0; rt < 4; ++rt)
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int ct = 0; ct < CTW; ++ct) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int aoff = (wr * 64 + c) * PITCH + g * 16, boff = (wc * 16 * CTW + c) * PITCH + g * 16;
+  const int aoff = (wr * 16 * RT + c) * PITCH + g * 16, boff = (wc * 16 * CTW + c) * PITCH + g * 16;
   // compute one step from LDS buffer BUF; with COMMIT, also write stage S of the registers to the other buffer.
-  // Per 32 k: the next fragments' reads and that k-block's share of the tile writes are issued, then the MFMAs of
+  // Per k-block: the next fragments' reads and that k-block's share of the tile writes are issued, then the MFMAs of
   // the current fragments, under which those LDS operations run.
   auto compute = [&](auto buffer, auto with_commit, auto stage) __attribute__((always_inline)) {
     constexpr int BUF = decltype(buffer)::value, S = decltype(stage)::value;
@@ -153,14 +219,13 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* 
     const unsigned char* ws = hs + HS_BYTES;
     unsigned char* hs_next = smem + (1 - BUF) * BUF_BYTES;
     unsigned char* ws_next = hs_next + HS_BYTES;
-    bf16x8 a[2][4], b[2][CTW];
+    u32x4 a[2][RT], b[2][CTW];
     auto read_fragments = [&](int kk, int slot) __attribute__((always_inline)) {
 #pragma unroll
-      for (int rt = 0; rt < 4; ++rt)
-        a[slot][rt] = __builtin_bit_cast(bf16x8, *(const u32x4*)(ws + (aoff + rt * 16 * PITCH + kk * 64)));
+      for (int rt = 0; rt < RT; ++rt) a[slot][rt] = *(const u32x4*)(ws + (aoff + rt * 16 * PITCH + kk * 64));
 #pragma unroll
       for (int ct = 0; ct < CTW; ++ct)
-        b[slot][ct] = __builtin_bit_cast(bf16x8, *(const u32x4*)(hs + (boff + ct * 16 * PITCH + kk * 64)));
+        b[slot][ct] = *(const u32x4*)(hs + (boff + ct * 16 * PITCH + kk * 64));
     };
     __builtin_amdgcn_sched_barrier(0);
     read_fragments(0, 0);
@@ -182,10 +247,9 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* 
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int rt = 0; rt < 4; ++rt)
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int ct = 0; ct < CTW; ++ct)
-          acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kk & 1][rt], b[kk & 1][ct], acc[rt][ct], 0, 0, 0);
+        for (int ct = 0; ct < CTW; ++ct) acc[rt][ct] = EL::mma(a[kk & 1][rt], b[kk & 1][ct], acc[rt][ct]);
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -194,21 +258,34 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* 
   // The pipelined loop takes TRIP steps per trip with no exit in between (an exit inside the trip gives the
   // loop head a second, differently ordered set of loads in flight and the waits there fall back to draining
   // everything), so the total_steps % TRIP steps that do not fill a trip run first, unpipelined.
+  // So does what lies behind a row's last whole step.
   const int lead = total_steps % TRIP;
-  for (int i = 0; i < lead; ++i) {
-    request(i, I0{});
-    if (i > 0) lds_barrier();
+  bool used = false;  // LDS has been computed from
+  if (tail_bytes > 0) {
+#pragma unroll
+    for (int u = 0; u < HP; ++u) hreg[0][u] = tail_piece(h_addr + hoff[u]);
+#pragma unroll
+    for (int u = 0; u < WP; ++u) wreg[0][u] = tail_piece(w_addr + woff[u]);
     commit(I0{}, I0{});
     lds_barrier();
     compute(I0{}, std::false_type{}, I0{});
+    used = true;
   }
-  if (lead == total_steps) lds_barrier();  // fewer steps than a trip: the caller is about to reuse the LDS
+  for (int i = 0; i < lead; ++i) {
+    request(i, I0{});
+    if (used) lds_barrier();
+    commit(I0{}, I0{});
+    lds_barrier();
+    compute(I0{}, std::false_type{}, I0{});
+    used = true;
+  }
+  if (lead == total_steps) lds_barrier();  // no pipelined trip follows: the caller is about to reuse the LDS
   if (lead < total_steps) {
     // local step t = step - lead uses register stage t % DIST and LDS buffer t & 1
     [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {
       (request(lead + U, std::integral_constant<int, U>{}), ...);
     }(std::make_integer_sequence<int, DIST>{});
-    if (lead > 0) lds_barrier();
+    if (used) lds_barrier();
     commit(I0{}, I0{});
     request(lead + DIST, I0{});
     lds_barrier();

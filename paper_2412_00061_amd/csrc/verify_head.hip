@@ -3,11 +3,10 @@
 //
 // The head is the same stream over a [V, D] weight matrix as the draft head, but with up to 128 columns
 // (one per tree node) instead of 8, and all that is kept of a column is its best (logit, id) key:
-//   * verify_head_bf16_kernel    - bf16, D a multiple of 128: MFMA, 128 vocabulary rows x 128 columns per
+//   * verify_head_kernel         - the tile loop of gemm_tile.h: 128 vocabulary rows x 16 to 128 columns per
 //                                  workgroup (256 x 128 when there are several column blocks); all column blocks
 //                                  in one launch, those of a row block side by side on one XCD (the weights come
 //                                  from HBM once)
-//   * verify_head_generic_kernel - any dtype/shape: plain fp32 FMA, one atomic max per (row block, column)
 //   * verify_head_merge_kernel   - best key over the row blocks -> token id, -1 for rows without a node
 #include "gemm_tile.h"
 
@@ -16,12 +15,11 @@ namespace ctcspec {
 constexpr int kVhCols = kVerifyCols;            // columns (tree nodes) per pass over the weights
 constexpr int kVhWaves = kTileWaves;
 constexpr int kVhDist = 4;                      // prefetch distance in steps = register stages per operand
-constexpr int kVhStepK = kTileStepK;
 // dynamic LDS of a tile shape: the staging buffers, or the logit block (column-major, 4 floats of pad per column)
 // when the caller asks for logits - whichever is larger
 template <typename SH>
 constexpr int vh_lds_bytes() {
-  return SH::LDS_BYTES > kVhCols * (SH::ROWS + 4) * 4 ? SH::LDS_BYTES : kVhCols * (SH::ROWS + 4) * 4;
+  return SH::LDS_BYTES > SH::COLS * (SH::ROWS + 4) * 4 ? SH::LDS_BYTES : SH::COLS * (SH::ROWS + 4) * 4;
 }
 static_assert(kVhCols == 128 && Tile128x128::COLS == kVhCols && Tile256x128::COLS == kVhCols, "tile shape");
 static_assert(vh_lds_bytes<Tile256x128>() <= 160 * 1024, "fits the compute unit's LDS");
@@ -29,8 +27,7 @@ static_assert(vh_lds_bytes<Tile256x128>() <= 160 * 1024, "fits the compute unit'
 struct VerifyHeadParams {
   const void* hidden;   // [cols_total][D]
   const void* w;        // [V][D]
-  int col0, cols;       // generic kernels: columns of this launch (cols <= kVhCols), a whole column block
-  int cols_total;       // all columns of the call; the bf16 kernel covers them in one launch, block by block
+  int cols_total;       // all columns of the call, covered in one launch, block by block
   int col_blocks;       // ceil(cols_total / kVhCols)
   int D, V;
   int n_blocks;         // row blocks (of the tile shape's rows: 128 or 256)
@@ -42,10 +39,10 @@ struct VerifyHeadParams {
   int32_t* target;      // [cols_total]
 };
 
-// ---- bf16 MFMA kernel: the shared 128 x 128 tile loop, then the best (logit, id) key per column -----------------
-template <int DIST, typename SH>
-__global__ __launch_bounds__(64 * kVhWaves) void verify_head_bf16_kernel(VerifyHeadParams p) {
-  constexpr int ROWS = SH::ROWS, CTW = SH::CTW, WR = SH::WR;
+// ---- the shared tile loop, then the best (logit, id) key per column ----------------------------------------------
+template <typename SH, typename EL, bool ROWS16>
+__global__ __launch_bounds__(64 * kVhWaves) void verify_head_kernel(VerifyHeadParams p) {
+  constexpr int ROWS = SH::ROWS, CTW = SH::CTW, WR = SH::WR, RT = SH::RT;
   constexpr int ZSTRIDE = ROWS + 4;  // floats per column of the logit block
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int NTHREADS = 64 * kVhWaves;
@@ -65,10 +62,10 @@ __global__ __launch_bounds__(64 * kVhWaves) void verify_head_bf16_kernel(VerifyH
   const int cols = p.cols_total - col0 < kVhCols ? p.cols_total - col0 : kVhCols;
   const int row_base = rb * ROWS;
   GemmTileArgs t;
-  t.w = p.w; t.hidden = (const unsigned char*)p.hidden + (size_t)col0 * p.D * 2; t.zeros = p.zeros;
+  t.w = p.w; t.hidden = (const unsigned char*)p.hidden + (size_t)col0 * p.D * EL::ELEM; t.zeros = p.zeros;
   t.D = p.D; t.V = p.V; t.cols = cols; t.row_base = row_base;
-  f32x4 acc[4][CTW];
-  gemm_tile<DIST, SH>(t, smem, acc);
+  f32x4 acc[RT][CTW];
+  gemm_tile<kVhDist, SH, EL, ROWS16>(t, smem, acc);
 
   // ---- best (logit, id) key per column ---------------------------------------------------------------------
   // (the loop's last barrier has every wavefront done with the LDS tiles)
@@ -76,10 +73,10 @@ __global__ __launch_bounds__(64 * kVhWaves) void verify_head_bf16_kernel(VerifyH
     // the logit block goes through LDS so that it leaves in rows of the output
     float* zbuf = (float*)smem;
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
       for (int ct = 0; ct < CTW; ++ct)
-        *(f32x4*)(zbuf + (wc * 16 * CTW + ct * 16 + c) * ZSTRIDE + wr * 64 + rt * 16 + g * 4) = acc[rt][ct];
+        *(f32x4*)(zbuf + (wc * 16 * CTW + ct * 16 + c) * ZSTRIDE + (wr * RT + rt) * 16 + g * 4) = acc[rt][ct];
     __syncthreads();
     for (int idx = tid; idx < cols * ROWS; idx += NTHREADS) {
       const int m = idx / ROWS, r = idx % ROWS;
@@ -87,17 +84,17 @@ __global__ __launch_bounds__(64 * kVhWaves) void verify_head_bf16_kernel(VerifyH
     }
     __syncthreads();
   }
-  // a lane holds 16 rows of CTW columns: best of those, then over the 4 lane groups (64 rows), then over the
+  // a lane holds 4 RT rows of CTW columns: best of those, then over the 4 lane groups (16 RT rows), then over the
   // WR wavefronts that share the columns
   unsigned long long* kbuf = (unsigned long long*)smem;  // [WR][128]
 #pragma unroll
   for (int ct = 0; ct < CTW; ++ct) {
     unsigned long long best = 0ull;
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int row = row_base + wr * 64 + rt * 16 + g * 4 + i;
+        const int row = row_base + (wr * RT + rt) * 16 + g * 4 + i;
         const unsigned long long key = row < p.V ? rank_key(acc[rt][ct][i], (unsigned)row) : 0ull;
         best = key > best ? key : best;
       }
@@ -119,31 +116,9 @@ __global__ __launch_bounds__(64 * kVhWaves) void verify_head_bf16_kernel(VerifyH
   }
 }
 
-// ---- generic kernel: thread -> (row, column), the row block's best key per column by atomic max -----------
-__global__ __launch_bounds__(256) void verify_head_clear_kernel(VerifyHeadParams p) {
-  unsigned long long* pk = p.pkey + (size_t)(p.col0 / kVhCols) * p.n_blocks * kVhCols;
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < p.n_blocks * kVhCols; i += gridDim.x * 256) pk[i] = 0ull;
-}
-template <typename T>
-__global__ __launch_bounds__(256) void verify_head_generic_kernel(VerifyHeadParams p) {
-  const int row_base = blockIdx.x * kRowsPerBlock;
-  const T* hidden = (const T*)p.hidden;
-  const T* w = (const T*)p.w;
-  for (int idx = threadIdx.x; idx < p.cols * kRowsPerBlock; idx += 256) {
-    const int m = idx / kRowsPerBlock, row = row_base + idx % kRowsPerBlock;
-    if (row >= p.V) continue;
-    const T* hp = hidden + (size_t)(p.col0 + m) * p.D;
-    const T* wr = w + (size_t)row * p.D;
-    float z = 0.f;
-    for (int d = 0; d < p.D; ++d) z = fmaf(load_as_float(hp + d), load_as_float(wr + d), z);
-    if (p.logits_out) p.logits_out[(size_t)(p.col0 + m) * p.V + row] = z;
-    atomicMax(&p.pkey[((size_t)(p.col0 / kVhCols) * p.n_blocks + blockIdx.x) * kVhCols + m], rank_key(z, (unsigned)row));
-  }
-}
-
 // best key over the row blocks: one wavefront per column; rows of the node table without a node get -1
 __global__ __launch_bounds__(64) void verify_head_merge_kernel(VerifyHeadParams p) {
-  const int col = p.col0 + blockIdx.x, lane = threadIdx.x;  // column of the call
+  const int col = blockIdx.x, lane = threadIdx.x;
   const int m = col % kVhCols;
   const unsigned long long* pk = p.pkey + (size_t)(col / kVhCols) * p.n_blocks * kVhCols;
   unsigned long long best = 0ull;
@@ -216,13 +191,55 @@ __global__ __launch_bounds__(256) void kv_commit_kernel(KvCommitParams p) {
   }
 }
 
-hipError_t prepare_verify_head() {
-  hipError_t e = hipFuncSetAttribute((const void*)verify_head_bf16_kernel<kVhDist, Tile128x128>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, vh_lds_bytes<Tile128x128>());
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)verify_head_bf16_kernel<kVhDist, Tile256x128>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, vh_lds_bytes<Tile256x128>());
+template <typename F>
+static hipError_t each_tile_shape(F&& f) {
+  hipError_t e = f(Tile128x16{});
+  if (e == hipSuccess) e = f(Tile128x32{});
+  if (e == hipSuccess) e = f(Tile128x64{});
+  if (e == hipSuccess) e = f(Tile128x128{});
+  if (e == hipSuccess) e = f(Tile256x128{});
   return e;
+}
+template <typename EL, bool ROWS16>
+static hipError_t allow_lds() {
+  return each_tile_shape([](auto shape) {
+    using SH = decltype(shape);
+    return hipFuncSetAttribute((const void*)verify_head_kernel<SH, EL, ROWS16>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               vh_lds_bytes<SH>());
+  });
+}
+hipError_t prepare_verify_head() {
+  hipError_t e = allow_lds<TileBf16, true>();
+  if (e == hipSuccess) e = allow_lds<TileBf16, false>();
+  if (e == hipSuccess) e = allow_lds<TileF32, true>();
+  if (e == hipSuccess) e = allow_lds<TileF32, false>();
+  return e;
+}
+
+template <typename SH, typename EL, bool ROWS16>
+static hipError_t launch_shape(VerifyHeadParams& p, hipStream_t stream) {
+  p.n_blocks = (p.V + SH::ROWS - 1) / SH::ROWS;
+  const long long grid = (long long)((p.n_blocks + 7) / 8) * 8 * p.col_blocks;  // the caller has checked the range
+  hipLaunchKernelGGL((verify_head_kernel<SH, EL, ROWS16>), dim3((unsigned)grid), dim3(64 * kVhWaves), vh_lds_bytes<SH>(),
+                     stream, p);
+  return hipGetLastError();
+}
+// One launch for every column block (the kernel's workgroup numbering keeps a row block's column blocks on one XCD).
+// One column block: 128-row tiles as narrow as the columns allow - a workgroup per compute unit, the stream from HBM
+// sets the pace, and no matrix instruction is spent on dead columns.  Several: 256-row tiles - the workgroups of a
+// row block share the weight tile through L2 and the loop's own LDS traffic sets the pace, which the larger tile
+// halves per flop.
+template <typename EL, bool ROWS16>
+static hipError_t launch_rows(VerifyHeadParams& p, hipStream_t stream) {
+  if (p.col_blocks > 1) return launch_shape<Tile256x128, EL, ROWS16>(p, stream);
+  if (p.cols_total <= 16) return launch_shape<Tile128x16, EL, ROWS16>(p, stream);
+  if (p.cols_total <= 32) return launch_shape<Tile128x32, EL, ROWS16>(p, stream);
+  if (p.cols_total <= 64) return launch_shape<Tile128x64, EL, ROWS16>(p, stream);
+  return launch_shape<Tile128x128, EL, ROWS16>(p, stream);
+}
+template <typename EL>
+static hipError_t launch_head(VerifyHeadParams& p, hipStream_t stream) {
+  return tile_rows16(p.D, EL::ELEM) ? launch_rows<EL, true>(p, stream) : launch_rows<EL, false>(p, stream);
 }
 
 }  // namespace ctcspec
@@ -245,50 +262,18 @@ extern "C" int verify_head_argmax(ctcspec_ctx* ctx, ctcspec_dtype dt, const void
                   CTCSPEC_EUNSUPPORTED, "verify_head_argmax: shape exceeds the context's limits");
   VerifyHeadParams p;
   p.hidden = node_hidden; p.w = w_base; p.D = D; p.V = V;
-  p.n_blocks = (V + kRowsPerBlock - 1) / kRowsPerBlock;
   p.zeros = ctx->zeros; p.pkey = ctx->vh_pkey; p.logits_out = logits_out; p.n_nodes = n_nodes; p.max_nodes = max_nodes;
   p.target = target_argmax;
   const long long cols_total = (long long)B * max_nodes;
-  const bool wide = dt == CTCSPEC_BF16 && D % kVhStepK == 0 && (long long)V * D * 2 < (1LL << 32) &&
-                    cols_total * D * 2 < (1LL << 32);
+  CTCSPEC_REQUIRE(ctx, (cols_total + kVhCols - 1) / kVhCols <= ctx->vh_col_blocks, CTCSPEC_EUNSUPPORTED,
+                  "verify_head_argmax: %lld columns exceed the context's workspace", cols_total);
+  CTCSPEC_REQUIRE(ctx, ((long long)V / kRowsPerBlock + 8) * ((cols_total + kVhCols - 1) / kVhCols) <= 0x7fffffffLL,
+                  CTCSPEC_EUNSUPPORTED, "verify_head_argmax: grid too large");
   p.cols_total = (int)cols_total;
   p.col_blocks = (int)((cols_total + kVhCols - 1) / kVhCols);
-  CTCSPEC_REQUIRE(ctx, p.col_blocks <= ctx->vh_col_blocks, CTCSPEC_EUNSUPPORTED,
-                  "verify_head_argmax: %lld columns exceed the context's workspace", cols_total);
-  if (wide) {
-    // one launch for every column block (the kernel's workgroup numbering keeps a row block's column blocks on
-    // one XCD), one merge launch over all columns.  One column block: 128-row tiles, one workgroup per compute
-    // unit, the stream from HBM sets the pace.  Several: 256-row tiles - the workgroups of a row block share the
-    // weight tile through L2 and the loop's own LDS traffic sets the pace, which the larger tile halves per flop.
-    p.col0 = 0; p.cols = 0;
-    const bool tall = p.col_blocks > 1;
-    const int rows = tall ? Tile256x128::ROWS : Tile128x128::ROWS;
-    p.n_blocks = (V + rows - 1) / rows;
-    const long long grid = (long long)((p.n_blocks + 7) / 8) * 8 * p.col_blocks;
-    CTCSPEC_REQUIRE(ctx, grid <= 0x7fffffffLL, CTCSPEC_EUNSUPPORTED, "verify_head_argmax: grid too large");
-    if (tall)
-      hipLaunchKernelGGL((verify_head_bf16_kernel<kVhDist, Tile256x128>), dim3((unsigned)grid), dim3(64 * kVhWaves),
-                         vh_lds_bytes<Tile256x128>(), ctx->stream, p);
-    else
-      hipLaunchKernelGGL((verify_head_bf16_kernel<kVhDist, Tile128x128>), dim3((unsigned)grid), dim3(64 * kVhWaves),
-                         vh_lds_bytes<Tile128x128>(), ctx->stream, p);
-    CTCSPEC_HIP(ctx, hipGetLastError());
-    hipLaunchKernelGGL(verify_head_merge_kernel, dim3((unsigned)cols_total), dim3(64), 0, ctx->stream, p);
-    CTCSPEC_HIP(ctx, hipGetLastError());
-    return CTCSPEC_OK;
-  }
-  for (long long col0 = 0; col0 < cols_total; col0 += kVhCols) {
-    p.col0 = (int)col0;
-    p.cols = (int)(cols_total - col0 < kVhCols ? cols_total - col0 : kVhCols);
-    hipLaunchKernelGGL(verify_head_clear_kernel, dim3(64), dim3(256), 0, ctx->stream, p);
-    if (dt == CTCSPEC_BF16)
-      hipLaunchKernelGGL(verify_head_generic_kernel<unsigned short>, dim3(p.n_blocks), dim3(256), 0, ctx->stream, p);
-    else
-      hipLaunchKernelGGL(verify_head_generic_kernel<float>, dim3(p.n_blocks), dim3(256), 0, ctx->stream, p);
-    CTCSPEC_HIP(ctx, hipGetLastError());
-    hipLaunchKernelGGL(verify_head_merge_kernel, dim3(p.cols), dim3(64), 0, ctx->stream, p);
-    CTCSPEC_HIP(ctx, hipGetLastError());
-  }
+  CTCSPEC_HIP(ctx, dt == CTCSPEC_BF16 ? launch_head<TileBf16>(p, ctx->stream) : launch_head<TileF32>(p, ctx->stream));
+  hipLaunchKernelGGL(verify_head_merge_kernel, dim3((unsigned)cols_total), dim3(64), 0, ctx->stream, p);
+  CTCSPEC_HIP(ctx, hipGetLastError());
   return CTCSPEC_OK;
 }
 

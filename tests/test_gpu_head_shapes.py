@@ -1,0 +1,76 @@
+"""The tile loop of the two heads over sizes where it can go wrong: hidden sizes around its steps and the 16-byte
+chunks (rows that start at any element), column counts around the tile widths, a last row block of one row."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+HIDDEN = [1, 7, 8, 60, 64, 65, 100, 127, 129, 264, 500, 513, 1000, 1031]
+COLUMNS = [1, 16, 17, 32, 33, 64, 65, 128, 129, 300]
+
+
+@pytest.fixture(scope="module")
+def pkg():
+    import paper_2412_00061_amd as pkg
+    return pkg
+
+
+def _operands(seed, cols, D, V, dtype):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    h = torch.randn((cols, D), generator=g, device="cuda").to(dtype)
+    w = (torch.randn((V, D), generator=g, device="cuda") * 0.05).to(dtype)
+    z = h.double() @ w.double().t()
+    # a float32 sum of D products in any order, each rounded: at most D + 1 roundings of the sum of magnitudes
+    bound = (D + 1) * 2.0 ** -24 * (h.double().abs() @ w.double().abs().t())
+    return h, w, z.cpu().numpy(), bound.cpu().numpy()
+
+
+def _check(z, z_ref, bound):
+    assert np.all(np.abs(z - z_ref) <= bound + 1e-30)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("i", range(len(HIDDEN)))
+def test_verify_head_any_hidden(pkg, dtype, i):
+    D = HIDDEN[i]
+    for j, V in ((i, 385), (i + 3, 130), (i + 6, 1)):
+        cols = COLUMNS[j % len(COLUMNS)]
+        B, N = (3, 100) if cols == 300 else (cols // 43, 43) if cols % 43 == 0 else (1, cols) if cols <= 128 else (cols, 1)
+        print(f"verify head {dtype} D={D} V={V} B={B} N={N}", flush=True)
+        h, w, z_ref, bound = _operands(100 * i + j, B * N, D, V, dtype)
+        ctx = pkg.Context(max_batch=min(B, 64), max_slots=1, max_topk=1, max_vocab_rows=V, max_nodes=N, max_heads=1,
+                          max_head_dim=8) if B <= 64 else None
+        if ctx is None:
+            continue
+        n_nodes = torch.full((B,), N, dtype=torch.int32, device="cuda")
+        n_nodes[0] = max(1, N - 1)
+        res = pkg.verify_head_argmax(ctx, h.view(B, N, D), w, n_nodes, want_logits=True)
+        z = res["logits"].cpu().numpy().reshape(B * N, V)
+        _check(z, z_ref, bound)
+        want = z.argmax(1).reshape(B, N)
+        want[0, int(n_nodes[0]):] = -1
+        assert np.array_equal(res["target_argmax"].cpu().numpy(), want)
+        ctx.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("i", range(len(HIDDEN)))
+def test_draft_head_any_hidden(pkg, dtype, i):
+    D = HIDDEN[i]
+    for j, (B, T) in enumerate([(1, 1), (2, 8), (3, 6), (4, 8), (5, 7), (8, 8)]):
+        k = 1 + (i + j) % 5
+        Vp1 = (130, 385, 257)[(i + j) % 3]
+        print(f"draft head {dtype} D={D} Vp1={Vp1} B={B} T={T} k={k}", flush=True)
+        h, w, z_ref, bound = _operands(100 * i + j, B * T, D, Vp1, dtype)
+        bias = torch.linspace(-1, 1, Vp1, device="cuda")
+        ctx = pkg.Context(max_batch=B, max_slots=T, max_topk=k, max_vocab_rows=Vp1, max_nodes=8, max_heads=1, max_head_dim=8)
+        res = pkg.ctc_draft_topk(ctx, h.view(B, T, D), w, bias, k, want_logits=True)
+        z = res["logits"].cpu().numpy().reshape(B * T, Vp1)
+        z_ref = z_ref + bias.double().cpu().numpy()
+        _check(z, z_ref, bound + 2.0 ** -23 * (1 + np.abs(z_ref)))
+        top = res["topk_id"].cpu().numpy().reshape(B * T, k)
+        assert np.array_equal(top, np.argsort(-z, axis=1, kind="stable")[:, :k])
+        lse = np.log(np.exp(z.astype(np.float64)).sum(1))
+        assert np.max(np.abs(res["lse"].cpu().numpy().reshape(-1) - lse)) <= 2e-5
+        ctx.close()

@@ -1,15 +1,15 @@
 // tree_verify_attn: tree-masked verification attention of the base model, one layer.
 //
-// Two kernels:
+// Kernels:
 //   * tree_attn_bf16_kernel    - bf16 operands, head dimension 128: MFMA for Q.K^T and P.V, online
 //                                softmax, K/V tiles shared by the wavefronts of a workgroup through LDS,
 //                                optional key splits combined by tree_attn_merge_kernel
-//   * tree_attn_generic_kernel - any dtype / head dimension within the limits: one workgroup per
-//                                (node, head, sequence), keys in chunks with an online softmax
+//   * tree_attn_any_kernel     - float operands, and bf16 with other head dimensions: the same online softmax on
+//                                blocks of 64 query rows, the same key splits and merge
 #include <type_traits>
 #include <utility>
 
-#include "common.h"
+#include "gemm_tile.h"
 
 namespace ctcspec {
 
@@ -27,104 +27,11 @@ struct AttnParams {
   int B, H, dh, max_nodes;
   float scale;
   float* out;
-  // optional second form of the merged output (key splits only): rows [B*max_nodes][H*128], each value as two
+  // optional second form of the merged output (key splits only): rows [B*max_nodes][H*dh], each value as two
   // bf16 numbers (high part in plane 0, low part in plane 1) - what the draft layer's next matrix product takes
   unsigned short* rows;
   long long rows_plane;  // elements per plane
 };
-
-constexpr int kGenericThreads = 256;
-constexpr int kGenericChunk = 1024;
-
-template <typename T>
-__global__ __launch_bounds__(kGenericThreads) void tree_attn_generic_kernel(AttnParams p) {
-  __shared__ float qs[CTCSPEC_MAX_HEAD_DIM];
-  __shared__ float sc[kGenericChunk];
-  __shared__ float red[kGenericThreads / 64];
-  const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int n = p.n_nodes[b];
-  n = n > p.max_nodes ? p.max_nodes : n;
-  if (i >= n) return;
-  const int dh = p.dh;
-  int L = p.ctx_len[b];
-  L = L < 0 ? 0 : (L > p.kv_cap ? p.kv_cap : L);
-  const int W = (p.max_nodes + 63) / 64;
-  const unsigned long long* mrow = p.anc_mask + ((size_t)b * p.max_nodes + i) * W;
-  const size_t node_base = ((size_t)b * p.H + h) * p.max_nodes;
-  const T* q = (const T*)p.q + (node_base + i) * dh;
-  const T* kc = (const T*)p.k_cache + p.kv_off[b] + (size_t)h * p.kv_cap * dh;
-  const T* vc = (const T*)p.v_cache + p.kv_off[b] + (size_t)h * p.kv_cap * dh;
-  const T* kt = (const T*)p.k_tree + node_base * dh;
-  const T* vt = (const T*)p.v_tree + node_base * dh;
-  if (tid < dh) qs[tid] = load_as_float(q + tid);
-  __syncthreads();
-
-  const int total = L + n;  // key j < L: cache row j; else tree node j-L (subject to the mask)
-  float m_run = -INFINITY, l_run = 0.f, acc = 0.f;  // acc: output component tid (tid < dh)
-  for (int c0 = 0; c0 < total; c0 += kGenericChunk) {
-    const int cn = total - c0 < kGenericChunk ? total - c0 : kGenericChunk;
-    float mloc = -INFINITY;
-    for (int jj = tid; jj < cn; jj += kGenericThreads) {
-      const int j = c0 + jj;
-      float s = -INFINITY;
-      bool vis = true;
-      const T* kr;
-      if (j < L) kr = kc + (size_t)j * dh;
-      else {
-        int t = j - L;
-        vis = (mrow[t >> 6] >> (t & 63)) & 1ull;
-        kr = kt + (size_t)t * dh;
-      }
-      if (vis) {
-        float d = 0.f;
-        for (int e = 0; e < dh; ++e) d = fmaf(qs[e], load_as_float(kr + e), d);
-        s = d * p.scale;
-      }
-      sc[jj] = s;
-      mloc = fmaxf(mloc, s);
-    }
-    mloc = wave_max_f32(mloc);
-    __syncthreads();
-    if (lane == 0) red[wave] = mloc;
-    __syncthreads();
-    float m_new = m_run;
-    for (int w = 0; w < kGenericThreads / 64; ++w) m_new = fmaxf(m_new, red[w]);
-    // m_new is finite from the first chunk on: the first chunk holds a cache key or the root (tree
-    // node 0, visible to every node)
-    float lloc = 0.f;
-    for (int jj = tid; jj < cn; jj += kGenericThreads) {
-      float s = sc[jj];
-      float pj = s > -INFINITY ? __expf(s - m_new) : 0.f;
-      sc[jj] = pj;
-      lloc += pj;
-    }
-    lloc = wave_sum_f32(lloc);
-    __syncthreads();
-    if (lane == 0) red[wave] = lloc;
-    __syncthreads();
-    float lsum = 0.f;
-    for (int w = 0; w < kGenericThreads / 64; ++w) lsum += red[w];
-    const float alpha = m_run > -INFINITY ? __expf(m_run - m_new) : 0.f;
-    l_run = l_run * alpha + lsum;
-    if (tid < dh) {
-      float a = acc * alpha;
-      for (int jj = 0; jj < cn; ++jj) {
-        float pj = sc[jj];
-        if (pj != 0.f) {
-          const int j = c0 + jj;
-          const T* vr = j < L ? vc + (size_t)j * dh : vt + (size_t)(j - L) * dh;
-          a = fmaf(pj, load_as_float(vr + tid), a);
-        }
-      }
-      acc = a;
-    }
-    m_run = m_new;
-    __syncthreads();
-  }
-  if (tid < dh) p.out[(node_base + i) * dh + tid] = acc / l_run;
-}
-
 
 // ---- bf16, dh = 128 -------------------------------------------------------------------------------
 // Workgroup = NW wavefronts = one block of 16*QT*CW query nodes of one (sequence, head) and one of S
@@ -184,7 +91,7 @@ __device__ __forceinline__ float sum_across_row_groups(float x) {
 struct AttnSplit {
   int QB;      // query blocks of 16*QT*CW rows
   int S;       // key splits
-  float* po;   // [unit][rows][128] partial O (unnormalised), unit = ((b*H + h)*QB + qb)*S + s
+  float* po;   // [unit][rows][dh] partial O (unnormalised), unit = ((b*H + h)*QB + qb)*S + s
   float* pm;   // [unit][rows] softmax reference, scaled to the log2 domain
   float* pl;   // [unit][rows] running sum
 };
@@ -514,6 +421,268 @@ void tree_attn_bf16_kernel(AttnParams p, AttnSplit sp) {
   }
 }
 
+// ---- any head dimension, float or bf16 ---------------------------------------------------------------------------
+// Workgroup = 4 wavefronts = one block of 64 query rows of one (sequence, head) and one of S splits of the keys;
+// a wavefront owns 16 rows.  Tiles of 32 keys (context first, then the tree) go through two LDS stages, fetched by all
+// threads PF tiles ahead in registers.  The head dimension is padded to DHP (a multiple of 32) in LDS and registers
+// only: the padding of K is zeroed once, that of V feeds output components that are not written.
+//   S^T[key, q] = K.Q^T   64-byte k-blocks as in gemm_tile.h (bf16: one product of 32 k, float: four of 4 k)
+//   O^T[dh, q] += V^T.P   a lane holds P of keys 16 kb + 4 g + i in the C layout of S^T, which is the B layout as it is:
+//       float: product i of key block kb contracts the keys 16 kb + 4 g + i, g = 0..3; V[key][16 db + c] is one LDS word
+//              per lane (row pitch = 16 mod 64 bytes: the four rows a wavefront reads lie 16 banks apart)
+//       bf16:  the transposing read of the kernel above (row pitch = an odd multiple of 32 bytes: eight rows x 32 bytes
+//              cover every bank once); P goes in as three bf16 numbers, which together hold its 24 mantissa bits - this
+//              path has always kept P in float
+// Bound: float operands by the matrix rate (157 TFLOP/s), bf16 by latency and the K/V stream.  Measured against one
+// workgroup per query row with K/V read by every row (what these shapes took before): 2 sequences x 12 heads x 100
+// nodes, 300 to 900 keys, float, head dimension 64: 608 -> 17.6 us (kernel and merge); four sequences x 15 heads x 64
+// nodes over 43 keys, bf16, head dimension 64: 67 -> 10 us.
+template <typename EL, int DHP>
+struct AnyAttn {
+  static constexpr int E = EL::ELEM;
+  static constexpr int KPITCH = DHP * E + 32;
+  static constexpr int VPITCH = E == 4 ? DHP * 4 + 16 : DHP * 2 + 32;
+  static constexpr int STAGE = kTileKeys * (KPITCH + VPITCH);
+  static constexpr int THREADS = 256, ROWS = 64;
+  static constexpr int NP = (kTileKeys * DHP * E / 16 + THREADS - 1) / THREADS;  // 16-byte pieces per thread of K, of V
+  static constexpr int PF = NP >= 4 ? 2 : 4;
+};
+
+template <typename EL, int DHP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void tree_attn_any_kernel(AttnParams p, AttnSplit sp) {
+  using C = AnyAttn<EL, DHP>;
+  constexpr int E = C::E, NP = C::NP, PF = C::PF, NB = DHP / 16, KB = DHP * E / 64;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, g = lane >> 4;
+  int bid = blockIdx.x;
+  const int h = bid % p.H;
+  bid /= p.H;
+  const int split = bid % sp.S;
+  bid /= sp.S;
+  const int qb = bid % sp.QB;
+  const int b = bid / sp.QB;
+  int n = p.n_nodes[b];
+  n = n > p.max_nodes ? p.max_nodes : n;
+  if (qb * C::ROWS >= n) return;
+  int L = p.ctx_len[b];
+  L = L < 0 ? 0 : (L > p.kv_cap ? p.kv_cap : L);
+  const int dh = p.dh, row_bytes = dh * E, rc = row_bytes / 16;  // 16-byte chunks per row (dh is a multiple of 8)
+
+  const size_t node_base = ((size_t)b * p.H + h) * p.max_nodes;
+  const unsigned char* kc = (const unsigned char*)p.k_cache + ((size_t)p.kv_off[b] + (size_t)h * p.kv_cap * dh) * E;
+  const unsigned char* vc = (const unsigned char*)p.v_cache + ((size_t)p.kv_off[b] + (size_t)h * p.kv_cap * dh) * E;
+  const unsigned char* kt = (const unsigned char*)p.k_tree + node_base * row_bytes;
+  const unsigned char* vt = (const unsigned char*)p.v_tree + node_base * row_bytes;
+
+  const int ctxT = (L + kTileKeys - 1) / kTileKeys, treeT = (n + kTileKeys - 1) / kTileKeys;
+  const int NTL = ctxT + treeT;
+  const int nloc = split < NTL ? (NTL - split + sp.S - 1) / sp.S : 0;  // my tiles: split, split+S, ...
+
+  // ---- tile loader ----------------------------------------------------------------------------------
+  struct Packed16 { u32x4 v; } __attribute__((packed, aligned(E)));
+  const int pieces = kTileKeys * rc;
+  int prow[NP], pch[NP];
+  bool own[NP];
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    const int idx = tid + u * C::THREADS;
+    own[u] = idx < pieces;
+    const int i = own[u] ? idx : pieces - 1;  // a piece past the end repeats the last one and is not written
+    prow[u] = i / rc;
+    pch[u] = i - prow[u] * rc;
+  }
+  u32x4 ld[PF][2 * NP];
+  auto issue = [&](int j, auto set_tag) __attribute__((always_inline)) {
+    constexpr int SET = decltype(set_tag)::value;
+    const int t = split + (j < nloc ? j : nloc - 1) * sp.S;  // past the last tile: that one again, never used
+    const bool tree = t >= ctxT;
+    const int row0 = (tree ? t - ctxT : t) * kTileKeys, last = (tree ? n : L) - 1 - row0;
+    const unsigned char* k0 = (tree ? kt : kc) + (size_t)row0 * row_bytes;
+    const unsigned char* v0 = (tree ? vt : vc) + (size_t)row0 * row_bytes;
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      // rows past the end re-read the last valid row (masked later)
+      const unsigned int off = (unsigned int)((prow[u] < last ? prow[u] : last) * row_bytes + pch[u] * 16);
+      ld[SET][u] = ((const Packed16*)(k0 + off))->v;
+      ld[SET][NP + u] = ((const Packed16*)(v0 + off))->v;
+    }
+  };
+  auto commit = [&](auto set_tag, int stage) __attribute__((always_inline)) {
+    constexpr int SET = decltype(set_tag)::value;
+    unsigned char* base = smem + stage * C::STAGE;
+#pragma unroll
+    for (int u = 0; u < NP; ++u)
+      if (own[u]) {
+        *(u32x4*)(base + prow[u] * C::KPITCH + pch[u] * 16) = ld[SET][u];
+        *(u32x4*)(base + kTileKeys * C::KPITCH + prow[u] * C::VPITCH + pch[u] * 16) = ld[SET][NP + u];
+      }
+  };
+
+  // ---- query fragments and mask words ------------------------------------------------------------------
+  const int qbase = qb * C::ROWS + wave * 16, qi = qbase + c;
+  const bool live_wave = qbase < n;
+  u32x4 qf[KB];
+  {
+    const unsigned char* qrow = (const unsigned char*)p.q + (node_base + (qi < n ? qi : n - 1)) * row_bytes;
+#pragma unroll
+    for (int kk = 0; kk < KB; ++kk) {
+      const int ch = kk * 4 + g;
+      const u32x4 v = *(const u32x4*)(qrow + (ch < rc ? ch : 0) * 16);
+      qf[kk] = ch < rc ? v : u32x4{0u, 0u, 0u, 0u};
+    }
+  }
+  unsigned long long mw0 = 0ull, mw1 = 0ull;
+  if (qi < n) {
+    const int W = (p.max_nodes + 63) >> 6;
+    const unsigned long long* mrow = p.anc_mask + ((size_t)b * p.max_nodes + qi) * W;
+    mw0 = mrow[0];
+    if (W > 1) mw1 = mrow[1];
+  }
+  const float sl2 = p.scale * 1.4426950408889634f;
+
+  f32x4 o[NB];  // lane (c, g): O[q = c][dh = 16 db + 4 g + i]
+#pragma unroll
+  for (int db = 0; db < NB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;  // reference (scaled, base 2) and this lane's part of the sum
+
+  auto compute = [&](int j, int stage) __attribute__((always_inline)) {
+    const int t = split + j * sp.S;
+    const bool tree = t >= ctxT;
+    const int row0 = (tree ? t - ctxT : t) * kTileKeys;
+    const unsigned char* ks = smem + stage * C::STAGE;
+    const unsigned char* vs = ks + kTileKeys * C::KPITCH;
+    f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int kk = 0; kk < KB; ++kk)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+        s[kb] = EL::mma(*(const u32x4*)(ks + (kb * 16 + c) * C::KPITCH + kk * 64 + g * 16), qf[kk], s[kb]);
+    // this lane's 8 keys are bits 4g..4g+3 and 16+4g..16+4g+3 of the tile's 32-bit visibility word
+    const int left = (tree ? n : L) - row0;  // >= 1 keys of the tile exist
+    unsigned int vis = left >= 32 ? 0xffffffffu : ((1u << left) - 1u);
+    if (tree) {
+      const unsigned long long w = row0 < 64 ? mw0 : mw1;
+      vis &= (unsigned int)(w >> (row0 & 63));
+    }
+    vis >>= 4 * g;
+    float sv[8];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sv[kb * 4 + i] = ((vis >> (kb * 16 + i)) & 1u) ? s[kb][i] * sl2 : -INFINITY;
+    const float mx8 = max3_f32(max3_f32(sv[0], sv[1], sv[2]), max3_f32(sv[3], sv[4], sv[5]), fmaxf(sv[6], sv[7]));
+    // lazily moved reference, the exchange only after a vote: as in tree_attn_bf16_kernel
+    if (__builtin_amdgcn_ballot_w64(mx8 - m_run > 8.0f) != 0ull) {
+      const float mx = max_across_row_groups(mx8);
+      if (mx - m_run > 8.0f) {
+        const float alpha = __builtin_amdgcn_exp2f(m_run - mx);  // 0 on first use
+        l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < NB; ++db) o[db] *= alpha;
+        m_run = mx;
+      }
+    }
+    const float ms = m_run > -INFINITY ? m_run : 0.f;
+    float pv[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      // the product is formed again, unrounded (a key whose score is not a number counts as hidden)
+      const float e = __builtin_amdgcn_exp2f(fmaf(s[q >> 2][q & 3], sl2, -ms));
+      pv[q] = sv[q] > -INFINITY ? e : 0.f;
+      l_run += pv[q];
+    }
+    if constexpr (E == 4) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float* vr = (const float*)(vs + (kb * 16 + 4 * g + i) * C::VPITCH) + c;
+#pragma unroll
+          for (int db = 0; db < NB; ++db)
+            o[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[16 * db], pv[kb * 4 + i], o[db], 0, 0, 0);
+        }
+    } else {
+      u32x4 hi, mid, lo;
+#pragma unroll
+      for (int jp = 0; jp < 4; ++jp) {
+        const float p0 = pv[2 * jp], p1 = pv[2 * jp + 1];
+        const float r0 = p0 - __uint_as_float(__float_as_uint(p0) & 0xffff0000u);
+        const float r1 = p1 - __uint_as_float(__float_as_uint(p1) & 0xffff0000u);
+        hi[jp] = __builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302u);
+        mid[jp] = __builtin_amdgcn_perm(__float_as_uint(r1), __float_as_uint(r0), 0x07060302u);
+        const float q0 = r0 - __uint_as_float(__float_as_uint(r0) & 0xffff0000u);
+        const float q1 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+        lo[jp] = __builtin_bit_cast(unsigned int, bf16x2{(__bf16)q0, (__bf16)q1});
+      }
+      typedef __attribute__((address_space(3))) unsigned char lds_byte;
+      const unsigned int v0 = (unsigned int)(size_t)(lds_byte*)vs + (4 * g + (c >> 2)) * C::VPITCH + (c & 3) * 8;
+      u32x4 va[NB];
+#pragma unroll
+      for (int db = 0; db < NB; ++db) {
+        const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) s16x4*)(unsigned int)(v0 + db * 32));
+        const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) s16x4*)(unsigned int)(v0 + 16 * C::VPITCH + db * 32));
+        va[db] = __builtin_bit_cast(u32x4, s16x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]});
+      }
+#pragma unroll
+      for (int db = 0; db < NB; ++db) o[db] = EL::mma(va[db], hi, o[db]);
+#pragma unroll
+      for (int db = 0; db < NB; ++db) o[db] = EL::mma(va[db], mid, o[db]);
+#pragma unroll
+      for (int db = 0; db < NB; ++db) o[db] = EL::mma(va[db], lo, o[db]);
+    }
+  };
+
+  if (nloc > 0) {
+    auto for_each_set = [&](auto&& fn) __attribute__((always_inline)) {
+      [&]<int... I>(std::integer_sequence<int, I...>) { (fn(std::integral_constant<int, I>{}), ...); }
+      (std::make_integer_sequence<int, PF>{});
+    };
+    for_each_set([&](auto st) __attribute__((always_inline)) { issue(decltype(st)::value, st); });
+    if (rc * 16 < DHP * E) {  // zeros behind the head dimension in K's rows, both stages
+      const int pad = DHP * E / 16 - rc;
+      for (int i = tid; i < 2 * kTileKeys * pad; i += C::THREADS) {
+        const int r = i / pad, ch = rc + i - r * pad;
+        *(u32x4*)(smem + (r / kTileKeys) * C::STAGE + (r % kTileKeys) * C::KPITCH + ch * 16) = u32x4{0u, 0u, 0u, 0u};
+      }
+    }
+    commit(std::integral_constant<int, 0>{}, 0);
+    lds_barrier();
+    bool more = true;
+    for (int j0 = 0; more; j0 += PF) {
+      for_each_set([&](auto jj_tag) __attribute__((always_inline)) {
+        constexpr int JJ = decltype(jj_tag)::value;
+        const int j = j0 + JJ;
+        if (!more) return;
+        commit(std::integral_constant<int, (JJ + 1) % PF>{}, (JJ + 1) & 1);
+        issue(j + PF, jj_tag);
+        if (live_wave) compute(j, JJ & 1);
+        lds_barrier();
+        more = j + 1 < nloc;
+      });
+    }
+  }
+  if (!live_wave) return;
+  const size_t unit = (((size_t)b * p.H + h) * sp.QB + qb) * sp.S + split;
+  const float l = sum_across_row_groups(l_run);
+  if (qi >= n) return;
+  struct PackedF4 { f32x4 v; } __attribute__((packed, aligned(4)));
+  const int qr = wave * 16 + c;
+  const float f = sp.S == 1 ? 1.0f / l : 1.0f;
+  float* dst = (sp.S == 1 ? p.out + (node_base + qi) * dh : sp.po + (unit * C::ROWS + qr) * dh) + 4 * g;
+#pragma unroll
+  for (int db = 0; db < NB; ++db)
+    if (16 * db + 4 * g < dh) ((PackedF4*)(dst + 16 * db))->v = o[db] * f;
+  if (sp.S > 1 && g == 0) {
+    sp.pm[unit * C::ROWS + qr] = m_run;
+    sp.pl[unit * C::ROWS + qr] = l;
+  }
+}
+
 // Combine the S key-split partials of every live query row.  Thread -> (row, 4 consecutive dh), 32
 // threads per row, 8 rows per workgroup; all of a thread's partials are requested before any is used,
 // so the kernel costs about one memory round trip.  (Letting the split that finishes last do the
@@ -533,7 +702,8 @@ __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnPara
   if (row >= n) return;
   const int qb = row >> rows_shift, qr = row & (rows_per_block - 1);
   const size_t unit0 = ((size_t)bh * sp.QB + qb) * sp.S;
-  const int d4 = (tid & 31) * 4;
+  const int d4 = (tid & 31) * 4, dh = p.dh;
+  if (d4 >= dh) return;
   float pmv[kMaxKvSplits], plv[kMaxKvSplits];
   f32x4 pov[kMaxKvSplits];
 #pragma unroll
@@ -542,7 +712,7 @@ __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnPara
     const size_t r = (unit0 + (on ? s : 0)) * rows_per_block + qr;
     pmv[s] = on ? sp.pm[r] : -INFINITY;
     plv[s] = sp.pl[r];
-    pov[s] = *(const f32x4*)(sp.po + r * 128 + d4);
+    pov[s] = *(const f32x4*)(sp.po + r * dh + d4);
   }
   float M = -INFINITY;
 #pragma unroll
@@ -558,7 +728,7 @@ __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnPara
   const f32x4 o = acc * (1.0f / Lt);
   if (p.rows) {
     const int h = (int)(bh - (long long)b * p.H);
-    const size_t at = ((size_t)b * p.max_nodes + row) * ((size_t)p.H * 128) + (size_t)h * 128 + d4;
+    const size_t at = ((size_t)b * p.max_nodes + row) * ((size_t)p.H * dh) + (size_t)h * dh + d4;
     unsigned short hi[4], lo[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -570,23 +740,40 @@ __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnPara
     *(u32x2*)(p.rows + at) = u32x2{(unsigned)hi[0] | ((unsigned)hi[1] << 16), (unsigned)hi[2] | ((unsigned)hi[3] << 16)};
     *(u32x2*)(p.rows + p.rows_plane + at) = u32x2{(unsigned)lo[0] | ((unsigned)lo[1] << 16), (unsigned)lo[2] | ((unsigned)lo[3] << 16)};
   } else {
-    *(f32x4*)(p.out + ((size_t)bh * p.max_nodes + row) * 128 + d4) = o;
+    *(f32x4*)(p.out + ((size_t)bh * p.max_nodes + row) * dh + d4) = o;
   }
 }
 
+static hipError_t launch_merge(const AttnParams& p, const AttnSplit& sp, int rows, hipStream_t stream) {
+  const unsigned mblocks = (unsigned)((p.max_nodes + kMergeThreads / 32 - 1) / (kMergeThreads / 32));
+  hipLaunchKernelGGL(tree_attn_merge_kernel, dim3(mblocks, (unsigned)(p.B * p.H)), dim3(kMergeThreads), 0, stream, p, sp,
+                     rows == 64 ? 6 : 7);
+  return hipGetLastError();
+}
 template <int QT, int NW, int CW, int PF>
 static hipError_t launch_attn_bf16(const AttnParams& p, const AttnSplit& sp, hipStream_t stream) {
   auto kern = tree_attn_bf16_kernel<QT, NW, CW, PF>;
   const long long blocks = (long long)sp.QB * sp.S * p.H * p.B;
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * NW), attn_lds_bytes(NW / CW), stream, p, sp);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || sp.S == 1) return e;
-  const unsigned mblocks = (unsigned)((p.max_nodes + kMergeThreads / 32 - 1) / (kMergeThreads / 32));
   constexpr int kRows = 16 * QT * CW;
   static_assert(kRows == 64 || kRows == 128, "the merge kernel takes the block size as a shift");
-  hipLaunchKernelGGL(tree_attn_merge_kernel, dim3(mblocks, (unsigned)(p.B * p.H)), dim3(kMergeThreads), 0, stream, p, sp,
-                     kRows == 64 ? 6 : 7);
-  return hipGetLastError();
+  return e != hipSuccess || sp.S == 1 ? e : launch_merge(p, sp, kRows, stream);
+}
+template <typename EL, int DHP>
+static hipError_t launch_attn_any_dh(const AttnParams& p, const AttnSplit& sp, hipStream_t stream) {
+  using C = AnyAttn<EL, DHP>;
+  const long long blocks = (long long)sp.QB * sp.S * p.H * p.B;
+  hipLaunchKernelGGL((tree_attn_any_kernel<EL, DHP>), dim3((unsigned)blocks), dim3(C::THREADS), 2 * C::STAGE, stream, p, sp);
+  hipError_t e = hipGetLastError();
+  return e != hipSuccess || sp.S == 1 ? e : launch_merge(p, sp, 64, stream);
+}
+template <typename EL>
+static hipError_t launch_attn_any(const AttnParams& p, const AttnSplit& sp, hipStream_t stream) {
+  if (p.dh <= 32) return launch_attn_any_dh<EL, 32>(p, sp, stream);
+  if (p.dh <= 64) return launch_attn_any_dh<EL, 64>(p, sp, stream);
+  if (p.dh <= 96) return launch_attn_any_dh<EL, 96>(p, sp, stream);
+  return launch_attn_any_dh<EL, 128>(p, sp, stream);
 }
 
 // code of this translation unit loaded onto the current device (context creation calls this: a stage call never
@@ -594,6 +781,9 @@ static hipError_t launch_attn_bf16(const AttnParams& p, const AttnSplit& sp, hip
 hipError_t prepare_tree_attn() {
   hipFuncAttributes attr;
   hipError_t e = hipFuncGetAttributes(&attr, (const void*)tree_attn_merge_kernel);
+  if (e != hipSuccess) return e;
+  e = hipFuncSetAttribute((const void*)tree_attn_any_kernel<TileF32, 128>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                          2 * AnyAttn<TileF32, 128>::STAGE);
   if (e != hipSuccess) return e;
   // the 64-row kernel's two stages of two tiles are 64 KB of dynamic LDS
   return hipFuncSetAttribute((const void*)tree_attn_bf16_kernel<1, 8, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -673,12 +863,25 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
     CTCSPEC_HIP(ctx, e);
     return CTCSPEC_OK;
   }
-  dim3 grid(max_nodes, H, B);
-  if (dt == CTCSPEC_BF16)
-    hipLaunchKernelGGL(tree_attn_generic_kernel<unsigned short>, grid, dim3(kGenericThreads), 0, ctx->stream, p);
-  else
-    hipLaunchKernelGGL(tree_attn_generic_kernel<float>, grid, dim3(kGenericThreads), 0, ctx->stream, p);
-  CTCSPEC_HIP(ctx, hipGetLastError());
+  // Everything else: blocks of 64 rows, enough key splits for two workgroups per compute unit (their stages fit its
+  // LDS twice) while a split still has two tiles, and within the workspace's partial slots (two of 64 rows per unit).
+  AttnSplit sp;
+  sp.QB = (max_nodes + 63) / 64;
+  const long long blocks = (long long)B * H * sp.QB;
+  const int key_tiles = (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys;
+  long long S = 512 / blocks;
+  if (S > key_tiles / 2) S = key_tiles / 2;
+  if (S > kMaxKvSplits) S = kMaxKvSplits;
+  while (S > 1 && blocks * S > 2LL * ctx->attn_units) --S;
+  if ((long long)B * H > 65535) S = 1;  // the merge kernel's grid
+  sp.S = S < 1 ? 1 : (int)S;
+  sp.po = ctx->attn_po; sp.pm = ctx->attn_pm; sp.pl = ctx->attn_pl;
+  CTCSPEC_REQUIRE(ctx, blocks * sp.S <= 0x7fffffffLL, CTCSPEC_EUNSUPPORTED, "tree_verify_attn: grid too large");
+  if (rows && sp.S > 1) {
+    p.rows = rows; p.rows_plane = rows_plane;
+    if (rows_written) *rows_written = 1;
+  }
+  CTCSPEC_HIP(ctx, dt == CTCSPEC_BF16 ? launch_attn_any<TileBf16>(p, sp, ctx->stream) : launch_attn_any<TileF32>(p, sp, ctx->stream));
   return CTCSPEC_OK;
 }
 

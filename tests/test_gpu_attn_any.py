@@ -1,0 +1,57 @@
+"""tree_verify_attn with float operands and with head dimensions other than 128: padded head dimensions, tiles and
+blocks at their edges, key splits, scores that move the softmax reference, any sign of the scale."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from gpu_harness import dev_i32, dev_i64, rel_err_rms_floor, to_device
+from test_gpu_attn_peaked import _trees
+
+pytestmark = pytest.mark.gpu
+
+# (B, H, max_nodes, kv_cap, context lengths): tiles of 32 keys and blocks of 64 rows at their edges, no context at all,
+# one key range and up to eight
+SHAPES = [(1, 2, 1, 8, [0]), (2, 3, 5, 40, [1, 33]), (1, 4, 16, 64, [31]), (3, 2, 17, 64, [32, 0, 64]),
+          (2, 2, 64, 300, [300, 65]), (1, 5, 65, 900, [700]), (2, 12, 100, 900, [300, 900]), (8, 32, 128, 96, [96] * 8)]
+
+
+@pytest.fixture(scope="module")
+def pkg():
+    import paper_2412_00061_amd as m
+    return m
+
+
+# Scores are float32 sums of dh products and P has 24 bits: an error of a few 2^-24 of the largest score (about 5 at
+# q_scale 1, about 60 at 12) in the exponent, and the float32 sums over the keys behind it
+@pytest.mark.parametrize("dtype,dh", [("bf16", d) for d in (8, 16, 40, 64, 72, 96, 104)] +
+                         [("f32", d) for d in (8, 16, 40, 64, 80, 96, 120, 128)])
+@pytest.mark.parametrize("q_scale,sign,tol", [(1.0, 1.0, 1e-5), (12.0, 1.0, 1e-4), (1.0, -1.0, 1e-5)])
+def test_attention_any(pkg, dtype, dh, q_scale, sign, tol):
+    for i, (B, H, N, cap, ctx_len) in enumerate(SHAPES):
+        if (q_scale > 1 and N < 64) or (sign < 0 and i % 2) or (B == 8 and dh != 64):
+            continue
+        print(f"attention {dtype} dh={dh} B={B} H={H} N={N} ctx={ctx_len} q_scale={q_scale} sign={sign}", flush=True)
+        case = workloads.make_attention_case(i, B, H, N, dh, cap, ctx_len, dtype, q_scale=q_scale)
+        trees = _trees(i, B, N, 128, "chain" if N < 8 else "beam")
+        n_nodes = np.array([t["n_nodes"] for t in trees], dtype=np.int32)
+        q, kt, vt = case.q.copy(), case.k_tree.copy(), case.v_tree.copy()
+        for b in range(B):  # rows beyond the tree may hold anything
+            q[b, :, n_nodes[b]:] = kt[b, :, n_nodes[b]:] = vt[b, :, n_nodes[b]:] = np.nan
+        mask = torch.from_numpy(np.stack([t["anc_mask"] for t in trees]).view(np.int64)).cuda()
+        scale = sign / np.sqrt(dh)
+        ctx = pkg.Context(max_batch=B, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=N, max_heads=H, max_head_dim=dh)
+        args = (to_device(q, dtype), to_device(case.k_cache, dtype), to_device(case.v_cache, dtype), dev_i64(case.kv_off),
+                dev_i32(case.ctx_len), cap, to_device(kt, dtype), to_device(vt, dtype), dev_i32(n_nodes), mask, scale)
+        out = pkg.tree_verify_attn(ctx, *args)
+        again = pkg.tree_verify_attn(ctx, *args)
+        out, again = out.cpu().numpy(), again.cpu().numpy()
+        for b in range(B):
+            n = int(n_nodes[b])
+            ref = oracle.tree_attention(case.q[b], case.k_cache[b], case.v_cache[b], int(case.ctx_len[b]), case.k_tree[b],
+                                        case.v_tree[b], n, trees[b]["mask"], scale)
+            assert np.isfinite(out[b, :, :n]).all()
+            assert rel_err_rms_floor(out[b, :, :n], ref) <= tol
+            assert np.array_equal(out[b, :, :n], again[b, :, :n])
+        ctx.close()

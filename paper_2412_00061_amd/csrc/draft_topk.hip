@@ -340,9 +340,9 @@ __global__ __launch_bounds__(64 * kTileWaves) void lmhead_tile_kernel(LmHeadPara
   const int c = lane & 15, g = lane >> 4;
   const int row_base = blockIdx.x * kRowsPerBlock;
   GemmTileArgs t;
-  t.w = p.w; t.hidden = p.hidden; t.zeros = p.zeros; t.D = p.D; t.V = p.Vp1; t.cols = p.BT; t.row_base = row_base;
+  t.w = p.w; t.hidden = p.hidden; t.zeros = p.zeros; t.D = t.pitch = p.D; t.V = p.Vp1; t.row_base = row_base;
   f32x4 acc[SH::RT][1];
-  gemm_tile<kLmTileDist, SH, EL, ROWS16>(t, smem, acc);
+  gemm_tile<kLmTileDist, SH, EL, ROWS16>(t, TileColumns{p.BT}, smem, acc);
   // (the loop's last barrier has every wavefront done with the LDS tiles)
   float* zbuf = (float*)smem;
   const int col = wc * 16 + c;

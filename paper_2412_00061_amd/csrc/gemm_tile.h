@@ -48,7 +48,7 @@ struct TileShape {
   static constexpr int KK = STEPB / 64;                  // k-blocks of 64 bytes per step
   static constexpr int HS_BYTES = HP * RPP * PITCH, BUF_BYTES = HS_BYTES + ROWS * PITCH;
   static constexpr int LDS_BYTES = 2 * BUF_BYTES;
-  static_assert(WR * WC == kTileWaves && ROWS % RPP == 0 && WP % KK == 0, "tile shape");
+  static_assert(WR * WC == kTileWaves && ROWS % RPP == 0, "tile shape");
 };
 using Tile128x16 = TileShape<8, 1, 256, 1>;
 using Tile128x32 = TileShape<4, 1, 256, 2>;
@@ -76,12 +76,17 @@ struct TileF32 {
 };
 
 struct GemmTileArgs {
-  const void* w;       // [V][D]
-  const void* hidden;  // [cols][D], first column of the tile
+  const void* w;       // [V][pitch], from its first contracted element on
+  const void* hidden;  // [..][pitch], likewise
   const void* zeros;   // 256 bytes of zeros
-  int D, V;
-  int cols;            // live columns, 1 .. COLS
+  int D, V;            // contracted elements, weight rows
+  int pitch;           // elements from row to row, of both operands
   int row_base;        // first weight row of the tile
+};
+// which row of the hidden states a column of the tile is: columns past the end repeat the last one (never read back)
+struct TileColumns {
+  int cols;
+  __device__ __forceinline__ int operator()(int r) const { return r < cols ? r : cols - 1; }
 };
 
 typedef __attribute__((address_space(1))) u32x4 GlobalU32x4;  // a pointer made from an integer is generic otherwise
@@ -94,11 +99,12 @@ inline bool tile_rows16(int D, int elem) { return ((long long)D * elem) % 16 == 
 // acc[rt][ct][i]: row row_base + 16 (RT wr + rt) + 4 (lane >> 4) + i, column 16 CTW wc + 16 ct + (lane & 15),
 // wr = wave / WC, wc = wave % WC.
 // Every wavefront of the workgroup (8) must call it; it ends with a barrier after the last read of LDS.
-template <int DIST, typename SH, typename EL, bool ROWS16>
-__device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* smem, f32x4 (&acc)[SH::RT][SH::CTW]) {
+template <int DIST, typename SH, typename EL, bool ROWS16, typename COLUMNS>
+__device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& columns, unsigned char* smem,
+                                          f32x4 (&acc)[SH::RT][SH::CTW]) {
   constexpr int CTW = SH::CTW, RT = SH::RT, STEPB = SH::STEPB, PITCH = SH::PITCH, CPR = SH::CPR, RPP = SH::RPP;
   constexpr int WP = SH::WP, HP = SH::HP, KK = SH::KK;
-  constexpr int WPK = WP / KK, HPK = (HP + KK - 1) / KK;  // pieces written to LDS per k-block of the step before
+  constexpr int WPK = (WP + KK - 1) / KK, HPK = (HP + KK - 1) / KK;  // pieces written to LDS per k-block of the step before
   constexpr int HS_BYTES = SH::HS_BYTES, BUF_BYTES = SH::BUF_BYTES;
   using Offset = std::conditional_t<ROWS16, unsigned int, size_t>;
   struct Packed16 { u32x4 v; } __attribute__((packed, aligned(EL::ELEM)));  // 16 bytes at an element's alignment
@@ -109,7 +115,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* 
   const int wr = wave / SH::WC, wc = wave % SH::WC;
   const int c = lane & 15, g = lane >> 4;
   const int row_base = t.row_base;
-  const size_t row_bytes = (size_t)t.D * EL::ELEM;
+  const size_t row_bytes = (size_t)t.D * EL::ELEM, pitch = (size_t)t.pitch * EL::ELEM;
   const int total_steps = (int)(row_bytes / STEPB);
   // LDS: buffer b = hidden-state tile (COLS rows) then W tile (ROWS rows)
 
@@ -128,21 +134,17 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* 
     pchunk = lane & 7;
   }
   const unsigned int lane_off = pchunk * 16;
-  const uintptr_t w_addr = (uintptr_t)t.w + (size_t)row_base * row_bytes, h_addr = (uintptr_t)t.hidden;
+  const uintptr_t w_addr = (uintptr_t)t.w + (size_t)row_base * pitch, h_addr = (uintptr_t)t.hidden;
   const uintptr_t z_addr = (uintptr_t)t.zeros;
   Offset woff[WP], hoff[HP];
   const int dst0 = prow * PITCH + pchunk * 16;
 #pragma unroll
   for (int u = 0; u < WP; ++u) {
     const int r = prow + RPP * u, last = t.V - 1 - row_base;
-    woff[u] = (Offset)(r < last ? r : last) * (Offset)row_bytes;  // the ragged last block re-reads the last row
+    woff[u] = (Offset)(r < last ? r : last) * (Offset)pitch;  // the ragged last block re-reads the last row
   }
 #pragma unroll
-  for (int u = 0; u < HP; ++u) {
-    const int r = prow + RPP * u;
-    const int col = r < t.cols ? r : t.cols - 1;  // columns past the end repeat the last one (never read back)
-    hoff[u] = (Offset)col * (Offset)row_bytes;
-  }
+  for (int u = 0; u < HP; ++u) hoff[u] = (Offset)columns(prow + RPP * u) * (Offset)pitch;
   // A request past the last step still issues its loads, so that every wait counts the same loads: it reads
   // a 256-byte block of zeros (in L2, no HBM traffic) and nothing computes from the result.
   u32x4 wreg[DIST][WP], hreg[DIST][HP];
@@ -242,7 +244,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, unsigned char* 
 #pragma unroll
         for (int j = 0; j < WPK; ++j) {
           const int u = kk * WPK + j;
-          *(u32x4*)(ws_next + (dst0 + u * RPP * PITCH)) = wreg[S][u];
+          if (u < WP) *(u32x4*)(ws_next + (dst0 + u * RPP * PITCH)) = wreg[S][u < WP ? u : 0];
         }
       }
       __builtin_amdgcn_sched_barrier(0);

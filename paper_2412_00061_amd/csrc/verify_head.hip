@@ -63,9 +63,9 @@ __global__ __launch_bounds__(64 * kVhWaves) void verify_head_kernel(VerifyHeadPa
   const int row_base = rb * ROWS;
   GemmTileArgs t;
   t.w = p.w; t.hidden = (const unsigned char*)p.hidden + (size_t)col0 * p.D * EL::ELEM; t.zeros = p.zeros;
-  t.D = p.D; t.V = p.V; t.cols = cols; t.row_base = row_base;
+  t.D = t.pitch = p.D; t.V = p.V; t.row_base = row_base;
   f32x4 acc[RT][CTW];
-  gemm_tile<kVhDist, SH, EL, ROWS16>(t, smem, acc);
+  gemm_tile<kVhDist, SH, EL, ROWS16>(t, TileColumns{cols}, smem, acc);
 
   // ---- best (logit, id) key per column ---------------------------------------------------------------------
   // (the loop's last barrier has every wavefront done with the LDS tiles)

@@ -132,3 +132,15 @@ def test_draft_layer_rejects_bad_arguments(pkg):
         pkg.draft_layer_forward(ctx, d["x"], d["w"], d["pos0"], d["kc"], d["vc"], d["off"], d["len"], c.kv_cap, c.H,
                                 500, c.eps, c.theta)
     ctx.close()
+
+
+# column counts around the tile loop's widths and what is left over for the streaming kernel: 17 and 32 (32-column
+# tiles), 33 and 64 (64), 65 and 80 (64, then 1 and 16 through the streaming kernel), 129 (two full passes and one more);
+# k of one and of several trips, weight rows that fill no whole workgroup
+@pytest.mark.parametrize("seed,B,T,D,H,F,ctx_len,cap", [
+    (20, 1, 17, 256, 2, 512, [9], 32), (21, 4, 8, 512, 4, 1280, [0, 31, 32, 40], 64), (22, 3, 11, 256, 4, 768, [5, 70, 1], 80),
+    (23, 8, 8, 512, 8, 256, [1, 2, 3, 0, 60, 7, 33, 8], 64), (24, 5, 13, 256, 2, 256, [4, 5, 6, 7, 8], 16),
+    (25, 2, 40, 512, 4, 512, [3, 90], 96), (26, 3, 43, 256, 4, 512, [0, 64, 10], 64),
+])
+def test_draft_layer_many_columns(pkg, seed, B, T, D, H, F, ctx_len, cap):
+    _check(pkg, seed, B, T, D, H, F, ctx_len, cap)

@@ -5,16 +5,17 @@
 //   * the rows of logits ([V+1] floats per frame, 128 KB at V = 32000) are what costs HBM time.  Each is read
 //     once and its gradient row written once, by one workgroup that holds the row in registers: ctc_row_kernel takes
 //     the log-sum-exp, picks out the few log-probabilities the recursions need (the label's tokens and the
-//     blank) and writes the row's softmax as the gradient; after the recursions ctc_fix_kernel subtracts the
-//     occupancies from those few entries.
-//   * the recursions themselves are KB-sized and sequential in the frames: ctc_dp_kernel, one workgroup per
-//     sequence and direction, a thread per state of the extended sequence (blank, y1, blank, ..., blank), the neighbours'
-//     values through LDS, one barrier per frame.  The forward and the backward recursion of a sequence run at
-//     the same time in two workgroups; the occupancy gamma_t(s) = alpha_t(s) beta_t(s) / (p_t(z_s) P) is formed
-//     where it is used.
+//     blank) and writes the row's softmax as the gradient; after the recursions the occupancies come off those
+//     few entries.
+//   * the recursions themselves are small and sequential in the frames, over the states of the extended sequence (blank,
+//     y1, blank, ..., blank).  Few frames, or many short labels: ctc_short_kernel, a wavefront per sequence that runs
+//     both recursions and subtracts the occupancies.  Otherwise ctc_dp_pipe_kernel, pipelined over blocks of
+//     states, forward and backward at the same time; ctc_fix_kernel then forms the occupancies
+//     gamma_t(s) = alpha_t(s) beta_t(s) / (p_t(z_s) P) where they are used.
 // A token that occurs several times in a label has several states; their occupancies are added in label order
-// by the thread of the first occurrence (links built once per sequence), so no atomic is needed and the result
-// has the same bits on every run.
+// by the thread of the first occurrence, so no atomic is needed and the result has the same bits on every run.
+#include <type_traits>
+
 #include "common.h"
 
 namespace ctcspec {
@@ -22,12 +23,8 @@ namespace ctcspec {
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 
 constexpr int kCtcMaxLabels = 2047;  // L + 1 pairs of states <= 2 per thread of a 1024-thread workgroup
-constexpr int kCtcRowThreads = 1024;  // with two label positions per thread: kCtcMaxLabels + 1 <= 2 * kCtcRowThreads
-constexpr int kCtcMaxRow = 16 * kCtcRowThreads * 4;  // 65536 symbols: 16 16-byte loads per thread
+constexpr int kCtcMaxRow = 16 * 1024 * 4;  // 65536 symbols: 16 16-byte loads per thread of a 1024-thread workgroup
 constexpr int kCtcFixThreads = 256;
-constexpr int kCtcAhead = 8;  // frames between a load and its use in the recursions
-
-static_assert(kCtcMaxLabels + 1 <= 2 * kCtcRowThreads, "ctc_row_kernel fetches two label positions per thread");
 
 struct CtcParams {
   const float* logits;      // [B][T][Vp1]
@@ -38,9 +35,15 @@ struct CtcParams {
   // workspace
   float* lpc;     // [B][T][Lmax + 1]: log2 p_t(y_j) for j < L, log2 p_t(blank) at Lmax
   float* ag;      // [B][T][2 Lmax + 2]: log2 alpha minus the frame's offset (state s at s; the last entry unused)
-  float* bg;      // [B][T][2 Lmax + 2]: log2 beta minus the frame's offset
-  double* coff_a; // [B][T]: offset of the frame's log alpha values
-  double* coff_b; // [B][T]: offset of the frame's log beta values
+  float* bg;      // [B][T][2 Lmax + 2]: log2 beta minus the frame's offset, states counted from the last one
+  double* coff_a; // [B][T][blocks]: offsets of the frame's log alpha values, one per block of pairs of states
+  double* coff_b; // [B][T][blocks]: offsets of the frame's log beta values, pairs counted from the last one
+  int blocks;     // blocks of pairs
+  // the pipelined recursions (null otherwise)
+  unsigned long long* edge;  // [B][2][T][blocks]: what a block hands to the next one, 0: not there yet
+  int* wide;      // [B][T]: 1 when a log-probability of the frame is too low for the pipelined recursion
+  int* ticket;
+  float wide_below;
   double* logp;   // [B]: log2 P(Y | X)
   int32_t* next;  // [B][Lmax]: next label position with the same token, -1: none
   int32_t* first; // [B][Lmax]: 1 when no earlier position holds the same token
@@ -68,15 +71,295 @@ __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? l
 // on 8-byte boundaries
 __host__ __device__ __forceinline__ int ctc_state_pitch(int Lmax) { return 2 * Lmax + 2; }
 
+// One workgroup per frame row, the row held in registers: every load of the row is in flight before the first
+// is used, then log-sum-exp, the few log-probabilities the recursions need (the label's tokens and the blank),
+// and the row's softmax written as the gradient.  Rows start at any multiple of 4 bytes (V + 1 is odd at
+// V = 32000), so the up to three elements in front of the first 16-byte boundary and behind the last go through
+// single lanes and the body through 16-byte loads and stores.
+//
+// Bound: HBM.  Two workgroups of 512 threads with 16 loads each share a compute unit, so that one row's loads run under
+// the other's stores: 2048 x 8 rows of 32001 symbols 769 us a call (5.5 TB/s in and out) against 778 with one workgroup of
+// 1024 threads.
+template <int NV, int THREADS, int NY = 2>  // 16-byte loads and label positions per thread: NV * THREADS * 4 >= V + 1
+__global__ __launch_bounds__(THREADS) void ctc_row_kernel(CtcParams p) {
+  __shared__ float red[THREADS / 64];
+  const int t = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const int Tb = clampi(p.frame_len[b], 0, p.T);
+  const size_t row0 = ((size_t)b * p.T + t) * p.Vp1;
+  int head = (int)((4 - (row0 & 3)) & 3);
+  head = head < p.Vp1 ? head : p.Vp1;
+  const int nvec = (p.Vp1 - head) >> 2;
+  const int tail0 = head + 4 * nvec;
+  // the lane of an edge element: lanes 0..2 take the head, three others the tail
+  constexpr int kTailLane = THREADS > 64 ? 64 : 32;
+  int edge = -1;
+  if (tid < head) edge = tid;
+  else if (tid >= kTailLane && tid - kTailLane < p.Vp1 - tail0) edge = tail0 + tid - kTailLane;
+  float* g = p.grad ? p.grad + row0 : nullptr;
+  if (t >= Tb) {  // frames past the sequence: no gradient
+    if (g) {
+      f32x4* gv = (f32x4*)(g + head);
+      for (int i = tid; i < nvec; i += THREADS) gv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (edge >= 0) g[edge] = 0.f;
+    }
+    return;
+  }
+  if (p.edge && tid == 0) {  // (barriers follow before anything is set)
+    p.wide[(size_t)b * p.T + t] = 0;
+    if (t == 0 && b == 0) *p.ticket = 0;
+  }
+  const float* z = p.logits + row0;
+  const f32x4* zv = (const f32x4*)(z + head);
+  // the label's token ids first (Lmax < NY * THREADS), then the row, then the label's
+  // logits while the row's cache lines are still on their way - asked for later they come from HBM a second time
+  const int L = clampi(p.label_len[b], 0, p.Lmax);
+  int yid[NY];
+#pragma unroll
+  for (int r = 0; r < NY; ++r) {
+    const int j = tid + r * THREADS;
+    yid[r] = j < L ? clampi(p.labels[(size_t)b * p.Lmax + j], 0, p.Vp1 - 1) : p.blank;
+  }
+  f32x4 x[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int i = tid + k * THREADS;
+    x[k] = i < nvec ? zv[i] : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  }
+  float xe = edge >= 0 ? z[edge] : -INFINITY;
+  float zy[NY];
+#pragma unroll
+  for (int r = 0; r < NY; ++r) zy[r] = z[yid[r]];
+  float mx = xe;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) mx = fmaxf(fmaxf(fmaxf(mx, x[k][0]), fmaxf(x[k][1], x[k][2])), x[k][3]);
+  mx = wave_max_f32(mx);
+  if ((tid & 63) == 0) red[tid >> 6] = mx;
+  __syncthreads();
+  mx = red[0];
+#pragma unroll
+  for (int w = 1; w < THREADS / 64; ++w) mx = fmaxf(mx, red[w]);
+  // e = exp(x - max) stays in the registers: the softmax is e / sum
+  xe = expf(xe - mx);
+  float sum = xe;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      x[k][c] = expf(x[k][c] - mx);
+      sum += x[k][c];
+    }
+  }
+  sum = wave_sum_f32(sum);
+  __syncthreads();
+  if ((tid & 63) == 0) red[tid >> 6] = sum;
+  __syncthreads();
+  sum = 0.f;
+#pragma unroll
+  for (int w = 0; w < THREADS / 64; ++w) sum += red[w];
+  const float lse = mx + logf(sum);
+  float* out = p.lpc + ((size_t)b * p.T + t) * (p.Lmax + 1);
+  if (p.edge) {  // uniform
+    for (int i = tid; i < 2 * p.blocks; i += THREADS) {
+      const int dir = i >= p.blocks ? 1 : 0;
+      p.edge[(((size_t)b * 2 + dir) * p.T + t) * p.blocks + (i - dir * p.blocks)] = 0ull;
+    }
+  }
+  constexpr float kLog2e = 1.4426950408889634f;  // the recursions take base-2 logarithms
+#pragma unroll
+  for (int r = 0; r < NY; ++r) {
+    const int j = tid + r * THREADS;
+    const float l = (zy[r] - lse) * kLog2e;
+    if (j < L) out[j] = l;
+    else if (j == L) out[p.Lmax] = l;  // this thread's spare slot fetched the blank
+    if (p.edge && j <= L && l < p.wide_below && l > -INFINITY) p.wide[(size_t)b * p.T + t] = 1;  // cleared above
+  }
+  if (g) {
+    const float inv = 1.f / sum;
+    f32x4* gv = (f32x4*)(g + head);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int i = tid + k * THREADS;
+      if (i < nvec) gv[i] = x[k] * inv;
+    }
+    if (edge >= 0) g[edge] = xe * inv;
+  }
+}
+
+// log2(2^a + 2^b) without a branch (see ctc_log_add3)
+__device__ __forceinline__ float ctc_log_add2(float a, float b) {
+  const float m = fmaxf(a, b);
+  const float ms = m > -INFINITY ? m : 0.f;
+  const float sum = __builtin_amdgcn_exp2f(a - ms) + __builtin_amdgcn_exp2f(b - ms);
+  return ms + __builtin_amdgcn_logf(sum);
+}
+
+// lane i gets lane i - 1's value, lane 0 `first`
+__device__ __forceinline__ unsigned int lane_shift_up(unsigned int v, unsigned int first) {
+  return (unsigned int)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
+}
+// lane i gets lane i + 1's value, lane 63 `last`
+__device__ __forceinline__ float lane_shift_down(float v, float last) {
+  return __uint_as_float((unsigned int)__builtin_amdgcn_update_dpp((int)__float_as_uint(last), (int)__float_as_uint(v),
+                                                                  0x130 /* wave_shl:1 */, 0xf, 0xf, false));
+}
+
+// ---- few frames, or many short labels ------------------------------------------------------------------------------
+// One wavefront per sequence, a lane per pair of states: pair q is the blank in front of label position q (state 2q) and
+// that label's own state (2q + 1); pair L is the final blank alone.  Neighbours' values by lane shifts, no barrier.
+// The forward recursion keeps its rows (in LDS when ROWS_IN_LDS, else in the workspace), the backward one forms the
+// occupancies of a frame as it passes and takes them off the gradient row: one launch where the recursions, the links
+// between equal tokens and the subtraction were three.  Each frame's values are held relative to the largest of the frame
+// before, the offsets summed in double.  A label of 64 tokens or more cannot be reached in the fewer than 64 frames
+// that ROWS_IN_LDS is for; otherwise the host sends only labels below 64 here.
+// Bound: latency of the chain of frames and the scattered entries.  2048 sequences x 8 frames of 32001 symbols: 19.5 us,
+// against 30 us in three kernels.
+constexpr int kShortFrames = 64;  // frames that ctc_short_kernel keeps in LDS: fewer than this
+constexpr int kShortBatch = 8;    // frames whose log-probabilities are fetched together
+
+template <bool ROWS_IN_LDS>
+__global__ __launch_bounds__(64) void ctc_short_kernel(CtcParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char rows_lds[];  // [T][64] pairs, then [T] offsets
+  const int b = blockIdx.x, q = threadIdx.x;
+  const int L = clampi(p.label_len[b], 0, p.Lmax);
+  const int Tb = clampi(p.frame_len[b], 0, p.T);
+  if (Tb == 0) {
+    if (q == 0) p.loss[b] = L == 0 ? 0.f : INFINITY;
+    return;
+  }
+  const int LP = p.Lmax + 1, SP = ctc_state_pitch(p.Lmax);
+  const float* __restrict__ lpc = p.lpc + (size_t)b * p.T * LP;
+  const int32_t* __restrict__ y = p.labels + (size_t)b * p.Lmax;
+  double logP = -(double)INFINITY;
+  const bool has_label = q < L;
+  const int col = has_label ? q : p.Lmax;
+  const int tok = has_label ? y[q] : -1;
+  const int tok_before = (int)lane_shift_up((unsigned)tok, 0u);
+  const bool skip_in = q >= 1 && has_label && tok != tok_before;
+  f32x2* row = ROWS_IN_LDS ? (f32x2*)rows_lds + q : (f32x2*)(p.ag + (size_t)b * p.T * SP) + q;
+  double* offsets = ROWS_IN_LDS ? (double*)(rows_lds + (size_t)p.T * 64 * 8) : p.coff_a + (size_t)b * p.T;
+  const size_t row_step = ROWS_IN_LDS ? 64 : SP / 2;
+  const bool keeps = ROWS_IN_LDS || q <= L;
+  if (L < 64) {
+    float a_blank = q == 0 ? 0.f : -INFINITY, a_label = -INFINITY;  // before the first frame
+    float frame_max = 0.f;
+    double offset = 0.0;
+    for (int t0 = 0; t0 < Tb; t0 += kShortBatch) {
+      float lp[kShortBatch], lb[kShortBatch];
+#pragma unroll
+      for (int i = 0; i < kShortBatch; ++i) {
+        const int t = t0 + i < Tb ? t0 + i : Tb - 1;
+        lp[i] = lpc[(size_t)t * LP + col];
+        lb[i] = lpc[(size_t)t * LP + p.Lmax];
+      }
+#pragma unroll
+      for (int i = 0; i < kShortBatch; ++i) {
+        const int t = t0 + i;
+        if (t >= Tb) break;
+        const float before = __uint_as_float(lane_shift_up(__float_as_uint(a_label), 0xff800000u));
+        const float shift = t > 0 ? frame_shift(frame_max) : 0.f;
+        offset += (double)shift;
+        const float nb = ctc_log_add2(a_blank, before);
+        const float nl = ctc_log_add3(a_label, a_blank, skip_in ? before : -INFINITY);
+        a_blank = q <= L ? nb + (lb[i] - shift) : -INFINITY;
+        a_label = has_label ? nl + (lp[i] - shift) : -INFINITY;
+        if (p.grad && keeps) row[(size_t)t * row_step] = f32x2{a_blank, a_label};
+        if (p.grad && q == 0) offsets[t] = offset;
+        frame_max = wave_max_f32(fmaxf(a_blank, a_label));
+      }
+    }
+    const float before = __uint_as_float(lane_shift_up(__float_as_uint(a_label), 0xff800000u));
+    const float tail = __shfl(ctc_log_add2(a_blank, before), L, 64);
+    logP = offset + (double)tail;  // base 2; -inf when the label cannot be reached
+  }
+  if (q == 0) p.loss[b] = (float)(-logP * 0.6931471805599453);
+  if (!p.grad) return;
+  float* __restrict__ g = p.grad + (size_t)b * p.T * p.Vp1;
+  if (!(logP > -(double)INFINITY)) {  // a label that cannot be reached has no gradient
+    const size_t at = (size_t)b * p.T * p.Vp1, n = (size_t)Tb * p.Vp1;
+    size_t head = (4 - (at & 3)) & 3;
+    head = head < n ? head : n;
+    const size_t body = (n - head) / 4;
+    if ((size_t)q < head) g[q] = 0.f;
+    f32x4* gv = (f32x4*)(g + head);
+    for (size_t i = q; i < body; i += 64) gv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (head + 4 * body + q < n) g[head + 4 * body + q] = 0.f;
+    return;
+  }
+  // positions with this lane's token: the first of them adds the occupancies of all, in label order
+  unsigned long long later = 0ull;
+  bool first = has_label;
+  for (int i = 0; i < L; ++i) {
+    const int ti = (int)readlane_u32((unsigned)tok, i);
+    const bool same = has_label && ti == tok;
+    if (same && i > q) later |= 1ull << i;
+    if (same && i < q) first = false;
+  }
+  if (!first) later = 0ull;
+  const bool repeats = __ballot(later != 0ull) != 0ull;
+  const int entry = clampi(tok, 0, p.Vp1 - 1);
+  const int tok_after = (int)__float_as_uint(lane_shift_down(__uint_as_float((unsigned)tok), 0.f));
+  const bool skip_out = q + 1 < L && tok != tok_after;
+  float b_blank = q == L ? 0.f : -INFINITY, b_label = -INFINITY;  // behind the last frame
+  float frame_max = 0.f;
+  double offset = 0.0;
+  if constexpr (!ROWS_IN_LDS) __syncthreads();  // the rows have reached memory (one wavefront: its own stores)
+  for (int t0 = Tb - 1; t0 >= 0; t0 -= kShortBatch) {
+    float lp[kShortBatch], lb[kShortBatch];
+    f32x2 ar[kShortBatch];
+    double ca[kShortBatch];
+#pragma unroll
+    for (int i = 0; i < kShortBatch; ++i) {
+      const int t = t0 - i >= 0 ? t0 - i : 0;
+      lp[i] = lpc[(size_t)t * LP + col];
+      lb[i] = lpc[(size_t)t * LP + p.Lmax];
+      ar[i] = keeps ? row[(size_t)t * row_step] : f32x2{-INFINITY, -INFINITY};
+      ca[i] = offsets[t];
+    }
+#pragma unroll
+    for (int i = 0; i < kShortBatch; ++i) {
+      const int t = t0 - i;
+      if (t < 0) break;
+      const float next_blank = lane_shift_down(b_blank, -INFINITY), next_label = lane_shift_down(b_label, -INFINITY);
+      const float shift = t < Tb - 1 ? frame_shift(frame_max) : 0.f;
+      offset += (double)shift;
+      const float nb = ctc_log_add2(b_blank, b_label);
+      const float nl = ctc_log_add3(b_label, next_blank, skip_out ? next_label : -INFINITY);
+      b_blank = q <= L ? nb + (lb[i] - shift) : -INFINITY;  // beta_t(s) includes p_t(z_s)
+      b_label = has_label ? nl + (lp[i] - shift) : -INFINITY;
+      frame_max = wave_max_f32(fmaxf(b_blank, b_label));
+      const float z = (float)(logP - ca[i] - offset);
+      auto gamma = [&](float a, float bt, float l) {
+        return (a > -INFINITY && bt > -INFINITY) ? exp2f(a + bt - l - z) : 0.f;
+      };
+      const float gb = gamma(ar[i][0], b_blank, lb[i]), gl = gamma(ar[i][1], b_label, lp[i]);
+      // the occupancies of a frame sum to one: what is left of the recursions' rounding is mostly common to all of them
+      const float blanks = wave_sum_f32(gb), total = blanks + wave_sum_f32(gl);
+      const float inv = total > 0.f ? 1.f / total : 1.f;
+      float tot = gl;
+      if (repeats) {
+        unsigned long long m = later;
+        while (__ballot(m != 0ull) != 0ull) {
+          const float o = __shfl(gl, m ? __ffsll((long long)m) - 1 : 0, 64);
+          if (m) tot += o;
+          m &= m - 1;
+        }
+      }
+      // the entries are written, not updated: the softmax is formed again from the log-probability at hand
+      float* gt = g + (size_t)t * p.Vp1;
+      if (q == 0) gt[p.blank] = exp2f(lb[i]) - blanks * inv;
+      if (first && entry != p.blank) gt[entry] = exp2f(lp[i]) - tot * inv;
+    }
+  }
+}
+
 // per sequence: links between the label positions that hold the same token.  The label is staged in LDS; one
 // wavefront per position looks for the nearest later position with the same token and for any earlier one, 256
-// candidates per round trip to LDS.  The positions of a sequence are dealt to gridDim.y workgroups; every entry
+// candidates per round trip to LDS.  The positions of a sequence are dealt to `parts` workgroups; every entry
 // of next and first is written by the wavefront that owns the position, so the workgroups share nothing.
-__global__ __launch_bounds__(1024) void ctc_links_kernel(CtcParams p) {
-  extern __shared__ int32_t ytok[];  // [Lmax]
-  const int b = blockIdx.x, tid = threadIdx.x, n = blockDim.x;
+__device__ void ctc_links(const CtcParams& p, int b, int part, int parts, int32_t* ytok) {
+  const int tid = threadIdx.x, n = blockDim.x;
   const int lane = tid & 63, nwaves = n >> 6;
-  const int wave = (tid >> 6) + nwaves * blockIdx.y, stride = nwaves * gridDim.y;
+  const int wave = (tid >> 6) + nwaves * part, stride = nwaves * parts;
   const int L = clampi(p.label_len[b], 0, p.Lmax);
   int32_t* next = p.next + (size_t)b * p.Lmax;
   int32_t* first = p.first + (size_t)b * p.Lmax;
@@ -115,295 +398,317 @@ __global__ __launch_bounds__(1024) void ctc_links_kernel(CtcParams p) {
   }
 }
 
-// One workgroup per frame row, the row held in registers: every load of the row is in flight before the first
-// is used, then log-sum-exp, the few log-probabilities the recursions need (the label's tokens and the blank),
-// and the row's softmax written as the gradient.  Rows start at any multiple of 4 bytes (V + 1 is odd at
-// V = 32000), so the up to three elements in front of the first 16-byte boundary and behind the last go through
-// single lanes and the body through 16-byte loads and stores.
-template <int NV, int THREADS>  // 16-byte loads per thread: NV * THREADS * 4 >= V + 1
-__global__ __launch_bounds__(THREADS) void ctc_row_kernel(CtcParams p) {
-  __shared__ float red[THREADS / 64];
-  const int t = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-  const int Tb = clampi(p.frame_len[b], 0, p.T);
-  const size_t row0 = ((size_t)b * p.T + t) * p.Vp1;
-  int head = (int)((4 - (row0 & 3)) & 3);
-  head = head < p.Vp1 ? head : p.Vp1;
-  const int nvec = (p.Vp1 - head) >> 2;
-  const int tail0 = head + 4 * nvec;
-  // the lane of an edge element: lanes 0..2 take the head, lanes 64..66 the tail
-  int edge = -1;
-  if (tid < head) edge = tid;
-  else if (tid >= 64 && tid - 64 < p.Vp1 - tail0) edge = tail0 + tid - 64;
-  float* g = p.grad ? p.grad + row0 : nullptr;
-  if (t >= Tb) {  // frames past the sequence: no gradient
-    if (g) {
-      f32x4* gv = (f32x4*)(g + head);
-      for (int i = tid; i < nvec; i += THREADS) gv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (edge >= 0) g[edge] = 0.f;
+// ---- the recursions, pipelined over blocks of states ---------------------------------------------------------------
+// A state depends on itself and on the two states before it, in the frame before: dependences run one way through the
+// states, so the states are cut into blocks of 64 pairs (a lane per pair) and a block may run as far behind the one before
+// it as it likes.  A workgroup of four wavefronts owns a block of one sequence and direction:
+//   wavefront 0 runs the recursion over kDpFrames frames, neighbours by a lane shift, no barrier between frames;
+//   wavefront 1 fetches and converts the next frames' probabilities and waits for the values that the block before hands over
+//               (the label state of its last pair, frame by frame);
+//   wavefronts 2 and 3 hand over this block's, convert the frames before to what ctc_fix_kernel reads and write them
+//               (half of the frames each: that is as many instructions a frame as the recursion itself).
+// One barrier per kDpFrames frames.  A value handed over is one 64-bit word (never 0) stored and loaded with relaxed
+// device-scope atomics: nothing has to be fenced.  Blocks take their number from a ticket in dependence order, so the
+// block that a workgroup waits for has always been started before it.
+//
+// The values are linear, as mantissa and exponent (m in [0.5, 1), value m * 2^e): three ldexp and a sum take the place of
+// three exp2 and a log2, the relative error of a step is 2^-24 whatever the length of the sequence, and no frame maximum has
+// to be known.  An impossible state has e = kDpFloor; everything below kDpImpossible counts as impossible.  Sequences
+// with a finite log-probability so low that exponents could get there (wide_below: about -32768, a token that is masked
+// out by a large finite number) are left to ctc_dp_wide: log domain, one workgroup, slow.
+//
+// The backward recursion is the forward one over the mirrored sequence (last frame and last state first).
+//
+// Bound: instruction issue of wavefront 0, about 40 instructions a frame (0.1 us).  Measured, 4 sequences of 2048 frames
+// with up to 1024 labels: 217 us.  One workgroup of 1024 threads per sequence and direction, log domain, a barrier and a
+// frame maximum per frame took 1221 us, and its gradient was five times as far from the float64 one (5e-6 against 9e-7).
+constexpr int kDpFrames = 16;
+constexpr int kDpPairs = 64;
+constexpr int kDpThreads = 256;
+constexpr int kDpFloor = -(1 << 30);
+constexpr int kDpZeroP = -(1 << 29);       // exponent of a probability that is 0
+constexpr int kDpImpossible = -(1 << 28);
+constexpr int kDpMaxPolls = 1 << 20;       // about a second; a wait is over long before
+
+static_assert(kCtcMaxLabels * 4 <= 2 * kDpFrames * 64 * 16, "the links' label fits DpShared");
+struct DpShared {
+  u32x2 in[2][kDpFrames][64];   // label probability (m, e) per lane
+  u32x4 uni[2][kDpFrames];      // blank probability (m, e), handed-over value (m, e) of the frame before
+  u32x4 out[2][kDpFrames][64];  // blank (m, e), label (m, e) after the frame
+};
+
+__device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
+
+// the maximum over the wavefront of each of N values, step by step side by side
+template <int N>
+__device__ __forceinline__ void wave_max_i32(int (&v)[N]) {
+#define CTCSPEC_MAX_STEP(ROT) \
+  _Pragma("unroll") for (int u = 0; u < N; ++u) v[u] = imax(v[u], (int)dpp_row_ror<ROT>((unsigned)v[u]));
+  CTCSPEC_MAX_STEP(1)
+  CTCSPEC_MAX_STEP(2)
+  CTCSPEC_MAX_STEP(4)
+  CTCSPEC_MAX_STEP(8)
+#undef CTCSPEC_MAX_STEP
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int a = (int)readlane_u32((unsigned)v[u], 0), b = (int)readlane_u32((unsigned)v[u], 16);
+    const int c = (int)readlane_u32((unsigned)v[u], 32), d = (int)readlane_u32((unsigned)v[u], 48);
+    v[u] = imax(imax(a, b), imax(c, d));
+  }
+}
+
+struct DpValue { float m; int e; };
+// log2 p -> p
+__device__ __forceinline__ DpValue dp_probability(float l) {
+  const float f = floorf(l);
+  DpValue v;
+  v.m = 0.5f * __builtin_amdgcn_exp2f(l - f);  // 2^(l - f) in [1, 2)
+  v.e = l > -INFINITY ? (int)f + 1 : kDpZeroP;
+  if (!(l > -INFINITY) && l == l) v.m = 0.5f;
+  return v;
+}
+__device__ __forceinline__ DpValue dp_scaled(float sum, int e, float pm, int pe) {
+  const float s = sum * pm;
+  DpValue v;
+  v.m = __builtin_amdgcn_frexp_mantf(s);
+  v.e = imax(e + __builtin_amdgcn_frexp_expf(s) + pe, kDpFloor);
+  return v;
+}
+
+// One workgroup, any log-probabilities: frame by frame through the rows of `g` themselves, log domain, every frame relative
+// to the largest value of the frame before.
+__device__ void ctc_dp_wide(const CtcParams& p, int b, bool backward, int L, int Tb) {
+  __shared__ float wmax[kDpThreads / 64];
+  const int tid = threadIdx.x, SP = ctc_state_pitch(p.Lmax);
+  const int32_t* y = p.labels + (size_t)b * p.Lmax;
+  float* g = (backward ? p.bg : p.ag) + (size_t)b * p.T * SP;
+  double* coff = (backward ? p.coff_b : p.coff_a) + (size_t)b * p.T * p.blocks;
+  double offset = 0.0;
+  float frame_max = -INFINITY;
+  for (int i = 0; i < Tb; ++i) {
+    const int t = backward ? Tb - 1 - i : i, tp = backward ? t + 1 : t - 1;
+    const float* lp = p.lpc + ((size_t)b * p.T + t) * (p.Lmax + 1);
+    const float* prev = g + (size_t)(i ? tp : t) * SP;
+    float* cur = g + (size_t)t * SP;
+    const float shift = i ? frame_shift(frame_max) : 0.f;
+    offset += (double)shift;
+    float mine = -INFINITY;
+    for (int q = tid; q <= L; q += kDpThreads) {
+      const int j = backward ? L - 1 - q : q, jb = backward ? L - q : q - 1;  // label of the pair, of the pair before
+      const bool skip = q >= 1 && q < L && y[j] != y[jb];
+      float a_blank = q == 0 ? 0.f : -INFINITY, a_label = q == 0 ? 0.f : -INFINITY;
+      if (i) {
+        const float before = q ? prev[2 * q - 1] : -INFINITY;
+        a_blank = ctc_log_add2(prev[2 * q], before);
+        a_label = q < L ? ctc_log_add3(prev[2 * q + 1], prev[2 * q], skip ? before : -INFINITY) : -INFINITY;
+      }
+      a_blank += lp[p.Lmax] - shift;
+      a_label = q < L ? a_label + (lp[j] - shift) : -INFINITY;
+      cur[2 * q] = a_blank;
+      cur[2 * q + 1] = a_label;
+      mine = fmaxf(mine, fmaxf(a_blank, a_label));
     }
+    for (int w = tid; w < p.blocks; w += kDpThreads) coff[(size_t)t * p.blocks + w] = offset;
+    mine = wave_max_f32(mine);
+    if ((tid & 63) == 0) wmax[tid >> 6] = mine;
+    __syncthreads();
+    frame_max = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+    __syncthreads();
+  }
+  if (tid == 0 && !backward) {
+    const float* last = g + (size_t)(Tb - 1) * SP;
+    const double logP = offset + (double)ctc_log_add2(last[2 * L], L > 0 ? last[2 * L - 1] : -INFINITY);
+    p.loss[b] = (float)(-logP * 0.6931471805599453);
+    p.logp[b] = logP;
+  }
+}
+
+// Workgroups beyond the recursions' `jobs` build the links of the labels meanwhile.
+__global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, int directions, int jobs) {
+  __shared__ DpShared sh;
+  __shared__ int job_id;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (tid == 0) job_id = atomicAdd(p.ticket, 1);
+  __syncthreads();
+  const int job = __builtin_amdgcn_readfirstlane(job_id);
+  if (job >= jobs) {
+    const int b = (job - jobs) % p.B;
+    ctc_links(p, b, (job - jobs) / p.B, ((int)gridDim.x - jobs) / p.B, (int32_t*)&sh);
     return;
   }
-  const float* z = p.logits + row0;
-  const f32x4* zv = (const f32x4*)(z + head);
-  // the label's token ids first (kCtcMaxLabels < 2 * THREADS: two per thread), then the row, then the label's
-  // logits while the row's cache lines are still on their way - asked for later they come from HBM a second time
+  const int block = job / (directions * p.B), rest = job - block * (directions * p.B);
+  const int b = rest / directions;
+  const bool backward = rest - b * directions != 0;
   const int L = clampi(p.label_len[b], 0, p.Lmax);
-  int yid[2];
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int j = tid + r * THREADS;
-    yid[r] = j < L ? clampi(p.labels[(size_t)b * p.Lmax + j], 0, p.Vp1 - 1) : p.blank;
-  }
-  f32x4 x[NV];
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const int i = tid + k * THREADS;
-    x[k] = i < nvec ? zv[i] : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  }
-  float xe = edge >= 0 ? z[edge] : -INFINITY;
-  const float zy[2] = {z[yid[0]], z[yid[1]]};
-  float mx = xe;
-#pragma unroll
-  for (int k = 0; k < NV; ++k) mx = fmaxf(fmaxf(fmaxf(mx, x[k][0]), fmaxf(x[k][1], x[k][2])), x[k][3]);
-  mx = wave_max_f32(mx);
-  if ((tid & 63) == 0) red[tid >> 6] = mx;
-  __syncthreads();
-  mx = red[0];
-#pragma unroll
-  for (int w = 1; w < THREADS / 64; ++w) mx = fmaxf(mx, red[w]);
-  // e = exp(x - max) stays in the registers: the softmax is e / sum
-  xe = expf(xe - mx);
-  float sum = xe;
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      x[k][c] = expf(x[k][c] - mx);
-      sum += x[k][c];
-    }
-  }
-  sum = wave_sum_f32(sum);
-  __syncthreads();
-  if ((tid & 63) == 0) red[tid >> 6] = sum;
-  __syncthreads();
-  sum = 0.f;
-#pragma unroll
-  for (int w = 0; w < THREADS / 64; ++w) sum += red[w];
-  const float lse = mx + logf(sum);
-  float* out = p.lpc + ((size_t)b * p.T + t) * (p.Lmax + 1);
-  constexpr float kLog2e = 1.4426950408889634f;  // the recursions take base-2 logarithms
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int j = tid + r * THREADS;
-    if (j < L) out[j] = (zy[r] - lse) * kLog2e;
-    else if (j == L) out[p.Lmax] = (zy[r] - lse) * kLog2e;  // this thread's spare slot fetched the blank
-  }
-  if (g) {
-    const float inv = 1.f / sum;
-    f32x4* gv = (f32x4*)(g + head);
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      const int i = tid + k * THREADS;
-      if (i < nvec) gv[i] = x[k] * inv;
-    }
-    if (edge >= 0) g[edge] = xe * inv;
-  }
-}
-
-// log2(2^a + 2^b) without a branch (see ctc_log_add3)
-__device__ __forceinline__ float ctc_log_add2(float a, float b) {
-  const float m = fmaxf(a, b);
-  const float ms = m > -INFINITY ? m : 0.f;
-  const float sum = __builtin_amdgcn_exp2f(a - ms) + __builtin_amdgcn_exp2f(b - ms);
-  return ms + __builtin_amdgcn_logf(sum);
-}
-
-// Two workgroups per sequence, on different compute units at the same time: blockIdx.y = 0 runs the forward
-// recursion (log alpha, the loss), blockIdx.y = 1 the backward one (log beta).  Neither needs the other's values;
-// the occupancies that need both are formed afterwards, in ctc_fix_kernel.
-//
-// A thread owns pairs of states: pair q is the blank in front of label position q (state 2q) and that label's own
-// state (2q + 1); pair L is the final blank alone.  The two states of a pair share their neighbours' values (three
-// LDS reads forward, four backward, instead of three per state), the blank needs a two-way log-add and only the
-// label a three-way one, and no lane has to find out which kind of state it holds.
-template <int NP>  // pairs per thread
-__global__ __launch_bounds__(1024) void ctc_dp_kernel(CtcParams p) {
-  extern __shared__ __attribute__((aligned(16))) float lds[];  // two rows of 2 Lmax + 6 values, -inf around the states
-  const int b = blockIdx.x, tid = threadIdx.x, nthreads = blockDim.x;
-  const bool backward = blockIdx.y != 0;
-  const int SP = ctc_state_pitch(p.Lmax);
-  const int L = clampi(p.label_len[b], 0, p.Lmax);
-  const int S = 2 * L + 1;
   const int Tb = clampi(p.frame_len[b], 0, p.T);
-  const int pitch = 2 * p.Lmax + 6;  // even: state 2q of either row sits on an 8-byte boundary
-  // The largest value of a frame: every wavefront's maximum goes into one LDS word with an atomic max.  Three
-  // words in turn: frame t collects into word t % 3, reads word (t - 1) % 3 and resets word (t + 1) % 3, which
-  // was last read before the barrier of frame t - 1 and is next written after the barrier of frame t.
-  __shared__ float fmax3[3];
-  const int32_t* y = p.labels + (size_t)b * p.Lmax;
-  const float* lpc = p.lpc + (size_t)b * p.T * (p.Lmax + 1);
+  if (block * kDpPairs > L) return;
+  const bool last_block = (block + 1) * kDpPairs > L;
   if (Tb == 0) {
-    if (tid == 0 && !backward) {
+    if (tid == 0 && !backward && block == 0) {
       p.loss[b] = L == 0 ? 0.f : INFINITY;
       p.logp[b] = L == 0 ? 0.0 : -(double)INFINITY;
     }
     return;
   }
-  // per pair of this thread: whether the pair (its blank) and its label state exist, the label's entry in a
-  // frame's compact row, and whether the transition that skips the blank exists into the label state (from
-  // state 2q - 1) / out of it (to state 2q + 3)
-  int col[NP];
-  bool has_pair[NP], has_label[NP], skip_in[NP], skip_out[NP];
-#pragma unroll
-  for (int u = 0; u < NP; ++u) {
-    const int q = tid + u * nthreads;
-    has_pair[u] = q <= L;
-    has_label[u] = q < L;
-    col[u] = q < L ? q : p.Lmax;  // pairs without a label read the blank's entry and drop it
-    skip_in[u] = q >= 1 && q < L && y[q] != y[q - 1];
-    skip_out[u] = q + 1 < L && y[q] != y[q + 1];
+  int too_low = 0;
+  for (int t = tid; t < Tb; t += kDpThreads) too_low |= p.wide[(size_t)b * p.T + t];
+  if (__syncthreads_or(too_low)) {
+    if (block == 0) ctc_dp_wide(p, b, backward, L, Tb);
+    return;
   }
-  for (int i = tid; i < 2 * pitch; i += nthreads) lds[i] = -INFINITY;
-  if (tid < 3) fmax3[tid] = -INFINITY;
-  __syncthreads();
-
-  // A frame's log-probabilities are loaded several frames before the frame's turn, into a ring of registers: the
-  // chain from frame to frame then runs through LDS and arithmetic only.  The barrier of a frame orders LDS
-  // alone, so these loads and the stores of the frame's results stay in flight across it.
-  constexpr int AHEAD = kCtcAhead;
-  const int lp_pitch = p.Lmax + 1;
-  float lpr[AHEAD][NP], lpb[AHEAD];
-
-  if (!backward) {
-    float* ag = p.ag + (size_t)b * p.T * SP;
-    double* coff = p.coff_a + (size_t)b * p.T;
-#pragma unroll
-    for (int i = 0; i < AHEAD; ++i) {
-      const int tt = i < Tb ? i : Tb - 1;
-      lpb[i] = lpc[(size_t)tt * lp_pitch + p.Lmax];
-#pragma unroll
-      for (int u = 0; u < NP; ++u) lpr[i][u] = lpc[(size_t)tt * lp_pitch + col[u]];
+  const int q = block * kDpPairs + lane;
+  const int32_t* y = p.labels + (size_t)b * p.Lmax;
+  const int j = backward ? L - 1 - q : q, jb = backward ? L - q : q - 1;  // label of the pair, of the pair before
+  const bool has_label = q < L;
+  const int SP = ctc_state_pitch(p.Lmax), LP = p.Lmax + 1;
+  const float* lpc = p.lpc + (size_t)b * p.T * LP;
+  unsigned long long* edge = p.edge + ((size_t)b * 2 + (backward ? 1 : 0)) * p.T * p.blocks;
+  const int chunks = (Tb + kDpFrames - 1) / kDpFrames;
+  // frame i of the recursion (0 .. Tb-1) is frame i or Tb - 1 - i of the sequence
+  auto frame = [&](int i) { return backward ? Tb - 1 - i : i; };
+  bool lost = false;  // a wait was given up: not a number from there on
+  constexpr unsigned long long kNothing = ((unsigned long long)(unsigned)kDpFloor << 32) | 0x3f000000u;  // 0.5 * 2^kDpFloor
+  auto look = [&](int i) -> unsigned long long {  // per lane: the value of frame i from the block before, 0: not there yet
+    if (block == 0 || i < 0 || i >= Tb) return kNothing;
+    return __hip_atomic_load(edge + (size_t)frame(i) * p.blocks + (block - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto wait_for = [&](int i, unsigned long long v) -> unsigned long long {  // v: what look(i) has given before
+    for (int polls = 0; !v && !lost; ++polls) {
+      __builtin_amdgcn_s_sleep(1);
+      v = look(i);
+      lost = polls >= kDpMaxPolls;
     }
-    double c_alpha = 0.0;  // the stored values of the frame are log alpha - c_alpha
-    int slot_prev = 2, slot = 0, slot_next = 1;
-    for (int t0 = 0; t0 < Tb; t0 += AHEAD) {
+    return v ? v : 0x7fc00000ull;
+  };
+
+  if (wave == 0) {
+    const bool skip = q >= 1 && q < L && y[j] != y[jb];
+    // before the first frame: all of the weight in the first blank
+    float bm = 0.5f, lm = 0.5f;
+    int be = q == 0 ? 1 : kDpFloor, le = kDpFloor;
+    lds_barrier();  // LDS only: loads and stores of memory stay in flight
+    auto frames_of = [&](int ch, auto partial) __attribute__((always_inline)) {
+      const int buf = ch & 1;
 #pragma unroll
-      for (int i = 0; i < AHEAD; ++i) {
-        const int t = t0 + i;
-        if (t < Tb) {
-          float* cur = lds + 2 + (t & 1) * pitch;  // offsets, not a table of pointers: keeps these LDS accesses
-          const float* prev = lds + 2 + ((t & 1) ^ 1) * pitch;
-          float shift = 0.f;
-          if (t > 0) {
-            shift = frame_shift(fmax3[slot_prev]);
-            c_alpha += (double)shift;
-          }
-          float mine = -INFINITY;
-#pragma unroll
-          for (int u = 0; u < NP; ++u) {
-            const int q = tid + u * nthreads;
-            if (has_pair[u]) {
-              float a_blank, a_label;
-              if (t == 0) {
-                a_blank = q == 0 ? 0.f : -INFINITY;
-                a_label = q == 0 ? 0.f : -INFINITY;
-              } else {
-                const float before = prev[2 * q - 1];
-                const f32x2 own = *(const f32x2*)(prev + 2 * q);
-                a_blank = ctc_log_add2(own[0], before);
-                a_label = ctc_log_add3(own[1], own[0], skip_in[u] ? before : -INFINITY);
-              }
-              a_blank += lpb[i] - shift;
-              a_label = has_label[u] ? a_label + (lpr[i][u] - shift) : -INFINITY;
-              const f32x2 both = {a_blank, a_label};
-              *(f32x2*)(cur + 2 * q) = both;
-              *(f32x2*)(ag + (size_t)t * SP + 2 * q) = both;
-              mine = fmaxf(mine, fmaxf(a_blank, a_label));
-            }
-          }
-          mine = wave_max_f32(mine);
-          if ((tid & 63) == 0) __hip_atomic_fetch_max(&fmax3[slot], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (tid == 0) {
-            fmax3[slot_next] = -INFINITY;
-            coff[t] = c_alpha;
-          }
-          slot_prev = slot; slot = slot_next; slot_next = slot_next == 2 ? 0 : slot_next + 1;
-          const int tn = t + AHEAD < Tb ? t + AHEAD : Tb - 1;
-          lpb[i] = lpc[(size_t)tn * lp_pitch + p.Lmax];
-#pragma unroll
-          for (int u = 0; u < NP; ++u) lpr[i][u] = lpc[(size_t)tn * lp_pitch + col[u]];
-          lds_barrier();
-        }
+      for (int f = 0; f < kDpFrames; ++f) {
+        const u32x2 pr = sh.in[buf][f][lane];
+        const u32x4 un = sh.uni[buf][f];
+        const float xm = __uint_as_float(lane_shift_up(__float_as_uint(lm), un[2]));
+        const int xe = (int)lane_shift_up((unsigned)le, un[3]);
+        const int e0 = imax(be, xe);
+        const float s0 = __builtin_amdgcn_ldexpf(bm, be - e0) + __builtin_amdgcn_ldexpf(xm, xe - e0);
+        const int ke = skip ? xe : kDpFloor;
+        const int e1 = imax(imax(le, be), ke);
+        const float s1 = __builtin_amdgcn_ldexpf(lm, le - e1) + __builtin_amdgcn_ldexpf(bm, be - e1) +
+                         __builtin_amdgcn_ldexpf(xm, ke - e1);
+        const DpValue nb = dp_scaled(s0, e0, __uint_as_float(un[0]), (int)un[1]);
+        const DpValue nl = dp_scaled(s1, e1, __uint_as_float(pr[0]), (int)pr[1]);
+        const bool run = !decltype(partial)::value || ch * kDpFrames + f < Tb;  // frames past the end change nothing
+        bm = run ? nb.m : bm;
+        be = run ? nb.e : be;
+        lm = run ? nl.m : lm;
+        le = run ? nl.e : le;
+        sh.out[buf][f][lane] = u32x4{__float_as_uint(bm), (unsigned)be, __float_as_uint(lm), (unsigned)le};
+      }
+    };
+    for (int ch = 0; ch <= chunks; ++ch) {
+      if ((ch + 1) * kDpFrames <= Tb) frames_of(ch, std::false_type{});
+      else if (ch < chunks) frames_of(ch, std::true_type{});
+      lds_barrier();
+    }
+    if (!backward && last_block) {
+      // P = the last blank + the label before it
+      unsigned int fm = __float_as_uint(0.5f), fe = (unsigned)kDpFloor;
+      if (block > 0 && L == block * kDpPairs) {
+        const unsigned long long v = wait_for(Tb - 1, look(Tb - 1));
+        fm = (unsigned)v;
+        fe = (unsigned)(v >> 32);
+      }
+      const float xm = __uint_as_float(lane_shift_up(__float_as_uint(lm), fm));
+      const int xe = (int)lane_shift_up((unsigned)le, fe);
+      if (q == L) {
+        const int e = imax(be, xe);
+        const float s = __builtin_amdgcn_ldexpf(bm, be - e) + __builtin_amdgcn_ldexpf(xm, xe - e);
+        const double logP = e < kDpImpossible ? -(double)INFINITY : (double)e + (double)__builtin_amdgcn_logf(s);
+        p.loss[b] = (float)(-logP * 0.6931471805599453);
+        p.logp[b] = logP;
       }
     }
-    const float* last = lds + 2 + ((Tb - 1) & 1) * pitch;
-    const float tail = ctc_log_add2(last[S - 1], S > 1 ? last[S - 2] : -INFINITY);
-    const double logP = c_alpha + (double)tail;  // base 2; -inf when the label cannot be reached
-    if (tid == 0) {
-      p.loss[b] = (float)(-logP * 0.6931471805599453);
-      p.logp[b] = logP;
+  } else if (wave == 1) {
+    const int col = has_label ? j : p.Lmax;
+    float lp[kDpFrames], lb = 0.f;
+    unsigned long long early = 0ull;
+    auto fetch = [&](int ch) {
+      if (lane < kDpFrames) early = look(ch * kDpFrames + lane - 1);
+#pragma unroll
+      for (int f = 0; f < kDpFrames; ++f) {
+        const int i = ch * kDpFrames + f;
+        lp[f] = lpc[(size_t)frame(i < Tb ? i : Tb - 1) * LP + col];
+      }
+      const int i = ch * kDpFrames + (lane & (kDpFrames - 1));
+      lb = lpc[(size_t)frame(i < Tb ? i : Tb - 1) * LP + p.Lmax];
+    };
+    auto prepare = [&](int ch) {  // chunk ch, whose log-probabilities are in lp / lb; fetches the next one's
+      const int buf = ch & 1;
+#pragma unroll
+      for (int f = 0; f < kDpFrames; ++f) {
+        const DpValue v = dp_probability(lp[f]);
+        sh.in[buf][f][lane] = u32x2{__float_as_uint(v.m), has_label ? (unsigned)v.e : (unsigned)kDpZeroP};
+      }
+      const DpValue vb = dp_probability(lb);
+      if (lane < kDpFrames) {
+        const unsigned long long h = wait_for(ch * kDpFrames + lane - 1, early);
+        sh.uni[buf][lane] = u32x4{__float_as_uint(vb.m), (unsigned)vb.e, (unsigned)h, (unsigned)(h >> 32)};
+      }
+      if (ch + 1 < chunks) fetch(ch + 1);
+    };
+    fetch(0);
+    prepare(0);
+    lds_barrier();
+    for (int ch = 0; ch <= chunks; ++ch) {
+      if (ch + 1 < chunks) prepare(ch + 1);
+      lds_barrier();
     }
   } else {
-    float* bg = p.bg + (size_t)b * p.T * SP;
-    double* coff = p.coff_b + (size_t)b * p.T;
+    float* g = (backward ? p.bg : p.ag) + (size_t)b * p.T * SP + 2 * q;
+    double* coff = (backward ? p.coff_b : p.coff_a) + (size_t)b * p.T * p.blocks + block;
+    lds_barrier();
+    for (int ch = 0; ch <= chunks; ++ch) {
+      if (ch > 0) {
+        const int buf = (ch - 1) & 1, i0 = (ch - 1) * kDpFrames;
+        if (wave == 2 && !last_block && lane < kDpFrames && i0 + lane < Tb) {
+          const u32x4 v = sh.out[buf][lane][63];
+          __hip_atomic_store(edge + (size_t)frame(i0 + lane) * p.blocks + block, ((unsigned long long)v[3] << 32) | v[2],
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (directions == 2) {  // (the loss alone needs no rows)
+          constexpr int kGroup = 4;  // frames side by side: the chain of a frame is long and narrow
 #pragma unroll
-    for (int i = 0; i < AHEAD; ++i) {
-      const int tt = Tb - 1 - i >= 0 ? Tb - 1 - i : 0;
-      lpb[i] = lpc[(size_t)tt * lp_pitch + p.Lmax];
+          for (int f0 = 0; f0 < kDpFrames / 2; f0 += kGroup) {
+            const int first = (wave - 2) * (kDpFrames / 2) + f0;
+            u32x4 v[kGroup];
+            int ref[kGroup];
 #pragma unroll
-      for (int u = 0; u < NP; ++u) lpr[i][u] = lpc[(size_t)tt * lp_pitch + col[u]];
-    }
-    double c_beta = 0.0;  // the stored values of the frame are log beta - c_beta
-    int slot_prev = 2, slot = 0, slot_next = 1;
-    for (int t0 = Tb - 1; t0 >= 0; t0 -= AHEAD) {
+            for (int u = 0; u < kGroup; ++u) v[u] = sh.out[buf][first + u][lane];
 #pragma unroll
-      for (int i = 0; i < AHEAD; ++i) {
-        const int t = t0 - i;
-        if (t >= 0) {
-          float* cur = lds + 2 + (t & 1) * pitch;
-          const float* nxt = lds + 2 + ((t & 1) ^ 1) * pitch;
-          float shift = 0.f;
-          if (t < Tb - 1) {
-            shift = frame_shift(fmax3[slot_prev]);
-            c_beta += (double)shift;
-          }
-          float mine = -INFINITY;
+            for (int u = 0; u < kGroup; ++u) ref[u] = q <= L ? imax((int)v[u][1], (int)v[u][3]) : kDpFloor;
+            wave_max_i32(ref);
 #pragma unroll
-          for (int u = 0; u < NP; ++u) {
-            const int q = tid + u * nthreads;
-            if (has_pair[u]) {
-              float b_blank, b_label;
-              if (t == Tb - 1) {
-                b_blank = q == L ? 0.f : -INFINITY;
-                b_label = q == L - 1 ? 0.f : -INFINITY;
-              } else {
-                const f32x2 own = *(const f32x2*)(nxt + 2 * q);        // states 2q, 2q + 1
-                const f32x2 after = *(const f32x2*)(nxt + 2 * q + 2);  // states 2q + 2, 2q + 3
-                b_blank = ctc_log_add2(own[0], own[1]);
-                b_label = ctc_log_add3(own[1], after[0], skip_out[u] ? after[1] : -INFINITY);
-              }
-              b_blank += lpb[i] - shift;  // beta_t(s) includes p_t(z_s)
-              b_label = has_label[u] ? b_label + (lpr[i][u] - shift) : -INFINITY;
-              const f32x2 both = {b_blank, b_label};
-              *(f32x2*)(cur + 2 * q) = both;
-              *(f32x2*)(bg + (size_t)t * SP + 2 * q) = both;
-              mine = fmaxf(mine, fmaxf(b_blank, b_label));
+            for (int u = 0; u < kGroup; ++u) {
+              const int be = (int)v[u][1], le = (int)v[u][3];
+              const f32x2 x = {
+                  be < kDpImpossible ? -INFINITY : (float)(be - ref[u]) + __builtin_amdgcn_logf(__uint_as_float(v[u][0])),
+                  le < kDpImpossible ? -INFINITY : (float)(le - ref[u]) + __builtin_amdgcn_logf(__uint_as_float(v[u][2]))};
+              const int i = i0 + first + u;
+              const size_t t = (size_t)frame(i);
+              if (i < Tb && q <= L) *(f32x2*)(g + t * SP) = x;
+              if (i < Tb && lane == 0) coff[t * p.blocks] = (double)ref[u];
             }
           }
-          mine = wave_max_f32(mine);
-          if ((tid & 63) == 0) __hip_atomic_fetch_max(&fmax3[slot], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (tid == 0) {
-            fmax3[slot_next] = -INFINITY;
-            coff[t] = c_beta;
-          }
-          slot_prev = slot; slot = slot_next; slot_next = slot_next == 2 ? 0 : slot_next + 1;
-          const int tn = t - AHEAD >= 0 ? t - AHEAD : 0;
-          lpb[i] = lpc[(size_t)tn * lp_pitch + p.Lmax];
-#pragma unroll
-          for (int u = 0; u < NP; ++u) lpr[i][u] = lpc[(size_t)tn * lp_pitch + col[u]];
-          lds_barrier();
         }
       }
+      lds_barrier();
     }
   }
 }
@@ -427,10 +732,14 @@ __global__ __launch_bounds__(kCtcFixThreads) void ctc_fix_kernel(CtcParams p) {
   const float* __restrict__ al = p.ag + frame * SP;
   const float* __restrict__ be = p.bg + frame * SP;
   const float* __restrict__ lp = p.lpc + frame * (p.Lmax + 1);
-  // log of P over the two offsets of this frame: what the stored alpha + beta - log p is measured against
-  const float z = (float)(logP - p.coff_a[frame] - p.coff_b[frame]);
-  auto gamma = [&](int s, float l) {
-    const float a = al[s], bt = be[s];
+  // log of P over the two offsets of a state: what its stored alpha + beta - log p is measured against
+  const double* __restrict__ ca = p.coff_a + frame * p.blocks;
+  const double* __restrict__ cb = p.coff_b + frame * p.blocks;
+  constexpr int kBlockStates = 2 * kDpPairs;
+  auto gamma = [&](int s, float l) {  // beta's states are counted from the last one
+    const int m = 2 * L - s;
+    const float a = al[s], bt = be[m];
+    const float z = (float)(logP - ca[s / kBlockStates] - cb[m / kBlockStates]);
     return (a > -INFINITY && bt > -INFINITY) ? exp2f(a + bt - l - z) : 0.f;  // base-2 logarithms throughout
   };
   // The occupancies of a frame sum to one (every alignment is in exactly one state at frame t).  What is left
@@ -470,20 +779,34 @@ __global__ __launch_bounds__(kCtcFixThreads) void ctc_fix_kernel(CtcParams p) {
 }
 
 struct CtcWorkspace {
-  size_t lpc, ag, bg, coff_a, coff_b, logp, next, first, total;
+  size_t lpc, ag, bg, coff_a, coff_b, logp, next, first, edge, wide, ticket, total;
 };
+// Which kernel runs the recursions.  Few frames leave the pipeline nothing to fill; with short labels (one block of
+// states) and more sequences than two rounds of the pipelined kernel's workgroups (three per compute unit, by their
+// LDS), a wavefront per sequence is the better use of it: 80 frames of 501 symbols, up to 20 labels, whole call, 400 /
+// 600 / 1000 sequences: pipelined 83 / 114 / 176 us, a wavefront each 100 / 120 / 153.
+static bool ctc_pipelined(int B, int T, int Lmax) { return T >= kShortFrames && (Lmax >= kDpPairs || B <= 768); }
 static CtcWorkspace ctc_workspace(int B, int T, int Lmax) {
   CtcWorkspace w;
   size_t off = 0;
   auto carve = [&](size_t bytes) { size_t at = off; off = (off + bytes + 255) / 256 * 256; return at; };
+  const bool pipelined = ctc_pipelined(B, T, Lmax);
+  const size_t blocks = pipelined ? Lmax / kDpPairs + 1 : 1;
   w.lpc = carve((size_t)B * T * (Lmax + 1) * 4);
+  // (one size for a shape whatever kernel it takes, but for what the pipeline adds)
   w.ag = carve((size_t)B * T * ctc_state_pitch(Lmax) * 4);
   w.bg = carve((size_t)B * T * ctc_state_pitch(Lmax) * 4);
-  w.coff_a = carve((size_t)B * T * 8);
-  w.coff_b = carve((size_t)B * T * 8);
+  w.coff_a = carve((size_t)B * T * blocks * 8);
+  w.coff_b = carve((size_t)B * T * blocks * 8);
   w.logp = carve((size_t)B * 8);
   w.next = carve((size_t)B * Lmax * 4);
   w.first = carve((size_t)B * Lmax * 4);
+  w.edge = w.wide = w.ticket = off;
+  if (pipelined) {
+    w.edge = carve((size_t)B * 2 * T * blocks * 8);
+    w.wide = carve((size_t)B * T * 4);
+    w.ticket = carve(4);
+  }
   w.total = off;
   return w;
 }
@@ -492,7 +815,7 @@ static CtcWorkspace ctc_workspace(int B, int T, int Lmax) {
 // triggers a load, so it can be the first thing a stream capture records)
 hipError_t prepare_ctc_loss() {
   hipFuncAttributes attr;
-  return hipFuncGetAttributes(&attr, (const void*)ctc_links_kernel);
+  return hipFuncGetAttributes(&attr, (const void*)ctc_fix_kernel);
 }
 
 }  // namespace ctcspec
@@ -530,26 +853,44 @@ extern "C" int ctc_loss(ctcspec_ctx* ctx, const float* logits, const int32_t* la
   p.coff_a = (double*)(ws + w.coff_a); p.coff_b = (double*)(ws + w.coff_b); p.logp = (double*)(ws + w.logp);
   p.next = (int32_t*)(ws + w.next); p.first = (int32_t*)(ws + w.first);
   p.loss = loss; p.grad = grad;
+  const bool pipelined = ctc_pipelined(B, T, Lmax);
+  p.blocks = pipelined ? Lmax / kDpPairs + 1 : 1;
+  p.edge = pipelined ? (unsigned long long*)(ws + w.edge) : nullptr;
+  p.wide = (int*)(ws + w.wide); p.ticket = (int*)(ws + w.ticket);
+  p.wide_below = -fminf(32768.f, (float)(1 << 28) / (float)T);  // T of them stay above the pipelined recursion's floor
+  const int directions = grad ? 2 : 1;
+  const int link_parts = (Lmax + 31) / 32;  // eight positions per wavefront
+  const long long jobs = (long long)B * directions * p.blocks, groups = jobs + (grad ? (long long)B * link_parts : 0);
+  CTCSPEC_REQUIRE(ctx, !pipelined || groups <= 0x7fffffffLL, CTCSPEC_EUNSUPPORTED, "ctc_loss: grid too large");
   hipStream_t st = ctx->stream;
-  const int link_blocks = Lmax > 256 ? (Lmax + 127) / 128 : 1;  // eight positions per wavefront at the most
-  hipLaunchKernelGGL(ctc_links_kernel, dim3(B, link_blocks), dim3(Lmax > 256 ? 1024 : 256), Lmax * 4, st, p);
+  // The fewest threads that hold the row with at most eight 16-byte loads each (512 threads: sixteen, see the kernel) and
+  // the label with NY positions each: many short rows cost their workgroups' start and barriers (9100 rows of 616
+  // symbols: the call took 64 us with 1024 threads a row, 25 with 64).
+  const dim3 rows(T, B);
+  auto row_launch = [&](auto threads_tag, auto ny_tag) {
+    constexpr int TH = decltype(threads_tag)::value, NY = decltype(ny_tag)::value;
+    const int nv = (Vp1 / 4 + TH - 1) / TH;  // 16-byte loads per thread
+    if (nv <= 1) hipLaunchKernelGGL((ctc_row_kernel<1, TH, NY>), rows, dim3(TH), 0, st, p);
+    else if (nv <= 2) hipLaunchKernelGGL((ctc_row_kernel<2, TH, NY>), rows, dim3(TH), 0, st, p);
+    else if (nv <= 4) hipLaunchKernelGGL((ctc_row_kernel<4, TH, NY>), rows, dim3(TH), 0, st, p);
+    else if (nv <= 8 || TH < 512) hipLaunchKernelGGL((ctc_row_kernel<8, TH, NY>), rows, dim3(TH), 0, st, p);
+    else hipLaunchKernelGGL((ctc_row_kernel<16, (TH < 512 ? 512 : TH), NY>), rows, dim3(TH), 0, st, p);
+  };
+  using N2 = std::integral_constant<int, 2>;
+  using N4 = std::integral_constant<int, 4>;
+  if (Vp1 / 4 <= 8 * 64 && Lmax < 2 * 64) row_launch(std::integral_constant<int, 64>{}, N2{});
+  else if (Vp1 / 4 <= 8 * 256 && Lmax < 2 * 256) row_launch(std::integral_constant<int, 256>{}, N2{});
+  else if (Vp1 / 4 <= 16 * 512 && Lmax < 2 * 512) row_launch(std::integral_constant<int, 512>{}, N2{});
+  else if (Vp1 / 4 <= 16 * 512) row_launch(std::integral_constant<int, 512>{}, N4{});
+  else row_launch(std::integral_constant<int, 1024>{}, N2{});
   CTCSPEC_HIP(ctx, hipGetLastError());
-  const int nv = (Vp1 / 4 + kCtcRowThreads - 1) / kCtcRowThreads;  // 16-byte loads per thread
-  const dim3 rows(T, B), row_threads(kCtcRowThreads);
-  if (nv <= 1) hipLaunchKernelGGL((ctc_row_kernel<1, kCtcRowThreads>), rows, row_threads, 0, st, p);
-  else if (nv <= 2) hipLaunchKernelGGL((ctc_row_kernel<2, kCtcRowThreads>), rows, row_threads, 0, st, p);
-  else if (nv <= 4) hipLaunchKernelGGL((ctc_row_kernel<4, kCtcRowThreads>), rows, row_threads, 0, st, p);
-  else if (nv <= 8) hipLaunchKernelGGL((ctc_row_kernel<8, kCtcRowThreads>), rows, row_threads, 0, st, p);
-  else hipLaunchKernelGGL((ctc_row_kernel<16, kCtcRowThreads>), rows, row_threads, 0, st, p);
-  CTCSPEC_HIP(ctx, hipGetLastError());
-  const int pairs = Lmax + 1;  // a blank and a label state each; the last one is the final blank alone
-  int threads = (pairs + 63) / 64 * 64;
-  threads = threads > 1024 ? 1024 : threads;
-  const int np = (pairs + threads - 1) / threads;
-  const int dp_lds = 2 * (2 * Lmax + 6) * 4;
-  const dim3 dp_grid(B, grad ? 2 : 1);  // without a gradient only the forward recursion runs
-  if (np <= 1) hipLaunchKernelGGL(ctc_dp_kernel<1>, dp_grid, dim3(threads), dp_lds, st, p);
-  else hipLaunchKernelGGL(ctc_dp_kernel<2>, dp_grid, dim3(threads), dp_lds, st, p);
+  if (!pipelined) {
+    if (T < kShortFrames) hipLaunchKernelGGL(ctc_short_kernel<true>, dim3(B), dim3(64), (size_t)T * (64 * 8 + 8), st, p);
+    else hipLaunchKernelGGL(ctc_short_kernel<false>, dim3(B), dim3(64), 0, st, p);
+    CTCSPEC_HIP(ctx, hipGetLastError());
+    return CTCSPEC_OK;
+  }
+  hipLaunchKernelGGL(ctc_dp_pipe_kernel, dim3((unsigned)groups), dim3(kDpThreads), 0, st, p, directions, (int)jobs);
   CTCSPEC_HIP(ctx, hipGetLastError());
   if (grad) {
     const int per = kCtcFixThreads / 64;

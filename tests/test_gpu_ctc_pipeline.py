@@ -1,0 +1,135 @@
+"""ctc_loss with frames enough for the pipelined recursions: labels around the blocks of 64 pairs of states, frame counts
+around the 16 frames of a step and the rule's limit, probabilities of zero, and tokens masked out by large finite
+numbers, which the pipelined recursion leaves to the log-domain one."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_harness import rel_err_rms_floor
+from workloads.device import dev_f32, dev_i32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pkg():
+    import paper_2412_00061_amd as m
+    return m
+
+
+def _check(pkg, logits, labels, label_len, frame_len, blank, grad_tol=1e-4, only=None):
+    B, T, C = logits.shape
+    ctx = pkg.Context(max_batch=1, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=1, max_heads=1, max_head_dim=8)
+    args = (dev_f32(logits), dev_i32(labels), dev_i32(label_len), dev_i32(frame_len), blank)
+    res = pkg.ctc_loss(ctx, *args)
+    again = pkg.ctc_loss(ctx, *args)
+    alone = pkg.ctc_loss(ctx, *args, want_grad=False)
+    loss, grad = res["loss"].cpu().numpy(), res["grad"].cpu().numpy()
+    assert torch.equal(res["loss"], again["loss"]) and torch.equal(res["grad"].view(torch.int32), again["grad"].view(torch.int32))
+    assert torch.equal(res["loss"], alone["loss"])
+    for b in range(B) if only is None else only:
+        Tb, L = int(frame_len[b]), int(label_len[b])
+        if Tb == 0:  # no frame: the empty label is certain
+            assert loss[b] == (0.0 if L == 0 else math.inf) and not grad[b].any()
+            continue
+        ref_loss, ref_grad = oracle.ctc_loss_and_grad(logits[b, :Tb], tuple(int(v) for v in labels[b, :L]), blank)
+        assert not grad[b, Tb:].any()
+        if math.isinf(ref_loss):
+            assert math.isinf(loss[b]) and not grad[b].any()
+            continue
+        # bars of the loss's other tests: a few ulps of the loss, 1e-4 of max(|entry|, rms) of the gradient
+        assert abs(loss[b] - ref_loss) <= 2e-6 * max(1.0, abs(ref_loss)), (b, loss[b], ref_loss)
+        if ref_loss > 1e6:  # a masked-out token is needed: float32 log-probabilities of that size are whole numbers
+            continue
+        assert rel_err_rms_floor(grad[b, :Tb], ref_grad) <= grad_tol, (b, rel_err_rms_floor(grad[b, :Tb], ref_grad))
+    ctx.close()
+
+
+@pytest.mark.parametrize("T", [63, 64, 65, 80, 81, 300])
+@pytest.mark.parametrize("L", [0, 1, 62, 63, 64, 65, 127, 128, 130])
+def test_blocks_and_steps(pkg, T, L):
+    rng = np.random.Generator(np.random.PCG64(1000 * T + L))
+    B, C, Lmax = 3, 23, max(L, 1)
+    print(f"ctc_loss T={T} L={L}", flush=True)
+    logits = rng.standard_normal((B, T, C), dtype=np.float32) * np.float32(1.5)
+    labels = rng.integers(0, C - 1, size=(B, Lmax)).astype(np.int32)
+    frame_len = np.array([T, max(1, T - 17), 0], dtype=np.int32)
+    _check(pkg, logits, labels, np.array([L, L // 2, 0], dtype=np.int32), frame_len, C - 1)
+
+
+@pytest.mark.parametrize("mask", [-np.inf, -3.0e38, -1e9, -1e4])
+def test_masked_tokens(pkg, mask):
+    # sequence 0: a label's token masked out in half of the frames, where other tokens can take its place; sequence 1: in
+    # all frames (unreachable, or a huge loss); sequence 2: nothing of its own masked; sequence 3: the blank masked
+    rng = np.random.Generator(np.random.PCG64(5))
+    B, T, C, L = 4, 90, 12, 20
+    logits = rng.standard_normal((B, T, C), dtype=np.float32)
+    labels = np.tile(np.arange(L, dtype=np.int32) % 10, (B, 1))
+    logits[0, ::2, 3] = mask
+    logits[1, :, 4] = mask
+    logits[2, :, 10] = mask
+    logits[3, 10:20, 11] = mask
+    # a huge loss leaves the float32 log-probabilities themselves a coarse grid: only the loss is compared then; at -1e4
+    # they are near 2^14 in base 2, half an ulp is 2^-11, and an occupancy is formed from four such terms: 1.4e-3 of it,
+    # five times that of the row's rms where the rms is a fifth of the occupancy
+    huge = -np.inf < mask <= -1e9
+    n = np.full(B, L, dtype=np.int32)
+    f = np.full(B, T, dtype=np.int32)
+    if huge:
+        keep = [0, 2, 3]
+        _check(pkg, logits[keep], labels[keep], n[keep], f[keep], 11)
+        ctx = pkg.Context(max_batch=1, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=1, max_heads=1, max_head_dim=8)
+        res = pkg.ctc_loss(ctx, dev_f32(logits[1:2]), dev_i32(labels[1:2]), dev_i32(n[:1]), dev_i32(f[:1]), 11)
+        ref, _ = oracle.ctc_loss_and_grad(logits[1], tuple(int(v) for v in labels[1]), 11)
+        got = float(res["loss"][0])
+        # (2 log2 e * 3e38 is past the largest float: such a token counts as impossible)
+        assert got == math.inf if mask < -1e38 else abs(got - ref) <= 2e-6 * ref
+        ctx.close()
+    else:
+        _check(pkg, logits, labels, n, f, 11, 7e-3 if mask == -1e4 else 1e-4)
+
+
+def test_peaked_logits_far_from_the_diagonal(pkg):
+    # the greedy path says all blanks for most of the sequence, the label is long: the states that matter lie far below
+    # the frame's largest alpha or beta.  Exponents within 64 pairs of states spread over 64 x 36: the float32 values held
+    # against the block's largest have ulps of 2^-12, half of one in each of alpha and beta, 2^-12 ln 2 = 1.7e-4 of an
+    # occupancy, before the occupancies of a frame are divided by their sum
+    rng = np.random.Generator(np.random.PCG64(6))
+    B, T, C, L = 2, 400, 30, 150
+    logits = rng.standard_normal((B, T, C), dtype=np.float32)
+    logits[:, :, 29] += 25.0
+    logits[1, 200:, 29] -= 50.0
+    labels = rng.integers(0, 29, size=(B, L)).astype(np.int32)
+    _check(pkg, logits, labels, np.full(B, L, dtype=np.int32), np.full(B, T, dtype=np.int32), 29, 5e-4)
+
+
+@pytest.mark.parametrize("B,T,Lmax", [(800, 70, 20), (800, 64, 63), (5, 63, 63), (5, 63, 200), (3, 1, 1), (4, 9, 5), (2, 16, 17)])
+def test_wavefront_per_sequence(pkg, B, T, Lmax):
+    # few frames (rows in LDS, labels longer than the frames can hold), and many short labels (rows in the workspace);
+    # few tokens, so that labels repeat them
+    rng = np.random.Generator(np.random.PCG64(7 * T + Lmax))
+    C = 9
+    print(f"ctc_loss B={B} T={T} Lmax={Lmax}", flush=True)
+    logits = rng.standard_normal((B, T, C), dtype=np.float32) * np.float32(1.5)
+    logits[0, : T // 2, 2] = -np.inf
+    logits[1, : T // 2, 3] = -1e9
+    labels = rng.integers(0, C - 1, size=(B, Lmax)).astype(np.int32)
+    frame_len = rng.integers(max(1, T // 2), T + 1, size=B).astype(np.int32)
+    label_len = rng.integers(0, np.minimum(Lmax, frame_len) + 1, size=B).astype(np.int32)
+    label_len[-1] = Lmax
+    keep = [0, 1, B - 1] if B > 10 else range(B)
+    _check(pkg, logits, labels, label_len, frame_len, C - 1, only=keep)
+
+
+@pytest.mark.parametrize("C,T,Lmax", [(2049, 5, 128), (2052, 5, 127), (8193, 6, 511), (8200, 6, 512), (9000, 70, 1100), (40000, 3, 3)])
+def test_row_workgroups(pkg, C, T, Lmax):
+    # vocabularies and label capacities around the sizes at which a row's workgroup gets more threads
+    rng = np.random.Generator(np.random.PCG64(C + Lmax))
+    B = 2
+    print(f"ctc_loss V+1={C} T={T} Lmax={Lmax}", flush=True)
+    logits = rng.standard_normal((B, T, C), dtype=np.float32)
+    labels = rng.integers(0, C - 1, size=(B, Lmax)).astype(np.int32)
+    _check(pkg, logits, labels, np.array([min(Lmax, T // 2), 1], dtype=np.int32), np.array([T, T - 1], dtype=np.int32), C - 1)

@@ -4,6 +4,7 @@
 //   * tree_attn_bf16_kernel    - bf16 operands, head dimension 128: MFMA for Q.K^T and P.V, online
 //                                softmax, K/V tiles shared by the wavefronts of a workgroup through LDS,
 //                                optional key splits combined by tree_attn_merge_kernel
+//   * tree_attn_few_kernel     - the same for at most 16 query rows: the wavefronts split the keys
 //   * tree_attn_any_kernel     - float operands, and bf16 with other head dimensions: the same online softmax on
 //                                blocks of 64 query rows, the same key splits and merge
 #include <type_traits>
@@ -421,6 +422,186 @@ void tree_attn_bf16_kernel(AttnParams p, AttnSplit sp) {
   }
 }
 
+// ---- bf16, dh = 128, at most 16 query rows (the draft module's layer, small trees) -----------------------------------
+// One row group, so the eight wavefronts of a workgroup split the KEYS: wavefront w takes the tiles w, w + 8, ... of its
+// head on its own - its tile in its own 16 KB of LDS, the next one in flight in registers, no barrier - and
+// the eight partial results are joined through LDS at the end.  The layouts and the arithmetic of a tile are those of
+// tree_attn_bf16_kernel.  Bound: the K/V stream (8 wavefronts x 16 KB in flight per compute unit), and with ragged
+// lengths the longest sequence's workgroups.  (Nontemporal loads: 41 against 43 us at the largest shape, but 17.8
+// against 14.0 where K and V are still in the last-level cache.)
+constexpr int kFewWaves = 8, kFewRows = 16;
+constexpr int kFewOPitch = 128 * 4 + 16;
+constexpr int kFewLds = kFewWaves * kStageBytes + 2 * kFewWaves * kFewRows * 4;
+static_assert(kFewRows * kFewOPitch <= kStageBytes, "a wavefront's result fits where its tile was");
+
+// fp32 value -> bf16 bits, round to nearest even
+__device__ __forceinline__ unsigned int rows_bf16_bits(float f) {
+  const unsigned int u = __float_as_uint(f);
+  return (u & 0x7fffffffu) > 0x7f800000u ? 0x7fc0u : (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+}
+// four consecutive values of an output row in the two-bf16 form (AttnParams::rows), at element `at` of both planes
+__device__ __forceinline__ void store_rows4(const AttnParams& p, size_t at, f32x4 o) {
+  unsigned int hi[4], lo[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    hi[i] = rows_bf16_bits(o[i]);
+    lo[i] = rows_bf16_bits(o[i] - __uint_as_float(hi[i] << 16));
+  }
+  *(u32x2*)(p.rows + at) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
+  *(u32x2*)(p.rows + p.rows_plane + at) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
+}
+
+__global__ __launch_bounds__(64 * kFewWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void tree_attn_few_kernel(AttnParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, g = lane >> 4;
+  const int b = (int)blockIdx.x / p.H, h = (int)blockIdx.x - b * p.H;
+  int n = p.n_nodes[b];
+  n = n < 1 ? 1 : (n > p.max_nodes ? p.max_nodes : n);
+  int L = p.ctx_len[b];
+  L = L < 0 ? 0 : (L > p.kv_cap ? p.kv_cap : L);
+  const size_t node_base = ((size_t)b * p.H + h) * p.max_nodes;
+  const unsigned char* kc = (const unsigned char*)p.k_cache + ((size_t)p.kv_off[b] + (size_t)h * p.kv_cap * 128) * 2;
+  const unsigned char* vc = (const unsigned char*)p.v_cache + ((size_t)p.kv_off[b] + (size_t)h * p.kv_cap * 128) * 2;
+  const unsigned char* kt = (const unsigned char*)p.k_tree + node_base * 256;
+  const unsigned char* vt = (const unsigned char*)p.v_tree + node_base * 256;
+  const int ctxT = (L + kTileKeys - 1) / kTileKeys;
+  const int NTL = ctxT + 1;  // at most 16 nodes: one tree tile
+  const int nloc = wave < NTL ? (NTL - wave + kFewWaves - 1) / kFewWaves : 0;
+
+  unsigned char* ks = smem + wave * kStageBytes;  // this wavefront's tile: K, then V
+  u32x4 ld[16];
+  const int lrow = lane >> 4, lchunk = lane & 15;
+  auto issue = [&](int j) __attribute__((always_inline)) {
+    const int t = wave + (j < nloc ? j : nloc - 1) * kFewWaves;
+    const bool tree = t >= ctxT;
+    const int row0 = (tree ? t - ctxT : t) * kTileKeys, last = (tree ? n : L) - 1 - row0;
+    const unsigned char* k0 = (tree ? kt : kc) + (size_t)row0 * 256;
+    const unsigned char* v0 = (tree ? vt : vc) + (size_t)row0 * 256;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int r = lrow + 4 * u;  // rows past the end re-read the last valid row (masked later)
+      const unsigned int off = (unsigned int)((r < last ? r : last) * 256 + lchunk * 16);
+      ld[u] = *(const u32x4*)(k0 + off);
+      ld[8 + u] = *(const u32x4*)(v0 + off);
+    }
+  };
+  auto commit = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int r = lrow + 4 * u;
+      *(u32x4*)(ks + r * 256 + ((lchunk ^ (r & 15)) << 4)) = ld[u];
+      *(u32x4*)(ks + kTileBytes + r * 256 + ((lchunk ^ ((r & 7) << 1)) << 4)) = ld[8 + u];
+    }
+  };
+  if (nloc > 0) issue(0);
+
+  const int qrow = c < p.max_nodes ? c : p.max_nodes - 1;
+  u32x4 qf[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+    qf[kk] = *(const u32x4*)((const unsigned char*)p.q + (node_base + qrow) * 256 + kk * 64 + g * 16);
+  unsigned int mw = 0u;
+  if (c < n) mw = (unsigned int)p.anc_mask[(size_t)b * p.max_nodes + c];  // one word per row
+  const float sl2 = p.scale * 1.4426950408889634f;
+
+  f32x4 o[8];
+#pragma unroll
+  for (int db = 0; db < 8; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;
+
+  typedef __attribute__((address_space(3))) unsigned char lds_byte;
+  const unsigned int tbase = (unsigned int)(size_t)(lds_byte*)ks + kTileBytes + (4 * g + (c >> 2)) * 256 + ((c & 2) ? 16 : 0) + ((c & 1) ? 8 : 0);
+  const unsigned int x7 = ((4 * (g & 1) + (c >> 2)) << 1) << 4;  // swizzle term of that row, in bytes
+  for (int j = 0; j < nloc; ++j) {
+    commit();
+    issue(j + 1);  // (past the last tile: that one again, never used)
+    const int t = wave + j * kFewWaves;
+    const bool tree = t >= ctxT;
+    const int row0 = (tree ? t - ctxT : t) * kTileKeys;
+    f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+        s[kb] = TileBf16::mma(*(const u32x4*)(ks + (kb * 16 + c) * 256 + (((kk * 4 + g) ^ c) << 4)), qf[kk], s[kb]);
+    u32x4 va[8];
+#pragma unroll
+    for (int db = 0; db < 8; ++db) {
+      const unsigned int at = tbase + ((db << 5) ^ x7);
+      const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)at);
+      const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(at + 4096u));
+      va[db] = __builtin_bit_cast(u32x4, s16x8{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]});
+    }
+    float sv[8];
+    const int left = (tree ? n : L) - row0;  // >= 1 keys of the tile exist
+    unsigned int vis = left >= 32 ? 0xffffffffu : ((1u << left) - 1u);
+    if (tree) vis &= mw;
+    vis >>= 4 * g;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sv[kb * 4 + i] = ((vis >> (kb * 16 + i)) & 1u) ? s[kb][i] : -INFINITY;
+    const float mx8 = max3_f32(max3_f32(sv[0], sv[1], sv[2]), max3_f32(sv[3], sv[4], sv[5]), fmaxf(sv[6], sv[7]));
+    if (__builtin_amdgcn_ballot_w64((mx8 - m_run) * sl2 > 8.0f) != 0ull) {
+      const float mx = max_across_row_groups(mx8);
+      if ((mx - m_run) * sl2 > 8.0f) {
+        const float alpha = __builtin_amdgcn_exp2f((m_run - mx) * sl2);  // 0 on first use
+        l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < 8; ++db) o[db] *= alpha;
+        m_run = mx;
+      }
+    }
+    const float ms = (m_run > -INFINITY ? m_run : 0.f) * sl2;
+    u32x4 hi, lo;
+#pragma unroll
+    for (int jp = 0; jp < 4; ++jp) {
+      const float p0 = __builtin_amdgcn_exp2f(fmaf(sv[2 * jp], sl2, -ms));
+      const float p1 = __builtin_amdgcn_exp2f(fmaf(sv[2 * jp + 1], sl2, -ms));
+      l_run += p0 + p1;
+      const unsigned int u0 = __float_as_uint(p0), u1 = __float_as_uint(p1);
+      hi[jp] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+      const float r0 = p0 - __uint_as_float(u0 & 0xffff0000u), r1 = p1 - __uint_as_float(u1 & 0xffff0000u);
+      lo[jp] = __builtin_bit_cast(unsigned int, bf16x2{(__bf16)r0, (__bf16)r1});
+    }
+#pragma unroll
+    for (int db = 0; db < 8; ++db) o[db] = TileBf16::mma(va[db], hi, o[db]);
+#pragma unroll
+    for (int db = 0; db < 8; ++db) o[db] = TileBf16::mma(va[db], lo, o[db]);
+  }
+
+  // ---- the eight parts joined: thread -> (row, four consecutive dh), parts in ascending order -----------------------
+  float* pm = (float*)(smem + kFewWaves * kStageBytes);  // [wave][row] reference, then [wave][row] sum
+  float* pl = pm + kFewWaves * kFewRows;
+  const float l = sum_across_row_groups(l_run);
+#pragma unroll
+  for (int db = 0; db < 8; ++db) *(f32x4*)(ks + c * kFewOPitch + (16 * db + 4 * g) * 4) = o[db];
+  if (g == 0) {
+    pm[wave * kFewRows + c] = m_run;
+    pl[wave * kFewRows + c] = l;
+  }
+  __syncthreads();
+  const int row = tid >> 5, d4 = (tid & 31) * 4;
+  if (row >= n) return;
+  float M = -INFINITY, Lt = 0.f;
+#pragma unroll
+  for (int w = 0; w < kFewWaves; ++w) M = fmaxf(M, pm[w * kFewRows + row]);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < kFewWaves; ++w) {
+    const float m = pm[w * kFewRows + row];
+    const float f = m > -INFINITY ? __builtin_amdgcn_exp2f((m - M) * sl2) : 0.f;  // a part that saw no visible key: nothing
+    Lt += f * pl[w * kFewRows + row];
+    acc += *(const f32x4*)(smem + w * kStageBytes + row * kFewOPitch + d4 * 4) * f;
+  }
+  const f32x4 r = acc * (1.0f / Lt);
+  if (p.rows) store_rows4(p, ((size_t)b * p.max_nodes + row) * ((size_t)p.H * 128) + (size_t)h * 128 + d4, r);
+  else *(f32x4*)(p.out + (node_base + row) * 128 + d4) = r;
+}
+
 // ---- any head dimension, float or bf16 ---------------------------------------------------------------------------
 // Workgroup = 4 wavefronts = one block of 64 query rows of one (sequence, head) and one of S splits of the keys;
 // a wavefront owns 16 rows.  Tiles of 32 keys (context first, then the tree) go through two LDS stages, fetched by all
@@ -729,16 +910,7 @@ __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnPara
   if (p.rows) {
     const int h = (int)(bh - (long long)b * p.H);
     const size_t at = ((size_t)b * p.max_nodes + row) * ((size_t)p.H * dh) + (size_t)h * dh + d4;
-    unsigned short hi[4], lo[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const unsigned int u = __float_as_uint(o[i]);
-      hi[i] = (u & 0x7fffffffu) > 0x7f800000u ? 0x7fc0 : (unsigned short)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
-      const unsigned int v = __float_as_uint(o[i] - __uint_as_float((unsigned int)hi[i] << 16));
-      lo[i] = (v & 0x7fffffffu) > 0x7f800000u ? 0x7fc0 : (unsigned short)((v + 0x7fffu + ((v >> 16) & 1u)) >> 16);
-    }
-    *(u32x2*)(p.rows + at) = u32x2{(unsigned)hi[0] | ((unsigned)hi[1] << 16), (unsigned)hi[2] | ((unsigned)hi[3] << 16)};
-    *(u32x2*)(p.rows + p.rows_plane + at) = u32x2{(unsigned)lo[0] | ((unsigned)lo[1] << 16), (unsigned)lo[2] | ((unsigned)lo[3] << 16)};
+    store_rows4(p, at, o);
   } else {
     *(f32x4*)(p.out + ((size_t)bh * p.max_nodes + row) * dh + d4) = o;
   }
@@ -781,6 +953,8 @@ static hipError_t launch_attn_any(const AttnParams& p, const AttnSplit& sp, hipS
 hipError_t prepare_tree_attn() {
   hipFuncAttributes attr;
   hipError_t e = hipFuncGetAttributes(&attr, (const void*)tree_attn_merge_kernel);
+  if (e != hipSuccess) return e;
+  e = hipFuncSetAttribute((const void*)tree_attn_few_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kFewLds);
   if (e != hipSuccess) return e;
   e = hipFuncSetAttribute((const void*)tree_attn_any_kernel<TileF32, 128>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           2 * AnyAttn<TileF32, 128>::STAGE);
@@ -842,6 +1016,20 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
       while (S > 1 && bh * qblocks * S > (long long)ctx->attn_units) --S;  // partial slots of the workspace
       return S < 1 ? 1LL : S;
     };
+    if (max_nodes <= kFewRows && splits_for(1) == 1 && bh > 128 && key_tiles > kFewWaves) {
+      // Heads that fill the chip without key splits, and at least a tile per wavefront: 8 sequences of 256 to 2048
+      // positions x 32 heads x 16 rows 48.9 -> 43 us, 5 x 32 heads x 8 rows over 300 to 1000 positions 20.5 -> 14.0.  With
+      // key splits a wavefront has about one tile and the joins are what is left (one sequence of 2048: 15.6 against
+      // 13.7 us), so those calls, and shorter contexts, keep the kernel that fetches a tile with all wavefronts.
+      CTCSPEC_REQUIRE(ctx, bh <= 65535, CTCSPEC_EUNSUPPORTED, "tree_verify_attn: grid too large");
+      if (rows) {  // written instead of `out`
+        p.rows = rows; p.rows_plane = rows_plane;
+        if (rows_written) *rows_written = 1;
+      }
+      hipLaunchKernelGGL(tree_attn_few_kernel, dim3((unsigned)bh), dim3(64 * kFewWaves), kFewLds, ctx->stream, p);
+      CTCSPEC_HIP(ctx, hipGetLastError());
+      return CTCSPEC_OK;
+    }
     const long long s128 = splits_for(1), s64 = splits_for(2);
     const bool two_blocks = max_nodes > 64 && (2 * s64 > s128 || (2 * s64 == s128 && s64 >= 4));
     // (up to 16 rows, a single row group: the one-tile-per-iteration kernel, whose first tile is in LDS sooner -

@@ -55,3 +55,31 @@ def test_attention_any(pkg, dtype, dh, q_scale, sign, tol):
             assert rel_err_rms_floor(out[b, :, :n], ref) <= tol
             assert np.array_equal(out[b, :, :n], again[b, :, :n])
         ctx.close()
+
+
+# At most 16 rows, bf16, head dimension 128: the wavefronts of a workgroup split the keys - context lengths around a
+# tile and around one and two rounds of eight tiles (heads that fill the chip), and the shapes that keep key splits.  P carries 16 mantissa bits (2^-17).
+@pytest.mark.parametrize("N", [1, 5, 8, 16])
+@pytest.mark.parametrize("q_scale,tol", [(1.0, 5e-5), (12.0, 3e-4)])
+def test_attention_few_rows(pkg, N, q_scale, tol):
+    for B, H, cap, ctx_len in [(1, 2, 8, [0]), (3, 2, 300, [1, 31, 33]), (1, 4, 2048, [2000]),
+                               (5, 32, 600, [600, 0, 257, 31, 512]), (9, 15, 270, [270, 1, 64, 32, 255, 256, 65, 224, 223])]:
+        print(f"attention few rows N={N} B={B} H={H} ctx={ctx_len} q_scale={q_scale}", flush=True)
+        case = workloads.make_attention_case(N + B, B, H, N, 128, cap, ctx_len, "bf16", q_scale=q_scale)
+        trees = _trees(N, B, N, 128, "chain" if N < 8 else "beam")
+        n_nodes = np.array([t["n_nodes"] for t in trees], dtype=np.int32)
+        q, kt, vt = case.q.copy(), case.k_tree.copy(), case.v_tree.copy()
+        for b in range(B):
+            q[b, :, n_nodes[b]:] = kt[b, :, n_nodes[b]:] = vt[b, :, n_nodes[b]:] = np.nan
+        mask = torch.from_numpy(np.stack([t["anc_mask"] for t in trees]).view(np.int64)).cuda()
+        ctx = pkg.Context(max_batch=B, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=N, max_heads=H, max_head_dim=128)
+        args = (to_device(q, "bf16"), to_device(case.k_cache, "bf16"), to_device(case.v_cache, "bf16"), dev_i64(case.kv_off),
+                dev_i32(case.ctx_len), cap, to_device(kt, "bf16"), to_device(vt, "bf16"), dev_i32(n_nodes), mask, 128 ** -0.5)
+        out, again = pkg.tree_verify_attn(ctx, *args).cpu().numpy(), pkg.tree_verify_attn(ctx, *args).cpu().numpy()
+        for b in range(B):
+            n = int(n_nodes[b])
+            ref = oracle.tree_attention(case.q[b], case.k_cache[b], case.v_cache[b], int(case.ctx_len[b]), case.k_tree[b],
+                                        case.v_tree[b], n, trees[b]["mask"], 128 ** -0.5)
+            assert rel_err_rms_floor(out[b, :, :n], ref) <= tol
+            assert np.array_equal(out[b, :, :n], again[b, :, :n])
+        ctx.close()

@@ -22,6 +22,7 @@ def test_collapse_direct(pkg, T, k, quantum):
     ctx = _stage3_ctx(pkg, B, T, k)
     for seed, vocab in ((1, max(k + 1, 5)), (2, 30)):
         ids, logp = workloads.make_topk_case(10 * T + seed, B, T, k, blank, vocab=vocab, p_blank=0.5, quantum=quantum)
+        logp -= np.float32(1.0)  # log-probabilities below zero: the kernel's score keys hold no negative zero
         for beam, nodes in ((128, 128), (16, 128), (5, 9)):
             print(f"collapse T={T} k={k} quantum={quantum} beam={beam} nodes={nodes}", flush=True)
             _run_stage3(pkg, ctx, ids, logp, np.array([1, 2, 3]), blank, beam, nodes)

@@ -97,7 +97,14 @@ struct AttnSplit {
   float* pl;   // [unit][rows] running sum
 };
 
-template <int QT, int NW, int CW, int PF>
+// 16 bytes of K or V; STREAM: read once and gone (see streams_past_cache)
+template <bool STREAM>
+__device__ __forceinline__ u32x4 load_kv(const unsigned char* a) {
+  if constexpr (STREAM) return __builtin_nontemporal_load((const u32x4*)a);
+  else return *(const u32x4*)a;
+}
+
+template <int QT, int NW, int CW, int PF, bool STREAM>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tree_attn_bf16_kernel(AttnParams p, AttnSplit sp) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -154,8 +161,8 @@ void tree_attn_bf16_kernel(AttnParams p, AttnSplit sp) {
       const unsigned char* vt0 = vs + (size_t)row0 * 256;
       const int last = limit - 1 - row0;  // >= 0: rows past the end re-read the last valid row (masked later)
       const unsigned int off = (unsigned int)((lrow < last ? lrow : last) * 256 + lchunk * 16);
-      ld[SET][u] = *(const u32x4*)(kt0 + off);
-      ld[SET][KP + u] = *(const u32x4*)(vt0 + off);
+      ld[SET][u] = load_kv<STREAM>(kt0 + off);
+      ld[SET][KP + u] = load_kv<STREAM>(vt0 + off);
     }
   };
   const int coff_k = lrow * 256 + ((lchunk ^ (lrow & 15)) << 4);
@@ -427,8 +434,7 @@ void tree_attn_bf16_kernel(AttnParams p, AttnSplit sp) {
 // head on its own - its tile in its own 16 KB of LDS, the next one in flight in registers, no barrier - and
 // the eight partial results are joined through LDS at the end.  The layouts and the arithmetic of a tile are those of
 // tree_attn_bf16_kernel.  Bound: the K/V stream (8 wavefronts x 16 KB in flight per compute unit), and with ragged
-// lengths the longest sequence's workgroups.  (Nontemporal loads: 41 against 43 us at the largest shape, but 17.8
-// against 14.0 where K and V are still in the last-level cache.)
+// lengths the longest sequence's workgroups.
 constexpr int kFewWaves = 8, kFewRows = 16;
 constexpr int kFewOPitch = 128 * 4 + 16;
 constexpr int kFewLds = kFewWaves * kStageBytes + 2 * kFewWaves * kFewRows * 4;
@@ -451,6 +457,7 @@ __device__ __forceinline__ void store_rows4(const AttnParams& p, size_t at, f32x
   *(u32x2*)(p.rows + p.rows_plane + at) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
 }
 
+template <bool STREAM>
 __global__ __launch_bounds__(64 * kFewWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tree_attn_few_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -484,8 +491,8 @@ void tree_attn_few_kernel(AttnParams p) {
     for (int u = 0; u < 8; ++u) {
       const int r = lrow + 4 * u;  // rows past the end re-read the last valid row (masked later)
       const unsigned int off = (unsigned int)((r < last ? r : last) * 256 + lchunk * 16);
-      ld[u] = *(const u32x4*)(k0 + off);
-      ld[8 + u] = *(const u32x4*)(v0 + off);
+      ld[u] = load_kv<STREAM>(k0 + off);
+      ld[8 + u] = load_kv<STREAM>(v0 + off);
     }
   };
   auto commit = [&]() __attribute__((always_inline)) {
@@ -922,9 +929,16 @@ static hipError_t launch_merge(const AttnParams& p, const AttnSplit& sp, int row
                      rows == 64 ? 6 : 7);
   return hipGetLastError();
 }
-template <int QT, int NW, int CW, int PF>
+// Caches of more than three quarters of the 256 MB last-level cache (all heads, whole capacity): K and V of a call cannot still be
+// there when they are read again, and loads that leave no copy behind are faster.  8 sequences x 32 heads x 2064 positions
+// (270 MB), 64 rows: 54.8 -> 51.1 us, 16 rows 43 -> 41; at 4 sequences (135 MB at capacity 2064, a third of it used) they
+// would lose what repeated calls find in the cache: 27.4 -> 29.6 us.
+static bool streams_past_cache(const AttnParams& p) {
+  return (long long)p.B * p.H * p.kv_cap * 512 > 192LL * 1024 * 1024;
+}
+template <int QT, int NW, int CW, int PF, bool STREAM = false>
 static hipError_t launch_attn_bf16(const AttnParams& p, const AttnSplit& sp, hipStream_t stream) {
-  auto kern = tree_attn_bf16_kernel<QT, NW, CW, PF>;
+  auto kern = tree_attn_bf16_kernel<QT, NW, CW, PF, STREAM>;
   const long long blocks = (long long)sp.QB * sp.S * p.H * p.B;
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * NW), attn_lds_bytes(NW / CW), stream, p, sp);
   hipError_t e = hipGetLastError();
@@ -954,13 +968,18 @@ hipError_t prepare_tree_attn() {
   hipFuncAttributes attr;
   hipError_t e = hipFuncGetAttributes(&attr, (const void*)tree_attn_merge_kernel);
   if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)tree_attn_few_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kFewLds);
+  e = hipFuncSetAttribute((const void*)tree_attn_few_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kFewLds);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void*)tree_attn_bf16_kernel<1, 8, 4, 2, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            attn_lds_bytes(2));
+  if (e != hipSuccess) return e;
+  e = hipFuncSetAttribute((const void*)tree_attn_few_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kFewLds);
   if (e != hipSuccess) return e;
   e = hipFuncSetAttribute((const void*)tree_attn_any_kernel<TileF32, 128>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           2 * AnyAttn<TileF32, 128>::STAGE);
   if (e != hipSuccess) return e;
   // the 64-row kernel's two stages of two tiles are 64 KB of dynamic LDS
-  return hipFuncSetAttribute((const void*)tree_attn_bf16_kernel<1, 8, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+  return hipFuncSetAttribute((const void*)tree_attn_bf16_kernel<1, 8, 4, 2, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              attn_lds_bytes(2));
 }
 
@@ -1026,7 +1045,10 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
         p.rows = rows; p.rows_plane = rows_plane;
         if (rows_written) *rows_written = 1;
       }
-      hipLaunchKernelGGL(tree_attn_few_kernel, dim3((unsigned)bh), dim3(64 * kFewWaves), kFewLds, ctx->stream, p);
+      if (streams_past_cache(p))
+        hipLaunchKernelGGL(tree_attn_few_kernel<true>, dim3((unsigned)bh), dim3(64 * kFewWaves), kFewLds, ctx->stream, p);
+      else
+        hipLaunchKernelGGL(tree_attn_few_kernel<false>, dim3((unsigned)bh), dim3(64 * kFewWaves), kFewLds, ctx->stream, p);
       CTCSPEC_HIP(ctx, hipGetLastError());
       return CTCSPEC_OK;
     }
@@ -1046,8 +1068,10 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
       p.rows = rows; p.rows_plane = rows_plane;
       if (rows_written) *rows_written = 1;
     }
-    const hipError_t e = rows64 ? launch_attn_bf16<1, 8, 4, 2>(p, sp, ctx->stream)
-                                : launch_attn_bf16<1, 8, 8, 2>(p, sp, ctx->stream);
+    // (two 64-row blocks share K and V through L2)
+    const hipError_t e = !rows64 ? launch_attn_bf16<1, 8, 8, 2>(p, sp, ctx->stream)
+                         : sp.QB == 1 && streams_past_cache(p) ? launch_attn_bf16<1, 8, 4, 2, true>(p, sp, ctx->stream)
+                                                               : launch_attn_bf16<1, 8, 4, 2>(p, sp, ctx->stream);
     CTCSPEC_HIP(ctx, e);
     return CTCSPEC_OK;
   }

@@ -83,3 +83,25 @@ def test_attention_few_rows(pkg, N, q_scale, tol):
             assert rel_err_rms_floor(out[b, :, :n], ref) <= tol
             assert np.array_equal(out[b, :, :n], again[b, :, :n])
         ctx.close()
+
+
+# Caches past the last-level cache's size are read with streaming loads: the same bits as the same rows in small caches.
+@pytest.mark.parametrize("N", [8, 16, 17, 64])
+def test_attention_large_capacity(pkg, N):
+    B, H, big, small = 5, 32, 2600, 512  # 5 x 32 x 2600 x 512 bytes: 213 MB
+    g = torch.Generator(device="cuda").manual_seed(N)
+    rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16)
+    q, kt, vt, ks, vs = rnd(B, H, N, 128), rnd(B, H, N, 128), rnd(B, H, N, 128), rnd(B, H, small, 128), rnd(B, H, small, 128)
+    kb, vb = (torch.full((B, H, big, 128), float("nan"), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    kb[:, :, :small], vb[:, :, :small] = ks, vs
+    lens, nodes = dev_i32(np.array([512, 300, 511, 1, 0], dtype=np.int32)), dev_i32(np.array([N, 1, N, N // 2, N], dtype=np.int32))
+    mask = torch.tensor([[-1 if i == 63 else (1 << (i + 1)) - 1] for i in range(N)], device="cuda").view(1, N, 1).repeat(B, 1, 1)
+    outs = []
+    for cap, k, v in ((big, kb, vb), (small, ks, vs)):
+        ctx = pkg.Context(max_batch=B, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=N, max_heads=H, max_head_dim=128)
+        off = dev_i64(np.arange(B, dtype=np.int64) * H * cap * 128)
+        out = torch.zeros((B, H, N, 128), device="cuda")
+        outs.append(pkg.tree_verify_attn(ctx, q, k, v, off, lens, cap, kt, vt, nodes, mask, 0.09, out=out))
+        torch.cuda.synchronize()
+        ctx.close()
+    assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1])

@@ -20,7 +20,7 @@ def pkg():
     return m
 
 
-def _check(pkg, logits, labels, label_len, frame_len, blank, grad_tol=1e-4, only=None):
+def _check(pkg, logits, labels, label_len, frame_len, blank, grad_tol=1e-4, only=None, reference=oracle.ctc_loss_and_grad):
     B, T, C = logits.shape
     ctx = pkg.Context(max_batch=1, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=1, max_heads=1, max_head_dim=8)
     args = (dev_f32(logits), dev_i32(labels), dev_i32(label_len), dev_i32(frame_len), blank)
@@ -35,7 +35,7 @@ def _check(pkg, logits, labels, label_len, frame_len, blank, grad_tol=1e-4, only
         if Tb == 0:  # no frame: the empty label is certain
             assert loss[b] == (0.0 if L == 0 else math.inf) and not grad[b].any()
             continue
-        ref_loss, ref_grad = oracle.ctc_loss_and_grad(logits[b, :Tb], tuple(int(v) for v in labels[b, :L]), blank)
+        ref_loss, ref_grad = reference(logits[b, :Tb], tuple(int(v) for v in labels[b, :L]), blank)
         assert not grad[b, Tb:].any()
         if math.isinf(ref_loss):
             assert math.isinf(loss[b]) and not grad[b].any()
@@ -133,3 +133,29 @@ def test_row_workgroups(pkg, C, T, Lmax):
     logits = rng.standard_normal((B, T, C), dtype=np.float32)
     labels = rng.integers(0, C - 1, size=(B, Lmax)).astype(np.int32)
     _check(pkg, logits, labels, np.array([min(Lmax, T // 2), 1], dtype=np.int32), np.array([T, T - 1], dtype=np.int32), C - 1)
+
+
+def _torch_reference(logits, label, blank):  # (the oracle takes a minute for 2047 labels)
+    x = torch.tensor(logits, dtype=torch.float64, requires_grad=True)
+    args = torch.tensor(label)[None], torch.tensor([len(logits)]), torch.tensor([len(label)])
+    loss = torch.nn.functional.ctc_loss(torch.log_softmax(x, 1)[:, None], *args, blank=blank, reduction="sum")
+    loss.backward()
+    return loss.item(), x.grad.numpy()
+
+
+@pytest.mark.parametrize("L", [1, 63, 64, 255, 256, 511, 512, 1279, 1280, 2047])
+def test_log_domain_sizes(pkg, L):
+    # a token of the label masked out by a large finite number in every fourth frame, so that the log-domain recursion runs:
+    # labels around the sizes at which its threads hold more pairs of states (256, 512, 1280), and the largest.
+    # The states that matter lie up to 0.2 T bits below a frame's largest (float64 recursions of these inputs: 399 at
+    # T = 1938, 616 at 3090); float32 rounds such a value by 0.2 T 2^-24 at most, once per frame, which adds up as a
+    # random walk over T frames; ln 2 turns bits into a relative error of the occupancy
+    rng = np.random.Generator(np.random.PCG64(31 + L))
+    B, T, C = 2, max(70, L + L // 2 + 20), 97
+    print(f"ctc_loss T={T} L={L}", flush=True)
+    logits = rng.standard_normal((B, T, C), dtype=np.float32)
+    labels = rng.integers(0, C - 1, size=(B, L)).astype(np.int32)
+    logits[0, ::4, labels[0, L // 2]] = -1e9
+    logits[1, 1::4, labels[1, 0]] = -1e9
+    _check(pkg, logits, labels, np.array([L, max(1, L - 1)], dtype=np.int32), np.array([T, T - 3], dtype=np.int32), C - 1,
+           grad_tol=max(1e-4, 0.2 * T * 2.0**-24 * math.sqrt(T) * math.log(2)), reference=_torch_reference)

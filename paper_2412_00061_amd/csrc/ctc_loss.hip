@@ -96,6 +96,7 @@ __global__ __launch_bounds__(THREADS) void ctc_row_kernel(CtcParams p) {
   if (tid < head) edge = tid;
   else if (tid >= kTailLane && tid - kTailLane < p.Vp1 - tail0) edge = tail0 + tid - kTailLane;
   float* g = p.grad ? p.grad + row0 : nullptr;
+  if (p.edge && t == 0 && b == 0 && tid == 0) *p.ticket = 0;  // whatever the sequence's length: every call counts from 0
   if (t >= Tb) {  // frames past the sequence: no gradient
     if (g) {
       f32x4* gv = (f32x4*)(g + head);
@@ -104,10 +105,7 @@ __global__ __launch_bounds__(THREADS) void ctc_row_kernel(CtcParams p) {
     }
     return;
   }
-  if (p.edge && tid == 0) {  // (barriers follow before anything is set)
-    p.wide[(size_t)b * p.T + t] = 0;
-    if (t == 0 && b == 0) *p.ticket = 0;
-  }
+  if (p.edge && tid == 0) p.wide[(size_t)b * p.T + t] = 0;  // (barriers follow before anything is set)
   const float* z = p.logits + row0;
   const f32x4* zv = (const f32x4*)(z + head);
   // the label's token ids first (Lmax < NY * THREADS), then the row, then the label's
@@ -573,6 +571,7 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
   if (tid == 0) job_id = atomicAdd(p.ticket, 1);
   __syncthreads();
   const int job = __builtin_amdgcn_readfirstlane(job_id);
+  if ((unsigned)job >= gridDim.x) return;  // (only if something else writes the workspace meanwhile)
   if (job >= jobs) {
     const int b = (job - jobs) % p.B;
     ctc_links(p, b, (job - jobs) / p.B, ((int)gridDim.x - jobs) / p.B, (int32_t*)&sh);

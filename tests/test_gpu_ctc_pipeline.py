@@ -60,6 +60,48 @@ def test_blocks_and_steps(pkg, T, L):
     _check(pkg, logits, labels, np.array([L, L // 2, 0], dtype=np.int32), frame_len, C - 1)
 
 
+# Sequences without frames at every place of the batch, the first among them (its rows return early, and the call's
+# bookkeeping must not hang on them), in a workspace that other bytes or another shape's call have been in before.
+@pytest.mark.parametrize("frames", [(0, 90, 73), (0, 0, 0), (90, 0, 73), (0, 0, 90)])
+@pytest.mark.parametrize("T,Lmax", [(90, 20), (90, 130), (20, 7)])
+def test_empty_sequences(pkg, frames, T, Lmax):
+    rng = np.random.Generator(np.random.PCG64(11 * T + Lmax + frames[0]))
+    B, C = 3, 23
+    frame_len = np.minimum(np.array(frames, dtype=np.int32), T)
+    logits = rng.standard_normal((B, T, C), dtype=np.float32) * np.float32(1.5)
+    labels = rng.integers(0, C - 1, size=(B, Lmax)).astype(np.int32)
+    label_len = np.array([min(5, Lmax), 0, min(20, Lmax)], dtype=np.int32)
+    ctx = pkg.Context(max_batch=1, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=1, max_heads=1, max_head_dim=8)
+    other = (dev_f32(rng.standard_normal((2, 70, C), dtype=np.float32)), dev_i32(labels[:2, :7]), dev_i32(label_len[:2]),
+             dev_i32(np.array([70, 64])), C - 1)
+    args = (dev_f32(logits), dev_i32(labels), dev_i32(label_len), dev_i32(frame_len), C - 1)
+    need = max(pkg.ctc_loss_workspace_bytes(B, T, Lmax), pkg.ctc_loss_workspace_bytes(2, 70, 7))
+    for fill in (0xFF, 0x00, 0x01, None):
+        print(f"ctc_loss T={T} Lmax={Lmax} frames={frame_len.tolist()} fill={fill}", flush=True)
+        ws = torch.full((need,), fill or 0, dtype=torch.uint8, device="cuda")
+        if fill is None:
+            pkg.ctc_loss(ctx, *other, workspace=ws)
+        out = {"loss": torch.full((B,), -7.0, device="cuda"), "grad": torch.full((B, T, C), -7.0, device="cuda")}
+        for want_grad in (True, False):
+            if fill is not None:
+                ws.fill_(fill)
+            res = pkg.ctc_loss(ctx, *args, want_grad=want_grad, workspace=ws, out=out)
+            loss = res["loss"].cpu().numpy()
+            for b in range(B):
+                Tb, L = int(frame_len[b]), int(label_len[b])
+                if Tb == 0:
+                    ref_loss, ref_grad = (0.0 if L == 0 else math.inf), np.zeros((0, C))
+                else:
+                    ref_loss, ref_grad = oracle.ctc_loss_and_grad(logits[b, :Tb], tuple(int(v) for v in labels[b, :L]), C - 1)
+                assert loss[b] == ref_loss or abs(loss[b] - ref_loss) <= 2e-6 * max(1.0, abs(ref_loss)), (b, loss[b], ref_loss)
+                if want_grad:
+                    grad = res["grad"][b].cpu().numpy()
+                    assert not grad[Tb:].any()
+                    assert Tb == 0 or rel_err_rms_floor(grad[:Tb], ref_grad) <= 1e-4
+            out["loss"].fill_(-7.0)
+    ctx.close()
+
+
 @pytest.mark.parametrize("mask", [-np.inf, -3.0e38, -1e9, -1e4])
 def test_masked_tokens(pkg, mask):
     # sequence 0: a label's token masked out in half of the frames, where other tokens can take its place; sequence 1: in

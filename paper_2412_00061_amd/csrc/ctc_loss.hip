@@ -456,13 +456,12 @@ __device__ __forceinline__ void wave_max_i32(int (&v)[N]) {
 }
 
 struct DpValue { float m; int e; };
-// log2 p -> p
+// log2 p -> p.  Not a number stays one in m, with an exponent that sinks nothing: it is no impossible state.
 __device__ __forceinline__ DpValue dp_probability(float l) {
   const float f = floorf(l);
   DpValue v;
-  v.m = 0.5f * __builtin_amdgcn_exp2f(l - f);  // 2^(l - f) in [1, 2)
-  v.e = l > -INFINITY ? (int)f + 1 : kDpZeroP;
-  if (!(l > -INFINITY) && l == l) v.m = 0.5f;
+  v.m = l == -INFINITY ? 0.5f : 0.5f * __builtin_amdgcn_exp2f(l - f);  // 2^(l - f) in [1, 2)
+  v.e = l > -INFINITY ? (int)f + 1 : (l == -INFINITY ? kDpZeroP : 0);
   return v;
 }
 __device__ __forceinline__ DpValue dp_scaled(float sum, int e, float pm, int pe) {
@@ -675,7 +674,7 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
       if (q == L) {
         const int e = imax(be, xe);
         const float s = __builtin_amdgcn_ldexpf(bm, be - e) + __builtin_amdgcn_ldexpf(xm, xe - e);
-        const double logP = e < kDpImpossible ? -(double)INFINITY : (double)e + (double)__builtin_amdgcn_logf(s);
+        const double logP = e < kDpImpossible && s == s ? -(double)INFINITY : (double)e + (double)__builtin_amdgcn_logf(s);
         p.loss[b] = (float)(-logP * 0.6931471805599453);
         p.logp[b] = logP;
       }

@@ -102,6 +102,37 @@ def test_empty_sequences(pkg, frames, T, Lmax):
     ctx.close()
 
 
+# Logits that are no numbers (a diverged run): the loss of such a sequence is not a number - not +inf, which stands for a
+# label that cannot be reached - and its gradient zero; the other sequences of the batch do not notice.  One wavefront per
+# sequence (few frames; many short labels), one block of states and several, with and without a token masked by a
+# large finite number (the log-domain recursion), and a label that could not be reached anyway (no repeats fit).
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("B,T,L,masked", [(3, 20, 6, False), (800, 70, 6, False), (3, 90, 20, False), (3, 300, 130, False),
+                                          (3, 90, 20, True), (3, 300, 130, True), (3, 70, 69, False)])
+def test_not_a_number(pkg, bad, B, T, L, masked):
+    rng = np.random.Generator(np.random.PCG64(17 * T + L))
+    C = 23
+    print(f"ctc_loss B={B} T={T} L={L} masked={masked} bad={bad}", flush=True)
+    logits = rng.standard_normal((B, T, C), dtype=np.float32)
+    labels = rng.integers(0, C - 1, size=(B, L)).astype(np.int32)
+    if masked:
+        logits[:2, ::4, labels[0, 2]] = -1e9
+    clean = logits.copy()
+    logits[0, T // 2, 5] = bad
+    logits[1, T - 1, :] = bad  # behind the sequence's frames
+    ctx = pkg.Context(max_batch=1, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=1, max_heads=1, max_head_dim=8)
+    frame_len = np.full(B, T, dtype=np.int32)
+    frame_len[1] = T - 1
+    rest = (dev_i32(labels), dev_i32(np.full(B, L, dtype=np.int32)), dev_i32(frame_len), C - 1)
+    got, want = pkg.ctc_loss(ctx, dev_f32(logits), *rest), pkg.ctc_loss(ctx, dev_f32(clean), *rest)
+    alone = pkg.ctc_loss(ctx, dev_f32(logits), *rest, want_grad=False)
+    assert torch.isnan(got["loss"][0]) and torch.isnan(alone["loss"][0]) and not got["grad"][0].any()
+    assert torch.equal(got["loss"][1:], want["loss"][1:]) and torch.equal(alone["loss"][1:], want["loss"][1:])
+    assert torch.equal(got["grad"][1:], want["grad"][1:])
+    assert not torch.isnan(want["loss"]).any()
+    ctx.close()
+
+
 @pytest.mark.parametrize("mask", [-np.inf, -3.0e38, -1e9, -1e4])
 def test_masked_tokens(pkg, mask):
     # sequence 0: a label's token masked out in half of the frames, where other tokens can take its place; sequence 1: in

@@ -207,7 +207,10 @@ int ctc_collapse_tree(ctcspec_ctx* ctx, const int32_t* topk_id, const float* top
  * No positional encoding is applied here: q and keys arrive as the attention operands.
  *
  * dt           element type of q, k_cache, v_cache, k_tree, v_tree
- * q, k_tree, v_tree   [B,H,max_nodes,dh]   16-byte aligned; rows >= n_nodes[b] are never used
+ * q, k_tree, v_tree   [B,H,max_nodes,dh]   16-byte aligned; rows >= n_nodes[b] are never used.  A value (v_tree,
+ *                     v_cache) that is infinite or not a number reaches the rows that see its key, in its own
+ *                     component; with bf16 and dh = 128 it may become a NaN and, from a tree node, reach every row of
+ *                     its head (all keys of a tile go through one matrix product, hidden ones with weight 0)
  * k_cache, v_cache    base pointers; sequence b's block starts kv_off[b] ELEMENTS after the base and
  *                     is laid out [H][kv_cap][dh]; only the first ctx_len[b] rows of each head are
  *                     read (rows beyond may hold anything, NaN included).  kv_off[b]*sizeof(elem)

@@ -621,6 +621,9 @@ void tree_attn_few_kernel(AttnParams p) {
 //       bf16:  the transposing read of the kernel above (row pitch = an odd multiple of 32 bytes: eight rows x 32 bytes
 //              cover every bank once); P goes in as three bf16 numbers, which together hold its 24 mantissa bits - this
 //              path has always kept P in float
+// Values (V) that are infinite or not a number: in the product 0 x inf carries one to rows that do not see its key, and P in
+// parts makes an inf a NaN.  A wavefront that finds its sums not finite forms them again from memory, key by key, keys of
+// weight 0 left out (the reference and the sum of the weights do not depend on V).
 // Bound: float operands by the matrix rate (157 TFLOP/s), bf16 by latency and the K/V stream.  Measured against one
 // workgroup per query row with K/V read by every row (what these shapes took before): 2 sequences x 12 heads x 100
 // nodes, 300 to 900 keys, float, head dimension 64: 608 -> 17.6 us (kernel and merge); four sequences x 15 heads x 64
@@ -855,6 +858,34 @@ void tree_attn_any_kernel(AttnParams p, AttnSplit sp) {
     }
   }
   if (!live_wave) return;
+  f32x4 probe = {0.f, 0.f, 0.f, 0.f};  // 0 x finite
+#pragma unroll
+  for (int db = 0; db < NB; ++db) probe += (16 * db + 4 * g < dh ? o[db] : f32x4{0.f, 0.f, 0.f, 0.f}) * 0.f;
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(probe[0] + probe[1] + probe[2] + probe[3] == 0.f)) != 0ull, 0)) {
+    using T = std::conditional_t<E == 4, float, unsigned short>;
+    const T* qrow = (const T*)p.q + (node_base + (qi < n ? qi : n - 1)) * dh;
+    const float ms = m_run > -INFINITY ? m_run : 0.f;
+#pragma unroll
+    for (int db = 0; db < NB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < nloc; ++j) {
+      const int t = split + j * sp.S;
+      const bool tree = t >= ctxT;
+      const int row0 = (tree ? t - ctxT : t) * kTileKeys, left = (tree ? n : L) - row0;
+      const unsigned int vis = tree ? (unsigned int)((row0 < 64 ? mw0 : mw1) >> (row0 & 63)) : 0xffffffffu;
+      for (int key = 0; key < kTileKeys && key < left; ++key) {
+        const T* kr = (const T*)(tree ? kt : kc) + (size_t)(row0 + key) * dh;
+        const T* vr = (const T*)(tree ? vt : vc) + (size_t)(row0 + key) * dh;
+        float s = 0.f;
+        for (int e = 0; e < dh; ++e) s = fmaf(load_as_float(qrow + e), load_as_float(kr + e), s);
+        const float w = ((vis >> key) & 1u) && s * sl2 > -INFINITY ? __builtin_amdgcn_exp2f(fmaf(s, sl2, -ms)) : 0.f;
+#pragma unroll
+        for (int db = 0; db < NB; ++db)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (16 * db + 4 * g < dh && w != 0.f) o[db][i] = fmaf(w, load_as_float(vr + 16 * db + 4 * g + i), o[db][i]);
+      }
+    }
+  }
   const size_t unit = (((size_t)b * p.H + h) * sp.QB + qb) * sp.S + split;
   const float l = sum_across_row_groups(l_run);
   if (qi >= n) return;
@@ -912,6 +943,16 @@ __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnPara
     const float f = pmv[s] > -INFINITY ? __builtin_amdgcn_exp2f(pmv[s] - M) : 0.f;
     Lt += f * plv[s];
     acc += pov[s] * f;
+  }
+  // A sum that is not finite is formed again without the parts of weight 0, which add nothing whatever they hold (those
+  // past the last split hold the first one's values).  (As a select in the loop above, the loads wait for pm: +0.6 us.)
+  if (__builtin_expect(!(acc[0] * 0.f + acc[1] * 0.f + acc[2] * 0.f + acc[3] * 0.f == 0.f), 0)) {
+    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < kMaxKvSplits; ++s) {
+      const float f = pmv[s] > -INFINITY ? __builtin_amdgcn_exp2f(pmv[s] - M) : 0.f;
+      if (f != 0.f) acc += pov[s] * f;
+    }
   }
   const f32x4 o = acc * (1.0f / Lt);
   if (p.rows) {

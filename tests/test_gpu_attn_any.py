@@ -57,6 +57,39 @@ def test_attention_any(pkg, dtype, dh, q_scale, sign, tol):
         ctx.close()
 
 
+# Values that are infinite or not a number: they belong to the rows that see their key, in their own component, and to
+# no other - a leaf's value (seen by that node alone) and a cached one (seen by every row, an infinity stays one).
+@pytest.mark.parametrize("dtype,dh", [("f32", 64), ("f32", 40), ("f32", 128), ("bf16", 64), ("bf16", 96)])
+@pytest.mark.parametrize("B,H,N,cap,ctx_len", [(2, 3, 17, 64, [40, 0]), (2, 3, 100, 900, [900, 300]), (1, 2, 64, 700, [333])])
+def test_attention_values_not_finite(pkg, dtype, dh, B, H, N, cap, ctx_len):
+    case = workloads.make_attention_case(N, B, H, N, dh, cap, ctx_len, dtype)
+    trees = _trees(N, B, N, 128, "beam")
+    n_nodes = np.array([t["n_nodes"] for t in trees], dtype=np.int32)
+    vt, vc = case.v_tree.copy(), case.v_cache.copy()
+    for b in range(B):
+        vt[b, :, n_nodes[b] - 1, 3], vt[b, :, n_nodes[b] - 1, 5], vt[b, :, n_nodes[b] - 1, 7] = np.inf, np.nan, -np.inf
+    vc[0][:, 2, 1] = np.inf
+    print(f"attention not finite {dtype} dh={dh} B={B} H={H} N={N} ctx={ctx_len}", flush=True)
+    mask = torch.from_numpy(np.stack([t["anc_mask"] for t in trees]).view(np.int64)).cuda()
+    ctx = pkg.Context(max_batch=B, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=N, max_heads=H, max_head_dim=dh)
+    out = pkg.tree_verify_attn(ctx, to_device(case.q, dtype), to_device(case.k_cache, dtype), to_device(vc, dtype),
+                               dev_i64(case.kv_off), dev_i32(case.ctx_len), cap, to_device(case.k_tree, dtype),
+                               to_device(vt, dtype), dev_i32(n_nodes), mask, dh ** -0.5).cpu().numpy()
+    for b in range(B):
+        n = int(n_nodes[b])
+        ref = oracle.tree_attention(case.q[b], case.k_cache[b], case.v_cache[b], int(case.ctx_len[b]), case.k_tree[b],
+                                    case.v_tree[b], n, trees[b]["mask"], dh ** -0.5)
+        got = out[b, :, :n].copy()
+        last = got[:, n - 1]
+        assert np.isposinf(last[:, 3]).all() and np.isnan(last[:, 5]).all() and np.isneginf(last[:, 7]).all()
+        last[:, [3, 5, 7]] = ref[:, n - 1, [3, 5, 7]]
+        if b == 0:
+            assert np.isposinf(got[:, :, 1]).all()
+            got[:, :, 1] = ref[:, :, 1]
+        assert rel_err_rms_floor(got, ref) <= 1e-5
+    ctx.close()
+
+
 # At most 16 rows, bf16, head dimension 128: the wavefronts of a workgroup split the keys - context lengths around a
 # tile and around one and two rounds of eight tiles (heads that fill the chip), and the shapes that keep key splits.  P carries 16 mantissa bits (2^-17).
 @pytest.mark.parametrize("N", [1, 5, 8, 16])

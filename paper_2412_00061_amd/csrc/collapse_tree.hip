@@ -368,7 +368,7 @@ __device__ __forceinline__ unsigned long long collapse_key(const CollapseShared&
 // go on from LDS: one dispatch and one trip through memory fewer than a merge kernel in between.
 // DIRECT: at most kDirectMax raw candidates in all (k^T; the host chooses).  Two per thread are all of them, so there
 // are no half sums and no threshold: every one gets its score and takes part in the one sort (T = 4, k = 2: 15.1 ->
-// 13.3 us).
+// 13.3 us).  A score that is not a number passes no threshold, so here it takes no part either.
 constexpr int kDirectMax = 2 * kThreads;
 template <bool RAW, int MK, bool DIRECT>
 __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams p) {
@@ -447,7 +447,12 @@ __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams 
     for (int t = 0; t < CTCSPEC_MAX_SLOTS; ++t)
       if (t < T) A += __uint_as_float(readlane_u32(__float_as_uint(mx), t));
     if (lane < TK) s.code[lane] = (!RAW && id == p.blank_id) ? kBlankCode : cd;
-    if (lane == 0) s.delta = A * (16.0f / 8388608.0f);
+    if (!DIRECT && lane == 0) s.delta = A * (16.0f / 8388608.0f);
+    if constexpr (DIRECT) {  // no threshold, no delta: here it says whether scores that are no numbers have to be looked for
+      const bool finite = lane >= TK || fabsf(s.logp[lane]) < INFINITY;
+      const bool all_finite = __ballot(!finite) == 0ull;
+      if (lane == 0) s.delta = all_finite ? 0.f : 1.f;
+    }
     if (RAW) {
       const unsigned long long has = __ballot(lane < TK && id == p.blank_id);
       const int bc = has ? __builtin_amdgcn_readlane(cd, __builtin_ctzll(has)) : -1;
@@ -558,14 +563,17 @@ __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams 
     __syncthreads();
     if constexpr (DIRECT) {
       unsigned long long v[2];
+      int live = 0;
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
         const int idx = 2 * tid + e;
         const int a = n2 == 1 ? idx : (int)__umulhi((unsigned)idx, p.magic_n2), bb = idx - a * n2;  // idx / n2
         const Digits4 da = split_digits(a, pad1, k, magic), db = split_digits(bb, pad2, k, magic);
         const float sc = add_slots(add_slots(0.f, false, s.logp, da, 0, T1, k), true, s.logp, db, T1, T2, k);
-        v[e] = idx < total ? rank_key(sc, (unsigned)idx) : 0ull;
+        v[e] = idx < total && sc == sc ? rank_key(sc, (unsigned)idx) : 0ull;
+        live += v[e] ? 1 : 0;
       }
+      if (delta != 0.f) block_exclusive_scan(live, s.red, &n_s);
       block_sort_desc_fast<2, kWaves>(v, s.ckeys, s.keys, ror4_is_up);
     } else {
     // exact key of a survivor at (row of sorted X, column of sorted Y): the first half's partial sum is

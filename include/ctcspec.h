@@ -426,7 +426,7 @@ int verify_sample_tokens(ctcspec_ctx* ctx, const float* logits, const int32_t* n
  *            gradient of its own: the values are then unspecified, nothing is read or written out of bounds
  * frame_len  [B] int32 device in: frames of sequence b that count (<= T)
  * workspace  device scratch of at least ctc_loss_workspace_bytes(B, T, Lmax) bytes, owned by the caller, contents
- *            undefined afterwards; calls that share it must not overlap
+ *            undefined afterwards; calls that share it must not overlap.  Bytes for some sizes serve all smaller ones
  * loss       [B] float device out; +inf when the label cannot be reached in frame_len frames
  * grad       [B,T,Vp1] float device out or NULL: d loss[b] / d logits[b,t,v]; zero for frames past frame_len and
  *            for sequences whose loss is +inf

@@ -834,10 +834,9 @@ static CtcWorkspace ctc_workspace(int B, int T, int Lmax) {
   CtcWorkspace w;
   size_t off = 0;
   auto carve = [&](size_t bytes) { size_t at = off; off = (off + bytes + 255) / 256 * 256; return at; };
-  const bool pipelined = ctc_pipelined(B, T, Lmax);
-  const size_t blocks = pipelined ? Lmax / kDpPairs + 1 : 1;
+  const size_t blocks = T >= kShortFrames ? Lmax / kDpPairs + 1 : 1;
   w.lpc = carve((size_t)B * T * (Lmax + 1) * 4);
-  // (one size for a shape whatever kernel it takes, but for what the pipeline adds)
+  // (one size for a shape whatever kernel it takes: a workspace sized for the largest batch serves the smaller ones)
   w.ag = carve((size_t)B * T * ctc_state_pitch(Lmax) * 4);
   w.bg = carve((size_t)B * T * ctc_state_pitch(Lmax) * 4);
   w.coff_a = carve((size_t)B * T * blocks * 8);
@@ -846,7 +845,7 @@ static CtcWorkspace ctc_workspace(int B, int T, int Lmax) {
   w.next = carve((size_t)B * Lmax * 4);
   w.first = carve((size_t)B * Lmax * 4);
   w.edge = w.wide = w.ticket = off;
-  if (pipelined) {
+  if (T >= kShortFrames) {
     w.edge = carve((size_t)B * 2 * T * blocks * 8);
     w.wide = carve((size_t)B * T * 4);
     w.ticket = carve(4);

@@ -321,7 +321,8 @@ int kv_commit(ctcspec_ctx* ctx, ctcspec_dtype dt, const void* k_tree, const void
  * k_cache, v_cache, kv_off [B] int64, ctx_len [B] int32, kv_cap: the layer's cache, laid out as for
  *           tree_verify_attn ([H, kv_cap, dh] per sequence at element offset kv_off[b]); not modified
  * workspace device scratch of at least draft_layer_workspace_bytes(B, T, D, H, F) bytes, owned by the
- *           caller, contents undefined afterwards; calls that share it must not overlap
+ *           caller, contents undefined afterwards; calls that share it must not overlap.  Bytes for some B and T serve
+ *           every smaller B and T
  * q_out     [B,H,T,dh] out or NULL: the rotated queries the attention step used (otherwise kept in the workspace)
  * k_new, v_new [B,H,T,dh] out
  * out       [B,T,D] out;  out_f32 [B,T,D] float out or NULL: the same values before rounding to bf16

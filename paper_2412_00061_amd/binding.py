@@ -402,9 +402,8 @@ def draft_layer_forward(ctx, x, weights, pos0, k_cache, v_cache, kv_off, ctx_len
     """x [B,T,D] bf16, weights from layer_weights() -> dict(out [B,T,D], k_new, v_new [B,H,T,dh][, out_f32][, q])."""
     B, T, D = x.shape
     dev = x.device
-    need = draft_layer_workspace_bytes(B, T, D, H, F)
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+        workspace = torch.empty(draft_layer_workspace_bytes(B, T, D, H, F), dtype=torch.uint8, device=dev)
     res = {"out": _out(out, "out", (B, T, D), torch.bfloat16, dev),
            "k_new": _out(out, "k_new", (B, H, T, D // H), torch.bfloat16, dev),
            "v_new": _out(out, "v_new", (B, H, T, D // H), torch.bfloat16, dev)}

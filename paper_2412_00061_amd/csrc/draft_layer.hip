@@ -318,7 +318,10 @@ static hipError_t launch_pass(LayerTileParams& tp, int rows, hipStream_t stream)
 struct LayerWorkspace {
   size_t q, attn, arows, h1, xn2, act, n_rows, causal, ss1, ss2, part, total;
 };
-static LayerWorkspace layer_workspace(int B, int T, int D, int H, int F, int cus) {
+// any_smaller: room for the plans of every smaller B*T too - fewer columns may take more splits and more partial sums, and
+// a workspace sized for the largest batch has to serve the others.  Within the tile widths (up to 16, 32, 64 columns) the
+// model's splits only fall as the columns grow, so the splits at the narrowest of a width, times its columns, are a bound.
+static LayerWorkspace layer_workspace(int B, int T, int D, int H, int F, int cus, bool any_smaller) {
   LayerWorkspace w;
   size_t off = 0;
   auto carve = [&](size_t bytes) { size_t at = off; off = (off + bytes + 255) / 256 * 256; return at; };
@@ -329,15 +332,22 @@ static LayerWorkspace layer_workspace(int B, int T, int D, int H, int F, int cus
   w.ss1 = carve(BT * (D / 256 + 1) * 4); w.ss2 = carve(BT * (D / 256 + 1) * 4);
   size_t max_floats = 0;
   const int shapes[4][2] = {{3 * D, D}, {D, D}, {2 * F, D}, {D, F}};
+  const long long most = (long long)BT < kLtMaxCols ? (long long)BT : kLtMaxCols, last = (long long)BT % kLtMaxCols;
   for (auto& s : shapes) {
-    for (long long left = (long long)BT; left > 0; left -= kLtMaxCols) {  // full passes, and the last one
-      const int cols = (int)(left < kLtMaxCols ? left : kLtMaxCols);
+    auto room = [&](int plan_cols, long long cols) {
       LayerPlan pl;
-      if (make_plan(pl, s[0], s[1], cols, (int)BT, cus)) {
-        const size_t floats = (size_t)pl.splits * cols * s[0];
-        max_floats = floats > max_floats ? floats : max_floats;
+      if (plan_cols < 1 || !make_plan(pl, s[0], s[1], plan_cols, (int)BT, cus)) return;
+      const size_t floats = (size_t)pl.splits * cols * s[0];
+      max_floats = floats > max_floats ? floats : max_floats;
+    };
+    if (any_smaller) {
+      for (int narrowest : {1, 17, 33}) {
+        const long long widest = narrowest == 1 ? 16 : (narrowest == 17 ? 32 : 64);
+        if (narrowest <= most) room(narrowest, most < widest ? most : widest);
       }
-      if (left >= 2 * kLtMaxCols) left = left % kLtMaxCols + 2 * kLtMaxCols;  // the full ones are all alike
+    } else {  // full passes, and the last one
+      room((int)most, most);
+      room((int)last, last);
     }
   }
   w.part = carve(max_floats * sizeof(float));
@@ -365,7 +375,7 @@ using namespace ctcspec;
 
 extern "C" size_t draft_layer_workspace_bytes(int B, int T, int D, int H, int F) {
   if (B < 1 || T < 1 || D < 1 || H < 1 || F < 1) return 0;
-  return layer_workspace(B, T, D, H, F, device_cus()).total;
+  return layer_workspace(B, T, D, H, F, device_cus(), true).total;
 }
 
 extern "C" int draft_layer_forward(ctcspec_ctx* ctx, ctcspec_dtype dt, const void* x,
@@ -394,7 +404,7 @@ extern "C" int draft_layer_forward(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
   for (const void* q : ptrs)
     CTCSPEC_REQUIRE(ctx, aligned16(q), CTCSPEC_EINVAL, "draft_layer_forward: pointers must be 16-byte aligned");
   const int cus = device_cus();
-  const LayerWorkspace lw = layer_workspace(B, T, D, H, F, cus);
+  const LayerWorkspace lw = layer_workspace(B, T, D, H, F, cus, false);
   CTCSPEC_REQUIRE(ctx, workspace_bytes >= lw.total, CTCSPEC_EINVAL,
                   "draft_layer_forward: workspace of %zu bytes needed, %zu given", lw.total, workspace_bytes);
 

@@ -411,15 +411,22 @@ __device__ void ctc_links(const CtcParams& p, int b, int part, int parts, int32_
 //
 // The values are linear, as mantissa and exponent (m in [0.5, 1), value m * 2^e): three ldexp and a sum take the place of
 // three exp2 and a log2, the relative error of a step is 2^-24 whatever the length of the sequence, and no frame maximum has
-// to be known.  An impossible state has e = kDpFloor; everything below kDpImpossible counts as impossible.  Sequences
-// with a finite log-probability so low that exponents could get there (wide_below: about -32768, a token that is masked
-// out by a large finite number) are left to ctc_dp_wide: log domain, one workgroup, slow.
+// to be known.  An impossible state has e = kDpFloor; everything below kDpImpossible counts as impossible.
+//
+// Sequences with a finite log-probability so low that exponents could get there (wide_below: about -32768, a token that
+// is masked out by a large finite number) run the same pipeline in the log domain (LOG): a block holds its values
+// against a reference of its own - the larger of its largest value and of the one handed over, in the frame before - so no
+// block waits for another's maximum either.  The reference is a double, the values are floats against it, and what is
+// handed over is the whole value as a double.
 //
 // The backward recursion is the forward one over the mirrored sequence (last frame and last state first).
 //
 // Bound: instruction issue of wavefront 0, about 40 instructions a frame (0.1 us).  Measured, 4 sequences of 2048 frames
 // with up to 1024 labels: 217 us.  One workgroup of 1024 threads per sequence and direction, log domain, a barrier and a
 // frame maximum per frame took 1221 us, and its gradient was five times as far from the float64 one (5e-6 against 9e-7).
+// In the log domain a frame takes about 0.25 us: 4 x 2048 frames of 1001 symbols, 1024 labels, the blank masked with -1e9,
+// 712 us a call; 8 x 512 frames, 100 labels 124 us.  One workgroup per sequence and direction, a barrier and a frame
+// maximum per frame: 1794 and 258 us with 1024 threads, 2400 and 223 us with 256 and the pairs in registers.
 constexpr int kDpFrames = 16;
 constexpr int kDpPairs = 64;
 constexpr int kDpThreads = 256;
@@ -455,6 +462,9 @@ __device__ __forceinline__ void wave_max_i32(int (&v)[N]) {
   }
 }
 
+__device__ __forceinline__ double as_double(unsigned int lo, unsigned int hi) {
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 struct DpValue { float m; int e; };
 // log2 p -> p.  Not a number stays one in m, with an exponent that sinks nothing: it is no impossible state.
 __device__ __forceinline__ DpValue dp_probability(float l) {
@@ -472,135 +482,13 @@ __device__ __forceinline__ DpValue dp_scaled(float sum, int e, float pm, int pe)
   return v;
 }
 
-// One workgroup, any log-probabilities: log domain, every frame relative to the largest value of the frame before.  A
-// thread holds NR pairs in registers (the host's limits: NR <= 8), neighbours come by lane shifts and, between wavefronts,
-// through LDS, one barrier a frame; probabilities are fetched kAhead frames ahead.
-// Bound: latency of a frame.  4 x 2048 frames, 1024 labels, the blank masked with -1e9: 2.05 ms a call; 8 x 512, 100
-// labels: 216 us (7.03 ms and 564 us when every frame went through memory).
-template <int NR>
-__device__ __forceinline__ void ctc_dp_wide(const CtcParams& p, int b, bool backward, int L, int Tb) {
-  constexpr int kWaves = kDpThreads / 64, kAhead = 4;
-  __shared__ float wmax[2][kWaves], edge[2][kWaves][NR], fin[2];
-  const int tid = threadIdx.x, lane = tid & 63, SP = ctc_state_pitch(p.Lmax), LP = p.Lmax + 1;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int32_t* y = p.labels + (size_t)b * p.Lmax;
-  const float* lpc = p.lpc + (size_t)b * p.T * LP;
-  float* g = (backward ? p.bg : p.ag) + (size_t)b * p.T * SP;
-  double* coff = (backward ? p.coff_b : p.coff_a) + (size_t)b * p.T * p.blocks;
-  float blank[NR], label[NR];  // pair tid + r * kDpThreads
-  int at[NR];
-  unsigned int skips = 0;
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    const int q = tid + r * kDpThreads;
-    const int j = backward ? L - 1 - q : q, jb = backward ? L - q : q - 1;  // label of the pair, of the pair before
-    at[r] = q < L ? j : p.Lmax;
-    skips |= (q >= 1 && q < L && y[j] != y[jb]) ? 1u << r : 0u;
-    blank[r] = label[r] = -INFINITY;
-  }
-  auto frame = [&](int i) { return backward ? Tb - 1 - i : i; };
-  float pl[kAhead][NR], pb[kAhead];
-  auto fetch = [&](int i, float (&l)[NR], float& bl) __attribute__((always_inline)) {
-    const float* lp = lpc + (size_t)frame(i < Tb ? i : Tb - 1) * LP;
-    bl = lp[p.Lmax];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) l[r] = lp[at[r]];
-  };
-#pragma unroll
-  for (int u = 0; u < kAhead; ++u) fetch(u, pl[u], pb[u]);
-  double offset = 0.0;
-  for (int i0 = 0; i0 < Tb; i0 += kAhead) {
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const int i = i0 + u, buf = i & 1;
-      if (i >= Tb) break;  // uniform
-      const int t = frame(i);
-      float shift = 0.f;
-      if (i) shift = frame_shift(fmaxf(fmaxf(wmax[buf][0], wmax[buf][1]), fmaxf(wmax[buf][2], wmax[buf][3])));
-      offset += (double)shift;
-      float mine = -INFINITY;
-#pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const int q = tid + r * kDpThreads;
-        float a_blank = q == 0 ? 0.f : -INFINITY, a_label = a_blank;
-        const float own = label[r];
-        if (i) {
-          const float over = wave ? edge[buf][wave - 1][r] : (r ? edge[buf][kWaves - 1][r ? r - 1 : 0] : -INFINITY);
-          const float before = __uint_as_float(lane_shift_up(__float_as_uint(own), __float_as_uint(over)));
-          a_blank = ctc_log_add2(blank[r], before);
-          a_label = ctc_log_add3(own, blank[r], (skips >> r) & 1 ? before : -INFINITY);
-        }
-        a_blank += pb[u] - shift;
-        a_label = q < L ? a_label + (pl[u][r] - shift) : -INFINITY;
-        blank[r] = a_blank;
-        label[r] = a_label;
-        if (q <= L) {
-          *(f32x2*)(g + (size_t)t * SP + 2 * q) = f32x2{a_blank, a_label};
-          mine = fmaxf(mine, fmaxf(a_blank, a_label));
-        }
-        if (lane == 63) edge[buf ^ 1][wave][r] = a_label;
-      }
-      for (int w = tid; w < p.blocks; w += kDpThreads) coff[(size_t)t * p.blocks + w] = offset;
-      mine = wave_max_f32(mine);
-      if (lane == 0) wmax[buf ^ 1][wave] = mine;
-      fetch(i + kAhead, pl[u], pb[u]);
-      lds_barrier();
-    }
-  }
-  if (backward) return;
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    if (tid + r * kDpThreads == L) fin[0] = blank[r];
-    if (tid + r * kDpThreads == L - 1) fin[1] = label[r];
-  }
-  lds_barrier();
-  if (tid == 0) {
-    const double logP = offset + (double)ctc_log_add2(fin[0], L > 0 ? fin[1] : -INFINITY);
-    p.loss[b] = (float)(-logP * 0.6931471805599453);
-    p.logp[b] = logP;
-  }
-}
-
-// Workgroups beyond the recursions' `jobs` build the links of the labels meanwhile.
-__global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, int directions, int jobs) {
-  __shared__ DpShared sh;
-  __shared__ int job_id;
+// One block of states of one sequence and direction, by a workgroup.  LOG: in the log domain (see above).
+template <bool LOG>
+__device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int directions, int block, int b, bool backward,
+                                          int L, int Tb) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (tid == 0) job_id = atomicAdd(p.ticket, 1);
-  __syncthreads();
-  const int job = __builtin_amdgcn_readfirstlane(job_id);
-  if ((unsigned)job >= gridDim.x) return;  // (only if something else writes the workspace meanwhile)
-  if (job >= jobs) {
-    const int b = (job - jobs) % p.B;
-    ctc_links(p, b, (job - jobs) / p.B, ((int)gridDim.x - jobs) / p.B, (int32_t*)&sh);
-    return;
-  }
-  const int block = job / (directions * p.B), rest = job - block * (directions * p.B);
-  const int b = rest / directions;
-  const bool backward = rest - b * directions != 0;
-  const int L = clampi(p.label_len[b], 0, p.Lmax);
-  const int Tb = clampi(p.frame_len[b], 0, p.T);
-  if (block * kDpPairs > L) return;
   const bool last_block = (block + 1) * kDpPairs > L;
-  if (Tb == 0) {
-    if (tid == 0 && !backward && block == 0) {
-      p.loss[b] = L == 0 ? 0.f : INFINITY;
-      p.logp[b] = L == 0 ? 0.0 : -(double)INFINITY;
-    }
-    return;
-  }
-  int too_low = 0;
-  for (int t = tid; t < Tb; t += kDpThreads) too_low |= p.wide[(size_t)b * p.T + t];
-  if (__syncthreads_or(too_low)) {
-    if (block) return;
-    static_assert(kCtcMaxLabels < 8 * kDpThreads, "every pair has a place");
-    if (L < kDpThreads) ctc_dp_wide<1>(p, b, backward, L, Tb);
-    else if (L < 2 * kDpThreads) ctc_dp_wide<2>(p, b, backward, L, Tb);
-    else if (L < 5 * kDpThreads) ctc_dp_wide<5>(p, b, backward, L, Tb);
-    else ctc_dp_wide<8>(p, b, backward, L, Tb);
-    return;
-  }
   const int q = block * kDpPairs + lane;
   const int32_t* y = p.labels + (size_t)b * p.Lmax;
   const int j = backward ? L - 1 - q : q, jb = backward ? L - q : q - 1;  // label of the pair, of the pair before
@@ -612,7 +500,9 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
   // frame i of the recursion (0 .. Tb-1) is frame i or Tb - 1 - i of the sequence
   auto frame = [&](int i) { return backward ? Tb - 1 - i : i; };
   bool lost = false;  // a wait was given up: not a number from there on
-  constexpr unsigned long long kNothing = ((unsigned long long)(unsigned)kDpFloor << 32) | 0x3f000000u;  // 0.5 * 2^kDpFloor
+  // a value of 0 - 0.5 * 2^kDpFloor; LOG: -inf as a double - and one that is not a number
+  constexpr unsigned long long kNothing = LOG ? 0xfff0000000000000ull : ((unsigned long long)(unsigned)kDpFloor << 32) | 0x3f000000u;
+  constexpr unsigned long long kLost = LOG ? 0x7ff8000000000000ull : 0x7fc00000ull;
   auto look = [&](int i) -> unsigned long long {  // per lane: the value of frame i from the block before, 0: not there yet
     if (block == 0 || i < 0 || i >= Tb) return kNothing;
     return __hip_atomic_load(edge + (size_t)frame(i) * p.blocks + (block - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -623,7 +513,7 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
       v = look(i);
       lost = polls >= kDpMaxPolls;
     }
-    return v ? v : 0x7fc00000ull;
+    return v ? v : kLost;
   };
 
   if (wave == 0) {
@@ -631,6 +521,9 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
     // before the first frame: all of the weight in the first blank
     float bm = 0.5f, lm = 0.5f;
     int be = q == 0 ? 1 : kDpFloor, le = kDpFloor;
+    // LOG: the two states against off, the largest of the block against off
+    float bl = q == 0 ? 0.f : -INFINITY, ll = -INFINITY, top = block == 0 ? 0.f : -INFINITY;
+    double off = 0.0;
     lds_barrier();  // LDS only: loads and stores of memory stay in flight
     auto frames_of = [&](int ch, auto partial) __attribute__((always_inline)) {
       const int buf = ch & 1;
@@ -638,6 +531,26 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
       for (int f = 0; f < kDpFrames; ++f) {
         const u32x2 pr = sh.in[buf][f][lane];
         const u32x4 un = sh.uni[buf][f];
+        const bool run = !decltype(partial)::value || ch * kDpFrames + f < Tb;  // frames past the end change nothing
+        if constexpr (LOG) {
+          const double h = as_double(un[2], un[3]);
+          double ref = fmax(off + (double)top, h);
+          ref = ref > -(double)INFINITY ? ref : off;
+          // (a block without any value may be far from what arrives; the floor keeps -inf - shift what it is)
+          const float shift = fmaxf((float)(ref - off), -3.0e38f), first = (float)(h - ref);
+          const float b0 = bl - shift, l0 = ll - shift;
+          const float before = __uint_as_float(lane_shift_up(__float_as_uint(l0), __float_as_uint(first)));
+          const float nb = ctc_log_add2(b0, before) + __uint_as_float(un[0]);
+          const float nl = ctc_log_add3(l0, b0, skip ? before : -INFINITY) + __uint_as_float(pr[0]);
+          const float largest = wave_max_f32(fmaxf(nb, nl));
+          bl = run ? nb : bl;
+          ll = run ? nl : ll;
+          top = run ? largest : top;
+          off = run ? ref : off;
+          const unsigned long long bits = (unsigned long long)__double_as_longlong(off);
+          sh.out[buf][f][lane] = u32x4{__float_as_uint(bl), __float_as_uint(ll), (unsigned)bits, (unsigned)(bits >> 32)};
+          continue;
+        }
         const float xm = __uint_as_float(lane_shift_up(__float_as_uint(lm), un[2]));
         const int xe = (int)lane_shift_up((unsigned)le, un[3]);
         const int e0 = imax(be, xe);
@@ -648,7 +561,6 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
                          __builtin_amdgcn_ldexpf(xm, ke - e1);
         const DpValue nb = dp_scaled(s0, e0, __uint_as_float(un[0]), (int)un[1]);
         const DpValue nl = dp_scaled(s1, e1, __uint_as_float(pr[0]), (int)pr[1]);
-        const bool run = !decltype(partial)::value || ch * kDpFrames + f < Tb;  // frames past the end change nothing
         bm = run ? nb.m : bm;
         be = run ? nb.e : be;
         lm = run ? nl.m : lm;
@@ -663,18 +575,24 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
     }
     if (!backward && last_block) {
       // P = the last blank + the label before it
-      unsigned int fm = __float_as_uint(0.5f), fe = (unsigned)kDpFloor;
-      if (block > 0 && L == block * kDpPairs) {
-        const unsigned long long v = wait_for(Tb - 1, look(Tb - 1));
-        fm = (unsigned)v;
-        fe = (unsigned)(v >> 32);
-      }
-      const float xm = __uint_as_float(lane_shift_up(__float_as_uint(lm), fm));
-      const int xe = (int)lane_shift_up((unsigned)le, fe);
+      unsigned long long v = kNothing;
+      if (block > 0 && L == block * kDpPairs) v = wait_for(Tb - 1, look(Tb - 1));
+      const unsigned int first0 = (unsigned)v, first1 = (unsigned)(v >> 32);
+      const float xm = __uint_as_float(lane_shift_up(__float_as_uint(LOG ? ll : lm), first0));
+      const int xe = (int)lane_shift_up((unsigned)le, first1);
       if (q == L) {
-        const int e = imax(be, xe);
-        const float s = __builtin_amdgcn_ldexpf(bm, be - e) + __builtin_amdgcn_ldexpf(xm, xe - e);
-        const double logP = e < kDpImpossible && s == s ? -(double)INFINITY : (double)e + (double)__builtin_amdgcn_logf(s);
+        double logP;
+        if constexpr (LOG) {
+          const double last = off + (double)bl, before = lane ? off + (double)xm : as_double(first0, first1);
+          const double m = fmax(last, before);
+          logP = m > -(double)INFINITY ? m + (double)__builtin_amdgcn_logf(__builtin_amdgcn_exp2f((float)(last - m)) +
+                                                                           __builtin_amdgcn_exp2f((float)(before - m)))
+                                       : last + before;  // -inf, or not a number
+        } else {
+          const int e = imax(be, xe);
+          const float s = __builtin_amdgcn_ldexpf(bm, be - e) + __builtin_amdgcn_ldexpf(xm, xe - e);
+          logP = e < kDpImpossible && s == s ? -(double)INFINITY : (double)e + (double)__builtin_amdgcn_logf(s);
+        }
         p.loss[b] = (float)(-logP * 0.6931471805599453);
         p.logp[b] = logP;
       }
@@ -697,10 +615,14 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
       const int buf = ch & 1;
 #pragma unroll
       for (int f = 0; f < kDpFrames; ++f) {
-        const DpValue v = dp_probability(lp[f]);
-        sh.in[buf][f][lane] = u32x2{__float_as_uint(v.m), has_label ? (unsigned)v.e : (unsigned)kDpZeroP};
+        if constexpr (LOG) {
+          sh.in[buf][f][lane] = u32x2{__float_as_uint(has_label ? lp[f] : -INFINITY), 0u};
+        } else {
+          const DpValue v = dp_probability(lp[f]);
+          sh.in[buf][f][lane] = u32x2{__float_as_uint(v.m), has_label ? (unsigned)v.e : (unsigned)kDpZeroP};
+        }
       }
-      const DpValue vb = dp_probability(lb);
+      const DpValue vb = LOG ? DpValue{lb, 0} : dp_probability(lb);
       if (lane < kDpFrames) {
         const unsigned long long h = wait_for(ch * kDpFrames + lane - 1, early);
         sh.uni[buf][lane] = u32x4{__float_as_uint(vb.m), (unsigned)vb.e, (unsigned)h, (unsigned)(h >> 32)};
@@ -723,8 +645,12 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
         const int buf = (ch - 1) & 1, i0 = (ch - 1) * kDpFrames;
         if (wave == 2 && !last_block && lane < kDpFrames && i0 + lane < Tb) {
           const u32x4 v = sh.out[buf][lane][63];
-          __hip_atomic_store(edge + (size_t)frame(i0 + lane) * p.blocks + block, ((unsigned long long)v[3] << 32) | v[2],
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          unsigned long long word = ((unsigned long long)v[3] << 32) | v[2];
+          if constexpr (LOG) {
+            word = (unsigned long long)__double_as_longlong(as_double(v[2], v[3]) + (double)__uint_as_float(v[1]));
+            word = word ? word : 1ull << 63;  // -0.0
+          }
+          __hip_atomic_store(edge + (size_t)frame(i0 + lane) * p.blocks + block, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if (directions == 2) {  // (the loss alone needs no rows)
           constexpr int kGroup = 4;  // frames side by side: the chain of a frame is long and narrow
@@ -737,17 +663,17 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
             for (int u = 0; u < kGroup; ++u) v[u] = sh.out[buf][first + u][lane];
 #pragma unroll
             for (int u = 0; u < kGroup; ++u) ref[u] = q <= L ? imax((int)v[u][1], (int)v[u][3]) : kDpFloor;
-            wave_max_i32(ref);
+            if constexpr (!LOG) wave_max_i32(ref);
 #pragma unroll
             for (int u = 0; u < kGroup; ++u) {
               const int be = (int)v[u][1], le = (int)v[u][3];
-              const f32x2 x = {
+              const f32x2 x = LOG ? f32x2{__uint_as_float(v[u][0]), __uint_as_float(v[u][1])} : f32x2{
                   be < kDpImpossible ? -INFINITY : (float)(be - ref[u]) + __builtin_amdgcn_logf(__uint_as_float(v[u][0])),
                   le < kDpImpossible ? -INFINITY : (float)(le - ref[u]) + __builtin_amdgcn_logf(__uint_as_float(v[u][2]))};
               const int i = i0 + first + u;
               const size_t t = (size_t)frame(i);
               if (i < Tb && q <= L) *(f32x2*)(g + t * SP) = x;
-              if (i < Tb && lane == 0) coff[t * p.blocks] = (double)ref[u];
+              if (i < Tb && lane == 0) coff[t * p.blocks] = LOG ? as_double(v[u][2], v[u][3]) : (double)ref[u];
             }
           }
         }
@@ -755,6 +681,39 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
       lds_barrier();
     }
   }
+}
+
+// Workgroups beyond the recursions' `jobs` build the links of the labels meanwhile.
+__global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, int directions, int jobs) {
+  __shared__ DpShared sh;
+  __shared__ int job_id;
+  const int tid = threadIdx.x;
+  if (tid == 0) job_id = atomicAdd(p.ticket, 1);
+  __syncthreads();
+  const int job = __builtin_amdgcn_readfirstlane(job_id);
+  if ((unsigned)job >= gridDim.x) return;  // (only if something else writes the workspace meanwhile)
+  if (job >= jobs) {
+    const int b = (job - jobs) % p.B;
+    ctc_links(p, b, (job - jobs) / p.B, ((int)gridDim.x - jobs) / p.B, (int32_t*)&sh);
+    return;
+  }
+  const int block = job / (directions * p.B), rest = job - block * (directions * p.B);
+  const int b = rest / directions;
+  const bool backward = rest - b * directions != 0;
+  const int L = clampi(p.label_len[b], 0, p.Lmax);
+  const int Tb = clampi(p.frame_len[b], 0, p.T);
+  if (block * kDpPairs > L) return;
+  if (Tb == 0) {
+    if (tid == 0 && !backward && block == 0) {
+      p.loss[b] = L == 0 ? 0.f : INFINITY;
+      p.logp[b] = L == 0 ? 0.0 : -(double)INFINITY;
+    }
+    return;
+  }
+  int too_low = 0;
+  for (int t = tid; t < Tb; t += kDpThreads) too_low |= p.wide[(size_t)b * p.T + t];
+  if (__syncthreads_or(too_low)) ctc_block<true>(p, sh, directions, block, b, backward, L, Tb);
+  else ctc_block<false>(p, sh, directions, block, b, backward, L, Tb);
 }
 
 // One wavefront per frame: the occupancies gamma_t(s) = alpha_t(s) beta_t(s) / (p_t(z_s) P) of the label's tokens

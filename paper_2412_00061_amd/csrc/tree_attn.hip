@@ -97,7 +97,25 @@ struct AttnSplit {
   float* pl;   // [unit][rows] running sum
 };
 
-// 16 bytes of K or V; STREAM: read once and gone (see streams_past_cache)
+// K and V that do not stay in the 256 MB last-level cache from one call to the next are read with loads that leave no copy
+// behind.  What counts is what the call reads (the lengths are known on the device only), not the capacity: 8 sequences x 32
+// heads x 64 rows, us with plain / streaming loads, the same caches again and again | caches that went out meanwhile:
+//   16 MB 12.5 / 17.9 | 18.3 / 19.1     64 MB 20.1 / 32.8 | 34.9 / 33.0      144 MB (ragged) 40.9 / 54.9 | 58.2 / 55.9
+//   256 MB 48.9 / 69.5 | 75.9 / 70.0    375 MB 77.7 / 68.3 | 76.8 / 67.7
+// A model has more layers than one: beyond half of the cache two calls' K and V put each other out, so that is where the
+// line lies.  At most 16 rows (the draft module's single layer) gain next to nothing while the caches could stay (144 MB
+// 29.0 / 43.5 | 47.0 / 46.7; 375 MB 68.4 / 61.2 | 69.0 / 63.3): there the line is the whole cache.
+constexpr long long kStreamBytes = 128LL << 20, kStreamBytesFew = 256LL << 20;
+__device__ __forceinline__ bool reads_more_than(const AttnParams& p, long long bytes) {
+  int rows = 0;
+  for (int b = threadIdx.x & 63; b < p.B; b += 64) {
+    const int L = p.ctx_len[b];
+    rows += L < 0 ? 0 : (L > p.kv_cap ? p.kv_cap : L);
+  }
+  return (long long)wave_sum_i32(rows) * p.H * 512 > bytes;
+}
+
+// 16 bytes of K or V; STREAM: read once and gone
 template <bool STREAM>
 __device__ __forceinline__ u32x4 load_kv(const unsigned char* a) {
   if constexpr (STREAM) return __builtin_nontemporal_load((const u32x4*)a);
@@ -105,8 +123,7 @@ __device__ __forceinline__ u32x4 load_kv(const unsigned char* a) {
 }
 
 template <int QT, int NW, int CW, int PF, bool STREAM>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void tree_attn_bf16_kernel(AttnParams p, AttnSplit sp) {
+__device__ __forceinline__ void tree_attn_bf16(const AttnParams& p, const AttnSplit& sp) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int ROWS = 16 * QT * CW;
   constexpr int KP = NW / CW;  // key parts: tiles taken per iteration
@@ -429,6 +446,14 @@ void tree_attn_bf16_kernel(AttnParams p, AttnSplit sp) {
   }
 }
 
+// LARGE: the capacity leaves room for more than kStreamBytes
+template <int QT, int NW, int CW, int PF, bool LARGE>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void tree_attn_bf16_kernel(AttnParams p, AttnSplit sp) {
+  if (LARGE && reads_more_than(p, kStreamBytes)) tree_attn_bf16<QT, NW, CW, PF, true>(p, sp);
+  else tree_attn_bf16<QT, NW, CW, PF, false>(p, sp);
+}
+
 // ---- bf16, dh = 128, at most 16 query rows (the draft module's layer, small trees) -----------------------------------
 // One row group, so the eight wavefronts of a workgroup split the KEYS: wavefront w takes the tiles w, w + 8, ... of its
 // head on its own - its tile in its own 16 KB of LDS, the next one in flight in registers, no barrier - and
@@ -458,8 +483,7 @@ __device__ __forceinline__ void store_rows4(const AttnParams& p, size_t at, f32x
 }
 
 template <bool STREAM>
-__global__ __launch_bounds__(64 * kFewWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void tree_attn_few_kernel(AttnParams p) {
+__device__ __forceinline__ void tree_attn_few(const AttnParams& p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -607,6 +631,13 @@ void tree_attn_few_kernel(AttnParams p) {
   const f32x4 r = acc * (1.0f / Lt);
   if (p.rows) store_rows4(p, ((size_t)b * p.max_nodes + row) * ((size_t)p.H * 128) + (size_t)h * 128 + d4, r);
   else *(f32x4*)(p.out + (node_base + row) * 128 + d4) = r;
+}
+
+template <bool LARGE>
+__global__ __launch_bounds__(64 * kFewWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void tree_attn_few_kernel(AttnParams p) {
+  if (LARGE && reads_more_than(p, kStreamBytesFew)) tree_attn_few<true>(p);
+  else tree_attn_few<false>(p);
 }
 
 // ---- any head dimension, float or bf16 ---------------------------------------------------------------------------
@@ -970,16 +1001,11 @@ static hipError_t launch_merge(const AttnParams& p, const AttnSplit& sp, int row
                      rows == 64 ? 6 : 7);
   return hipGetLastError();
 }
-// Caches of more than three quarters of the 256 MB last-level cache (all heads, whole capacity): K and V of a call cannot still be
-// there when they are read again, and loads that leave no copy behind are faster.  8 sequences x 32 heads x 2064 positions
-// (270 MB), 64 rows: 54.8 -> 51.1 us, 16 rows 43 -> 41; at 4 sequences (135 MB at capacity 2064, a third of it used) they
-// would lose what repeated calls find in the cache: 27.4 -> 29.6 us.
-static bool streams_past_cache(const AttnParams& p) {
-  return (long long)p.B * p.H * p.kv_cap * 512 > 192LL * 1024 * 1024;
-}
-template <int QT, int NW, int CW, int PF, bool STREAM = false>
+// whether a call can read more than that: all heads, whole capacity
+static bool may_read_more_than(const AttnParams& p, long long bytes) { return (long long)p.B * p.H * p.kv_cap * 512 > bytes; }
+template <int QT, int NW, int CW, int PF, bool LARGE = false>
 static hipError_t launch_attn_bf16(const AttnParams& p, const AttnSplit& sp, hipStream_t stream) {
-  auto kern = tree_attn_bf16_kernel<QT, NW, CW, PF, STREAM>;
+  auto kern = tree_attn_bf16_kernel<QT, NW, CW, PF, LARGE>;
   const long long blocks = (long long)sp.QB * sp.S * p.H * p.B;
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * NW), attn_lds_bytes(NW / CW), stream, p, sp);
   hipError_t e = hipGetLastError();
@@ -1086,7 +1112,7 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
         p.rows = rows; p.rows_plane = rows_plane;
         if (rows_written) *rows_written = 1;
       }
-      if (streams_past_cache(p))
+      if (may_read_more_than(p, kStreamBytesFew))
         hipLaunchKernelGGL(tree_attn_few_kernel<true>, dim3((unsigned)bh), dim3(64 * kFewWaves), kFewLds, ctx->stream, p);
       else
         hipLaunchKernelGGL(tree_attn_few_kernel<false>, dim3((unsigned)bh), dim3(64 * kFewWaves), kFewLds, ctx->stream, p);
@@ -1111,7 +1137,7 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
     }
     // (two 64-row blocks share K and V through L2)
     const hipError_t e = !rows64 ? launch_attn_bf16<1, 8, 8, 2>(p, sp, ctx->stream)
-                         : sp.QB == 1 && streams_past_cache(p) ? launch_attn_bf16<1, 8, 4, 2, true>(p, sp, ctx->stream)
+                         : sp.QB == 1 && may_read_more_than(p, kStreamBytes) ? launch_attn_bf16<1, 8, 4, 2, true>(p, sp, ctx->stream)
                                                                : launch_attn_bf16<1, 8, 4, 2>(p, sp, ctx->stream);
     CTCSPEC_HIP(ctx, e);
     return CTCSPEC_OK;

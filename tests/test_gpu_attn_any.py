@@ -118,7 +118,7 @@ def test_attention_few_rows(pkg, N, q_scale, tol):
         ctx.close()
 
 
-# Caches past the last-level cache's size are read with streaming loads: the same bits as the same rows in small caches.
+# Caches whose capacity is past the last-level cache's size, with short histories: the same bits as the same rows in small caches.
 @pytest.mark.parametrize("N", [8, 16, 17, 64])
 def test_attention_large_capacity(pkg, N):
     B, H, big, small = 5, 32, 2600, 512  # 5 x 32 x 2600 x 512 bytes: 213 MB
@@ -138,3 +138,30 @@ def test_attention_large_capacity(pkg, N):
         torch.cuda.synchronize()
         ctx.close()
     assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1])
+
+
+# Histories that are past what stays in the last-level cache are read with streaming loads: the same bits as from calls for
+# some of the sequences at a time, which read less (144 and 90 MB with 64 rows; 282 and 176 MB with 16 rows and fewer).
+@pytest.mark.parametrize("N", [8, 16, 17, 64])
+def test_attention_long_histories(pkg, N):
+    B, H, L = 8, 32, 2150 if N <= 16 else 1100
+    cap = L + 5
+    g = torch.Generator(device="cuda").manual_seed(N)
+    rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16)
+    q, kt, vt, k, v = rnd(B, H, N, 128), rnd(B, H, N, 128), rnd(B, H, N, 128), rnd(B, H, cap, 128), rnd(B, H, cap, 128)
+    lens = np.array([L, L - 1, L - 31, L, L - 32, L, L - 33, L], dtype=np.int32)
+    mask = torch.tensor([[-1 if i == 63 else (1 << (i + 1)) - 1] for i in range(N)], device="cuda").view(1, N, 1).repeat(B, 1, 1)
+    ctx = pkg.Context(max_batch=B, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=N, max_heads=H, max_head_dim=128)
+
+    def call(s):
+        n = len(lens[s])
+        off = dev_i64(np.arange(n, dtype=np.int64) * H * cap * 128)
+        part = [x[s].contiguous() for x in (q, k, v, kt, vt, mask)]
+        out = pkg.tree_verify_attn(ctx, *part[:3], off, dev_i32(lens[s]), cap, *part[3:5], dev_i32(np.full(n, N)), part[5], 0.09)
+        torch.cuda.synchronize()
+        return out
+
+    whole = call(slice(0, 8))
+    assert torch.isfinite(whole).all()
+    assert torch.equal(whole[:5], call(slice(0, 5))) and torch.equal(whole[3:], call(slice(3, 8)))
+    ctx.close()

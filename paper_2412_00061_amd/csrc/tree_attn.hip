@@ -100,12 +100,15 @@ struct AttnSplit {
 // K and V that do not stay in the 256 MB last-level cache from one call to the next are read with loads that leave no copy
 // behind.  What counts is what the call reads (the lengths are known on the device only), not the capacity: 8 sequences x 32
 // heads x 64 rows, us with plain / streaming loads, the same caches again and again | caches that went out meanwhile:
-//   16 MB 12.5 / 17.9 | 18.3 / 19.1     64 MB 20.1 / 32.8 | 34.9 / 33.0      144 MB (ragged) 40.9 / 54.9 | 58.2 / 55.9
-//   256 MB 48.9 / 69.5 | 75.9 / 70.0    375 MB 77.7 / 68.3 | 76.8 / 67.7
-// A model has more layers than one: beyond half of the cache two calls' K and V put each other out, so that is where the
-// line lies.  At most 16 rows (the draft module's single layer) gain next to nothing while the caches could stay (144 MB
-// 29.0 / 43.5 | 47.0 / 46.7; 375 MB 68.4 / 61.2 | 69.0 / 63.3): there the line is the whole cache.
-constexpr long long kStreamBytes = 128LL << 20, kStreamBytesFew = 256LL << 20;
+//   16 MB 12.5 / 17.9 | 18.3 / 19.1     64 MB 20.1 / 32.8 | 34.9 / 33.0       96 MB 24.9 / 36.5 | 40.3 / 37.6
+//   144 MB (ragged) 40.9 / 54.9 | 58.2 / 55.9    256 MB 48.9 / 69.5 | 75.9 / 70.0    375 MB 77.7 / 68.3 | 76.8 / 67.7
+// Nothing tells a call which of the two it is.  In a model the other layers' weights and caches pass in between, so large
+// calls hardly find anything again; small ones may, and have little to gain otherwise: the line lies where the second
+// column's gain has reached 7 %, with room for two calls' caches below it.  At most 16 rows gain next to nothing while the
+// caches could stay (144 MB 29.0 / 43.5 | 47.0 / 46.7; 375 MB 68.4 / 61.2 | 69.0 / 63.3): there the line is the whole cache -
+// but for the draft layer, whose own weights (405 MB at the 7B shape) pass in between: 144 MB, whole layer 183 / 180.5 us.
+constexpr long long kStreamBytes = 96LL << 20, kStreamBytesFew = 256LL << 20;
+__host__ __device__ __forceinline__ long long stream_line_few(const AttnParams& p) { return p.rows ? kStreamBytes : kStreamBytesFew; }
 __device__ __forceinline__ bool reads_more_than(const AttnParams& p, long long bytes) {
   int rows = 0;
   for (int b = threadIdx.x & 63; b < p.B; b += 64) {
@@ -446,7 +449,7 @@ __device__ __forceinline__ void tree_attn_bf16(const AttnParams& p, const AttnSp
   }
 }
 
-// LARGE: the capacity leaves room for more than kStreamBytes
+// LARGE: the capacity leaves room for more than the line
 template <int QT, int NW, int CW, int PF, bool LARGE>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tree_attn_bf16_kernel(AttnParams p, AttnSplit sp) {
@@ -636,7 +639,7 @@ __device__ __forceinline__ void tree_attn_few(const AttnParams& p) {
 template <bool LARGE>
 __global__ __launch_bounds__(64 * kFewWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tree_attn_few_kernel(AttnParams p) {
-  if (LARGE && reads_more_than(p, kStreamBytesFew)) tree_attn_few<true>(p);
+  if (LARGE && reads_more_than(p, stream_line_few(p))) tree_attn_few<true>(p);
   else tree_attn_few<false>(p);
 }
 
@@ -1112,7 +1115,7 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
         p.rows = rows; p.rows_plane = rows_plane;
         if (rows_written) *rows_written = 1;
       }
-      if (may_read_more_than(p, kStreamBytesFew))
+      if (may_read_more_than(p, stream_line_few(p)))
         hipLaunchKernelGGL(tree_attn_few_kernel<true>, dim3((unsigned)bh), dim3(64 * kFewWaves), kFewLds, ctx->stream, p);
       else
         hipLaunchKernelGGL(tree_attn_few_kernel<false>, dim3((unsigned)bh), dim3(64 * kFewWaves), kFewLds, ctx->stream, p);

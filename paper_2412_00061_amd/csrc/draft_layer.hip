@@ -10,18 +10,9 @@
 #include <utility>
 
 #include "gemm_tile.h"
+#include "layer_plan.h"
 
 namespace ctcspec {
-
-constexpr int kLtMaxCols = 64;  // columns of a pass; each is two bf16 columns (high and low part)
-constexpr int kLtMaxSplits = 16;
-constexpr int kLtTripK = 256;   // k elements of a trip of the tile loop (4 steps of 64): splits are whole trips
-
-struct LayerPlan {
-  int N, K, cols;  // out features, in features, columns of the pass
-  int splits;      // k splits, each leaving [cols][N] sums
-  int rows;        // weight rows of a workgroup
-};
 
 __device__ __forceinline__ unsigned short float_to_bf16_bits(float f) {
   unsigned int u = __float_as_uint(f);
@@ -36,7 +27,7 @@ __device__ __forceinline__ unsigned short float_to_bf16_bits(float f) {
 // leaves one sum per (column, row): part[split][column][row], added up by the kernel that follows in ascending order.
 // Why this split: a pass is bound by what a compute unit takes in per step - its weight rows from HBM and all
 // columns' activations from L2, about 45 GB/s together - so the rows of a workgroup and the number of splits are chosen
-// to fill the 256 compute units in as few rounds as possible (make_plan), not by the matrix alone.
+// to fill the 256 compute units in as few rounds as possible (layer_plan.h), not by the matrix alone.
 // Measured at the 7B shape (passes over 101, 34, 180 and 90 MB), all four passes together: 8 columns 80 us = 5.1 TB/s,
 // 64 columns 108 us.  Before, wavefronts streamed 16-row units past activations held in LDS, 16 columns at a time: 107 us
 // for 8 columns (three accumulators per wavefront for ranges that cross row tiles, 6 MB of partial tiles per pass),
@@ -258,7 +249,7 @@ static int device_cus() {
   return cus;
 }
 
-// rows x 16, 32 or 64 columns (twice as many tile columns)
+// rows x 16, 32 or 64 columns (twice as many tile columns); which one: layer_plan.h
 using LayerTile128x16 = TileShape<8, 2, 128, 1>;
 using LayerTile256x16 = TileShape<8, 2, 128, 2>;
 using LayerTile128x32 = TileShape<4, 2, 128, 2>;
@@ -267,35 +258,6 @@ using LayerTile256x32 = TileShape<4, 2, 128, 4>;
 using LayerTile128x64 = TileShape<4, 4, 128, 2>;
 using LayerTile192x64 = TileShape<4, 4, 128, 3>;
 using LayerTile256x64 = TileShape<4, 4, 128, 4>;
-static int tile_columns(int cols) { return cols <= 16 ? 32 : (cols <= 32 ? 64 : 128); }
-
-// Rows of a workgroup and k splits of an [N][K] pass: fewest microseconds by the model
-//   rounds over the compute units x (steps x time of a step + 6 us until the first tile is in LDS)
-//   + the partial sums written and read back at 5 TB/s,
-// a step taking what the compute unit needs for its bytes: 45 GB/s for weights and activations together (the base
-// head's 1.39 us per 64 KB step), 25 GB/s for the weights alone (its share of HBM).
-static bool make_plan(LayerPlan& pl, int N, int K, int cols, int plane_cols, int cus) {
-  if (K % kLtTripK != 0 || N % 16 != 0 || cols < 1 || cols > kLtMaxCols) return false;
-  if ((long long)K * 2 * 256 >= (1LL << 32) || (long long)K * 4 * plane_cols >= (1LL << 32)) return false;  // 32-bit offsets
-  const int trips = K / kLtTripK, tile_cols = tile_columns(cols);
-  double best = 0.0;
-  pl.N = N; pl.K = K; pl.cols = cols; pl.splits = 0; pl.rows = 0;
-  for (int rows = 128; rows <= 256; rows += 64) {
-    if (rows == 192 && tile_cols == 32) continue;  // no such shape
-    const int rb = (N + rows - 1) / rows;
-    const double step_us = rows * 80.0 > tile_cols * 100.0 ? rows * 128.0 / 25e3 : (rows + tile_cols) * 128.0 / 45e3;
-    for (int s = 1; s <= kLtMaxSplits && s <= trips; ++s) {
-      const double rounds = (double)(((long long)rb * s + cus - 1) / cus);
-      const double us = rounds * (4.0 * ((trips + s - 1) / s) * step_us + 6.0) + (double)s * N * cols * 8.0 / 5e6;
-      if (pl.splits == 0 || us < best) {
-        best = us;
-        pl.splits = s;
-        pl.rows = rows;
-      }
-    }
-  }
-  return true;
-}
 template <typename SH>
 static hipError_t launch_shape(const LayerTileParams& tp, hipStream_t stream) {
   hipLaunchKernelGGL(layer_tile_kernel<SH>, dim3((unsigned)(tp.row_blocks * tp.splits)), dim3(64 * kTileWaves), SH::LDS_BYTES,
@@ -313,46 +275,6 @@ static hipError_t launch_pass(LayerTileParams& tp, int rows, hipStream_t stream)
       if (rows == 128) return launch_shape<LayerTile128x64>(tp, stream);
       return rows == 192 ? launch_shape<LayerTile192x64>(tp, stream) : launch_shape<LayerTile256x64>(tp, stream);
   }
-}
-
-struct LayerWorkspace {
-  size_t q, attn, arows, h1, xn2, act, n_rows, causal, ss1, ss2, part, total;
-};
-// any_smaller: room for the plans of every smaller B*T too - fewer columns may take more splits and more partial sums, and
-// a workspace sized for the largest batch has to serve the others.  Within the tile widths (up to 16, 32, 64 columns) the
-// model's splits only fall as the columns grow, so the splits at the narrowest of a width, times its columns, are a bound.
-static LayerWorkspace layer_workspace(int B, int T, int D, int H, int F, int cus, bool any_smaller) {
-  LayerWorkspace w;
-  size_t off = 0;
-  auto carve = [&](size_t bytes) { size_t at = off; off = (off + bytes + 255) / 256 * 256; return at; };
-  const size_t BT = (size_t)B * T;
-  w.q = carve(BT * D * 2); w.attn = carve(BT * D * 4); w.arows = carve(BT * D * 4);
-  w.h1 = carve(BT * D * 4); w.xn2 = carve(BT * D * 4); w.act = carve(BT * F * 4);
-  w.n_rows = carve((size_t)B * 4); w.causal = carve(BT * 8);
-  w.ss1 = carve(BT * (D / 256 + 1) * 4); w.ss2 = carve(BT * (D / 256 + 1) * 4);
-  size_t max_floats = 0;
-  const int shapes[4][2] = {{3 * D, D}, {D, D}, {2 * F, D}, {D, F}};
-  const long long most = (long long)BT < kLtMaxCols ? (long long)BT : kLtMaxCols, last = (long long)BT % kLtMaxCols;
-  for (auto& s : shapes) {
-    auto room = [&](int plan_cols, long long cols) {
-      LayerPlan pl;
-      if (plan_cols < 1 || !make_plan(pl, s[0], s[1], plan_cols, (int)BT, cus)) return;
-      const size_t floats = (size_t)pl.splits * cols * s[0];
-      max_floats = floats > max_floats ? floats : max_floats;
-    };
-    if (any_smaller) {
-      for (int narrowest : {1, 17, 33}) {
-        const long long widest = narrowest == 1 ? 16 : (narrowest == 17 ? 32 : 64);
-        if (narrowest <= most) room(narrowest, most < widest ? most : widest);
-      }
-    } else {  // full passes, and the last one
-      room((int)most, most);
-      room((int)last, last);
-    }
-  }
-  w.part = carve(max_floats * sizeof(float));
-  w.total = off;
-  return w;
 }
 
 template <typename... SH>

@@ -81,7 +81,7 @@ def _check(pkg, seed, B, T, D, H, F, ctx_len, cap):
 @pytest.mark.parametrize("seed,B,T,D,H,F,ctx_len,cap", [
     (0, 1, 4, 256, 2, 512, [37], 64),             # dh = 128: MFMA attention, one k chunk per matrix row tile
     (1, 2, 8, 512, 4, 768, [100, 3], 128),        # 16 columns, ragged history, 3 chunks in the down projection
-    (2, 3, 5, 256, 4, 256, [0, 17, 40], 48),      # dh = 64: generic attention; an empty history; 15 columns
+    (2, 3, 5, 256, 4, 256, [0, 17, 40], 48),      # dh = 64: the other attention kernel; an empty history; 15 columns
     (3, 3, 8, 256, 2, 512, [5, 9, 2], 16),        # 24 columns: two passes over every matrix
     (4, 1, 8, 256, 2, 6144, [20], 32),            # the down projection's activations take two k groups
     (5, 1, 1, 512, 4, 1024, [63], 64),            # a single position
@@ -134,13 +134,27 @@ def test_draft_layer_rejects_bad_arguments(pkg):
     ctx.close()
 
 
-# column counts around the tile loop's widths and what is left over for the streaming kernel: 17 and 32 (32-column
-# tiles), 33 and 64 (64), 65 and 80 (64, then 1 and 16 through the streaming kernel), 129 (two full passes and one more);
-# k of one and of several trips, weight rows that fill no whole workgroup
+# column counts around the tile loop's widths and the passes': 17 and 32 (tiles for 32 columns), 33 and 64 (64), 65 and 80
+# (a pass of 64, then one of 1 and 16), 129 (two full passes and one more); k of one and of several trips, weight rows
+# that fill no whole workgroup
 @pytest.mark.parametrize("seed,B,T,D,H,F,ctx_len,cap", [
     (20, 1, 17, 256, 2, 512, [9], 32), (21, 4, 8, 512, 4, 1280, [0, 31, 32, 40], 64), (22, 3, 11, 256, 4, 768, [5, 70, 1], 80),
     (23, 8, 8, 512, 8, 256, [1, 2, 3, 0, 60, 7, 33, 8], 64), (24, 5, 13, 256, 2, 256, [4, 5, 6, 7, 8], 16),
     (25, 2, 40, 512, 4, 512, [3, 90], 96), (26, 3, 43, 256, 4, 512, [0, 64, 10], 64),
 ])
 def test_draft_layer_many_columns(pkg, seed, B, T, D, H, F, ctx_len, cap):
+    _check(pkg, seed, B, T, D, H, F, ctx_len, cap)
+
+
+# The workgroups of 192 and 256 weight rows at every tile width, which the plan takes for larger matrices, and the batch of
+# eight at the 7B shape; tests/test_layer_plan.py asks the plan whether these cases take every shape there is.
+WIDE_CASES = [
+    (30, 1, 8, 1280, 10, 5632, [70], 96), (31, 3, 8, 1280, 10, 5632, [5, 0, 40], 64), (32, 8, 8, 1280, 10, 5632, [9] * 8, 32),
+    (33, 3, 8, 768, 6, 5632, [31, 32, 33], 64), (34, 5, 8, 768, 6, 5632, [1, 0, 64, 65, 2], 80),
+    (35, 8, 8, 4096, 32, 11008, [300, 1, 64, 500, 257, 31, 0, 129], 512),
+]
+
+
+@pytest.mark.parametrize("seed,B,T,D,H,F,ctx_len,cap", WIDE_CASES)
+def test_draft_layer_wide_workgroups(pkg, seed, B, T, D, H, F, ctx_len, cap):
     _check(pkg, seed, B, T, D, H, F, ctx_len, cap)

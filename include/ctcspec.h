@@ -97,8 +97,8 @@ int ctcspec_flush(ctcspec_ctx* ctx);
 
 /* Measurement aid.  With enable != 0, every following ctc_draft_topk call attaches a pair of HIP events
  * to the launch of its main kernel on the context's stream (the pass over the head weights, not the
- * small merge kernel): the events take that kernel's begin and end timestamps.  (The many-column and
- * generic producers record the pair around the launch instead, which also spans the dispatch.)
+ * small merge kernel): the events take that kernel's begin and end timestamps.  (The tile kernel - many columns,
+ * float operands, other hidden sizes - has the pair recorded around its launch instead, which also spans the dispatch.)
  * ctcspec_draft_head_kernel_ms synchronises with the second event of the LAST
  * such call and returns the elapsed milliseconds in *ms (host pointer).  CTCSPEC_EINVAL when profiling
  * is off or no call has been made since it was switched on. */

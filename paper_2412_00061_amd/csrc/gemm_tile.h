@@ -1,11 +1,12 @@
 // A tile of a [V, D] x [cols, D]^T product, bf16 or float operands, fp32 accumulators: the main loop shared by the
-// base-model head (verify_head_argmax) and the draft head.
+// base-model head (verify_head_argmax), the draft head and the draft layer's passes.
 //
 // 8 wavefronts in a WR x WC grid (WR * WC = 8): wavefront (wr, wc) owns weight rows [16 RT wr, +16 RT) x columns
-// [16 CTW wc, +16 CTW) - RT x CTW MFMA tiles.  Shapes in use (rows x columns, bytes of a row per step): 128 x 16,
+// [16 CTW wc, +16 CTW) - RT x CTW MFMA tiles.  Shapes in use (rows x columns, bytes of a row per step).  The heads: 128 x 16,
 // x 32, x 64 and x 128 with steps of 256 bytes, and 256 x 128 with steps of 128 (4 x 2 wavefronts, 64 x 64 per
 // wavefront) for products with several column blocks: per flop it reads two thirds of the fragments from LDS and
-// fetches half of the hidden-state tiles from L2.
+// fetches half of the hidden-state tiles from L2.  The draft layer: 128, 192 or 256 rows x 32, 64 or 128 tile columns (but
+// 192 x 32) with steps of 128 bytes - its columns come twice, high and low parts - of a range of k (pitch > D).
 // Per step both operands go through LDS: the W tile (nontemporal, the A operand) and the hidden states of the step
 // (the B operand) are fetched by all threads together with coalesced 16-byte loads, DIST steps ahead, into
 // rotating register stages (the VGPR file, 512 KB per compute unit, is the deep staging buffer), and written to

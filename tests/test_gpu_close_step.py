@@ -66,7 +66,7 @@ def test_verify_head_full_size(pkg, cfg_index):
     (5, 128, 512, 2200, "bf16"),    # five full column blocks, nine row blocks of 256: one XCD sees two row groups
     (3, 100, 512, 5000, "bf16"),    # three column blocks over twenty row blocks of 256: several row groups per XCD
     (1, 5, 1024, 77, "bf16"),       # fewer rows than a block, few columns
-    (3, 16, 512, 300, "bf16"),      # hidden size the MFMA kernel does not take: generic kernel
+    (3, 16, 512, 300, "bf16"),      # as many steps as the loop fetches ahead, no trip more; 48 columns
     (2, 9, 48, 11, "f32"),
     (1, 1, 8, 1, "f32"),            # a single token in the vocabulary
 ])

@@ -36,13 +36,10 @@ def test_verify_head_any_hidden(pkg, dtype, i):
     D = HIDDEN[i]
     for j, V in ((i, 385), (i + 3, 130), (i + 6, 1)):
         cols = COLUMNS[j % len(COLUMNS)]
-        B, N = (3, 100) if cols == 300 else (cols // 43, 43) if cols % 43 == 0 else (1, cols) if cols <= 128 else (cols, 1)
+        B, N = (3, 100) if cols == 300 else (3, 43) if cols == 129 else (1, cols)
         print(f"verify head {dtype} D={D} V={V} B={B} N={N}", flush=True)
         h, w, z_ref, bound = _operands(100 * i + j, B * N, D, V, dtype)
-        ctx = pkg.Context(max_batch=min(B, 64), max_slots=1, max_topk=1, max_vocab_rows=V, max_nodes=N, max_heads=1,
-                          max_head_dim=8) if B <= 64 else None
-        if ctx is None:
-            continue
+        ctx = pkg.Context(max_batch=B, max_slots=1, max_topk=1, max_vocab_rows=V, max_nodes=N, max_heads=1, max_head_dim=8)
         n_nodes = torch.full((B,), N, dtype=torch.int32, device="cuda")
         n_nodes[0] = max(1, N - 1)
         res = pkg.verify_head_argmax(ctx, h.view(B, N, D), w, n_nodes, want_logits=True)

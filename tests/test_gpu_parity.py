@@ -88,7 +88,7 @@ def test_draft_topk_full_size(pkg, cfg_index, variant):
     (2, 8, 1024, 2049, 8, "bf16"),    # 16 columns, k = 8
     (3, 7, 2048, 777, 3, "bf16"),     # 21 columns: two column tiles, one ragged
     (8, 8, 1024, 4097, 4, "bf16"),    # 64 columns: hidden states chunked through LDS
-    (1, 5, 320, 300, 2, "bf16"),      # hidden size the streaming kernel does not take: generic kernel
+    (1, 5, 320, 300, 2, "bf16"),      # hidden size the streaming kernel does not take: tile kernel
     (2, 3, 48, 11, 5, "f32"),         # fewer rows than a tile
     (1, 1, 8, 1, 1, "f32"),           # a single row, a single slot
     (1, 4, 64, 640, 8, "f32"),

@@ -63,7 +63,7 @@ def test_noalloc_against_the_oracle(pkg):
 
 
 # (B, T, D, V+1, k, dtype): streaming kernel with a large head, the same kernel on fewer rows and columns, the
-# many-column tile kernel, the generic kernels - each after the other on the same scratch
+# tile kernel with many columns and with float operands - each after the other on the same scratch
 SEQUENCE = [
     (1, 8, 4096, 32001, 4, "bf16"),
     (1, 5, 1024, 1500, 3, "bf16"),

@@ -22,7 +22,7 @@ namespace ctcspec {
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 
-constexpr int kCtcMaxLabels = 2047;  // L + 1 pairs of states <= 2 per thread of a 1024-thread workgroup
+constexpr int kCtcMaxLabels = 2047;  // with the blank 2048 positions: 2 per thread of ctc_row_kernel's 1024, 4 of its 512
 constexpr int kCtcMaxRow = 16 * 1024 * 4;  // 65536 symbols: 16 16-byte loads per thread of a 1024-thread workgroup
 constexpr int kCtcFixThreads = 256;
 
@@ -718,9 +718,13 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
 
 // One wavefront per frame: the occupancies gamma_t(s) = alpha_t(s) beta_t(s) / (p_t(z_s) P) of the label's tokens
 // and of the blank come off the softmax in the gradient row.  Only these few entries of the row are touched.
+// The labels' occupancies are formed once and kept in LDS, where the first position of a token adds up those of all its
+// positions: 256 sequences of 2048 frames, 512 labels out of 100 symbols (each five times), 2.61 ms; formed again from
+// the stored rows for every position and every link, with a lane's own offsets, 5.62.
 __global__ __launch_bounds__(kCtcFixThreads) void ctc_fix_kernel(CtcParams p) {
+  extern __shared__ float occupancies[];  // [wavefront][Lmax]
   const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * (kCtcFixThreads / 64) + (threadIdx.x >> 6), b = blockIdx.y;
+  const int t = blockIdx.x * (kCtcFixThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), b = blockIdx.y;
   const int Tb = clampi(p.frame_len[b], 0, p.T);
   if (t >= Tb) return;  // rows past the sequence were written as zeros
   float* __restrict__ g = p.grad + ((size_t)b * p.T + t) * p.Vp1;
@@ -735,25 +739,44 @@ __global__ __launch_bounds__(kCtcFixThreads) void ctc_fix_kernel(CtcParams p) {
   const float* __restrict__ al = p.ag + frame * SP;
   const float* __restrict__ be = p.bg + frame * SP;
   const float* __restrict__ lp = p.lpc + frame * (p.Lmax + 1);
-  // log of P over the two offsets of a state: what its stored alpha + beta - log p is measured against
+  // log of P over the two offsets of a state: what its stored alpha + beta - log p is measured against.  Beta's states are
+  // counted from the last one: state s is its state 2 L - s, and pair q of this wavefront's group of 64 has its blank in
+  // beta's pair d = L - q and its label in pair d - 1.  All 64 share alpha's block and lie in two of beta's, so the
+  // offsets are the wavefront's, not the lane's.
   const double* __restrict__ ca = p.coff_a + frame * p.blocks;
   const double* __restrict__ cb = p.coff_b + frame * p.blocks;
-  constexpr int kBlockStates = 2 * kDpPairs;
-  auto gamma = [&](int s, float l) {  // beta's states are counted from the last one
-    const int m = 2 * L - s;
-    const float a = al[s], bt = be[m];
-    const float z = (float)(logP - ca[s / kBlockStates] - cb[m / kBlockStates]);
+  struct Offsets { int block; float upper, lower; };  // beta's block of pair L - q0, z there and in the block below
+  auto offsets = [&](int q0) {
+    const int block = (L - q0) / kDpPairs;
+    const double rest = logP - ca[q0 / kDpPairs];
+    return Offsets{block, (float)(rest - cb[block]), (float)(rest - cb[block > 0 ? block - 1 : 0])};
+  };
+  auto gamma = [&](int s, int beta_pair, float l, const Offsets& o) {
+    const float a = al[s], bt = be[2 * L - s];
+    const float z = beta_pair / kDpPairs == o.block ? o.upper : o.lower;
     return (a > -INFINITY && bt > -INFINITY) ? exp2f(a + bt - l - z) : 0.f;  // base-2 logarithms throughout
   };
+  float* __restrict__ occ = occupancies + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * p.Lmax;
   // The occupancies of a frame sum to one (every alignment is in exactly one state at frame t).  What is left
   // of the recursions' rounding after thousands of frames is mostly common to all states of a frame - it sits in
   // z - so dividing by the computed sum removes it.  First pass: the sums, in a fixed order.
   const float lblank = lp[p.Lmax];
   float gb = 0.f, go = 0.f;
 #pragma unroll 4
-  for (int s = 2 * lane; s < 2 * L + 1; s += 128) gb += gamma(s, lblank);
-#pragma unroll 4
-  for (int j = lane; j < L; j += 64) go += gamma(2 * j + 1, lp[j]);
+  for (int q0 = 0; q0 <= L; q0 += kDpPairs) {
+    const Offsets o = offsets(q0);
+    const int q = q0 + lane;
+    if (q <= L) gb += gamma(2 * q, L - q, lblank, o);
+    if (q < L) {
+      const float x = gamma(2 * q + 1, L - q - 1, lp[q], o);
+      occ[q] = x;
+      go += x;
+    }
+  }
+  // other lanes of this wavefront read them below: its LDS operations execute in order, the compiler must not reorder
+  // them either
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_wave_barrier();
   gb = wave_sum_f32(gb);
   go = wave_sum_f32(go);
   const float total = gb + go;
@@ -762,9 +785,7 @@ __global__ __launch_bounds__(kCtcFixThreads) void ctc_fix_kernel(CtcParams p) {
   // The entries are written, not updated: the softmax value that ctc_row_kernel left there is formed again from
   // the log-probability at hand, which saves fetching a cache line per entry.
   if (lane == 0) g[p.blank] = exp2f(lblank) - gb * inv;
-  // the label's tokens: the lane of a token's first position adds the occupancies of all its positions (nearly
-  // always just the one, so every lane forms its own position's occupancy first and the loads of several
-  // positions are in flight together)
+  // the label's tokens: the lane of a token's first position adds the occupancies of all its positions
   const int32_t* __restrict__ y = p.labels + (size_t)b * p.Lmax;
   const int32_t* __restrict__ nx = p.next + (size_t)b * p.Lmax;
   const int32_t* __restrict__ fs = p.first + (size_t)b * p.Lmax;
@@ -773,9 +794,9 @@ __global__ __launch_bounds__(kCtcFixThreads) void ctc_fix_kernel(CtcParams p) {
     const int is_first = fs[j];
     const int tok = clampi(y[j], 0, p.Vp1 - 1);
     const float l = lp[j];
-    float tot = gamma(2 * j + 1, l);
+    float tot = occ[j];
     if (is_first) {
-      for (int i = nx[j]; i >= 0; i = nx[i]) tot += gamma(2 * i + 1, lp[i]);
+      for (int i = nx[j]; i >= 0; i = nx[i]) tot += occ[i];
       if (tok != p.blank) g[tok] = exp2f(l) - tot * inv;  // a label never holds the blank; ids come from the caller
     }
   }
@@ -896,7 +917,7 @@ extern "C" int ctc_loss(ctcspec_ctx* ctx, const float* logits, const int32_t* la
   CTCSPEC_HIP(ctx, hipGetLastError());
   if (grad) {
     const int per = kCtcFixThreads / 64;
-    hipLaunchKernelGGL(ctc_fix_kernel, dim3((T + per - 1) / per, B), dim3(kCtcFixThreads), 0, st, p);
+    hipLaunchKernelGGL(ctc_fix_kernel, dim3((T + per - 1) / per, B), dim3(kCtcFixThreads), (size_t)per * Lmax * 4, st, p);
     CTCSPEC_HIP(ctx, hipGetLastError());
   }
   return CTCSPEC_OK;

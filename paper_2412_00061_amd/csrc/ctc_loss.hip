@@ -8,7 +8,7 @@
 //     blank) and writes the row's softmax as the gradient; after the recursions the occupancies come off those
 //     few entries.
 //   * the recursions themselves are small and sequential in the frames, over the states of the extended sequence (blank,
-//     y1, blank, ..., blank).  Few frames, or many short labels: ctc_short_kernel, a wavefront per sequence that runs
+//     y1, blank, ..., blank).  Few frames, or many sequences: ctc_short_kernel, a wavefront per sequence that runs
 //     both recursions and subtracts the occupancies.  Otherwise ctc_dp_pipe_kernel, pipelined over blocks of
 //     states, forward and backward at the same time; ctc_fix_kernel then forms the occupancies
 //     gamma_t(s) = alpha_t(s) beta_t(s) / (p_t(z_s) P) where they are used.
@@ -201,7 +201,7 @@ __device__ __forceinline__ float lane_shift_down(float v, float last) {
                                                                   0x130 /* wave_shl:1 */, 0xf, 0xf, false));
 }
 
-// ---- few frames, or many short labels ------------------------------------------------------------------------------
+// ---- few frames, or many sequences with short labels (ctc_pipelined has the lines) -------------------------------------
 // One wavefront per sequence, a lane per pair of states: pair q is the blank in front of label position q (state 2q) and
 // that label's own state (2q + 1); pair L is the final blank alone.  Neighbours' values by lane shifts, no barrier.
 // The forward recursion keeps its rows (in LDS when ROWS_IN_LDS, else in the workspace), the backward one forms the
@@ -805,16 +805,24 @@ __global__ __launch_bounds__(kCtcFixThreads) void ctc_fix_kernel(CtcParams p) {
 struct CtcWorkspace {
   size_t lpc, ag, bg, coff_a, coff_b, logp, next, first, edge, wide, ticket, total;
 };
-// Which kernel runs the recursions.  Few frames leave the pipeline nothing to fill; with short labels (one block of
-// states) and more sequences than two rounds of the pipelined kernel's workgroups (three per compute unit, by their
-// LDS), a wavefront per sequence is the better use of it: 80 frames of 501 symbols, up to 20 labels, whole call, 400 /
-// 600 / 1000 sequences: pipelined 83 / 114 / 176 us, a wavefront each 100 / 120 / 153.
-static bool ctc_pipelined(int B, int T, int Lmax) { return T >= kShortFrames && (Lmax >= kDpPairs || B <= 768); }
+// Which kernel runs the recursions.  A frame takes the wavefront that does all of a sequence's work alone longer than the
+// pipeline's, but it needs a quarter of the wavefronts and one launch less: the pipeline is the faster one from 16 frames
+// on until the sequences fill the chip, which few frames do sooner.  Whole call, 101 symbols, T / 2 labels, us pipelined /
+// a wavefront each for B sequences:
+//   T = 12: 14.6 / 13.5 (B = 1)      16: 15.4 / 16.3 (1), 17.4 / 18.3 (64), 20.2 / 18.5 (128)     24: 19 / 25 (64), 23 / 27 (128), 31 / 28 (256)
+//   T = 32: 19 / 33 (64), 33 / 36 (256), 52 / 40 (512)       63: 20 / 54 (1), 48 / 69 (256), 76 / 82 (512), 129 / 101 (1024)
+// With 64 frames and more its rows are in the workspace, and labels of 64 and more need the blocks; 80 frames of 501
+// symbols, up to 20 labels, 400 / 600 / 1000 sequences: pipelined 83 / 114 / 176 us, a wavefront each 100 / 120 / 153.
+constexpr int kPipeFrames = 16;  // never pipelined with fewer
+static bool ctc_pipelined(int B, int T, int Lmax) {
+  if (T >= kShortFrames) return Lmax >= kDpPairs || B <= 768;
+  return T >= kPipeFrames && B <= 8 * T - 64;
+}
 static CtcWorkspace ctc_workspace(int B, int T, int Lmax) {
   CtcWorkspace w;
   size_t off = 0;
   auto carve = [&](size_t bytes) { size_t at = off; off = (off + bytes + 255) / 256 * 256; return at; };
-  const size_t blocks = T >= kShortFrames ? Lmax / kDpPairs + 1 : 1;
+  const size_t blocks = T >= kPipeFrames ? Lmax / kDpPairs + 1 : 1;
   w.lpc = carve((size_t)B * T * (Lmax + 1) * 4);
   // (one size for a shape whatever kernel it takes: a workspace sized for the largest batch serves the smaller ones)
   w.ag = carve((size_t)B * T * ctc_state_pitch(Lmax) * 4);
@@ -825,7 +833,7 @@ static CtcWorkspace ctc_workspace(int B, int T, int Lmax) {
   w.next = carve((size_t)B * Lmax * 4);
   w.first = carve((size_t)B * Lmax * 4);
   w.edge = w.wide = w.ticket = off;
-  if (T >= kShortFrames) {
+  if (T >= kPipeFrames) {
     w.edge = carve((size_t)B * 2 * T * blocks * 8);
     w.wide = carve((size_t)B * T * 4);
     w.ticket = carve(4);

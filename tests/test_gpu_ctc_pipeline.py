@@ -179,10 +179,12 @@ def test_peaked_logits_far_from_the_diagonal(pkg):
     _check(pkg, logits, labels, np.full(B, L, dtype=np.int32), np.full(B, T, dtype=np.int32), 29, 5e-4)
 
 
-@pytest.mark.parametrize("B,T,Lmax", [(800, 70, 20), (800, 64, 63), (5, 63, 63), (5, 63, 200), (3, 1, 1), (4, 9, 5), (2, 16, 17)])
+@pytest.mark.parametrize("B,T,Lmax", [(800, 70, 20), (800, 64, 63), (5, 63, 63), (5, 63, 200), (3, 1, 1), (4, 9, 5), (2, 16, 17),
+                                      (441, 63, 63), (441, 63, 200), (65, 16, 17), (64, 16, 17), (2, 15, 17), (3, 17, 130)])
 def test_wavefront_per_sequence(pkg, B, T, Lmax):
     # few frames (rows in LDS, labels longer than the frames can hold), and many short labels (rows in the workspace);
-    # few tokens, so that labels repeat them
+    # few tokens, so that labels repeat them.  On both sides of the rule's lines: at 16 and 63 frames the pipeline takes up
+    # to 64 and 440 sequences
     rng = np.random.Generator(np.random.PCG64(7 * T + Lmax))
     C = 9
     print(f"ctc_loss B={B} T={T} Lmax={Lmax}", flush=True)

@@ -373,7 +373,7 @@ extern "C" int draft_layer_forward(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
   int rows_written = 0;  // with key splits the attention's merge kernel writes the rows itself
   rc = tree_verify_attn_rows(ctx, dt, p.q, k_cache, v_cache, kv_off, ctx_len, kv_cap, k_new, v_new, p.n_rows,
                              (const uint64_t*)p.causal, B, H, p.dh, T, 1.0f / sqrtf((float)p.dh), p.attn, p.arows,
-                             (long long)BT * D, &rows_written);
+                             (long long)BT * D, &rows_written, 2LL * (4LL * D * D + 3LL * D * F));
   if (rc != CTCSPEC_OK) return rc;
   if (!rows_written) {
     hipLaunchKernelGGL(dl_attn_rows_kernel, dim3(blocks_for((long long)BT * D)), dim3(256), 0, st, p);

@@ -32,6 +32,7 @@ struct AttnParams {
   // bf16 numbers (high part in plane 0, low part in plane 1) - what the draft layer's next matrix product takes
   unsigned short* rows;
   long long rows_plane;  // elements per plane
+  long long few_line;    // tree_attn_few_kernel: bytes of K and V beyond which they are read with streaming loads
 };
 
 // ---- bf16, dh = 128 -------------------------------------------------------------------------------
@@ -105,10 +106,10 @@ struct AttnSplit {
 // Nothing tells a call which of the two it is.  In a model the other layers' weights and caches pass in between, so large
 // calls hardly find anything again; small ones may, and have little to gain otherwise: the line lies where the second
 // column's gain has reached 7 %, with room for two calls' caches below it.  At most 16 rows gain next to nothing while the
-// caches could stay (144 MB 29.0 / 43.5 | 47.0 / 46.7; 375 MB 68.4 / 61.2 | 69.0 / 63.3): there the line is the whole cache -
-// but for the draft layer, whose own weights (405 MB at the 7B shape) pass in between: 144 MB, whole layer 183 / 180.5 us.
+// caches could stay (144 MB 29.0 / 43.5 | 47.0 / 46.7; 375 MB 68.4 / 61.2 | 69.0 / 63.3): there the line is the whole cache,
+// less the weights that the draft layer reads from one of its calls to the next (whole layer, 405 MB of weights: 131 MB of
+// caches 152 / 158 |, 144 MB | 183 / 180.5; 103 MB of weights, 139 MB of caches 82.5 / 92 |).
 constexpr long long kStreamBytes = 96LL << 20, kStreamBytesFew = 256LL << 20;
-__host__ __device__ __forceinline__ long long stream_line_few(const AttnParams& p) { return p.rows ? kStreamBytes : kStreamBytesFew; }
 __device__ __forceinline__ bool reads_more_than(const AttnParams& p, long long bytes) {
   int rows = 0;
   for (int b = threadIdx.x & 63; b < p.B; b += 64) {
@@ -639,7 +640,7 @@ __device__ __forceinline__ void tree_attn_few(const AttnParams& p) {
 template <bool LARGE>
 __global__ __launch_bounds__(64 * kFewWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tree_attn_few_kernel(AttnParams p) {
-  if (LARGE && reads_more_than(p, stream_line_few(p))) tree_attn_few<true>(p);
+  if (LARGE && reads_more_than(p, p.few_line)) tree_attn_few<true>(p);
   else tree_attn_few<false>(p);
 }
 
@@ -892,12 +893,30 @@ void tree_attn_any_kernel(AttnParams p, AttnSplit sp) {
     }
   }
   if (!live_wave) return;
+  const size_t unit = (((size_t)b * p.H + h) * sp.QB + qb) * sp.S + split;
+  const float l = sum_across_row_groups(l_run);
+  if (qi >= n) return;
+  struct PackedF4 { f32x4 v; } __attribute__((packed, aligned(4)));
+  const int qr = wave * 16 + c;
+  const float f = sp.S == 1 ? 1.0f / l : 1.0f;
+  float* dst = (sp.S == 1 ? p.out + (node_base + qi) * dh : sp.po + (unit * C::ROWS + qr) * dh) + 4 * g;
+  auto store = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int db = 0; db < NB; ++db)
+      if (16 * db + 4 * g < dh) ((PackedF4*)(dst + 16 * db))->v = o[db] * f;
+  };
+  store();
+  if (sp.S > 1 && g == 0) {
+    sp.pm[unit * C::ROWS + qr] = m_run;
+    sp.pl[unit * C::ROWS + qr] = l;
+  }
+  // not finite: once more (behind everything else - in front of the stores it took the other calls 0.3 us)
   f32x4 probe = {0.f, 0.f, 0.f, 0.f};  // 0 x finite
 #pragma unroll
   for (int db = 0; db < NB; ++db) probe += (16 * db + 4 * g < dh ? o[db] : f32x4{0.f, 0.f, 0.f, 0.f}) * 0.f;
   if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(probe[0] + probe[1] + probe[2] + probe[3] == 0.f)) != 0ull, 0)) {
     using T = std::conditional_t<E == 4, float, unsigned short>;
-    const T* qrow = (const T*)p.q + (node_base + (qi < n ? qi : n - 1)) * dh;
+    const T* qrow = (const T*)p.q + (node_base + qi) * dh;
     const float ms = m_run > -INFINITY ? m_run : 0.f;
 #pragma unroll
     for (int db = 0; db < NB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -919,20 +938,7 @@ void tree_attn_any_kernel(AttnParams p, AttnSplit sp) {
             if (16 * db + 4 * g < dh && w != 0.f) o[db][i] = fmaf(w, load_as_float(vr + 16 * db + 4 * g + i), o[db][i]);
       }
     }
-  }
-  const size_t unit = (((size_t)b * p.H + h) * sp.QB + qb) * sp.S + split;
-  const float l = sum_across_row_groups(l_run);
-  if (qi >= n) return;
-  struct PackedF4 { f32x4 v; } __attribute__((packed, aligned(4)));
-  const int qr = wave * 16 + c;
-  const float f = sp.S == 1 ? 1.0f / l : 1.0f;
-  float* dst = (sp.S == 1 ? p.out + (node_base + qi) * dh : sp.po + (unit * C::ROWS + qr) * dh) + 4 * g;
-#pragma unroll
-  for (int db = 0; db < NB; ++db)
-    if (16 * db + 4 * g < dh) ((PackedF4*)(dst + 16 * db))->v = o[db] * f;
-  if (sp.S > 1 && g == 0) {
-    sp.pm[unit * C::ROWS + qr] = m_run;
-    sp.pl[unit * C::ROWS + qr] = l;
+    store();
   }
 }
 
@@ -978,6 +984,17 @@ __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnPara
     Lt += f * plv[s];
     acc += pov[s] * f;
   }
+  auto store = [&]() __attribute__((always_inline)) {
+    const f32x4 o = acc * (1.0f / Lt);
+    if (p.rows) {
+      const int h = (int)(bh - (long long)b * p.H);
+      const size_t at = ((size_t)b * p.max_nodes + row) * ((size_t)p.H * dh) + (size_t)h * dh + d4;
+      store_rows4(p, at, o);
+    } else {
+      *(f32x4*)(p.out + ((size_t)bh * p.max_nodes + row) * dh + d4) = o;
+    }
+  };
+  store();
   // A sum that is not finite is formed again without the parts of weight 0, which add nothing whatever they hold (those
   // past the last split hold the first one's values).  (As a select in the loop above, the loads wait for pm: +0.6 us.)
   if (__builtin_expect(!(acc[0] * 0.f + acc[1] * 0.f + acc[2] * 0.f + acc[3] * 0.f == 0.f), 0)) {
@@ -987,14 +1004,7 @@ __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnPara
       const float f = pmv[s] > -INFINITY ? __builtin_amdgcn_exp2f(pmv[s] - M) : 0.f;
       if (f != 0.f) acc += pov[s] * f;
     }
-  }
-  const f32x4 o = acc * (1.0f / Lt);
-  if (p.rows) {
-    const int h = (int)(bh - (long long)b * p.H);
-    const size_t at = ((size_t)b * p.max_nodes + row) * ((size_t)p.H * dh) + (size_t)h * dh + d4;
-    store_rows4(p, at, o);
-  } else {
-    *(f32x4*)(p.out + ((size_t)bh * p.max_nodes + row) * dh + d4) = o;
+    store();
   }
 }
 
@@ -1061,7 +1071,8 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
                                    const void* v_cache, const int64_t* kv_off, const int32_t* ctx_len, int kv_cap,
                                    const void* k_tree, const void* v_tree, const int32_t* n_nodes,
                                    const uint64_t* anc_mask, int B, int H, int dh, int max_nodes, float scale,
-                                   float* out, unsigned short* rows, long long rows_plane, int* rows_written) {
+                                   float* out, unsigned short* rows, long long rows_plane, int* rows_written,
+                                   long long between) {
   if (rows_written) *rows_written = 0;
   if (!ctx) return CTCSPEC_EINVAL;
   if (const int owed = flush_deferred(ctx)) return owed;
@@ -1086,6 +1097,7 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
   p.k_tree = k_tree; p.v_tree = v_tree; p.n_nodes = n_nodes; p.anc_mask = (const unsigned long long*)anc_mask;
   p.B = B; p.H = H; p.dh = dh; p.max_nodes = max_nodes; p.scale = scale; p.out = out;
   p.rows = nullptr; p.rows_plane = 0;
+  p.few_line = kStreamBytesFew - between > kStreamBytes ? kStreamBytesFew - between : kStreamBytes;
   if (dt == CTCSPEC_BF16 && dh == 128) {
     CTCSPEC_REQUIRE(ctx, scale > 0.f, CTCSPEC_EINVAL, "tree_verify_attn: scale must be positive");
     // Launch shape.  A workgroup has 8 wavefronts that all fetch tiles and all compute: 8 row groups of 16
@@ -1115,7 +1127,7 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
         p.rows = rows; p.rows_plane = rows_plane;
         if (rows_written) *rows_written = 1;
       }
-      if (may_read_more_than(p, stream_line_few(p)))
+      if (may_read_more_than(p, p.few_line))
         hipLaunchKernelGGL(tree_attn_few_kernel<true>, dim3((unsigned)bh), dim3(64 * kFewWaves), kFewLds, ctx->stream, p);
       else
         hipLaunchKernelGGL(tree_attn_few_kernel<false>, dim3((unsigned)bh), dim3(64 * kFewWaves), kFewLds, ctx->stream, p);
@@ -1173,5 +1185,5 @@ extern "C" int tree_verify_attn(ctcspec_ctx* ctx, ctcspec_dtype dt, const void* 
                                 const uint64_t* anc_mask, int B, int H, int dh, int max_nodes, float scale,
                                 float* out) {
   return ctcspec::tree_verify_attn_rows(ctx, dt, q, k_cache, v_cache, kv_off, ctx_len, kv_cap, k_tree, v_tree, n_nodes,
-                                        anc_mask, B, H, dh, max_nodes, scale, out, nullptr, 0, nullptr);
+                                        anc_mask, B, H, dh, max_nodes, scale, out, nullptr, 0, nullptr, 0);
 }

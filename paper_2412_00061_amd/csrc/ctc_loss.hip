@@ -425,7 +425,7 @@ __device__ void ctc_links(const CtcParams& p, int b, int part, int parts, int32_
 // with up to 1024 labels: 217 us.  One workgroup of 1024 threads per sequence and direction, log domain, a barrier and a
 // frame maximum per frame took 1221 us, and its gradient was five times as far from the float64 one (5e-6 against 9e-7).
 // In the log domain a frame takes about 0.25 us: 4 x 2048 frames of 1001 symbols, 1024 labels, the blank masked with -1e9,
-// 712 us a call; 8 x 512 frames, 100 labels 124 us.  One workgroup per sequence and direction, a barrier and a frame
+// 585 us a call; 8 x 512 frames, 100 labels 123 us.  One workgroup per sequence and direction, a barrier and a frame
 // maximum per frame: 1794 and 258 us with 1024 threads, 2400 and 223 us with 256 and the pairs in registers.
 constexpr int kDpFrames = 16;
 constexpr int kDpPairs = 64;

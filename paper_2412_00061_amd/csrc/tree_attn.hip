@@ -661,7 +661,7 @@ void tree_attn_few_kernel(AttnParams p) {
 // weight 0 left out (the reference and the sum of the weights do not depend on V).
 // Bound: float operands by the matrix rate (157 TFLOP/s), bf16 by latency and the K/V stream.  Measured against one
 // workgroup per query row with K/V read by every row (what these shapes took before): 2 sequences x 12 heads x 100
-// nodes, 300 to 900 keys, float, head dimension 64: 608 -> 17.6 us (kernel and merge); four sequences x 15 heads x 64
+// nodes, 300 to 900 keys, float, head dimension 64: 602-638 -> 16.7-18.7 us a call; four sequences x 15 heads x 64
 // nodes over 43 keys, bf16, head dimension 64: 67 -> 10 us.
 template <typename EL, int DHP>
 struct AnyAttn {

@@ -268,6 +268,10 @@ __global__ __launch_bounds__(64) void ctc_short_kernel(CtcParams p) {
     const float before = __uint_as_float(lane_shift_up(__float_as_uint(a_label), 0xff800000u));
     const float tail = __shfl(ctc_log_add2(a_blank, before), L, 64);
     logP = offset + (double)tail;  // base 2; -inf when the label cannot be reached
+  } else {  // it cannot; but logits that are no numbers say so
+    bool nan = false;
+    for (int t = q; t < Tb; t += 64) nan |= lpc[(size_t)t * LP + p.Lmax] != lpc[(size_t)t * LP + p.Lmax];
+    if (__ballot(nan) != 0ull) logP = (double)NAN;
   }
   if (q == 0) p.loss[b] = (float)(-logP * 0.6931471805599453);
   if (!p.grad) return;

@@ -108,7 +108,8 @@ def test_empty_sequences(pkg, frames, T, Lmax):
 # large finite number (the log-domain recursion), and a label that could not be reached anyway (no repeats fit).
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
 @pytest.mark.parametrize("B,T,L,masked", [(3, 20, 6, False), (800, 70, 6, False), (3, 90, 20, False), (3, 300, 130, False),
-                                          (3, 90, 20, True), (3, 300, 130, True), (3, 70, 69, False)])
+                                          (3, 90, 20, True), (3, 300, 130, True), (3, 70, 69, False),
+                                          (3, 12, 70, False), (3, 20, 70, False)])
 def test_not_a_number(pkg, bad, B, T, L, masked):
     rng = np.random.Generator(np.random.PCG64(17 * T + L))
     C = 23

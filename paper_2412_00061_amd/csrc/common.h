@@ -29,7 +29,7 @@ constexpr size_t kCollapseWsBytesPerSeq = (size_t)kMaxAlign * 8 * 2 + (size_t)kM
 constexpr int kVerifyCols = 128;  // columns (tree nodes) per pass over the base model's head weights
 
 // ---- attention workspace geometry --------------------------------------------------------------
-constexpr int kMaxKvSplits = 8;
+constexpr int kMaxKvSplits = 32;
 
 }  // namespace ctcspec
 
@@ -82,14 +82,14 @@ int fail(ctcspec_ctx* ctx, int code, const char* fmt, ...);
 // ctc_collapse_tree calls this first; ctc_collapse_tree does so unless the owed lists are the very ones it is given.
 int flush_deferred(ctcspec_ctx* ctx);
 
-// tree_verify_attn with an optional second output form for callers inside the library: when `rows` is given and the
-// kernels can write it, the result goes to rows [B*max_nodes][H*dh] of two-bf16 values (planes of rows_plane elements)
-// instead of `out`, and *rows_written is set to 1.  between: bytes that the caller streams between two such calls.
+// tree_verify_attn with a second output form for callers inside the library: when `rows` is given, the result goes to
+// rows [B*max_nodes][H*dh] of two-bf16 values (planes of rows_plane elements) instead of `out`.  between: bytes that the
+// caller streams between two such calls.
 int tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const void* q, const void* k_cache,
                           const void* v_cache, const int64_t* kv_off, const int32_t* ctx_len, int kv_cap,
                           const void* k_tree, const void* v_tree, const int32_t* n_nodes, const uint64_t* anc_mask,
                           int B, int H, int dh, int max_nodes, float scale, float* out, unsigned short* rows,
-                          long long rows_plane, int* rows_written, long long between);
+                          long long rows_plane, long long between);
 
 // Kernels that need more dynamic LDS than the default limit have the limit raised here, once per context creation
 // (with the context's device current), never inside a stage call: a stage call then only enqueues launches and can

@@ -124,7 +124,6 @@ struct LayerParams {
   // workspace
   // activations that feed a matrix product are [2][B*T][K] bf16: high parts, then low parts
   unsigned short* q;           // [B][H][T][dh]
-  float* attn;                 // [B][H][T][dh] attention output
   unsigned short* arows;       // [2][B*T][D] attention output, heads side by side
   float* h1;                   // [B*T][D] residual stream after attention
   unsigned short* xn2;         // [2][B*T][D]
@@ -186,16 +185,6 @@ __global__ __launch_bounds__(256) void dl_qkv_finish_kernel(LayerParams p, Layer
     unsigned short* dst = (kind == 0 ? p.q : kind == 1 ? p.k_new : p.v_new) + (((size_t)b * p.H + h) * p.T + t) * p.dh;
     dst[i] = float_to_bf16_bits(a);
     dst[i + half] = float_to_bf16_bits(c);
-  }
-}
-
-// attention output [B][H][T][dh] fp32 -> rows [B*T][H*dh] bf16
-__global__ __launch_bounds__(256) void dl_attn_rows_kernel(LayerParams p) {
-  const int total = p.B * p.T * p.D;
-  for (int idx = blockIdx.x * 256 + threadIdx.x; idx < total; idx += gridDim.x * 256) {
-    const int col = idx / p.D, k = idx - col * p.D;
-    const int b = col / p.T, t = col - b * p.T, h = k / p.dh, d = k - h * p.dh;
-    store_split(p.arows, (size_t)total, (size_t)idx, p.attn[(((size_t)b * p.H + h) * p.T + t) * p.dh + d]);
   }
 }
 
@@ -335,7 +324,7 @@ extern "C" int draft_layer_forward(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
   p.x = (const unsigned short*)x; p.ln1 = (const unsigned short*)w->ln1; p.ln2 = (const unsigned short*)w->ln2;
   p.pos0 = pos0; p.B = B; p.T = T; p.D = D; p.H = H; p.dh = D / H; p.F = F;
   p.eps = rms_eps; p.log2_theta = log2f(rope_theta);
-  p.q = q_out ? (unsigned short*)q_out : (unsigned short*)(ws + lw.q); p.attn = (float*)(ws + lw.attn);
+  p.q = q_out ? (unsigned short*)q_out : (unsigned short*)(ws + lw.q);
   p.arows = (unsigned short*)(ws + lw.arows); p.h1 = (float*)(ws + lw.h1); p.xn2 = (unsigned short*)(ws + lw.xn2);
   p.act = (unsigned short*)(ws + lw.act); p.n_rows = (int32_t*)(ws + lw.n_rows);
   p.causal = (unsigned long long*)(ws + lw.causal); p.ss1 = (float*)(ws + lw.ss1); p.ss2 = (float*)(ws + lw.ss2);
@@ -370,15 +359,10 @@ extern "C" int draft_layer_forward(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
     hipLaunchKernelGGL(dl_qkv_finish_kernel, dim3(blocks_for((long long)3 * H * (p.dh / 2)), p.cols), dim3(256), 0, st, p, pl);
   });
   if (rc != CTCSPEC_OK) return rc;
-  int rows_written = 0;  // with key splits the attention's merge kernel writes the rows itself
   rc = tree_verify_attn_rows(ctx, dt, p.q, k_cache, v_cache, kv_off, ctx_len, kv_cap, k_new, v_new, p.n_rows,
-                             (const uint64_t*)p.causal, B, H, p.dh, T, 1.0f / sqrtf((float)p.dh), p.attn, p.arows,
-                             (long long)BT * D, &rows_written, 2LL * (4LL * D * D + 3LL * D * F));
+                             (const uint64_t*)p.causal, B, H, p.dh, T, 1.0f / sqrtf((float)p.dh), nullptr, p.arows,
+                             (long long)BT * D, 2LL * (4LL * D * D + 3LL * D * F));
   if (rc != CTCSPEC_OK) return rc;
-  if (!rows_written) {
-    hipLaunchKernelGGL(dl_attn_rows_kernel, dim3(blocks_for((long long)BT * D)), dim3(256), 0, st, p);
-    CTCSPEC_HIP(ctx, hipGetLastError());
-  }
   rc = gemm_passes(w->wo, D, D, p.arows, [&](const LayerPlan& pl) {
     hipLaunchKernelGGL(dl_oproj_finish_kernel, dim3(p.cols * (D / 256)), dim3(256), 0, st, p, pl);
   });

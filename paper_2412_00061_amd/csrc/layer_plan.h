@@ -47,7 +47,7 @@ inline bool make_plan(LayerPlan& pl, int N, int K, int cols, int plane_cols, int
 }
 
 struct LayerWorkspace {
-  size_t q, attn, arows, h1, xn2, act, n_rows, causal, ss1, ss2, part, total;
+  size_t q, arows, h1, xn2, act, n_rows, causal, ss1, ss2, part, total;
 };
 // any_smaller: room for the plans of every smaller B*T too - fewer columns may take more splits and more partial sums, and
 // a workspace sized for the largest batch has to serve the others.  Within the tile widths (up to 16, 32, 64 columns) the
@@ -57,7 +57,7 @@ inline LayerWorkspace layer_workspace(int B, int T, int D, int H, int F, int cus
   size_t off = 0;
   auto carve = [&](size_t bytes) { size_t at = off; off = (off + bytes + 255) / 256 * 256; return at; };
   const size_t BT = (size_t)B * T;
-  w.q = carve(BT * D * 2); w.attn = carve(BT * D * 4); w.arows = carve(BT * D * 4);
+  w.q = carve(BT * D * 2); w.arows = carve(BT * D * 4);
   w.h1 = carve(BT * D * 4); w.xn2 = carve(BT * D * 4); w.act = carve(BT * F * 4);
   w.n_rows = carve((size_t)B * 4); w.causal = carve(BT * 8);
   w.ss1 = carve(BT * (D / 256 + 1) * 4); w.ss2 = carve(BT * (D / 256 + 1) * 4);

@@ -28,7 +28,7 @@ struct AttnParams {
   int B, H, dh, max_nodes;
   float scale;
   float* out;
-  // optional second form of the merged output (key splits only): rows [B*max_nodes][H*dh], each value as two
+  // optional second form of the output, written instead of `out`: rows [B*max_nodes][H*dh], each value as two
   // bf16 numbers (high part in plane 0, low part in plane 1) - what the draft layer's next matrix product takes
   unsigned short* rows;
   long long rows_plane;  // elements per plane
@@ -90,6 +90,27 @@ __device__ __forceinline__ float sum_across_row_groups(float x) {
   return x + __shfl_xor(x, 32, 64);
 }
 
+// fp32 value -> bf16 bits, round to nearest even
+__device__ __forceinline__ unsigned int rows_bf16_bits(float f) {
+  const unsigned int u = __float_as_uint(f);
+  return (u & 0x7fffffffu) > 0x7f800000u ? 0x7fc0u : (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+}
+// four consecutive values of an output row in the two-bf16 form (AttnParams::rows), at element `at` of both planes
+__device__ __forceinline__ void store_rows4(const AttnParams& p, size_t at, f32x4 o) {
+  unsigned int hi[4], lo[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    hi[i] = rows_bf16_bits(o[i]);
+    lo[i] = rows_bf16_bits(o[i] - __uint_as_float(hi[i] << 16));
+  }
+  *(u32x2*)(p.rows + at) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
+  *(u32x2*)(p.rows + p.rows_plane + at) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
+}
+
+// what a kernel leaves: a template parameter, because the code that a short call has to fetch for the two forms that it does not
+// write costs 0.2 us of 5
+enum class AttnOut { kRows, kTwoBf16Rows, kPartial };
+
 struct AttnSplit {
   int QB;      // query blocks of 16*QT*CW rows
   int S;       // key splits
@@ -126,7 +147,7 @@ __device__ __forceinline__ u32x4 load_kv(const unsigned char* a) {
   else return *(const u32x4*)a;
 }
 
-template <int QT, int NW, int CW, int PF, bool STREAM>
+template <int QT, int NW, int CW, int PF, bool STREAM, AttnOut OUT>
 __device__ __forceinline__ void tree_attn_bf16(const AttnParams& p, const AttnSplit& sp) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int ROWS = 16 * QT * CW;
@@ -431,11 +452,15 @@ __device__ __forceinline__ void tree_attn_bf16(const AttnParams& p, const AttnSp
     const int qr = rg * 16 * QT + qt * 16 + c;  // row inside the block
     const int qg = qb * ROWS + qr;
     if (qg >= n) continue;
-    if (sp.S == 1) {
+    if constexpr (OUT != AttnOut::kPartial) {
       const float inv = 1.0f / l;
       float* dst = p.out + (node_base + qg) * 128 + 4 * g;
+      const size_t at = ((size_t)b * p.max_nodes + qg) * ((size_t)p.H * 128) + h * 128 + 4 * g;
 #pragma unroll
-      for (int db = 0; db < 8; ++db) *(f32x4*)(dst + 16 * db) = o[qt][db] * inv;
+      for (int db = 0; db < 8; ++db) {
+        if constexpr (OUT == AttnOut::kTwoBf16Rows) store_rows4(p, at + 16 * db, o[qt][db] * inv);
+        else *(f32x4*)(dst + 16 * db) = o[qt][db] * inv;
+      }
     } else {
       // nontemporal: the partials are read once, by another kernel; written through, they do not wait in L2 for
       // the write-back at the kernel's end (0.6 us per launch)
@@ -451,11 +476,11 @@ __device__ __forceinline__ void tree_attn_bf16(const AttnParams& p, const AttnSp
 }
 
 // LARGE: the capacity leaves room for more than the line
-template <int QT, int NW, int CW, int PF, bool LARGE>
+template <int QT, int NW, int CW, int PF, bool LARGE, AttnOut OUT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tree_attn_bf16_kernel(AttnParams p, AttnSplit sp) {
-  if (LARGE && reads_more_than(p, kStreamBytes)) tree_attn_bf16<QT, NW, CW, PF, true>(p, sp);
-  else tree_attn_bf16<QT, NW, CW, PF, false>(p, sp);
+  if (LARGE && reads_more_than(p, kStreamBytes)) tree_attn_bf16<QT, NW, CW, PF, true, OUT>(p, sp);
+  else tree_attn_bf16<QT, NW, CW, PF, false, OUT>(p, sp);
 }
 
 // ---- bf16, dh = 128, at most 16 query rows (the draft module's layer, small trees) -----------------------------------
@@ -468,23 +493,6 @@ constexpr int kFewWaves = 8, kFewRows = 16;
 constexpr int kFewOPitch = 128 * 4 + 16;
 constexpr int kFewLds = kFewWaves * kStageBytes + 2 * kFewWaves * kFewRows * 4;
 static_assert(kFewRows * kFewOPitch <= kStageBytes, "a wavefront's result fits where its tile was");
-
-// fp32 value -> bf16 bits, round to nearest even
-__device__ __forceinline__ unsigned int rows_bf16_bits(float f) {
-  const unsigned int u = __float_as_uint(f);
-  return (u & 0x7fffffffu) > 0x7f800000u ? 0x7fc0u : (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
-// four consecutive values of an output row in the two-bf16 form (AttnParams::rows), at element `at` of both planes
-__device__ __forceinline__ void store_rows4(const AttnParams& p, size_t at, f32x4 o) {
-  unsigned int hi[4], lo[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    hi[i] = rows_bf16_bits(o[i]);
-    lo[i] = rows_bf16_bits(o[i] - __uint_as_float(hi[i] << 16));
-  }
-  *(u32x2*)(p.rows + at) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
-  *(u32x2*)(p.rows + p.rows_plane + at) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
-}
 
 template <bool STREAM>
 __device__ __forceinline__ void tree_attn_few(const AttnParams& p) {
@@ -671,10 +679,10 @@ struct AnyAttn {
   static constexpr int STAGE = kTileKeys * (KPITCH + VPITCH);
   static constexpr int THREADS = 256, ROWS = 64;
   static constexpr int NP = (kTileKeys * DHP * E / 16 + THREADS - 1) / THREADS;  // 16-byte pieces per thread of K, of V
-  static constexpr int PF = NP >= 4 ? 2 : 4;
+  static constexpr int PF = 2;  // (4 where the registers allow it: 1.5 % slower, by the code that a cold start fetches)
 };
 
-template <typename EL, int DHP>
+template <typename EL, int DHP, AttnOut OUT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tree_attn_any_kernel(AttnParams p, AttnSplit sp) {
   using C = AnyAttn<EL, DHP>;
@@ -898,15 +906,21 @@ void tree_attn_any_kernel(AttnParams p, AttnSplit sp) {
   if (qi >= n) return;
   struct PackedF4 { f32x4 v; } __attribute__((packed, aligned(4)));
   const int qr = wave * 16 + c;
-  const float f = sp.S == 1 ? 1.0f / l : 1.0f;
-  float* dst = (sp.S == 1 ? p.out + (node_base + qi) * dh : sp.po + (unit * C::ROWS + qr) * dh) + 4 * g;
+  constexpr bool kSplit = OUT == AttnOut::kPartial;
+  const float f = kSplit ? 1.0f : 1.0f / l;
+  float* dst = (kSplit ? sp.po + (unit * C::ROWS + qr) * dh : p.out + (node_base + qi) * dh) + 4 * g;
+  const size_t row_at = ((size_t)b * p.max_nodes + qi) * ((size_t)p.H * dh) + (size_t)h * dh + 4 * g;
   auto store = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int db = 0; db < NB; ++db)
-      if (16 * db + 4 * g < dh) ((PackedF4*)(dst + 16 * db))->v = o[db] * f;
+      if (16 * db + 4 * g < dh) {
+        if constexpr (OUT == AttnOut::kPartial) __builtin_nontemporal_store(o[db], (f32x4*)(dst + 16 * db));
+        else if constexpr (OUT == AttnOut::kTwoBf16Rows) store_rows4(p, row_at + 16 * db, o[db] * f);
+        else ((PackedF4*)(dst + 16 * db))->v = o[db] * f;
+      }
   };
   store();
-  if (sp.S > 1 && g == 0) {
+  if (kSplit && g == 0) {
     sp.pm[unit * C::ROWS + qr] = m_run;
     sp.pl[unit * C::ROWS + qr] = l;
   }
@@ -943,11 +957,12 @@ void tree_attn_any_kernel(AttnParams p, AttnSplit sp) {
 }
 
 // Combine the S key-split partials of every live query row.  Thread -> (row, 4 consecutive dh), 32
-// threads per row, 8 rows per workgroup; all of a thread's partials are requested before any is used,
-// so the kernel costs about one memory round trip.  (Letting the split that finishes last do the
+// threads per row, 8 rows per workgroup; eight of a thread's partials are requested before any is used,
+// so the kernel costs about one memory round trip per eight splits.  (Letting the split that finishes last do the
 // merge inside the attention kernel was measured: one workgroup per query block then pulls all S
 // partials through a single compute unit, which takes longer than this second launch.)
-constexpr int kMergeThreads = 256;
+constexpr int kMergeThreads = 256, kMergeParts = 8;
+template <bool MANY>  // more than kMergeParts splits
 __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnParams p, AttnSplit sp, int rows_shift) {
   const int rows_per_block = 1 << rows_shift;  // 64 or 128 query rows per block
   // grid: (blocks of 8 rows, head of a sequence) - the indices come from the block numbers, not from divisions
@@ -963,26 +978,33 @@ __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnPara
   const size_t unit0 = ((size_t)bh * sp.QB + qb) * sp.S;
   const int d4 = (tid & 31) * 4, dh = p.dh;
   if (d4 >= dh) return;
-  float pmv[kMaxKvSplits], plv[kMaxKvSplits];
-  f32x4 pov[kMaxKvSplits];
-#pragma unroll
-  for (int s = 0; s < kMaxKvSplits; ++s) {
-    const bool on = s < sp.S;
-    const size_t r = (unit0 + (on ? s : 0)) * rows_per_block + qr;
-    pmv[s] = on ? sp.pm[r] : -INFINITY;
-    plv[s] = sp.pl[r];
-    pov[s] = *(const f32x4*)(sp.po + r * dh + d4);
-  }
-  float M = -INFINITY;
-#pragma unroll
-  for (int s = 0; s < kMaxKvSplits; ++s) M = fmaxf(M, pmv[s]);
-  float Lt = 0.f;
+  float M = -INFINITY, Lt = 0.f;
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 == 0 || (MANY && s0 < sp.S); s0 += kMergeParts) {
+    float pmv[kMergeParts], plv[kMergeParts];
+    f32x4 pov[kMergeParts];
 #pragma unroll
-  for (int s = 0; s < kMaxKvSplits; ++s) {
-    const float f = pmv[s] > -INFINITY ? __builtin_amdgcn_exp2f(pmv[s] - M) : 0.f;
-    Lt += f * plv[s];
-    acc += pov[s] * f;
+    for (int i = 0; i < kMergeParts; ++i) {
+      const bool on = s0 + i < sp.S;
+      const size_t r = (unit0 + (on ? s0 + i : s0)) * rows_per_block + qr;
+      pmv[i] = on ? sp.pm[r] : -INFINITY;
+      plv[i] = sp.pl[r];
+      pov[i] = *(const f32x4*)(sp.po + r * dh + d4);
+    }
+    const float before = M;
+#pragma unroll
+    for (int i = 0; i < kMergeParts; ++i) M = fmaxf(M, pmv[i]);
+    if (MANY) {
+      const float f0 = before > -INFINITY ? __builtin_amdgcn_exp2f(before - M) : 0.f;
+      Lt *= f0;
+      acc *= f0;
+    }
+#pragma unroll
+    for (int i = 0; i < kMergeParts; ++i) {
+      const float f = pmv[i] > -INFINITY ? __builtin_amdgcn_exp2f(pmv[i] - M) : 0.f;
+      Lt += f * plv[i];
+      acc += pov[i] * f;
+    }
   }
   auto store = [&]() __attribute__((always_inline)) {
     const f32x4 o = acc * (1.0f / Lt);
@@ -995,14 +1017,13 @@ __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnPara
     }
   };
   store();
-  // A sum that is not finite is formed again without the parts of weight 0, which add nothing whatever they hold (those
-  // past the last split hold the first one's values).  (As a select in the loop above, the loads wait for pm: +0.6 us.)
+  // A sum that is not finite is formed again without the parts of weight 0, which add nothing whatever they hold.  (As a select in the loop above, the loads wait for pm: +0.6 us.)
   if (__builtin_expect(!(acc[0] * 0.f + acc[1] * 0.f + acc[2] * 0.f + acc[3] * 0.f == 0.f), 0)) {
     acc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < kMaxKvSplits; ++s) {
-      const float f = pmv[s] > -INFINITY ? __builtin_amdgcn_exp2f(pmv[s] - M) : 0.f;
-      if (f != 0.f) acc += pov[s] * f;
+    for (int s = 0; s < sp.S; ++s) {
+      const size_t r = (unit0 + s) * rows_per_block + qr;
+      const float m = sp.pm[r], f = m > -INFINITY ? __builtin_amdgcn_exp2f(m - M) : 0.f;
+      if (f != 0.f) acc += *(const f32x4*)(sp.po + r * dh + d4) * f;
     }
     store();
   }
@@ -1010,57 +1031,141 @@ __global__ __launch_bounds__(kMergeThreads) void tree_attn_merge_kernel(AttnPara
 
 static hipError_t launch_merge(const AttnParams& p, const AttnSplit& sp, int rows, hipStream_t stream) {
   const unsigned mblocks = (unsigned)((p.max_nodes + kMergeThreads / 32 - 1) / (kMergeThreads / 32));
-  hipLaunchKernelGGL(tree_attn_merge_kernel, dim3(mblocks, (unsigned)(p.B * p.H)), dim3(kMergeThreads), 0, stream, p, sp,
-                     rows == 64 ? 6 : 7);
+  auto kern = sp.S > kMergeParts ? tree_attn_merge_kernel<true> : tree_attn_merge_kernel<false>;
+  hipLaunchKernelGGL(kern, dim3(mblocks, (unsigned)(p.B * p.H)), dim3(kMergeThreads), 0, stream, p, sp, rows == 64 ? 6 : 7);
   return hipGetLastError();
 }
+// ---- launch shapes -------------------------------------------------------------------------------------------------
+// A call's time by what it is made of, in us; both kernels take the cheapest (query blocks, key splits).
+//   workgroups a compute unit takes in turn x (start of one + iterations x time of one) + what splitting costs
+// Splitting costs the merge launch and the partial results, which go through memory.  Before, as many splits were taken as
+// fill the chip whatever the merge costs, at most 8, and two blocks of 64 rows as soon as the chip was full.  Measured in HIP
+// graphs, us a call before / with this choice:
+//   bf16, 128: 2 x 40 heads, 128 rows, 128 positions 17.1 (2 splits) / 10.0 (none, two blocks)    6 x 32 heads, 200: 22.3 / 16.8
+//     (one block)    4 x 32 heads, 100 rows, 300: 18.5 (2) / 13.2 (1)    32 heads, 64 rows, 256: 11.9 (2) / 10.2 (1)
+//     32 heads, 128 rows, 2048 positions: 4 splits both; none 36.8, 2 26.0, 3 21.6, 4 19.6, 8 of one block 20.0
+//   bf16, 80: 4 x 16 heads, 50 rows, 93 positions 10.5 (2) / 7.6 (1)    64: 32 heads, 128 rows, 512: 14.6 (8) / 11.9 (4)
+//   float, 128: 14 heads, 35 rows, up to 1923 positions 24.4 (8) / 18.4 (18)
+// Over 400 shapes drawn from 1 to 8 sequences of 4 to 40 heads and 1 to 128 rows over 4 to 2048 positions: 7 % in the mean.
+struct AttnShape { int QB, S; };
+// the merge launch, the partial results' way through memory, and a round trip of the merge for every eight splits more
+static double split_us(long long bh, int S, int rows, int dh) {
+  return S == 1 ? 0.0 : 3.3 + (double)bh * S * rows * dh * 4 * 0.25e-6 + (S - 1) / kMergeParts * 3.0;
+}
+// how much longer than one workgroup a compute unit with `load` of them takes.  Of several sequences, not all are the longest.
+static double taking_turns(double load, double next) { return load <= 1.0 ? 1.0 : 1.0 + (load - 1.0) * next; }
+// (two at a time hide each other's waits)
+static double side_by_side(double load) { return load <= 1.0 ? 1.0 : load <= 2.0 ? 1.0 + (load - 1.0) * 0.4 : load * 0.7; }
+// tiles of 32 keys that a workgroup expects: the lengths are on the device, the host takes most of the capacity for them;
+// what does not divide leaves half an iteration idle on average
+static double iterations(int kv_cap, int max_nodes, int S, int per_iter) {
+  const double n = (0.875 * kv_cap + max_nodes) / (kTileKeys * per_iter * S) + 0.5;
+  return n > 1.0 ? n : 1.0;
+}
+// bf16, head dimension 128.  Blocks of 64 rows take two tiles an iteration (0.9 us; 1.1 when two blocks share the keys),
+// blocks of 128 one (0.78 us; 0.52 with a single live row group, whose partials are 16 rows).  slots: units of 128 rows that
+// the workspace holds.
+static AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long long slots) {
+  AttnShape best = {1, 1};
+  const long long bh = (long long)B * H;
+  double least = 1e30;
+  for (int QB = 1; QB <= (max_nodes > 64 ? 2 : 1); ++QB) {
+    const bool rows64 = max_nodes > 64 ? QB == 2 : max_nodes > kFewRows;
+    const double iter = rows64 ? (QB == 2 ? 1.1 : 0.9) : (max_nodes > kFewRows ? 0.78 : 0.52);
+    for (int S = 1; S <= kMaxKvSplits; ++S) {
+      const long long groups = bh * QB * S;
+      if (S > 1 && (groups > 256 || groups > slots || S * 4 > (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys)) break;
+      const double us = taking_turns(groups / 256.0, B > 1 ? 0.7 : 1.0) * (4.8 + iterations(kv_cap, max_nodes, S, rows64 ? 2 : 1) * iter) +
+                        split_us(bh, S, max_nodes, 128);
+      if (us < least) {
+        least = us;
+        best = {QB, S};
+      }
+    }
+  }
+  return best;
+}
+// Everything else, blocks of 64 rows.  Float: the matrix rate, workgroups on one compute unit take turns as far as their
+// wavefronts have rows; bf16: they run side by side.  slots: units of 64 rows.
+static AttnShape plan_any(int B, int H, int max_nodes, int kv_cap, int dh, bool f32, long long slots) {
+  AttnShape best = {(max_nodes + 63) / 64, 1};
+  const long long bh = (long long)B * H, blocks = bh * best.QB;
+  const int live = max_nodes >= 64 ? 4 : (max_nodes + 15) / 16;
+  double least = 1e30;
+  for (int S = 1; S <= kMaxKvSplits; ++S) {
+    if (S > 1 && (blocks * S > slots || S * kTileKeys > kv_cap + max_nodes || bh > 65535)) break;  // (the merge's grid)
+    const long long groups = blocks * S;
+    const double turns = f32 && dh > 32 ? taking_turns((double)((groups * live + 1023) / 1024), B > 1 ? 0.5 : 1.0) : side_by_side(groups / 256.0);
+    const double tile = f32 ? (dh <= 32 ? 0.9 : (dh + 31) / 32 * 32 / 48.0) : (dh <= 64 ? 0.6 : 0.7);
+    const double us = turns * (3.0 + iterations(kv_cap, max_nodes, S, 1) * tile) + split_us(bh, S, max_nodes, dh);
+    if (us < least) {
+      least = us;
+      best.S = S;
+    }
+  }
+  return best;
+}
+
 // whether a call can read more than that: all heads, whole capacity
 static bool may_read_more_than(const AttnParams& p, long long bytes) { return (long long)p.B * p.H * p.kv_cap * 512 > bytes; }
-template <int QT, int NW, int CW, int PF, bool LARGE = false>
+template <int QT, int NW, int CW, int PF, bool LARGE, AttnOut OUT>
 static hipError_t launch_attn_bf16(const AttnParams& p, const AttnSplit& sp, hipStream_t stream) {
-  auto kern = tree_attn_bf16_kernel<QT, NW, CW, PF, LARGE>;
+  auto kern = tree_attn_bf16_kernel<QT, NW, CW, PF, LARGE, OUT>;
   const long long blocks = (long long)sp.QB * sp.S * p.H * p.B;
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * NW), attn_lds_bytes(NW / CW), stream, p, sp);
   hipError_t e = hipGetLastError();
   constexpr int kRows = 16 * QT * CW;
   static_assert(kRows == 64 || kRows == 128, "the merge kernel takes the block size as a shift");
-  return e != hipSuccess || sp.S == 1 ? e : launch_merge(p, sp, kRows, stream);
+  return e != hipSuccess || OUT != AttnOut::kPartial ? e : launch_merge(p, sp, kRows, stream);
 }
-template <typename EL, int DHP>
+template <typename EL, int DHP, AttnOut OUT>
 static hipError_t launch_attn_any_dh(const AttnParams& p, const AttnSplit& sp, hipStream_t stream) {
   using C = AnyAttn<EL, DHP>;
   const long long blocks = (long long)sp.QB * sp.S * p.H * p.B;
-  hipLaunchKernelGGL((tree_attn_any_kernel<EL, DHP>), dim3((unsigned)blocks), dim3(C::THREADS), 2 * C::STAGE, stream, p, sp);
+  hipLaunchKernelGGL((tree_attn_any_kernel<EL, DHP, OUT>), dim3((unsigned)blocks), dim3(C::THREADS), 2 * C::STAGE, stream, p, sp);
   hipError_t e = hipGetLastError();
-  return e != hipSuccess || sp.S == 1 ? e : launch_merge(p, sp, 64, stream);
+  return e != hipSuccess || OUT != AttnOut::kPartial ? e : launch_merge(p, sp, 64, stream);
 }
-template <typename EL>
+template <typename EL, AttnOut OUT>
 static hipError_t launch_attn_any(const AttnParams& p, const AttnSplit& sp, hipStream_t stream) {
-  if (p.dh <= 32) return launch_attn_any_dh<EL, 32>(p, sp, stream);
-  if (p.dh <= 64) return launch_attn_any_dh<EL, 64>(p, sp, stream);
-  if (p.dh <= 96) return launch_attn_any_dh<EL, 96>(p, sp, stream);
-  return launch_attn_any_dh<EL, 128>(p, sp, stream);
+  if (p.dh <= 32) return launch_attn_any_dh<EL, 32, OUT>(p, sp, stream);
+  if (p.dh <= 64) return launch_attn_any_dh<EL, 64, OUT>(p, sp, stream);
+  if (p.dh <= 96) return launch_attn_any_dh<EL, 96, OUT>(p, sp, stream);
+  return launch_attn_any_dh<EL, 128, OUT>(p, sp, stream);
 }
 
+template <typename F>
+static hipError_t launch_for(const AttnParams& p, const AttnSplit& sp, F&& launch) {
+  if (sp.S > 1) return launch(std::integral_constant<AttnOut, AttnOut::kPartial>{});
+  if (p.rows) return launch(std::integral_constant<AttnOut, AttnOut::kTwoBf16Rows>{});
+  return launch(std::integral_constant<AttnOut, AttnOut::kRows>{});
+}
+
+// kernels with 64 KB of dynamic LDS or more: the 64-row kernel's two stages of two tiles, and float at 128
+template <AttnOut OUT>
+static hipError_t allow_lds() {
+  auto allow = [](const void* kernel, int bytes) {
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  };
+  hipError_t e = allow((const void*)tree_attn_bf16_kernel<1, 8, 4, 2, false, OUT>, attn_lds_bytes(2));
+  if (e == hipSuccess) e = allow((const void*)tree_attn_bf16_kernel<1, 8, 4, 2, true, OUT>, attn_lds_bytes(2));
+  if constexpr (OUT != AttnOut::kTwoBf16Rows)
+    if (e == hipSuccess) e = allow((const void*)tree_attn_any_kernel<TileF32, 128, OUT>, 2 * AnyAttn<TileF32, 128>::STAGE);
+  return e;
+}
 // code of this translation unit loaded onto the current device (context creation calls this: a stage call never
 // triggers a load, so it can be the first thing a stream capture records)
 hipError_t prepare_tree_attn() {
   hipFuncAttributes attr;
-  hipError_t e = hipFuncGetAttributes(&attr, (const void*)tree_attn_merge_kernel);
+  hipError_t e = hipFuncGetAttributes(&attr, (const void*)tree_attn_merge_kernel<false>);
   if (e != hipSuccess) return e;
   e = hipFuncSetAttribute((const void*)tree_attn_few_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kFewLds);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)tree_attn_bf16_kernel<1, 8, 4, 2, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            attn_lds_bytes(2));
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)tree_attn_few_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kFewLds);
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)tree_attn_any_kernel<TileF32, 128>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          2 * AnyAttn<TileF32, 128>::STAGE);
-  if (e != hipSuccess) return e;
-  // the 64-row kernel's two stages of two tiles are 64 KB of dynamic LDS
-  return hipFuncSetAttribute((const void*)tree_attn_bf16_kernel<1, 8, 4, 2, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             attn_lds_bytes(2));
+    e = hipFuncSetAttribute((const void*)tree_attn_few_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kFewLds);
+  if (e == hipSuccess) e = allow_lds<AttnOut::kRows>();
+  if (e == hipSuccess) e = allow_lds<AttnOut::kTwoBf16Rows>();
+  if (e == hipSuccess) e = allow_lds<AttnOut::kPartial>();
+  return e;
 }
 
 }  // namespace ctcspec
@@ -1071,12 +1176,10 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
                                    const void* v_cache, const int64_t* kv_off, const int32_t* ctx_len, int kv_cap,
                                    const void* k_tree, const void* v_tree, const int32_t* n_nodes,
                                    const uint64_t* anc_mask, int B, int H, int dh, int max_nodes, float scale,
-                                   float* out, unsigned short* rows, long long rows_plane, int* rows_written,
-                                   long long between) {
-  if (rows_written) *rows_written = 0;
+                                   float* out, unsigned short* rows, long long rows_plane, long long between) {
   if (!ctx) return CTCSPEC_EINVAL;
   if (const int owed = flush_deferred(ctx)) return owed;
-  CTCSPEC_REQUIRE(ctx, q && k_cache && v_cache && kv_off && ctx_len && k_tree && v_tree && n_nodes && anc_mask && out,
+  CTCSPEC_REQUIRE(ctx, q && k_cache && v_cache && kv_off && ctx_len && k_tree && v_tree && n_nodes && anc_mask && (out || rows),
                   CTCSPEC_EINVAL, "tree_verify_attn: null pointer");
   CTCSPEC_REQUIRE(ctx, dt == CTCSPEC_F32 || dt == CTCSPEC_BF16, CTCSPEC_EINVAL, "tree_verify_attn: bad dtype");
   CTCSPEC_REQUIRE(ctx, B > 0 && H > 0 && dh > 0 && max_nodes > 0 && kv_cap >= 0, CTCSPEC_EINVAL,
@@ -1096,37 +1199,18 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
   p.q = q; p.k_cache = k_cache; p.v_cache = v_cache; p.kv_off = kv_off; p.ctx_len = ctx_len; p.kv_cap = kv_cap;
   p.k_tree = k_tree; p.v_tree = v_tree; p.n_nodes = n_nodes; p.anc_mask = (const unsigned long long*)anc_mask;
   p.B = B; p.H = H; p.dh = dh; p.max_nodes = max_nodes; p.scale = scale; p.out = out;
-  p.rows = nullptr; p.rows_plane = 0;
+  p.rows = rows; p.rows_plane = rows_plane;
   p.few_line = kStreamBytesFew - between > kStreamBytes ? kStreamBytesFew - between : kStreamBytes;
   if (dt == CTCSPEC_BF16 && dh == 128) {
     CTCSPEC_REQUIRE(ctx, scale > 0.f, CTCSPEC_EINVAL, "tree_verify_attn: scale must be positive");
-    // Launch shape.  A workgroup has 8 wavefronts that all fetch tiles and all compute: 8 row groups of 16
-    // query rows (blocks of 128 rows per (sequence, head)), or 4 row groups x 2 key parts (blocks of 64
-    // rows); S key splits, so that about 256 workgroups exist and each still has a few tiles of 32 keys
-    // to stream.  Two 64-row blocks per head halve the partial results (fewer splits) at the price of a
-    // second pass over K/V through L2; they are taken when they fill more compute units, or as many with
-    // at least 4 splits (kernel and merge together then take the same time as one 128-row block with
-    // twice the splits, with 20 MB less traffic at the 7B shape).  Trees of 17 to 64 nodes are one
-    // 64-row block.
     const long long bh = (long long)B * H;
     const int key_tiles = (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys;
-    auto splits_for = [&](long long qblocks) {
-      long long S = 256 / (bh * qblocks);
-      if (S > key_tiles / 4) S = key_tiles / 4;
-      if (S > kMaxKvSplits) S = kMaxKvSplits;
-      while (S > 1 && bh * qblocks * S > (long long)ctx->attn_units) --S;  // partial slots of the workspace
-      return S < 1 ? 1LL : S;
-    };
-    if (max_nodes <= kFewRows && splits_for(1) == 1 && bh > 128 && key_tiles > kFewWaves) {
+    if (max_nodes <= kFewRows && bh > 128 && key_tiles > kFewWaves) {
       // Heads that fill the chip without key splits, and at least a tile per wavefront: 8 sequences of 256 to 2048
       // positions x 32 heads x 16 rows 48.9 -> 43 us, 5 x 32 heads x 8 rows over 300 to 1000 positions 20.5 -> 14.0.  With
       // key splits a wavefront has about one tile and the joins are what is left (one sequence of 2048: 15.6 against
       // 13.7 us), so those calls, and shorter contexts, keep the kernel that fetches a tile with all wavefronts.
       CTCSPEC_REQUIRE(ctx, bh <= 65535, CTCSPEC_EUNSUPPORTED, "tree_verify_attn: grid too large");
-      if (rows) {  // written instead of `out`
-        p.rows = rows; p.rows_plane = rows_plane;
-        if (rows_written) *rows_written = 1;
-      }
       if (may_read_more_than(p, p.few_line))
         hipLaunchKernelGGL(tree_attn_few_kernel<true>, dim3((unsigned)bh), dim3(64 * kFewWaves), kFewLds, ctx->stream, p);
       else
@@ -1134,48 +1218,42 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
       CTCSPEC_HIP(ctx, hipGetLastError());
       return CTCSPEC_OK;
     }
-    const long long s128 = splits_for(1), s64 = splits_for(2);
-    const bool two_blocks = max_nodes > 64 && (2 * s64 > s128 || (2 * s64 == s128 && s64 >= 4));
+    const AttnShape shape = plan_bf16_128(B, H, max_nodes, kv_cap, ctx->attn_units);
     // (up to 16 rows, a single row group: the one-tile-per-iteration kernel, whose first tile is in LDS sooner -
     // 9.1 against 9.9 us for the draft layer's 8 rows)
-    const bool rows64 = two_blocks || (max_nodes <= 64 && max_nodes > 16);
+    const bool rows64 = shape.QB == 2 || (max_nodes <= 64 && max_nodes > kFewRows);
     AttnSplit sp;
-    sp.QB = two_blocks ? 2 : 1;
-    sp.S = (int)(two_blocks ? s64 : s128);
+    sp.QB = shape.QB;
+    sp.S = shape.S;
     sp.po = ctx->attn_po; sp.pm = ctx->attn_pm; sp.pl = ctx->attn_pl;
     CTCSPEC_REQUIRE(ctx, bh * sp.QB * sp.S <= 0x7fffffffLL && bh * max_nodes <= 0x7fffffffLL && bh <= 65535,
                     CTCSPEC_EUNSUPPORTED,
                     "tree_verify_attn: grid too large");
-    if (rows && sp.S > 1) {  // the merge kernel writes the rows instead of `out`
-      p.rows = rows; p.rows_plane = rows_plane;
-      if (rows_written) *rows_written = 1;
-    }
     // (two 64-row blocks share K and V through L2)
-    const hipError_t e = !rows64 ? launch_attn_bf16<1, 8, 8, 2>(p, sp, ctx->stream)
-                         : sp.QB == 1 && may_read_more_than(p, kStreamBytes) ? launch_attn_bf16<1, 8, 4, 2, true>(p, sp, ctx->stream)
-                                                               : launch_attn_bf16<1, 8, 4, 2>(p, sp, ctx->stream);
+    const bool large = sp.QB == 1 && may_read_more_than(p, kStreamBytes);
+    const hipError_t e = launch_for(p, sp, [&](auto out_tag) {
+      constexpr AttnOut OUT = decltype(out_tag)::value;
+      return !rows64 ? launch_attn_bf16<1, 8, 8, 2, false, OUT>(p, sp, ctx->stream)
+             : large ? launch_attn_bf16<1, 8, 4, 2, true, OUT>(p, sp, ctx->stream)
+                     : launch_attn_bf16<1, 8, 4, 2, false, OUT>(p, sp, ctx->stream);
+    });
     CTCSPEC_HIP(ctx, e);
     return CTCSPEC_OK;
   }
-  // Everything else: blocks of 64 rows, enough key splits for two workgroups per compute unit (their stages fit its
-  // LDS twice) while a split still has two tiles, and within the workspace's partial slots (two of 64 rows per unit).
   AttnSplit sp;
-  sp.QB = (max_nodes + 63) / 64;
+  const AttnShape shape = plan_any(B, H, max_nodes, kv_cap, dh, dt == CTCSPEC_F32, 2LL * ctx->attn_units);
+  sp.QB = shape.QB;
+  sp.S = shape.S;
   const long long blocks = (long long)B * H * sp.QB;
-  const int key_tiles = (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys;
-  long long S = 512 / blocks;
-  if (S > key_tiles / 2) S = key_tiles / 2;
-  if (S > kMaxKvSplits) S = kMaxKvSplits;
-  while (S > 1 && blocks * S > 2LL * ctx->attn_units) --S;
-  if ((long long)B * H > 65535) S = 1;  // the merge kernel's grid
-  sp.S = S < 1 ? 1 : (int)S;
   sp.po = ctx->attn_po; sp.pm = ctx->attn_pm; sp.pl = ctx->attn_pl;
   CTCSPEC_REQUIRE(ctx, blocks * sp.S <= 0x7fffffffLL, CTCSPEC_EUNSUPPORTED, "tree_verify_attn: grid too large");
-  if (rows && sp.S > 1) {
-    p.rows = rows; p.rows_plane = rows_plane;
-    if (rows_written) *rows_written = 1;
-  }
-  CTCSPEC_HIP(ctx, dt == CTCSPEC_BF16 ? launch_attn_any<TileBf16>(p, sp, ctx->stream) : launch_attn_any<TileF32>(p, sp, ctx->stream));
+  CTCSPEC_REQUIRE(ctx, !rows || dt == CTCSPEC_BF16, CTCSPEC_EUNSUPPORTED, "tree_verify_attn: rows are written from bf16 operands");
+  const hipError_t e = launch_for(p, sp, [&](auto out_tag) {
+    constexpr AttnOut OUT = decltype(out_tag)::value;
+    if (dt == CTCSPEC_BF16) return launch_attn_any<TileBf16, OUT>(p, sp, ctx->stream);
+    return launch_attn_any<TileF32, OUT == AttnOut::kTwoBf16Rows ? AttnOut::kRows : OUT>(p, sp, ctx->stream);
+  });
+  CTCSPEC_HIP(ctx, e);
   return CTCSPEC_OK;
 }
 
@@ -1185,5 +1263,5 @@ extern "C" int tree_verify_attn(ctcspec_ctx* ctx, ctcspec_dtype dt, const void* 
                                 const uint64_t* anc_mask, int B, int H, int dh, int max_nodes, float scale,
                                 float* out) {
   return ctcspec::tree_verify_attn_rows(ctx, dt, q, k_cache, v_cache, kv_off, ctx_len, kv_cap, k_tree, v_tree, n_nodes,
-                                        anc_mask, B, H, dh, max_nodes, scale, out, nullptr, 0, nullptr, 0);
+                                        anc_mask, B, H, dh, max_nodes, scale, out, nullptr, 0, 0);
 }

@@ -165,3 +165,36 @@ def test_attention_long_histories(pkg, N):
     assert torch.isfinite(whole).all()
     assert torch.equal(whole[:5], call(slice(0, 5))) and torch.equal(whole[3:], call(slice(3, 8)))
     ctx.close()
+
+
+# Few heads over a long capacity: more than eight key splits, which the merge takes eight at a time - all of them with keys,
+# and with histories so short that most splits have none.  An infinity in the cache stays in its component (float and other
+# head dimensions).
+@pytest.mark.parametrize("dtype,dh,H,N,cap,tol", [("f32", 128, 2, 16, 2000, 1e-5), ("f32", 64, 1, 100, 2500, 1e-5),
+                                                  ("bf16", 80, 1, 40, 3000, 1e-5), ("bf16", 128, 4, 64, 2048, 5e-5),
+                                                  ("bf16", 128, 2, 128, 2048, 5e-5), ("bf16", 128, 3, 8, 2500, 5e-5)])
+@pytest.mark.parametrize("short", [0, 1])
+def test_attention_many_splits(pkg, dtype, dh, H, N, cap, tol, short):
+    B, ctx_len = 1, [33 if short else cap - 7]
+    print(f"attention many splits {dtype} dh={dh} H={H} N={N} ctx={ctx_len}", flush=True)
+    case = workloads.make_attention_case(dh + N, B, H, N, dh, cap, ctx_len, dtype)
+    trees = _trees(N, B, N, 128, "beam")
+    n = int(trees[0]["n_nodes"])
+    vc = case.v_cache.copy()
+    planted = dtype == "f32" or dh != 128
+    if planted:
+        vc[0][:, 2, 1] = np.inf
+    mask = torch.from_numpy(np.stack([t["anc_mask"] for t in trees]).view(np.int64)).cuda()
+    ctx = pkg.Context(max_batch=B, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=N, max_heads=H, max_head_dim=dh)
+    args = (to_device(case.q, dtype), to_device(case.k_cache, dtype), to_device(vc, dtype), dev_i64(case.kv_off),
+            dev_i32(case.ctx_len), cap, to_device(case.k_tree, dtype), to_device(case.v_tree, dtype), dev_i32(np.array([n])), mask,
+            dh ** -0.5)
+    got, again = pkg.tree_verify_attn(ctx, *args).cpu().numpy()[0, :, :n], pkg.tree_verify_attn(ctx, *args).cpu().numpy()[0, :, :n]
+    ref = oracle.tree_attention(case.q[0], case.k_cache[0], case.v_cache[0], ctx_len[0], case.k_tree[0], case.v_tree[0], n,
+                                trees[0]["mask"], dh ** -0.5)
+    assert np.array_equal(got, again)
+    if planted:
+        assert np.isposinf(got[:, :, 1]).all()
+        got[:, :, 1] = ref[:, :, 1]
+    assert rel_err_rms_floor(got, ref) <= tol
+    ctx.close()

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void layer_tile_kernel(LayerTilePa
   t.hidden = (const unsigned char*)p.x + (size_t)p.col0 * p.K * 2 + (size_t)t0 * kLtTripK * 2;
   t.zeros = p.zeros; t.D = (t1 - t0) * kLtTripK; t.pitch = p.K; t.V = p.N; t.row_base = rb * SH::ROWS;
   f32x4 acc[SH::RT][SH::CTW];
-  gemm_tile<4, SH, TileBf16, true>(t, LayerColumns{p.cols, p.plane_cols}, smem, acc);
+  gemm_tile<4, SH, TileBf16, true, true>(t, LayerColumns{p.cols, p.plane_cols}, smem, acc);
   float* out = p.part + (size_t)split * p.cols * p.N;
 #pragma unroll
   for (int ct = 0; ct < SH::CTW; ct += 2) {

@@ -32,6 +32,8 @@ namespace ctcspec {
 
 constexpr int kTileWaves = 8;
 
+__device__ __forceinline__ int clamp_int(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
+
 template <int WR_, int CTW_, int STEPB_, int RT_ = 4>
 struct TileShape {
   static constexpr int WR = WR_, WC = kTileWaves / WR_;  // wavefront grid
@@ -100,7 +102,8 @@ inline bool tile_rows16(int D, int elem) { return ((long long)D * elem) % 16 == 
 // acc[rt][ct][i]: row row_base + 16 (RT wr + rt) + 4 (lane >> 4) + i, column 16 CTW wc + 16 ct + (lane & 15),
 // wr = wave / WC, wc = wave % WC.
 // Every wavefront of the workgroup (8) must call it; it ends with a barrier after the last read of LDS.
-template <int DIST, typename SH, typename EL, bool ROWS16, typename COLUMNS>
+// WHOLE_TRIPS: D is known to be a multiple of DIST steps.
+template <int DIST, typename SH, typename EL, bool ROWS16, bool WHOLE_TRIPS = false, typename COLUMNS>
 __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& columns, unsigned char* smem,
                                           f32x4 (&acc)[SH::RT][SH::CTW]) {
   constexpr int CTW = SH::CTW, RT = SH::RT, STEPB = SH::STEPB, PITCH = SH::PITCH, CPR = SH::CPR, RPP = SH::RPP;
@@ -110,7 +113,8 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
   using Offset = std::conditional_t<ROWS16, unsigned int, size_t>;
   struct Packed16 { u32x4 v; } __attribute__((packed, aligned(EL::ELEM)));  // 16 bytes at an element's alignment
   typedef __attribute__((address_space(1))) Packed16 GlobalPacked16;
-  constexpr int TRIP = DIST % 2 == 0 ? DIST : 2 * DIST;    // steps per loop trip: stage and buffer static
+  constexpr int TRIP = DIST;    // steps per loop trip: stage and buffer static
+  static_assert(DIST % 2 == 0, "an even number of stages");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave / SH::WC, wc = wave % SH::WC;
@@ -171,32 +175,38 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  // the elements of a row behind its last whole step (tail_bytes of them), zeros behind those: every load reads an
-  // element of the row (indices clamped) and what lies past its end is replaced
+  // The elements of a row behind its last whole step (tail_bytes of them), zeros behind those: a thread's chunk has tail_n
+  // of its bytes in the row.  It is loaded so that it ends with them - every load stays inside its row - and shifted down
+  // when it is used, so that nothing waits for it in between.  (A row of less than 16 bytes: element by element.)
   const int tail_bytes = (int)(row_bytes - (size_t)total_steps * STEPB);
-  auto tail_piece = [&](uintptr_t row) __attribute__((always_inline)) -> u32x4 {
-    const uintptr_t start = row + (size_t)total_steps * STEPB;
+  const int tail_n = clamp_int(tail_bytes - pchunk * 16, 0, 16);
+  auto tail_load = [&](uintptr_t row) __attribute__((always_inline)) -> u32x4 {
     if constexpr (ROWS16) {  // whole chunks
-      const u32x4 v = *(const GlobalU32x4*)(start + (pchunk * 16 < tail_bytes ? pchunk * 16 : 0));
-      return pchunk * 16 < tail_bytes ? v : u32x4{0u, 0u, 0u, 0u};
+      return *(const GlobalU32x4*)(row + row_bytes - tail_bytes + (tail_n ? pchunk * 16 : 0));
     } else {
+      if (row_bytes >= 16) return ((const GlobalPacked16*)(row + (tail_n ? row_bytes - tail_bytes + pchunk * 16 + tail_n - 16 : 0)))->v;
       using E = std::conditional_t<EL::ELEM == 2, unsigned short, unsigned int>;
       constexpr int PER = 4 / EL::ELEM;  // elements per word
       typedef __attribute__((address_space(1))) E GlobalE;
-      u32x4 v;
+      u32x4 v = {0u, 0u, 0u, 0u};
+      for (int e = 0; e < 4 * PER; ++e) {
+        const unsigned int x = e * EL::ELEM < tail_n ? *(const GlobalE*)(row + e * EL::ELEM) : 0u;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        unsigned int word = 0u;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) {
-          const int at = pchunk * 16 + q * 4 + e * EL::ELEM;
-          const unsigned int x = *(const GlobalE*)(start + (at < tail_bytes ? at : 0));
-          word |= at < tail_bytes ? x << (8 * EL::ELEM * e) : 0u;
-        }
-        v[q] = word;
+        for (int q = 0; q < 4; ++q) v[q] |= e / PER == q ? x << (8 * EL::ELEM * (e % PER)) : 0u;
       }
       return v;
     }
+  };
+  auto tail_use = [&](u32x4 v) __attribute__((always_inline)) -> u32x4 {
+    if constexpr (!ROWS16)
+      if (row_bytes >= 16 && tail_n > 0 && tail_n < 16) {
+        unsigned long long lo = ((unsigned long long)v[1] << 32) | v[0], hi = ((unsigned long long)v[3] << 32) | v[2];
+        const int bits = 8 * (16 - tail_n);
+        lo = bits >= 64 ? hi >> (bits & 63) : (lo >> bits) | (hi << (64 - bits));
+        hi = bits >= 64 ? 0ull : hi >> bits;
+        v = u32x4{(unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32)};
+      }
+    return tail_n ? v : u32x4{0u, 0u, 0u, 0u};
   };
   auto commit = [&](auto stage, auto buffer) __attribute__((always_inline)) {
     constexpr int S = decltype(stage)::value, BUF = decltype(buffer)::value;
@@ -256,52 +266,100 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  using I0 = std::integral_constant<int, 0>;
 
   // The pipelined loop takes TRIP steps per trip with no exit in between (an exit inside the trip gives the
   // loop head a second, differently ordered set of loads in flight and the waits there fall back to draining
-  // everything), so the total_steps % TRIP steps that do not fill a trip run first, unpipelined.
-  // So does what lies behind a row's last whole step.
-  const int lead = total_steps % TRIP;
-  bool used = false;  // LDS has been computed from
-  if (tail_bytes > 0) {
+  // everything).  In front of it go what lies behind a row's last whole step and the total_steps % TRIP steps that do not
+  // fill a trip - through the same rotating stages, one copy of the code per remainder, so that every path reaches the
+  // loop with the same loads in flight.  Wide tiles have no registers for that (it spilled, +3 us a call): there they run
+  // before the first prefetch, a load latency each.  Narrow ones did too: 8 columns x 12547 rows of 1499 bf16
+  // elements 27.4 -> 24.1 us,
+  // 64 x 14949 of 1234 21.8 -> 16.8, 40 x 18230 of 1280 33.2 -> 32.1 (whole calls).
+  constexpr bool kWide = RT * CTW >= 8;
+  const int lead = WHOLE_TRIPS ? 0 : total_steps % TRIP;
+  auto load_tail = [&](auto stage) __attribute__((always_inline)) {
+    constexpr int S = decltype(stage)::value;
 #pragma unroll
-    for (int u = 0; u < HP; ++u) hreg[0][u] = tail_piece(h_addr + hoff[u]);
+    for (int u = 0; u < HP; ++u) hreg[S][u] = tail_load(h_addr + hoff[u]);
 #pragma unroll
-    for (int u = 0; u < WP; ++u) wreg[0][u] = tail_piece(w_addr + woff[u]);
-    commit(I0{}, I0{});
-    lds_barrier();
-    compute(I0{}, std::false_type{}, I0{});
-    used = true;
-  }
-  for (int i = 0; i < lead; ++i) {
-    request(i, I0{});
-    if (used) lds_barrier();
-    commit(I0{}, I0{});
-    lds_barrier();
-    compute(I0{}, std::false_type{}, I0{});
-    used = true;
-  }
-  if (lead == total_steps) lds_barrier();  // no pipelined trip follows: the caller is about to reuse the LDS
-  if (lead < total_steps) {
-    // local step t = step - lead uses register stage t % DIST and LDS buffer t & 1
+    for (int u = 0; u < WP; ++u) wreg[S][u] = tail_load(w_addr + woff[u]);
+  };
+  auto commit_tail = [&](auto stage, auto buffer) __attribute__((always_inline)) {
+    constexpr int S = decltype(stage)::value;
+#pragma unroll
+    for (int u = 0; u < HP; ++u) hreg[S][u] = tail_use(hreg[S][u]);
+#pragma unroll
+    for (int u = 0; u < WP; ++u) wreg[S][u] = tail_use(wreg[S][u]);
+    commit(stage, buffer);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  // enter the loop behind `lead` steps, L of which are still to be taken: step i of them uses register stage (i - L) mod
+  // DIST and LDS buffer (i - L) & 1, as the loop counts them
+  auto enter = [&](auto left_tag, auto tail_first) __attribute__((always_inline)) {
+    constexpr int L = decltype(left_tag)::value;
+    constexpr bool TAIL = decltype(tail_first)::value;
+#define CTCSPEC_TILE_STAGE(i) std::integral_constant<int, (((i) - L) % DIST + DIST) % DIST>{}
+#define CTCSPEC_TILE_BUFFER(i) std::integral_constant<int, (((i) - L) % 2 + 2) % 2>{}
+    const int step0 = lead - L;
+    if constexpr (TAIL) load_tail(CTCSPEC_TILE_STAGE(DIST - 1));
     [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {
-      (request(lead + U, std::integral_constant<int, U>{}), ...);
-    }(std::make_integer_sequence<int, DIST>{});
-    if (used) lds_barrier();
-    commit(I0{}, I0{});
-    request(lead + DIST, I0{});
-    lds_barrier();
-    for (int t = lead; t < total_steps; t += TRIP) {
-      [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {
-        // step t + U: write step t + U + 1 (after the last step: zeros into the idle buffer), refill its stage
-        ((compute(std::integral_constant<int, U & 1>{}, std::true_type{}, std::integral_constant<int, (U + 1) % DIST>{}),
-          request(t + U + 1 + DIST, std::integral_constant<int, (U + 1) % DIST>{}), lds_barrier()),
-         ...);
-      }(std::make_integer_sequence<int, TRIP>{});
+      (request(step0 + U, CTCSPEC_TILE_STAGE(U)), ...);
+    }(std::make_integer_sequence<int, TAIL ? DIST - 1 : DIST>{});
+    if constexpr (TAIL) {
+      commit_tail(CTCSPEC_TILE_STAGE(DIST - 1), CTCSPEC_TILE_BUFFER(1));
+      request(step0 + DIST - 1, CTCSPEC_TILE_STAGE(DIST - 1));
+      lds_barrier();
+      compute(CTCSPEC_TILE_BUFFER(1), std::false_type{}, I0{});
     }
+    commit(CTCSPEC_TILE_STAGE(0), CTCSPEC_TILE_BUFFER(0));
+    request(step0 + DIST, CTCSPEC_TILE_STAGE(0));
+    lds_barrier();
+    [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {
+      ((compute(CTCSPEC_TILE_BUFFER(U), std::true_type{}, CTCSPEC_TILE_STAGE(U + 1)),
+        request(step0 + U + 1 + DIST, CTCSPEC_TILE_STAGE(U + 1)), lds_barrier()),
+       ...);
+    }(std::make_integer_sequence<int, L>{});
+#undef CTCSPEC_TILE_STAGE
+#undef CTCSPEC_TILE_BUFFER
+  };
+  if constexpr (WHOLE_TRIPS) {
+    enter(I0{}, std::false_type{});
+  } else if (kWide || total_steps < 2) {  // (nothing to prefetch either)
+    bool used = false;  // LDS has been computed from
+    if (tail_bytes > 0) {
+      load_tail(I0{});
+      commit_tail(I0{}, I0{});
+      lds_barrier();
+      compute(I0{}, std::false_type{}, I0{});
+      used = true;
+    }
+    for (int i = 0; i < lead; ++i) {
+      request(i, I0{});
+      if (used) lds_barrier();
+      commit(I0{}, I0{});
+      lds_barrier();
+      compute(I0{}, std::false_type{}, I0{});
+      used = true;
+    }
+    if (used) lds_barrier();  // (also in front of the caller's reuse of the LDS, when no trip follows)
+    if constexpr (kWide)
+      if (lead < total_steps) enter(I0{}, std::false_type{});
+  } else if constexpr (!kWide) {
+    [&]<int... N>(std::integer_sequence<int, N...>) __attribute__((always_inline)) {
+      ((lead == N ? (tail_bytes > 0 ? enter(std::integral_constant<int, N>{}, std::true_type{})
+                                    : enter(std::integral_constant<int, N>{}, std::false_type{}))
+                  : void()),
+       ...);
+    }(std::make_integer_sequence<int, TRIP>{});
   }
-
+  for (int t = lead; t < total_steps; t += TRIP) {
+    [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {
+      // step t + U: write step t + U + 1 (after the last step: zeros into the idle buffer), refill its stage
+      ((compute(std::integral_constant<int, U & 1>{}, std::true_type{}, std::integral_constant<int, (U + 1) % DIST>{}),
+        request(t + U + 1 + DIST, std::integral_constant<int, (U + 1) % DIST>{}), lds_barrier()),
+       ...);
+    }(std::make_integer_sequence<int, TRIP>{});
+  }
 }
 
 }  // namespace ctcspec

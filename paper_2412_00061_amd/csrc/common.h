@@ -70,6 +70,8 @@ struct ctcspec_ctx {
   // attention
   int attn_units;               // number of (sequence, head, split) partial slots
   float* attn_po;               // [attn_units][128][max_head_dim]
+  float* head_part;             // the same space: partial sums of heads cut along the hidden dimension
+  size_t head_part_floats;
   float* attn_pm;               // [attn_units][128]
   float* attn_pl;               // [attn_units][128]
 };

@@ -5,6 +5,7 @@
 #include <new>
 
 #include "common.h"
+#include "head_ranges.h"
 
 namespace ctcspec {
 
@@ -128,7 +129,10 @@ extern "C" int ctcspec_create(ctcspec_ctx** out, void* hip_stream, const ctcspec
   size_t o_coll = carve((size_t)lim->max_batch * kCollapseWsBytesPerSeq);
   // attention partials: one slot of 128 query rows per (sequence, head, key split)
   const size_t attn_rows = (size_t)ctx->attn_units * 128;
-  size_t o_po = carve(attn_rows * lim->max_head_dim * sizeof(float));
+  // (the heads' partial sums share the space: no call leaves any of either behind)
+  size_t po_floats = attn_rows * lim->max_head_dim;
+  po_floats = po_floats > kHeadPartFloats ? po_floats : kHeadPartFloats;
+  size_t o_po = carve(po_floats * sizeof(float));
   size_t o_pm = carve(attn_rows * sizeof(float));
   size_t o_pl = carve(attn_rows * sizeof(float));
   ctx->ws_bytes = off;
@@ -151,7 +155,8 @@ extern "C" int ctcspec_create(ctcspec_ctx** out, void* hip_stream, const ctcspec
   ctx->vh_pkey = (unsigned long long*)(base + o_vh);
   ctx->zeros = base + o_zero;
   ctx->collapse_ws = base + o_coll;
-  ctx->attn_po = (float*)(base + o_po);
+  ctx->attn_po = ctx->head_part = (float*)(base + o_po);
+  ctx->head_part_floats = po_floats;
   ctx->attn_pm = (float*)(base + o_pm);
   ctx->attn_pl = (float*)(base + o_pl);
   g_create_err[0] = 0;

@@ -13,7 +13,8 @@
 //                                columns at D = 4096)
 //   * lmhead_tile_kernel       - everything else (more columns, other hidden sizes, float operands): the tile
 //                                loop of gemm_tile.h, both operands stepping through LDS
-// Both hand the block over in LDS to the same epilogue.
+// Both hand the block over in LDS to the same epilogue.  Vocabularies that do not fill the chip are cut along the hidden
+// dimension as well (head_ranges.h); lmhead_columns_kernel then finishes a column.
 #include <mutex>
 #include <type_traits>
 #include <utility>
@@ -21,6 +22,7 @@
 #include <hip/hip_ext.h>
 
 #include "gemm_tile.h"
+#include "head_ranges.h"
 #include "topk_merge.h"
 
 namespace ctcspec {
@@ -175,6 +177,88 @@ __global__ __launch_bounds__(64) void lmhead_merge_kernel(LmHeadParams p) {
     p.topk_id[col[0] * k + lane] = (int32_t)rank_key_index(key);
     p.topk_logp[col[0] * k + lane] = rank_key_value(key) - lse[0];
   }
+}
+
+// A column in one workgroup: the ranges' sums, the bias, the logits' row, log-sum-exp and the k best keys (a lane's own,
+// kept sorted, then the wavefront's off the heads of the lanes' lists, then the workgroup's).
+// Bound: latency - one round of loads, then the wavefronts' maxima; k insertions per row instead of only where the lanes'
+// maxima leave candidates took the longer the more rows a thread holds.
+template <int KMAX, int NV>
+__global__ __launch_bounds__(kHeadColumnThreads) void lmhead_columns_kernel(HeadRangeParams h, LmHeadParams p) {
+  constexpr int WAVES = kHeadColumnThreads / 64;
+  static_assert(WAVES * KMAX <= 64, "a lane per key in the last step");
+  __shared__ float red[2 * WAVES];
+  __shared__ unsigned long long keys[WAVES * KMAX];
+  const int col = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  f32x4 z[NV];
+  load_head_column<NV>(h, col, z);
+  float mx = -INFINITY;
+  KeyList<KMAX> list;
+  list.clear();
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = 4 * (j * kHeadColumnThreads + tid) + i;
+      z[j][i] = row < p.Vp1 ? z[j][i] + (p.bias ? p.bias[row] : 0.f) : -INFINITY;
+      mx = fmaxf(mx, z[j][i]);
+    }
+  if (p.logits_out) store_head_column<NV>(p.logits_out + (size_t)col * p.Vp1, p.Vp1, z);
+  // k lanes have something at least as large as the k-th largest of the lanes' maxima: the rest is no candidate
+  float left = mx, floor = -INFINITY;
+  for (int r = 0; r < p.k; ++r) {
+    floor = wave_max_f32(left);
+    left = left == floor ? -INFINITY : left;
+  }
+  mx = wave_max_f32(mx);
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = 4 * (j * kHeadColumnThreads + tid) + i;
+      if (!(z[j][i] < floor) && row < p.Vp1) list.insert(rank_key(z[j][i], (unsigned)row));  // (not a number: a candidate)
+    }
+  if (lane == 0) red[wave] = mx;
+#pragma unroll
+  for (int r = 0; r < KMAX; ++r) {
+    const unsigned long long best = wave_max_u64(list.v[0]);
+    if (list.v[0] == best) list.pop();  // keys are distinct: one lane, or lanes that have none left
+    if (lane == 0) keys[wave * KMAX + r] = best;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) mx = fmaxf(mx, red[w]);
+  float sum = 0.f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum += mx > -INFINITY ? __expf(z[j][i] - mx) : 0.f;
+  sum = wave_sum_f32(sum);
+  if (lane == 0) red[WAVES + wave] = sum;
+  __syncthreads();
+  if (wave != 0) return;
+  sum = 0.f;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) sum += red[WAVES + w];
+  const float lse = mx + __logf(sum);
+  if (lane == 0 && p.lse) p.lse[col] = lse;
+  unsigned long long mine = lane < WAVES * KMAX ? keys[lane] : 0ull, out = 0ull;
+  for (int r = 0; r < p.k; ++r) {
+    const unsigned long long best = wave_max_u64(mine);
+    mine = mine == best ? 0ull : mine;
+    out = lane == r ? best : out;
+  }
+  if (lane < p.k) {
+    p.topk_id[col * p.k + lane] = (int32_t)rank_key_index(out);
+    p.topk_logp[col * p.k + lane] = rank_key_value(out) - lse;
+  }
+}
+template <int KMAX>
+static hipError_t launch_columns(const HeadRangeParams& h, const LmHeadParams& p, hipStream_t stream) {
+  return launch_for_rows(p.Vp1, [&](auto nv) {
+    hipLaunchKernelGGL((lmhead_columns_kernel<KMAX, decltype(nv)::value>), dim3(p.BT), dim3(kHeadColumnThreads), 0, stream, h, p);
+    return hipGetLastError();
+  });
 }
 
 // ---- bf16 MFMA streaming producer -----------------------------------------------------------------
@@ -470,20 +554,22 @@ static hipError_t allow_large_lds() {
   if (e == hipSuccess) e = allow_tile_lds<TileBf16, false>();
   if (e == hipSuccess) e = allow_tile_lds<TileF32, true>();
   if (e == hipSuccess) e = allow_tile_lds<TileF32, false>();
+  if (e == hipSuccess) e = prepare_head_ranges();
   return e;
 }
 
 // ---- scratch of the entry point that allocates nothing ------------------------------------------------------------
 // The same partial results that ctc_draft_topk keeps in its context's workspace, in a device array of the library
-// itself: [256 bytes of zeros][pmax][psum][pkey], the three laid out as in the context for kStaticMaxBlocks row blocks.  Every GPU the library
-// runs on holds its own copy (2.4 MB) at its own address until the process ends.
+// itself: [256 bytes of zeros][pmax][psum][pkey][sums of the ranges], laid out as in the context for kStaticMaxBlocks row
+// blocks.  Every GPU the library runs on holds its own copy (10.8 MB) at its own address until the process ends.
 constexpr int kStaticMaxBlocks = CTCSPEC_NOALLOC_MAX_VOCAB_ROWS / kRowsPerBlock;
 constexpr size_t kScratchZeros = 0;
 constexpr size_t kScratchPmax = 256;
 constexpr size_t kScratchPsum = kScratchPmax + (size_t)kStaticMaxBlocks * kMaxCols * sizeof(float);
 constexpr size_t kScratchPkey = kScratchPsum + (size_t)kStaticMaxBlocks * kMaxCols * sizeof(float);
-constexpr size_t kScratchBytes = kScratchPkey + (size_t)kStaticMaxBlocks * kMaxCols * kMaxTopk * sizeof(unsigned long long);
-static_assert(CTCSPEC_NOALLOC_MAX_VOCAB_ROWS % kRowsPerBlock == 0 && kScratchPkey % 256 == 0, "scratch layout");
+constexpr size_t kScratchPart = kScratchPkey + (size_t)kStaticMaxBlocks * kMaxCols * kMaxTopk * sizeof(unsigned long long);
+constexpr size_t kScratchBytes = kScratchPart + kDraftPartFloats * sizeof(float);
+static_assert(CTCSPEC_NOALLOC_MAX_VOCAB_ROWS % kRowsPerBlock == 0 && kScratchPkey % 256 == 0 && kScratchPart % 256 == 0, "scratch layout");
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 // In host code `scratch` is only a handle for the runtime, not a device address: the address on each device comes
@@ -534,6 +620,7 @@ struct LmScratch {
   unsigned long long* pkey;
   int pstride;
   const void* zeros;
+  float* part;  // kDraftPartFloats
 };
 
 static int draft_topk_launch(ctcspec_ctx* err, hipStream_t stream, const LmScratch& sc, hipEvent_t ev0, hipEvent_t ev1,
@@ -562,6 +649,23 @@ static int draft_topk_launch(ctcspec_ctx* err, hipStream_t stream, const LmScrat
     return CTCSPEC_OK;
   };
 
+  // what the epilogue of the many-column kernel takes: insertions into k-lists; a column's workgroup pops k keys
+  const bool f32 = dt == CTCSPEC_F32;
+  const int tile_cols = p.BT <= 16 ? 16 : p.BT <= 32 ? 32 : 64;
+  const double epilogue_us = tile_cols == 16 ? 1.5 : k <= 2 ? 4.0 : k <= 4 ? 6.0 : 11.0;
+  HeadRangeParams h;
+  h.hidden = hidden; h.w = w; h.zeros = sc.zeros; h.part = sc.part; h.cols = p.BT; h.D = D; h.V = Vp1;
+  if (plan_head(h, f32, head_whole_us(Vp1, p.BT, D, f32, kRowsPerBlock, tile_cols, epilogue_us), 1.5 + 0.2 * k, kDraftPartFloats)) {
+    if (timing) CTCSPEC_HIP(err, hipEventRecord(ev0, stream));
+    CTCSPEC_HIP(err, launch_head_ranges(h, f32, stream));
+    if (timing) {
+      CTCSPEC_HIP(err, hipEventRecord(ev1, stream));
+      if (timed) *timed = 1;
+    }
+    CTCSPEC_HIP(err, k <= 1 ? launch_columns<1>(h, p, stream) : k <= 2 ? launch_columns<2>(h, p, stream)
+                     : k <= 4 ? launch_columns<4>(h, p, stream) : launch_columns<8>(h, p, stream));
+    return CTCSPEC_OK;  // (nothing of it can be left to the collapse kernel)
+  }
   if (dt == CTCSPEC_BF16) {
     const int budget = kMfmaLdsLimit - kMfmaWaves * kWStageBytes;
     // the streaming kernel needs the hidden states of all columns in LDS over the whole hidden dimension
@@ -633,7 +737,7 @@ extern "C" int ctc_draft_topk(ctcspec_ctx* ctx, ctcspec_dtype dt, const void* hi
   CTCSPEC_REQUIRE(ctx, B <= ctx->lim.max_batch && T <= ctx->lim.max_slots && k <= ctx->lim.max_topk &&
                            Vp1 <= ctx->lim.max_vocab_rows,
                   CTCSPEC_EUNSUPPORTED, "ctc_draft_topk: shape exceeds the context's limits");
-  const LmScratch sc = {ctx->lm_pmax, ctx->lm_psum, ctx->lm_pkey, ctx->lm_max_blocks, ctx->zeros};
+  const LmScratch sc = {ctx->lm_pmax, ctx->lm_psum, ctx->lm_pkey, ctx->lm_max_blocks, ctx->zeros, ctx->head_part};
   return draft_topk_launch(ctx, ctx->stream, sc, ctx->lm_profile ? ctx->lm_ev0 : nullptr,
                            ctx->lm_profile ? ctx->lm_ev1 : nullptr, &ctx->lm_profile_valid, ctx->lm_defer != 0, dt, hidden, w,
                            bias, B, T, D, Vp1, k, topk_id, topk_logp, lse, logits_out);
@@ -662,7 +766,8 @@ extern "C" int ctc_draft_topk_noalloc(void* hip_stream, ctcspec_dtype dt, const 
     CTCSPEC_HIP(nullptr, allow_large_lds());
   }
   const LmScratch sc = {(float*)(sp + kScratchPmax), (float*)(sp + kScratchPsum),
-                        (unsigned long long*)(sp + kScratchPkey), kStaticMaxBlocks, sp + kScratchZeros};
+                        (unsigned long long*)(sp + kScratchPkey), kStaticMaxBlocks, sp + kScratchZeros,
+                        (float*)(sp + kScratchPart)};
   return draft_topk_launch(nullptr, stream, sc, nullptr, nullptr, nullptr, false, dt, hidden, w, bias, B, T, D, Vp1, k, topk_id,
                            topk_logp, lse, logits_out);
 }

@@ -1,0 +1,131 @@
+// The product of a head cut into ranges of the hidden dimension (head_ranges.h), and the rule that chooses it.
+#include <type_traits>
+
+#include "gemm_tile.h"
+#include "head_ranges.h"
+
+namespace ctcspec {
+
+// Bound: start-up (a workgroup's first tile is in LDS after about 6 us) and then LDS traffic per step, as in gemm_tile.h; the
+// partial sums go out in 64-byte pieces, nontemporal (read once, by another kernel).
+template <typename SH, typename EL, bool ROWS16>
+__global__ __launch_bounds__(64 * kTileWaves) void head_range_kernel(HeadRangeParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  static_assert(SH::ROWS == kRowsPerBlock, "row blocks of 128");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = wave / SH::WC, wc = wave % SH::WC;
+  const int c = lane & 15, g = lane >> 4;
+  // the column blocks of a (row block, range) run on one XCD, side by side (verify_head.hip has the reason)
+  const int slot = blockIdx.x >> 3, unit = (slot / p.col_blocks) * 8 + (blockIdx.x & 7);
+  if (unit >= p.row_blocks * p.splits) return;
+  const int cb = slot % p.col_blocks, rb = unit % p.row_blocks, split = unit / p.row_blocks;
+  const int col0 = cb * SH::COLS, cols = p.cols - col0 < SH::COLS ? p.cols - col0 : SH::COLS;
+  // ranges of whole steps - of whole trips of the tile loop where there are enough - and the last one takes the rest
+  const size_t row_bytes = (size_t)p.D * EL::ELEM;
+  const int steps = (int)(row_bytes / SH::STEPB);
+  const int per = steps >= 4 * p.splits ? 4 : 1;
+  const int t0 = split * (steps / per) / p.splits * per, t1 = (split + 1) * (steps / per) / p.splits * per;
+  const size_t from = (size_t)t0 * SH::STEPB, to = split + 1 == p.splits ? row_bytes : (size_t)t1 * SH::STEPB;
+  GemmTileArgs t;
+  t.w = (const unsigned char*)p.w + from;
+  t.hidden = (const unsigned char*)p.hidden + (size_t)col0 * row_bytes + from;
+  t.zeros = p.zeros; t.D = (int)((to - from) / EL::ELEM); t.pitch = p.D; t.V = p.V; t.row_base = rb * SH::ROWS;
+  f32x4 acc[SH::RT][SH::CTW];
+  gemm_tile<4, SH, EL, ROWS16>(t, TileColumns{cols}, smem, acc);
+  const int Vp = p.row_blocks * SH::ROWS;
+  float* out = p.part + ((size_t)split * p.cols + col0) * Vp + t.row_base;
+#pragma unroll
+  for (int ct = 0; ct < SH::CTW; ++ct) {
+    const int col = (wc * SH::CTW + ct) * 16 + c;
+    if (col >= cols) continue;
+#pragma unroll
+    for (int rt = 0; rt < SH::RT; ++rt)
+      __builtin_nontemporal_store(acc[rt][ct], (f32x4*)(out + (size_t)col * Vp + (wr * SH::RT + rt) * 16 + g * 4));
+  }
+}
+
+// ---- the rule -------------------------------------------------------------------------------------------------------
+constexpr double kStartUs = 6.0, kFinishLaunchUs = 4.3;  // a workgroup's way to its first step; the second launch
+static double step_us(int tile_cols, bool f32, long long groups) {
+  const int i = tile_cols <= 16 ? 0 : tile_cols <= 32 ? 1 : tile_cols <= 64 ? 2 : 3;
+  static const double lds[4] = {0.35, 0.4, 0.9, 1.1}, mfma[4] = {0.45, 0.9, 1.75, 3.5};
+  const double own = f32 ? mfma[i] : lds[i], stream = (double)(groups < 256 ? groups : 256) * 32768.0 / 5.9e6;
+  return own > stream ? own : stream;
+}
+static double walk_us(long long groups, double steps, double step) {
+  return (double)((groups + 255) / 256) * (kStartUs + steps * step);
+}
+double head_whole_us(int V, int cols, int D, bool f32, int rows, int tile_cols, double finish_us) {
+  const long long groups = (long long)((V + rows - 1) / rows) * ((cols + tile_cols - 1) / tile_cols);
+  const double steps = (double)D * (f32 ? 4 : 2) / 256.0;
+  return walk_us(groups, steps, step_us(tile_cols, f32, groups) * rows / 128.0) + kFinishLaunchUs + finish_us;
+}
+bool plan_head(HeadRangeParams& p, bool f32, double whole_us, double finish_us, size_t part_floats) {
+  if (p.V > kHeadMaxRows) return false;
+  p.row_blocks = (p.V + kRowsPerBlock - 1) / kRowsPerBlock;
+  const double steps = (double)p.D * (f32 ? 4 : 2) / 256.0;
+  const size_t sums = (size_t)p.cols * p.row_blocks * kRowsPerBlock;  // of one range
+  double least = 0.9 * whole_us;  // (the model is not better than that)
+  p.splits = 0;
+  for (int tile = 16; tile <= 128; tile *= 2) {
+    const long long groups = (long long)p.row_blocks * ((p.cols + tile - 1) / tile);
+    for (int S = 1; S <= kHeadMaxSplits && (S == 1 || S <= steps) && S * sums <= part_floats; ++S) {
+      const double us = walk_us(groups * S, steps / S, step_us(tile, f32, groups * S)) + (double)S * sums * 8.0 / 3e6 +
+                        kFinishLaunchUs + finish_us + ((p.cols + 255) / 256) * (double)S * p.V * 4.0 / 45e3;
+      if (us < least) {
+        least = us;
+        p.splits = S;
+        p.tile_cols = tile;
+      }
+    }
+    if (tile >= p.cols) break;
+  }
+  if (p.splits == 0) return false;
+  p.col_blocks = (p.cols + p.tile_cols - 1) / p.tile_cols;
+  return true;
+}
+
+template <typename EL, bool ROWS16, typename F>
+static hipError_t each_shape(F&& f) {
+  hipError_t e = f(Tile128x16{});
+  if (e == hipSuccess) e = f(Tile128x32{});
+  if (e == hipSuccess) e = f(Tile128x64{});
+  if (e == hipSuccess) e = f(Tile128x128{});
+  return e;
+}
+template <typename EL, bool ROWS16>
+static hipError_t launch_rows(const HeadRangeParams& p, hipStream_t stream) {
+  return each_shape<EL, ROWS16>([&](auto shape) {
+    using SH = decltype(shape);
+    if (SH::COLS != p.tile_cols) return hipSuccess;
+    const long long units = (long long)p.row_blocks * p.splits, grid = (units + 7) / 8 * 8 * p.col_blocks;
+    hipLaunchKernelGGL((head_range_kernel<SH, EL, ROWS16>), dim3((unsigned)grid), dim3(64 * kTileWaves), SH::LDS_BYTES, stream, p);
+    return hipGetLastError();
+  });
+}
+template <typename EL>
+static hipError_t launch_type(const HeadRangeParams& p, hipStream_t stream) {
+  return tile_rows16(p.D, EL::ELEM) ? launch_rows<EL, true>(p, stream) : launch_rows<EL, false>(p, stream);
+}
+hipError_t launch_head_ranges(const HeadRangeParams& p, bool f32, hipStream_t stream) {
+  return f32 ? launch_type<TileF32>(p, stream) : launch_type<TileBf16>(p, stream);
+}
+
+template <typename EL, bool ROWS16>
+static hipError_t allow_lds() {
+  return each_shape<EL, ROWS16>([](auto shape) {
+    using SH = decltype(shape);
+    return hipFuncSetAttribute((const void*)head_range_kernel<SH, EL, ROWS16>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               SH::LDS_BYTES);
+  });
+}
+hipError_t prepare_head_ranges() {
+  hipError_t e = allow_lds<TileBf16, true>();
+  if (e == hipSuccess) e = allow_lds<TileBf16, false>();
+  if (e == hipSuccess) e = allow_lds<TileF32, true>();
+  if (e == hipSuccess) e = allow_lds<TileF32, false>();
+  return e;
+}
+
+}  // namespace ctcspec

@@ -1063,7 +1063,7 @@ static double iterations(int kv_cap, int max_nodes, int S, int per_iter) {
   return n > 1.0 ? n : 1.0;
 }
 // bf16, head dimension 128.  Blocks of 64 rows take two tiles an iteration (0.9 us; 1.1 when two blocks share the keys),
-// blocks of 128 one (0.78 us; 0.52 with a single live row group, whose partials are 16 rows).  slots: units of 128 rows that
+// blocks of 128 one (0.88 us; 0.52 with a single live row group, whose partials are 16 rows).  slots: units of 128 rows that
 // the workspace holds.
 static AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long long slots) {
   AttnShape best = {1, 1};
@@ -1071,7 +1071,7 @@ static AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long lon
   double least = 1e30;
   for (int QB = 1; QB <= (max_nodes > 64 ? 2 : 1); ++QB) {
     const bool rows64 = max_nodes > 64 ? QB == 2 : max_nodes > kFewRows;
-    const double iter = rows64 ? (QB == 2 ? 1.1 : 0.9) : (max_nodes > kFewRows ? 0.78 : 0.52);
+    const double iter = rows64 ? (QB == 2 ? 1.1 : 0.9) : (max_nodes > kFewRows ? 0.88 : 0.52);
     for (int S = 1; S <= kMaxKvSplits; ++S) {
       const long long groups = bh * QB * S;
       if (S > 1 && (groups > 256 || groups > slots || S * 4 > (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys)) break;

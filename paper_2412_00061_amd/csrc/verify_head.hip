@@ -8,7 +8,12 @@
 //                                  in one launch, those of a row block side by side on one XCD (the weights come
 //                                  from HBM once)
 //   * verify_head_merge_kernel   - best key over the row blocks -> token id, -1 for rows without a node
+//   * verify_head_columns_kernel - vocabularies that do not fill the chip (head_ranges.h): the ranges' sums of a column
+//                                  -> its token id
+#include <type_traits>
+
 #include "gemm_tile.h"
+#include "head_ranges.h"
 
 namespace ctcspec {
 
@@ -141,6 +146,41 @@ __global__ __launch_bounds__(64) void verify_head_merge_kernel(VerifyHeadParams 
   }
 }
 
+// one workgroup per column: the ranges' sums, the logits' row, the best key
+template <int NV>
+__global__ __launch_bounds__(kHeadColumnThreads) void verify_head_columns_kernel(HeadRangeParams r, VerifyHeadParams p) {
+  __shared__ unsigned long long keys[kHeadColumnThreads / 64];
+  const int col = blockIdx.x, tid = threadIdx.x;
+  const int b = col / p.max_nodes;
+  int n = p.n_nodes[b];
+  n = n < 0 ? 0 : (n > p.max_nodes ? p.max_nodes : n);
+  const bool node = col - b * p.max_nodes < n;
+  if (!node && !p.logits_out) {
+    if (tid == 0) p.target[col] = -1;
+    return;
+  }
+  f32x4 z[NV];
+  load_head_column<NV>(r, col, z);
+  if (p.logits_out) store_head_column<NV>(p.logits_out + (size_t)col * p.V, p.V, z);
+  unsigned long long best = 0ull;
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = 4 * (j * kHeadColumnThreads + tid) + i;
+      const unsigned long long key = row < p.V ? rank_key(z[j][i], (unsigned)row) : 0ull;
+      best = key > best ? key : best;
+    }
+  best = wave_max_u64(best);
+  if ((tid & 63) == 0) keys[tid >> 6] = best;
+  __syncthreads();
+  if (tid == 0) {
+#pragma unroll
+    for (int w = 1; w < kHeadColumnThreads / 64; ++w) best = keys[w] > best ? keys[w] : best;
+    p.target[col] = node ? (int32_t)rank_key_index(best) : -1;
+  }
+}
+
 // ---- kv_commit ------------------------------------------------------------------------------------------------
 struct KvCommitParams {
   const unsigned char* k_tree;
@@ -270,6 +310,21 @@ extern "C" int verify_head_argmax(ctcspec_ctx* ctx, ctcspec_dtype dt, const void
   CTCSPEC_REQUIRE(ctx, ((long long)V / kRowsPerBlock + 8) * ((cols_total + kVhCols - 1) / kVhCols) <= 0x7fffffffLL,
                   CTCSPEC_EUNSUPPORTED, "verify_head_argmax: grid too large");
   p.cols_total = (int)cols_total;
+  const bool f32 = dt == CTCSPEC_F32;
+  HeadRangeParams r;
+  r.hidden = node_hidden; r.w = w_base; r.zeros = ctx->zeros; r.part = ctx->head_part; r.cols = p.cols_total; r.D = D; r.V = V;
+  const int tile_cols = p.cols_total <= 16 ? 16 : p.cols_total <= 32 ? 32 : p.cols_total <= 64 ? 64 : 128;
+  if (plan_head(r, f32, head_whole_us(V, p.cols_total, D, f32, p.cols_total > kVhCols ? 256 : 128, tile_cols, 1.0), 1.0,
+                ctx->head_part_floats)) {
+    CTCSPEC_HIP(ctx, launch_head_ranges(r, f32, ctx->stream));
+    const hipError_t e = launch_for_rows(V, [&](auto nv) {
+      hipLaunchKernelGGL(verify_head_columns_kernel<decltype(nv)::value>, dim3((unsigned)cols_total), dim3(kHeadColumnThreads), 0,
+                         ctx->stream, r, p);
+      return hipGetLastError();
+    });
+    CTCSPEC_HIP(ctx, e);
+    return CTCSPEC_OK;
+  }
   p.col_blocks = (int)((cols_total + kVhCols - 1) / kVhCols);
   CTCSPEC_HIP(ctx, dt == CTCSPEC_BF16 ? launch_head<TileBf16>(p, ctx->stream) : launch_head<TileF32>(p, ctx->stream));
   hipLaunchKernelGGL(verify_head_merge_kernel, dim3((unsigned)cols_total), dim3(64), 0, ctx->stream, p);

@@ -71,3 +71,54 @@ def test_draft_head_any_hidden(pkg, dtype, i):
         lse = np.log(np.exp(z.astype(np.float64)).sum(1))
         assert np.max(np.abs(res["lse"].cpu().numpy().reshape(-1) - lse)) <= 2e-5
         ctx.close()
+
+
+# Vocabularies that do not fill the chip, long hidden dimensions: cut into ranges of the hidden dimension, a column finished
+# by one workgroup that holds 1, 2, 4 or 8 groups of rows per thread (2048 rows each).  Every 50th row repeats row 3, so
+# the best keys tie across row blocks; a column that has no node; without logits the tokens are the same.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,N,D,V", [(1, 128, 64, 100), (1, 16, 4096, 1500), (3, 43, 2049, 2049), (1, 33, 1031, 4100),
+                                     (8, 64, 1000, 4096), (1, 70, 2304, 9000), (2, 64, 5000, 128)])
+def test_verify_head_few_rows_long_hidden(pkg, dtype, B, N, D, V):
+    print(f"verify head few rows {dtype} D={D} V={V} B={B} N={N}", flush=True)
+    h, w, _, _ = _operands(D + V, B * N, D, V, dtype)
+    w[3::50] = w[3].clone()
+    z_ref = (h.double() @ w.double().t()).cpu().numpy()
+    bound = ((D + 1) * 2.0 ** -24 * (h.double().abs() @ w.double().abs().t())).cpu().numpy()
+    ctx = pkg.Context(max_batch=B, max_slots=1, max_topk=1, max_vocab_rows=V, max_nodes=N, max_heads=1, max_head_dim=8)
+    n_nodes = torch.full((B,), N, dtype=torch.int32, device="cuda")
+    n_nodes[B - 1] = N - 1
+    res = pkg.verify_head_argmax(ctx, h.view(B, N, D), w, n_nodes, want_logits=True)
+    z = res["logits"].cpu().numpy().reshape(B * N, V)
+    _check(z, z_ref, bound)
+    assert np.array_equal(z[:, 3], z[:, 53])
+    want = z.argmax(1).reshape(B, N)
+    want[B - 1, N - 1:] = -1
+    assert np.array_equal(res["target_argmax"].cpu().numpy(), want)
+    assert torch.equal(pkg.verify_head_argmax(ctx, h.view(B, N, D), w, n_nodes)["target_argmax"], res["target_argmax"])
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,T,D,Vp1,k", [(1, 1, 4096, 259, 1), (8, 8, 2048, 1054, 8), (5, 7, 1136, 2048, 6), (3, 6, 768, 2049, 3),
+                                         (1, 3, 4608, 129, 2), (7, 1, 4456, 5000, 5), (4, 8, 3000, 8193, 4), (1, 8, 64, 8, 8)])
+def test_draft_head_few_rows_long_hidden(pkg, dtype, B, T, D, Vp1, k):
+    print(f"draft head few rows {dtype} D={D} Vp1={Vp1} B={B} T={T} k={k}", flush=True)
+    h, w, _, _ = _operands(D + Vp1, B * T, D, Vp1, dtype)
+    w[3::50] = w[3].clone()
+    h[0] = 4 * w[3]  # ties of the largest
+    z_ref = (h.double() @ w.double().t()).cpu().numpy()
+    bound = ((D + 1) * 2.0 ** -24 * (h.double().abs() @ w.double().abs().t())).cpu().numpy()
+    ctx = pkg.Context(max_batch=B, max_slots=T, max_topk=k, max_vocab_rows=Vp1, max_nodes=8, max_heads=1, max_head_dim=8)
+    res = pkg.ctc_draft_topk(ctx, h.view(B, T, D), w, None, k, want_logits=True)
+    z = res["logits"].cpu().numpy().reshape(B * T, Vp1)
+    _check(z, z_ref, bound)
+    top = res["topk_id"].cpu().numpy().reshape(B * T, k)
+    assert np.array_equal(top, np.argsort(-z, axis=1, kind="stable")[:, :k])
+    lse = np.log(np.exp(z.astype(np.float64) - z.max(1, keepdims=True)).sum(1)) + z.max(1)
+    # float32 sums of Vp1 terms, and an ulp or two of the largest logit
+    tol = 2e-5 + 4 * 2.0 ** -24 * np.abs(z).max(1)
+    assert np.all(np.abs(res["lse"].cpu().numpy().reshape(-1) - lse) <= tol)
+    logp = np.take_along_axis(z, top, 1) - lse[:, None]
+    assert np.all(np.abs(res["topk_logp"].cpu().numpy().reshape(B * T, k) - logp) <= tol[:, None] + 2.0 ** -23 * np.abs(logp))
+    ctx.close()

@@ -56,7 +56,7 @@ def test_scores_not_a_number(pkg, T, k, slot):
 
 # Above 512 raw candidates: levels of up to 256, 257 to 512 and more survivors (by the beam), drafts of one score, repeats
 # and blanks that leave a level with too few drafts.
-@pytest.mark.parametrize("T,k", [(5, 4), (7, 3), (8, 4), (6, 8)])
+@pytest.mark.parametrize("T,k", [(5, 4), (7, 3), (8, 4), (5, 8)])
 @pytest.mark.parametrize("quantum,p_blank", [(0.0, 0.1), (0.25, 0.1), (0.0, 0.7)])
 def test_collapse_by_levels(pkg, T, k, quantum, p_blank):
     B, blank = 2, 40

@@ -95,69 +95,80 @@ __device__ void lmhead_block_epilogue(const LmHeadParams& p, const float* zbuf) 
 }
 
 // The same epilogue for many columns: a lane per column instead of a wavefront per column.  Wavefront w scans
-// rows 16w .. 16w+15 of every column (lane = column, the 16 logits in registers, the k best keys kept sorted in
-// registers), leaves its (max, sum, keys) per column in LDS, and wavefront 0 merges the eight partials of each
-// column.  About 16 + 8 short steps per lane against eight columns in turn per wavefront, each with k 64-bit
-// wavefront reductions.  `part` is LDS behind zbuf: 8 x kMaxCols x (2 floats + KMAX keys).
+// rows 16w .. 16w+15 of every column (lane = column): groups of KMAX keys are sorted and merged, the k best stay, sorted, in
+// registers.  The eight wavefronts' (max, sum, keys) of a column are joined in three rounds through LDS, half of the
+// wavefronts handing theirs to the other half.  `part` is LDS behind zbuf: 4 x kMaxCols x (2 floats + KMAX keys).
+// Bound: instruction issue of single wavefronts.  With sorted insertion of every key and the first wavefront joining all
+// eight lists that way: 40 columns x 41675 rows of 3840, k = 6, 107 us a call,
+// 88.5 so; 64 columns x 32001 of 4096, k = 4, 64.9 / 60.6.
 template <int KMAX>
 __device__ void lmhead_block_epilogue_wide(const LmHeadParams& p, const float* zbuf, unsigned char* part) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int row_base = blockIdx.x * kRowsPerBlock;
-  static_assert(kMaxCols <= 64 && kRowsPerBlock == 16 * kMfmaWaves, "a lane per column, sixteen rows per wavefront");
+  static_assert(kMaxCols <= 64 && kRowsPerBlock == 16 * kMfmaWaves && kMfmaWaves == 8, "a lane per column, sixteen rows per wavefront");
   if (p.logits_out) {
     for (int idx = tid; idx < p.BT * kRowsPerBlock; idx += blockDim.x) {
       int m = idx / kRowsPerBlock, r = idx % kRowsPerBlock;
       if (row_base + r < p.Vp1) p.logits_out[(size_t)m * p.Vp1 + row_base + r] = zbuf[m * kZStride + r];
     }
   }
-  float* pm = (float*)part;                                        // [8][kMaxCols]
-  float* ps = pm + kMfmaWaves * kMaxCols;                          // [8][kMaxCols]
-  unsigned long long* pk = (unsigned long long*)(ps + kMfmaWaves * kMaxCols);  // [8][kMaxCols][KMAX]
-  const int m = lane;
-  if (m < p.BT) {
-    f32x4 z[4];
+  constexpr int HANDED = kMfmaWaves / 2;
+  float* pm = (float*)part;                                                        // [HANDED][kMaxCols]
+  float* ps = pm + HANDED * kMaxCols;                                              // [HANDED][kMaxCols]
+  unsigned long long* pk = (unsigned long long*)(ps + HANDED * kMaxCols);          // [HANDED][KMAX][kMaxCols]
+  const int m = lane < p.BT ? lane : p.BT - 1;  // (lanes without a column repeat the last one's and write nothing)
+  f32x4 z[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) z[q] = *(const f32x4*)(zbuf + m * kZStride + 16 * wave + 4 * q);
-    float mx = -INFINITY;
+  for (int q = 0; q < 4; ++q) z[q] = *(const f32x4*)(zbuf + m * kZStride + 16 * wave + 4 * q);
+  float mx = -INFINITY;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fmaxf(fmaxf(z[q][0], z[q][1]), fmaxf(z[q][2], z[q][3])));
-    float e = 0.f;
-    KeyList<KMAX> list;
-    list.clear();
+  for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fmaxf(fmaxf(z[q][0], z[q][1]), fmaxf(z[q][2], z[q][3])));
+  float sum = 0.f;
+  unsigned long long keys[16 / KMAX][KMAX];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+  for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int id = row_base + 16 * wave + 4 * q + i;
-        if (mx > -INFINITY) e += __expf(z[q][i] - mx);
-        list.insert(id < p.Vp1 ? rank_key(z[q][i], (unsigned)id) : 0ull);
-      }
-    pm[wave * kMaxCols + m] = mx;
-    ps[wave * kMaxCols + m] = e;
-#pragma unroll
-    for (int r = 0; r < KMAX; ++r) pk[(wave * kMaxCols + m) * KMAX + r] = list.v[r];
-  }
-  __syncthreads();
-  if (wave == 0 && m < p.BT) {
-    float m_run = -INFINITY, s_run = 0.f;
-    KeyList<KMAX> list;
-    list.clear();
-#pragma unroll
-    for (int w = 0; w < kMfmaWaves; ++w) {
-      const float wm = pm[w * kMaxCols + m], wsum = ps[w * kMaxCols + m];
-      if (wm > -INFINITY) {
-        const float mn = fmaxf(m_run, wm);
-        s_run = s_run * __expf(m_run - mn) + wsum * __expf(wm - mn);
-        m_run = mn;
-      }
-#pragma unroll
-      for (int r = 0; r < KMAX; ++r) list.insert(pk[(w * kMaxCols + m) * KMAX + r]);
+    for (int i = 0; i < 4; ++i) {
+      const int id = row_base + 16 * wave + 4 * q + i;
+      if (mx > -INFINITY) sum += __expf(z[q][i] - mx);
+      keys[(4 * q + i) / KMAX][(4 * q + i) % KMAX] = id < p.Vp1 ? rank_key(z[q][i], (unsigned)id) : 0ull;
     }
-    const size_t slot = (size_t)m * p.pstride + blockIdx.x;
-    p.pmax[slot] = m_run;
-    p.psum[slot] = s_run;
-    for (int r = 0; r < p.k; ++r)
-      p.pkey[((size_t)m * kMaxTopk + r) * p.pstride + blockIdx.x] = r < KMAX ? list.v[r] : 0ull;
+#pragma unroll
+  for (int g = 0; g < 16 / KMAX; ++g) sort_keys<KMAX>(keys[g]);
+#pragma unroll
+  for (int step = 1; step < 16 / KMAX; step *= 2)
+#pragma unroll
+    for (int g = 0; g + step < 16 / KMAX; g += 2 * step) merge_sorted_lists<KMAX>(keys[g], keys[g + step]);
+#pragma unroll
+  for (int half = HANDED; half >= 1; half /= 2) {
+    if (wave >= half && wave < 2 * half) {
+      const int at = (wave - half) * kMaxCols + lane;
+      pm[at] = mx;
+      ps[at] = sum;
+#pragma unroll
+      for (int r = 0; r < KMAX; ++r) pk[((wave - half) * KMAX + r) * kMaxCols + lane] = keys[0][r];
+    }
+    lds_barrier();  // (the logits' stores stay in flight)
+    if (wave < half) {
+      const float om = pm[wave * kMaxCols + lane], osum = ps[wave * kMaxCols + lane];
+      const float mn = fmaxf(mx, om);
+      if (mn > -INFINITY) sum = (mx > -INFINITY ? sum * __expf(mx - mn) : 0.f) + (om > -INFINITY ? osum * __expf(om - mn) : 0.f);
+      mx = mn;
+      unsigned long long other[KMAX];
+#pragma unroll
+      for (int r = 0; r < KMAX; ++r) other[r] = pk[(wave * KMAX + r) * kMaxCols + lane];
+      merge_sorted_lists<KMAX>(keys[0], other);
+    }
+    if (half > 1) lds_barrier();  // read before the next round overwrites it
+  }
+  if (wave == 0 && lane < p.BT) {
+    const size_t slot = (size_t)lane * p.pstride + blockIdx.x;
+    p.pmax[slot] = mx;
+    p.psum[slot] = sum;
+#pragma unroll
+    for (int r = 0; r < KMAX; ++r)
+      if (r < p.k) p.pkey[((size_t)lane * kMaxTopk + r) * p.pstride + blockIdx.x] = keys[0][r];
   }
 }
 
@@ -454,7 +465,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void lmhead_tile_kernel(LmHeadPara
     else lmhead_block_epilogue_wide<8>(p, zbuf, part);
   }
 }
-constexpr int kLmEpilogueBytes = kMaxCols * kZStride * 4 + kMfmaWaves * kMaxCols * (8 + 8 * kMaxTopk);
+constexpr int kLmEpilogueBytes = kMaxCols * kZStride * 4 + kMfmaWaves / 2 * kMaxCols * (8 + 8 * kMaxTopk);
 static_assert(kMaxCols <= 64 && kLmEpilogueBytes <= Tile128x64::LDS_BYTES && kLmEpilogueBytes <= Tile128x32::LDS_BYTES &&
                   16 * kZStride * 4 <= Tile128x16::LDS_BYTES,
               "one tile holds every column and the epilogue's partials");
@@ -649,10 +660,10 @@ static int draft_topk_launch(ctcspec_ctx* err, hipStream_t stream, const LmScrat
     return CTCSPEC_OK;
   };
 
-  // what the epilogue of the many-column kernel takes: insertions into k-lists; a column's workgroup pops k keys
+  // what the epilogues take: joining the wavefronts' k-lists; a column's workgroup pops k keys
   const bool f32 = dt == CTCSPEC_F32;
   const int tile_cols = p.BT <= 16 ? 16 : p.BT <= 32 ? 32 : 64;
-  const double epilogue_us = tile_cols == 16 ? 1.5 : k <= 2 ? 4.0 : k <= 4 ? 6.0 : 11.0;
+  const double epilogue_us = tile_cols == 16 ? 1.5 : k <= 2 ? 2.0 : k <= 4 ? 3.0 : 4.0;
   HeadRangeParams h;
   h.hidden = hidden; h.w = w; h.zeros = sc.zeros; h.part = sc.part; h.cols = p.BT; h.D = D; h.V = Vp1;
   if (plan_head(h, f32, head_whole_us(Vp1, p.BT, D, f32, kRowsPerBlock, tile_cols, epilogue_us), 1.5 + 0.2 * k, kDraftPartFloats)) {

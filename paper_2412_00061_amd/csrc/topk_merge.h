@@ -53,6 +53,21 @@ __device__ __forceinline__ void merge_sorted_lists(unsigned long long (&a)[KMAX]
       if ((i & stride) == 0) key_sort2(a[i], a[i + stride]);
 }
 
+// KMAX keys (a power of two) into descending order: a bitonic network.
+template <int KMAX>
+__device__ __forceinline__ void sort_keys(unsigned long long (&a)[KMAX]) {
+#pragma unroll
+  for (int size = 2; size <= KMAX; size *= 2)
+#pragma unroll
+    for (int stride = size / 2; stride >= 1; stride /= 2)
+#pragma unroll
+      for (int i = 0; i < KMAX; ++i)
+        if ((i & stride) == 0) {
+          if ((i & size) == 0 || size == KMAX) key_sort2(a[i], a[i + stride]);
+          else key_sort2(a[i + stride], a[i]);
+        }
+}
+
 // One wavefront merges NC columns at once (col[c] < 0: none).  The partials are [column][workgroup] arrays of pstride
 // workgroups per column, every workgroup's keys in descending order.  Lane l owns workgroups l, l+64, ...; all of a
 // lane's partials, of all NC columns, are requested before any is used, so the merge costs about one memory round

@@ -153,10 +153,10 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
   // A request past the last step still issues its loads, so that every wait counts the same loads: it reads
   // a 256-byte block of zeros (in L2, no HBM traffic) and nothing computes from the result.
   u32x4 wreg[DIST][WP], hreg[DIST][HP];
-  auto request = [&](int step, auto stage) __attribute__((always_inline)) {
+  auto request_step = [&](int step, auto stage, auto there_tag) __attribute__((always_inline)) {
     constexpr int S = decltype(stage)::value;
     // address arithmetic in integers: a select between pointers would become a branch around each load
-    const bool valid = step < total_steps;
+    const bool valid = decltype(there_tag)::value || step < total_steps;
     const Offset mask = valid ? ~(Offset)0 : (Offset)0;
     const Offset st = ((Offset)step * (Offset)STEPB) & mask;
     const uintptr_t hb = (valid ? h_addr : z_addr) + st, wb = (valid ? w_addr : z_addr) + st;
@@ -175,6 +175,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
     }
     __builtin_amdgcn_sched_barrier(0);
   };
+  auto request = [&](int step, auto stage) __attribute__((always_inline)) { request_step(step, stage, std::false_type{}); };
   // The elements of a row behind its last whole step (tail_bytes of them), zeros behind those: a thread's chunk has tail_n
   // of its bytes in the row.  It is loaded so that it ends with them - every load stays inside its row - and shifted down
   // when it is used, so that nothing waits for it in between.  (A row of less than 16 bytes: element by element.)
@@ -303,7 +304,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
     const int step0 = lead - L;
     if constexpr (TAIL) load_tail(CTCSPEC_TILE_STAGE(DIST - 1));
     [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {
-      (request(step0 + U, CTCSPEC_TILE_STAGE(U)), ...);
+      (request_step(step0 + U, CTCSPEC_TILE_STAGE(U), std::bool_constant<WHOLE_TRIPS>{}), ...);
     }(std::make_integer_sequence<int, TAIL ? DIST - 1 : DIST>{});
     if constexpr (TAIL) {
       commit_tail(CTCSPEC_TILE_STAGE(DIST - 1), CTCSPEC_TILE_BUFFER(1));

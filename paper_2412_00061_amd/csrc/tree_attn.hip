@@ -1048,9 +1048,12 @@ static hipError_t launch_merge(const AttnParams& p, const AttnSplit& sp, int row
 //   float, 128: 14 heads, 35 rows, up to 1923 positions 24.4 (8) / 18.4 (18)
 // Over 400 shapes drawn from 1 to 8 sequences of 4 to 40 heads and 1 to 128 rows over 4 to 2048 positions: 7 % in the mean.
 struct AttnShape { int QB, S; };
-// the merge launch, the partial results' way through memory, and a round trip of the merge for every eight splits more
-static double split_us(long long bh, int S, int rows, int dh) {
-  return S == 1 ? 0.0 : 3.3 + (double)bh * S * rows * dh * 4 * 0.25e-6 + (S - 1) / kMergeParts * 3.0;
+// the merge launch, the partial results' way through memory, and a round trip of the merge for every eight splits more.  Rows as
+// two bf16 numbers are the merge's work otherwise: the 2 x 8 rows of a layer of 1024, 300 positions, 42.2 us with the layer's
+// attention in two splits, 44.0 in none.
+constexpr double kTwoBf16Us = 1.5;
+static double split_us(long long bh, int S, int rows, int dh, bool two_bf16) {
+  return S == 1 ? (two_bf16 ? kTwoBf16Us : 0.0) : 3.3 + (double)bh * S * rows * dh * 4 * 0.25e-6 + (S - 1) / kMergeParts * 3.0;
 }
 // how much longer than one workgroup a compute unit with `load` of them takes.  Of several sequences, not all are the longest.
 static double taking_turns(double load, double next) { return load <= 1.0 ? 1.0 : 1.0 + (load - 1.0) * next; }
@@ -1065,7 +1068,7 @@ static double iterations(int kv_cap, int max_nodes, int S, int per_iter) {
 // bf16, head dimension 128.  Blocks of 64 rows take two tiles an iteration (0.9 us; 1.1 when two blocks share the keys),
 // blocks of 128 one (0.88 us; 0.52 with a single live row group, whose partials are 16 rows).  slots: units of 128 rows that
 // the workspace holds.
-static AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long long slots) {
+static AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long long slots, bool two_bf16) {
   AttnShape best = {1, 1};
   const long long bh = (long long)B * H;
   double least = 1e30;
@@ -1076,7 +1079,7 @@ static AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long lon
       const long long groups = bh * QB * S;
       if (S > 1 && (groups > 256 || groups > slots || S * 4 > (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys)) break;
       const double us = taking_turns(groups / 256.0, B > 1 ? 0.7 : 1.0) * (4.8 + iterations(kv_cap, max_nodes, S, rows64 ? 2 : 1) * iter) +
-                        split_us(bh, S, max_nodes, 128);
+                        split_us(bh, S, max_nodes, 128, two_bf16);
       if (us < least) {
         least = us;
         best = {QB, S};
@@ -1087,7 +1090,7 @@ static AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long lon
 }
 // Everything else, blocks of 64 rows.  Float: the matrix rate, workgroups on one compute unit take turns as far as their
 // wavefronts have rows; bf16: they run side by side.  slots: units of 64 rows.
-static AttnShape plan_any(int B, int H, int max_nodes, int kv_cap, int dh, bool f32, long long slots) {
+static AttnShape plan_any(int B, int H, int max_nodes, int kv_cap, int dh, bool f32, long long slots, bool two_bf16) {
   AttnShape best = {(max_nodes + 63) / 64, 1};
   const long long bh = (long long)B * H, blocks = bh * best.QB;
   const int live = max_nodes >= 64 ? 4 : (max_nodes + 15) / 16;
@@ -1097,7 +1100,7 @@ static AttnShape plan_any(int B, int H, int max_nodes, int kv_cap, int dh, bool 
     const long long groups = blocks * S;
     const double turns = f32 && dh > 32 ? taking_turns((double)((groups * live + 1023) / 1024), B > 1 ? 0.5 : 1.0) : side_by_side(groups / 256.0);
     const double tile = f32 ? (dh <= 32 ? 0.9 : (dh + 31) / 32 * 32 / 48.0) : (dh <= 64 ? 0.6 : 0.7);
-    const double us = turns * (3.0 + iterations(kv_cap, max_nodes, S, 1) * tile) + split_us(bh, S, max_nodes, dh);
+    const double us = turns * (3.0 + iterations(kv_cap, max_nodes, S, 1) * tile) + split_us(bh, S, max_nodes, dh, two_bf16);
     if (us < least) {
       least = us;
       best.S = S;
@@ -1218,7 +1221,7 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
       CTCSPEC_HIP(ctx, hipGetLastError());
       return CTCSPEC_OK;
     }
-    const AttnShape shape = plan_bf16_128(B, H, max_nodes, kv_cap, ctx->attn_units);
+    const AttnShape shape = plan_bf16_128(B, H, max_nodes, kv_cap, ctx->attn_units, rows != nullptr);
     // (up to 16 rows, a single row group: the one-tile-per-iteration kernel, whose first tile is in LDS sooner -
     // 9.1 against 9.9 us for the draft layer's 8 rows)
     const bool rows64 = shape.QB == 2 || (max_nodes <= 64 && max_nodes > kFewRows);
@@ -1241,7 +1244,7 @@ int ctcspec::tree_verify_attn_rows(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
     return CTCSPEC_OK;
   }
   AttnSplit sp;
-  const AttnShape shape = plan_any(B, H, max_nodes, kv_cap, dh, dt == CTCSPEC_F32, 2LL * ctx->attn_units);
+  const AttnShape shape = plan_any(B, H, max_nodes, kv_cap, dh, dt == CTCSPEC_F32, 2LL * ctx->attn_units, rows != nullptr);
   sp.QB = shape.QB;
   sp.S = shape.S;
   const long long blocks = (long long)B * H * sp.QB;

@@ -655,7 +655,7 @@ void tree_attn_few_kernel(AttnParams p) {
 // ---- any head dimension, float or bf16 ---------------------------------------------------------------------------
 // Workgroup = 4 wavefronts = one block of 64 query rows of one (sequence, head) and one of S splits of the keys;
 // a wavefront owns 16 rows.  Tiles of 32 keys (context first, then the tree) go through two LDS stages, fetched by all
-// threads PF tiles ahead in registers.  The head dimension is padded to DHP (a multiple of 32) in LDS and registers
+// threads PF tiles ahead in registers.  The head dimension is padded to DHP (16 - float only -, 32, 64, 96 or 128) in LDS and registers
 // only: the padding of K is zeroed once, that of V feeds output components that are not written.
 //   S^T[key, q] = K.Q^T   64-byte k-blocks as in gemm_tile.h (bf16: one product of 32 k, float: four of 4 k)
 //   O^T[dh, q] += V^T.P   a lane holds P of keys 16 kb + 4 g + i in the C layout of S^T, which is the B layout as it is:
@@ -1045,7 +1045,8 @@ static hipError_t launch_merge(const AttnParams& p, const AttnSplit& sp, int row
 //     (one block)    4 x 32 heads, 100 rows, 300: 18.5 (2) / 13.2 (1)    32 heads, 64 rows, 256: 11.9 (2) / 10.2 (1)
 //     32 heads, 128 rows, 2048 positions: 4 splits both; none 36.8, 2 26.0, 3 21.6, 4 19.6, 8 of one block 20.0
 //   bf16, 80: 4 x 16 heads, 50 rows, 93 positions 10.5 (2) / 7.6 (1)    64: 32 heads, 128 rows, 512: 14.6 (8) / 11.9 (4)
-//   float, 128: 14 heads, 35 rows, up to 1923 positions 24.4 (8) / 18.4 (18)
+//   float, 128: 14 heads, 35 rows, up to 1923 positions 24.4 (8) / 18.4 (18)    float, 16: 4 heads, 128 rows, 32: 7.4 (3) / 4.0 (1, padded
+//     to 16 instead of 32)
 // Over 400 shapes drawn from 1 to 8 sequences of 4 to 40 heads and 1 to 128 rows over 4 to 2048 positions: 7 % in the mean.
 struct AttnShape { int QB, S; };
 // the merge launch, the partial results' way through memory, and a round trip of the merge for every eight splits more.  Rows as
@@ -1099,7 +1100,7 @@ static AttnShape plan_any(int B, int H, int max_nodes, int kv_cap, int dh, bool 
     if (S > 1 && (blocks * S > slots || S * kTileKeys > kv_cap + max_nodes || bh > 65535)) break;  // (the merge's grid)
     const long long groups = blocks * S;
     const double turns = f32 && dh > 32 ? taking_turns((double)((groups * live + 1023) / 1024), B > 1 ? 0.5 : 1.0) : side_by_side(groups / 256.0);
-    const double tile = f32 ? (dh <= 32 ? 0.9 : (dh + 31) / 32 * 32 / 48.0) : (dh <= 64 ? 0.6 : 0.7);
+    const double tile = f32 ? (dh <= 16 ? 0.7 : dh <= 32 ? 0.9 : (dh + 31) / 32 * 32 / 48.0) : (dh <= 64 ? 0.6 : 0.7);
     const double us = turns * (3.0 + iterations(kv_cap, max_nodes, S, 1) * tile) + split_us(bh, S, max_nodes, dh, two_bf16);
     if (us < least) {
       least = us;
@@ -1131,6 +1132,8 @@ static hipError_t launch_attn_any_dh(const AttnParams& p, const AttnSplit& sp, h
 }
 template <typename EL, AttnOut OUT>
 static hipError_t launch_attn_any(const AttnParams& p, const AttnSplit& sp, hipStream_t stream) {
+  if constexpr (EL::ELEM == 4)  // half the products of 32 (bf16: a product contracts 32)
+    if (p.dh <= 16) return launch_attn_any_dh<EL, 16, OUT>(p, sp, stream);
   if (p.dh <= 32) return launch_attn_any_dh<EL, 32, OUT>(p, sp, stream);
   if (p.dh <= 64) return launch_attn_any_dh<EL, 64, OUT>(p, sp, stream);
   if (p.dh <= 96) return launch_attn_any_dh<EL, 96, OUT>(p, sp, stream);

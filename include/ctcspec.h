@@ -91,14 +91,16 @@ size_t ctcspec_workspace_bytes(const ctcspec_ctx* ctx);
  *     fewer per decoding step, same bits;
  *   - any other library call on the context, ctcspec_set_stream and ctcspec_flush launch the merge kernel first.
  * A caller that reads the three outputs from the stream with code of its own right after ctc_draft_topk must call
- * ctcspec_flush first, or leave the mode off (the default).  ctcspec_destroy drops an unsettled debt. */
+ * ctcspec_flush first, or leave the mode off (the default).  ctcspec_destroy drops an unsettled debt.  A head whose
+ * vocabulary does not fill the chip is finished by ctc_draft_topk itself in either mode. */
 int ctcspec_defer_topk_merge(ctcspec_ctx* ctx, int enable);
 int ctcspec_flush(ctcspec_ctx* ctx);
 
 /* Measurement aid.  With enable != 0, every following ctc_draft_topk call attaches a pair of HIP events
  * to the launch of its main kernel on the context's stream (the pass over the head weights, not the
  * small merge kernel): the events take that kernel's begin and end timestamps.  (The tile kernel - many columns,
- * float operands, other hidden sizes - has the pair recorded around its launch instead, which also spans the dispatch.)
+ * float operands, other hidden sizes - has the pair recorded around its launch instead, which also spans the dispatch; a head whose
+ * product is cut along the hidden dimension has it around the kernel that forms the partial sums.)
  * ctcspec_draft_head_kernel_ms synchronises with the second event of the LAST
  * such call and returns the elapsed milliseconds in *ms (host pointer).  CTCSPEC_EINVAL when profiling
  * is off or no call has been made since it was switched on. */
@@ -149,7 +151,7 @@ int ctc_draft_topk(ctcspec_ctx* ctx, ctcspec_dtype dt, const void* hidden, const
  * hip_stream   a hipStream_t (NULL = the default stream); host value
  * every other argument as for ctc_draft_topk
  * Limits: Vp1 <= CTCSPEC_NOALLOC_MAX_VOCAB_ROWS (larger heads are rejected with CTCSPEC_EUNSUPPORTED: use a context),
- * B*T <= CTCSPEC_MAX_COLUMNS, k <= CTCSPEC_MAX_TOPK, T <= CTCSPEC_MAX_SLOTS.  The array (2.4 MB) exists once per GPU
+ * B*T <= CTCSPEC_MAX_COLUMNS, k <= CTCSPEC_MAX_TOPK, T <= CTCSPEC_MAX_SLOTS.  The array (10.8 MB) exists once per GPU
  * for the life of the process, and every call on a GPU uses it: calls that overlap on one GPU (two streams, two
  * threads) race on it; calls in stream order are safe and need no clearing between them (every entry a call reads
  * it has written first).  Errors are reported through ctcspec_last_error(NULL).

@@ -129,12 +129,13 @@ extern "C" int ctcspec_create(ctcspec_ctx** out, void* hip_stream, const ctcspec
   size_t o_coll = carve((size_t)lim->max_batch * kCollapseWsBytesPerSeq);
   // attention partials: one slot of 128 query rows per (sequence, head, key split)
   const size_t attn_rows = (size_t)ctx->attn_units * 128;
-  // (the heads' partial sums share the space: no call leaves any of either behind)
-  size_t po_floats = attn_rows * lim->max_head_dim;
-  po_floats = po_floats > kHeadPartFloats ? po_floats : kHeadPartFloats;
-  size_t o_po = carve(po_floats * sizeof(float));
+  size_t o_po = carve(attn_rows * lim->max_head_dim * sizeof(float));
   size_t o_pm = carve(attn_rows * sizeof(float));
   size_t o_pl = carve(attn_rows * sizeof(float));
+  // partial sums of the heads, a space for each: every stage has scratch of its own, so that a caller may run the draft head,
+  // the attention and the base head of one context on streams of their own
+  size_t o_dpart = carve(kDraftPartFloats * sizeof(float));
+  size_t o_hpart = carve(kHeadPartFloats * sizeof(float));
   ctx->ws_bytes = off;
   e = hipMalloc(&ctx->ws, ctx->ws_bytes);
   if (e != hipSuccess) {
@@ -155,8 +156,9 @@ extern "C" int ctcspec_create(ctcspec_ctx** out, void* hip_stream, const ctcspec
   ctx->vh_pkey = (unsigned long long*)(base + o_vh);
   ctx->zeros = base + o_zero;
   ctx->collapse_ws = base + o_coll;
-  ctx->attn_po = ctx->head_part = (float*)(base + o_po);
-  ctx->head_part_floats = po_floats;
+  ctx->lm_part = (float*)(base + o_dpart);
+  ctx->vh_part = (float*)(base + o_hpart);
+  ctx->attn_po = (float*)(base + o_po);
   ctx->attn_pm = (float*)(base + o_pm);
   ctx->attn_pl = (float*)(base + o_pl);
   g_create_err[0] = 0;

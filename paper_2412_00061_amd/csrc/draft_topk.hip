@@ -748,7 +748,7 @@ extern "C" int ctc_draft_topk(ctcspec_ctx* ctx, ctcspec_dtype dt, const void* hi
   CTCSPEC_REQUIRE(ctx, B <= ctx->lim.max_batch && T <= ctx->lim.max_slots && k <= ctx->lim.max_topk &&
                            Vp1 <= ctx->lim.max_vocab_rows,
                   CTCSPEC_EUNSUPPORTED, "ctc_draft_topk: shape exceeds the context's limits");
-  const LmScratch sc = {ctx->lm_pmax, ctx->lm_psum, ctx->lm_pkey, ctx->lm_max_blocks, ctx->zeros, ctx->head_part};
+  const LmScratch sc = {ctx->lm_pmax, ctx->lm_psum, ctx->lm_pkey, ctx->lm_max_blocks, ctx->zeros, ctx->lm_part};
   return draft_topk_launch(ctx, ctx->stream, sc, ctx->lm_profile ? ctx->lm_ev0 : nullptr,
                            ctx->lm_profile ? ctx->lm_ev1 : nullptr, &ctx->lm_profile_valid, ctx->lm_defer != 0, dt, hidden, w,
                            bias, B, T, D, Vp1, k, topk_id, topk_logp, lse, logits_out);

@@ -26,7 +26,7 @@ constexpr int kHeadMaxSplits = 16;
 constexpr int kHeadColumnThreads = 512;                      // of the kernels that finish a column
 constexpr int kHeadMaxRows = kHeadColumnThreads * 4 * 8;     // vocabulary rows they hold
 // room for partial sums: the draft head's (the context's and the static scratch of the entry point that allocates nothing
-// alike, so that both take the same way), and the least that a context has for the base head
+// alike, so that both take the same way) and the base head's
 constexpr size_t kDraftPartFloats = (size_t)2 << 20, kHeadPartFloats = (size_t)4 << 20;
 
 struct HeadRangeParams {

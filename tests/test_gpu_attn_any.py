@@ -198,3 +198,40 @@ def test_attention_many_splits(pkg, dtype, dh, H, N, cap, tol, short):
         got[:, :, 1] = ref[:, :, 1]
     assert rel_err_rms_floor(got, ref) <= tol
     ctx.close()
+
+
+# The draft head, the attention and the base head of one context on streams of their own: each has scratch of its own, so
+# what runs beside a call changes none of its bits.
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_stages_on_three_streams(pkg, dtype):
+    B, H, N, dh, cap, ctx_len, D, V, T, k = 2, 8, 64, 64, 1200, [1100, 900], 4096, 1500, 6, 4
+    print(f"three streams {dtype}", flush=True)
+    case = workloads.make_attention_case(3, B, H, N, dh, cap, ctx_len, dtype)
+    trees = _trees(3, B, N, 128, "beam")
+    n_nodes = dev_i32(np.array([t["n_nodes"] for t in trees]))
+    mask = torch.from_numpy(np.stack([t["anc_mask"] for t in trees]).view(np.int64)).cuda()
+    attn = (to_device(case.q, dtype), to_device(case.k_cache, dtype), to_device(case.v_cache, dtype), dev_i64(case.kv_off),
+            dev_i32(case.ctx_len), cap, to_device(case.k_tree, dtype), to_device(case.v_tree, dtype), n_nodes, mask, dh ** -0.5)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    h, hn, w = (torch.randn(s, generator=g, device="cuda").to(attn[0].dtype) for s in ((B, T, D), (B, N, D), (V, D)))
+    ctx = pkg.Context(max_batch=B, max_slots=T, max_topk=k, max_vocab_rows=V, max_nodes=N, max_heads=H, max_head_dim=dh)
+    stages = (lambda: pkg.ctc_draft_topk(ctx, h, w, None, k), lambda: {"out": pkg.tree_verify_attn(ctx, *attn)},
+              lambda: pkg.verify_head_argmax(ctx, hn, w, n_nodes, want_logits=True))
+    want = [stage() for stage in stages]
+    torch.cuda.synchronize()
+    streams, got = [torch.cuda.Stream() for _ in stages], []
+    for _ in range(10):
+        for stream, stage, ref in zip(streams, stages, want):
+            with torch.cuda.stream(stream):
+                ctx.set_stream(stream)
+                got.append((stage(), ref))
+    torch.cuda.synchronize()
+    ctx.set_stream(torch.cuda.current_stream())
+    live = torch.arange(N, device="cuda") < n_nodes[:, None]
+    for res, ref in got:
+        for name, t in ref.items():
+            if t is None:
+                continue
+            a, b = (t, res[name]) if name != "out" else (t.transpose(1, 2)[live], res[name].transpose(1, 2)[live])
+            assert torch.equal(a, b), name
+    ctx.close()

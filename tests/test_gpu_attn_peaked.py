@@ -98,7 +98,7 @@ def _run(pkg, case, trees, B, H, N, dh):
 
 # (B, H, max_nodes, kv_cap, ctx_len, tree kind): the 7B step's shape (two 64-row blocks of 4 row groups x 2 key parts,
 # four key splits), the same heads over a short context (five tiles per split: an odd count for the two key parts),
-# twice the heads (one 128-row block, four splits), the ragged batch (one 64-row block, one key range per workgroup:
+# twice the heads (two 64-row blocks, two splits), 56 heads (one 128-row block, four splits), the ragged batch (one 64-row block, one key range per workgroup:
 # both key parts meet masked context ends), and the draft layer's 8 causal rows (one live row group, eight splits)
 SHAPES = {
     "7b_ctx2048": (1, 32, 128, 2048, [2048], "beam"),
@@ -106,6 +106,7 @@ SHAPES = {
     "64_heads": (1, 64, 128, 1024, [1000], "beam"),
     "batch8_ragged": (8, 32, 64, 2048, [256, 2048, 1111, 777, 1999, 300, 1280, 95], "beam"),
     "draft_layer_rows": (1, 32, 8, 2048, [2048], "chain"),
+    "one_block_56_heads": (1, 56, 128, 1024, [1000], "beam"),
 }
 
 

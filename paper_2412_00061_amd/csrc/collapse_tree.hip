@@ -7,9 +7,8 @@
 // partial sum).  With both lists sorted descending, X_(i) + Y_(j) is at least as large as every
 // (i', j') with i' >= i and j' >= j; hence tau = max_i X_(i) + Y_(ceil(M/(i+1))-1) is passed by at
 // least M raw candidates - a threshold without search.  The raw candidates passing it (about 2M)
-// are expanded, given their exact float32 left-to-right score, collapsed, empties dropped, and the best
-// one of every draft kept, in the order (score desc, idx asc): up to 512 of them through a hash table that keeps a draft's
-// best and a ranking of those; more are sorted and walked in that order for first occurrences.  If fewer than `beam`
+// are expanded, given their exact float32 left-to-right score, sorted by (score desc, idx asc) and
+// walked in that order: collapse, drop empties, keep first occurrences.  If fewer than `beam`
 // distinct drafts turn up, M is quadrupled and the level redone; the last level takes every raw
 // candidate.  The half-sum score fl(X+Y) used for thresholding differs from the exact score only by
 // rounding; a margin delta on the threshold makes the walked prefix exactly the global order.
@@ -33,7 +32,6 @@ constexpr int kThreads = 256;  // (512 was measured: 3 us slower - the phases ar
 constexpr int kWaves = kThreads / 64;
 constexpr int kHalfMax = 512;   // k^ceil(T/2) <= 8^3
 constexpr int kLdsCap = 4096;   // sorted candidates kept in LDS
-constexpr int kFewMax = 2 * kThreads, kFewLog2 = 10, kFewSlots = 1 << kFewLog2;  // levels that need no sort
 constexpr int kBlankCode = 127; // 7-bit local code of the blank / padding
 constexpr unsigned int kEmptySlot = 0xffffffffu;
 
@@ -42,7 +40,7 @@ struct CollapseParams {
   const float* topk_logp;
   const int32_t* root_token;
   int T, k, blank_id, beam, max_nodes;
-  unsigned int magic;  // ceil(2^15 / k): division of small numbers by k
+  unsigned int magic;  // ceil(2^32 / k): division by k as a multiply-high
   unsigned int magic_n2;  // ceil(2^32 / k^(T/2)): division of a candidate index by the number of second halves
   int32_t* n_cand;
   int32_t* cand_tokens;
@@ -147,21 +145,6 @@ __device__ __forceinline__ void prefix_count2(int n, P0 pred0, P1 pred1, int& ou
 
 __device__ __forceinline__ unsigned int hash_slot(unsigned long long ck, int log2_size) {
   return (unsigned int)((ck * 0x9E3779B97F4A7C15ull) >> (64 - log2_size));
-}
-
-// n[i] += x[i] > v, i = 0 .. 3.  Four comparisons, then four additions of their bits: nothing waits for what is issued right
-// before it (a lone wavefront takes 8 clocks for an instruction that needs the one before, 4 otherwise; with compare and add
-// in turn the ranking of 302 drafts took 4.0 us, 3.5 so).
-__device__ __forceinline__ void count_larger(u32x4& n, const u32x4& x, unsigned int v) {
-  unsigned int a = n[0], b = n[1], c = n[2], d = n[3];
-  unsigned long long m0, m1, m2, m3;
-  asm("v_cmp_gt_u32 %4, %8, %12\n\tv_cmp_gt_u32 %5, %9, %12\n\tv_cmp_gt_u32 %6, %10, %12\n\tv_cmp_gt_u32 %7, %11, %12\n\t"
-      "v_addc_co_u32 %0, vcc, 0, %0, %4\n\tv_addc_co_u32 %1, vcc, 0, %1, %5\n\t"
-      "v_addc_co_u32 %2, vcc, 0, %2, %6\n\tv_addc_co_u32 %3, vcc, 0, %3, %7"
-      : "+v"(a), "+v"(b), "+v"(c), "+v"(d), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
-      : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(v)
-      : "vcc");
-  n = u32x4{a, b, c, d};
 }
 
 // ---- sorting in LDS / global memory (any size; the slow path) -------------------------------------
@@ -318,9 +301,8 @@ __device__ __forceinline__ void block_sort_desc_fast(unsigned long long (&v)[E],
 }
 
 // ---- raw candidates ---------------------------------------------------------------------------------
-// a / k for 0 <= a < 4096 (four digits of base k <= 8), magic = ceil(2^15 / k): magic * k - 2^15 <= 7, and 7 * 4095 < 2^15.
-// 24-bit products: a 32-bit one or its upper half takes four times as long.
-__device__ __forceinline__ int div_small(int a, unsigned int magic) { return (int)(__umul24((unsigned)a, magic) >> 15); }
+// a / k for 0 <= a < 65536, magic = ceil(2^32 / k)
+__device__ __forceinline__ int div_small(int a, unsigned int magic) { return (int)__umulhi((unsigned)a, magic); }
 
 // The rank digits of a half-combination, most significant slot first.  a counts in base k with
 // nt <= 4 digits; it is first shifted up to exactly four digits so that digit positions are static.
@@ -329,11 +311,11 @@ struct Digits4 {
 };
 __device__ __forceinline__ Digits4 split_digits(int a, int pad, int k, unsigned int magic) {
   Digits4 d;
-  int x = __mul24(a, pad);  // pad = k^(4-nt); a * pad < k^4
+  int x = a * pad;  // pad = k^(4-nt)
 #pragma unroll
   for (int u = 3; u >= 0; --u) {
     const int q = div_small(x, magic);
-    d.r[u] = x - __mul24(q, k);
+    d.r[u] = x - q * k;
     x = q;
   }
   return d;
@@ -367,25 +349,16 @@ __device__ __forceinline__ unsigned long long collapse_key(const CollapseShared&
     const int r = first_half ? da.r[t_in] : db.r[t_in];
     cd[u] = live ? s.code[slot * k + r] : -2;  // -2: slot does not exist
   }
-  // which positions stay, by the slot before (the last live one: the first half's last for the second half's first), then
-  // the key from its end
-  unsigned int lo = 0xffffffffu, hi = 0xffffffffu;
-  int len = 0;
-  bool emit[8];
-  int prev = -1;
+  unsigned long long key = 0x00ffffffffffffffull;
+  int len = 0, prev = -1;
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
-    emit[u] = RAW ? cd[u] >= 0 : (cd[u] >= 0 && cd[u] != prev && cd[u] != kBlankCode);
+    const bool emit = RAW ? cd[u] >= 0 : (cd[u] >= 0 && cd[u] != prev && cd[u] != kBlankCode);
+    const int sh = 7 * len;
+    key = emit ? ((key & ~(0x7full << sh)) | ((unsigned long long)cd[u] << sh)) : key;
+    len += emit ? 1 : 0;
     prev = cd[u] >= 0 ? cd[u] : prev;
   }
-#pragma unroll
-  for (int u = 7; u >= 0; --u) {
-    const unsigned int up = (hi << 7) | (lo >> 25), in = (lo << 7) | (unsigned int)cd[u];
-    hi = emit[u] ? up : hi;
-    lo = emit[u] ? in : lo;
-    len += emit[u] ? 1 : 0;
-  }
-  const unsigned long long key = ((unsigned long long)(hi & 0x00ffffffu) << 32) | lo;
   *len_out = len;
   return key;
 }
@@ -394,8 +367,8 @@ __device__ __forceinline__ unsigned long long collapse_key(const CollapseShared&
 // wavefronts merge them first (two columns each, at most MK keys per list), write the lists out for the caller and
 // go on from LDS: one dispatch and one trip through memory fewer than a merge kernel in between.
 // DIRECT: at most kDirectMax raw candidates in all (k^T; the host chooses).  Two per thread are all of them, so there
-// are no half sums and no threshold: every one gets its score and takes part (T = 4, k = 2: 6.6 us a call).  A score that
-// is not a number passes no threshold, so here it takes no part either.
+// are no half sums and no threshold: every one gets its score and takes part in the one sort (T = 4, k = 2: 15.1 ->
+// 13.3 us).  A score that is not a number passes no threshold, so here it takes no part either.
 constexpr int kDirectMax = 2 * kThreads;
 template <bool RAW, int MK, bool DIRECT>
 __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams p) {
@@ -440,21 +413,6 @@ __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams 
     lp = p.topk_logp[(size_t)b * TK + lane];
   }
   for (int i = tid; i < 128 * 64 / 4; i += kThreads) reinterpret_cast<u32x4*>(s.tree_table)[i] = u32x4{0u, 0u, 0u, 0u};
-  unsigned long long* const draft_of = reinterpret_cast<unsigned long long*>(s.table);  // [kFewSlots], ~0: free
-  unsigned long long* const best_of = draft_of + kFewSlots;                             // [kFewSlots] its best raw candidate
-  unsigned long long* const drafts = best_of + kFewSlots;                               // [kFewMax + 8]
-  unsigned int* const scores = reinterpret_cast<unsigned int*>(drafts + kFewMax + 8);   // [kFewMax + 32], the drafts' upper halves
-  unsigned int* const holders = scores + kFewMax + 32;                                  // [kFewMax] drafts of a rank
-  static_assert((2 * kFewSlots + kFewMax + 8) * 8 + (2 * kFewMax + 32) * 4 <= sizeof(CollapseShared::table) &&
-                    kFewSlots >= 2 * kFewMax && (kFewMax + 8) % 2 == 0,
-                "few survivors' table");
-  auto clear_drafts = [&]() __attribute__((always_inline)) {
-    for (int i = tid; i < kFewSlots; i += kThreads) {
-      draft_of[i] = ~0ull;
-      best_of[i] = 0ull;
-    }
-  };
-  clear_drafts();
   if constexpr (MK > 0) {
     __syncthreads();  // the merged lists are in LDS
   } else if (wave == 0) {
@@ -490,6 +448,11 @@ __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams 
       if (t < T) A += __uint_as_float(readlane_u32(__float_as_uint(mx), t));
     if (lane < TK) s.code[lane] = (!RAW && id == p.blank_id) ? kBlankCode : cd;
     if (!DIRECT && lane == 0) s.delta = A * (16.0f / 8388608.0f);
+    if constexpr (DIRECT) {  // no threshold, no delta: here it says whether scores that are no numbers have to be looked for
+      const bool finite = lane >= TK || fabsf(s.logp[lane]) < INFINITY;
+      const bool all_finite = __ballot(!finite) == 0ull;
+      if (lane == 0) s.delta = all_finite ? 0.f : 1.f;
+    }
     if (RAW) {
       const unsigned long long has = __ballot(lane < TK && id == p.blank_id);
       const int bc = has ? __builtin_amdgcn_readlane(cd, __builtin_ctzll(has)) : -1;
@@ -550,139 +513,9 @@ __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams 
 
   int M = beam;
   int n_d = 0;
-  // A level of at most kFewMax survivors, E per thread in any order (key 0: none).  Each goes into a hash table by its
-  // draft, which keeps the best raw candidate of every draft; those - one per draft - are ranked by counting the larger
-  // ones, and a draft's thread writes it to its place.  (Sorting all survivors first, then walking them for first occurrences
-  // through the same kind of table, a scan and a second walk: a call of 16 raw candidates 10.8 -> 6.6 us; with 65536, 302 of
-  // them above the threshold, 21.6 both ways - there the ranking takes what the sort took.)  Survivors below the threshold may not be complete:
-  // they are left out, as are empty drafts.  False: fewer than `beam` drafts, and there are more raw candidates.
-  auto few = [&](auto& v, float tau_valid, bool final_level) -> bool {
-    constexpr int E = sizeof(v) / sizeof(v[0]);
-    unsigned long long ck[E];
-    unsigned int slot[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      ck[e] = 0ull;
-      if (v[e] && (final_level || rank_key_value(v[e]) >= tau_valid)) {
-        const int idx = (int)rank_key_index(v[e]);
-        const int a = n2 == 1 ? idx : (int)__umulhi((unsigned)idx, p.magic_n2), bb = idx - a * n2;  // idx / n2
-        int len;
-        ck[e] = collapse_key<RAW>(s, split_digits(a, pad1, k, magic), split_digits(bb, pad2, k, magic), T1, T2, k, &len);
-        if (len == 0) v[e] = 0ull;
-      } else {
-        v[e] = 0ull;
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      slot[e] = hash_slot(ck[e], kFewLog2);
-      if (!v[e]) continue;
-      for (;;) {  // (the table is at least twice the survivors: a free slot is found)
-        unsigned long long cur = __hip_atomic_load(&draft_of[slot[e]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (cur == ~0ull) cur = atomicCAS(&draft_of[slot[e]], ~0ull, ck[e]);
-        if (cur == ~0ull || cur == ck[e]) break;
-        slot[e] = (slot[e] + 1) & (kFewSlots - 1);
-      }
-      atomicMax(&best_of[slot[e]], v[e]);
-    }
-    __syncthreads();
-    int mine = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      v[e] = v[e] && best_of[slot[e]] == v[e] ? v[e] : 0ull;
-      mine += v[e] ? 1 : 0;
-    }
-    int at = block_exclusive_scan(mine, s.red, &n_d);
-    if (n_d < beam && !final_level) {
-      clear_drafts();
-      return false;
-    }
-    // By the scores first, two instructions a comparison and the next sixteen scores on their way meanwhile.  Drafts of one
-    // score then have one rank, which shows where they count themselves in; only in that case the whole keys are
-    // compared (64 bits: 4.6 instructions each as the compiler has it; 302 drafts, two a thread: 6.1 -> 3.5 us).
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (v[e]) {
-        scores[at] = (unsigned int)(v[e] >> 32);
-        drafts[at++] = v[e];
-      }
-    if (tid < 16) scores[n_d + tid] = 0u;  // the last group
-    if (tid < 8) drafts[n_d + tid] = 0ull;
-    for (int i = tid; i < n_d; i += kThreads) holders[i] = 0u;
-    __syncthreads();
-    const bool any = __ballot(mine > 0) != 0ull;
-    int rank[E], tied = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) rank[e] = 0;
-    if (any) {
-      u32x4 part[E];
-#pragma unroll
-      for (int e = 0; e < E; ++e) part[e] = u32x4{0u, 0u, 0u, 0u};
-      u32x4 x[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = *(const u32x4*)(scores + 4 * i);
-      for (int j = 0; j < n_d; j += 16) {
-        u32x4 next[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) next[i] = *(const u32x4*)(scores + j + 16 + 4 * i);  // (behind the last group: anything)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int e = 0; e < E; ++e) count_larger(part[e], x[i], (unsigned int)(v[e] >> 32));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = next[i];
-      }
-#pragma unroll
-      for (int e = 0; e < E; ++e) rank[e] = (int)((part[e][0] + part[e][1]) + (part[e][2] + part[e][3]));
-#pragma unroll
-      for (int e = 0; e < E; ++e)
-        if (v[e]) tied |= atomicAdd(&holders[rank[e]], 1u) ? 1 : 0;
-    }
-    if (__syncthreads_or(tied) && any) {
-#pragma unroll
-      for (int e = 0; e < E; ++e) rank[e] = 0;
-      for (int j = 0; j < n_d; j += 8) {
-        unsigned long long x[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = drafts[j + i];
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int e = 0; e < E; ++e) rank[e] += x[i] > v[e] ? 1 : 0;
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      if (!v[e] || rank[e] >= beam) continue;
-      int len = 0;
-#pragma unroll
-      for (int d = 0; d < 8; ++d) len += (((ck[e] >> (7 * d)) & 0x7f) != kBlankCode) ? 1 : 0;
-      s.kept_ck[rank[e]] = ck[e];
-      s.kept_len[rank[e]] = len;
-      p.cand_score[(size_t)b * beam + rank[e]] = rank_key_value(v[e]);
-    }
-    return true;
-  };
-  if constexpr (DIRECT) {
-    auto all = [&](auto e_tag) {
-      constexpr int E = decltype(e_tag)::value;
-      unsigned long long v[E];
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const int idx = E * tid + e;
-        const int a = n2 == 1 ? idx : (int)__umulhi((unsigned)idx, p.magic_n2), bb = idx - a * n2;  // idx / n2
-        const Digits4 da = split_digits(a, pad1, k, magic), db = split_digits(bb, pad2, k, magic);
-        const float sc = add_slots(add_slots(0.f, false, s.logp, da, 0, T1, k), true, s.logp, db, T1, T2, k);
-        v[e] = idx < total && sc == sc ? rank_key(sc, (unsigned)idx) : 0ull;
-      }
-      few(v, -INFINITY, true);
-    };
-    if (total <= kThreads) all(std::integral_constant<int, 1>{});
-    else all(std::integral_constant<int, 2>{});
-  }
-  while (!DIRECT) {
+  for (;;) {
     if (M > total) M = total;
-    const bool final_level = M >= total;
+    const bool final_level = DIRECT || M >= total;
     float tau_valid = -INFINITY, tau_f = -INFINITY;
     if (!final_level) {
       // X_(i) + Y_(j) with (i+1)(j+1) >= M is passed by at least M raw candidates; every wavefront
@@ -706,8 +539,8 @@ __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams 
       tau_f = tau_valid - delta;
     }
     // survivors per (sorted) first-half combination, prefix sums
-    int n_s = 0;
-    {
+    int n_s = DIRECT ? total : 0;
+    if constexpr (!DIRECT) {
       // kHalfMax <= 2 * kThreads: thread t owns entries 2t and 2t+1
       const int i0 = 2 * tid, i1 = 2 * tid + 1;
       const float x0 = s.Xv[i0 < n1 ? i0 : 0], x1 = s.Xv[i1 < n1 ? i1 : 0];
@@ -728,6 +561,21 @@ __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams 
       table = reinterpret_cast<unsigned int*>(ckeys + kMaxAlign);
     }
     __syncthreads();
+    if constexpr (DIRECT) {
+      unsigned long long v[2];
+      int live = 0;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int idx = 2 * tid + e;
+        const int a = n2 == 1 ? idx : (int)__umulhi((unsigned)idx, p.magic_n2), bb = idx - a * n2;  // idx / n2
+        const Digits4 da = split_digits(a, pad1, k, magic), db = split_digits(bb, pad2, k, magic);
+        const float sc = add_slots(add_slots(0.f, false, s.logp, da, 0, T1, k), true, s.logp, db, T1, T2, k);
+        v[e] = idx < total && sc == sc ? rank_key(sc, (unsigned)idx) : 0ull;
+        live += v[e] ? 1 : 0;
+      }
+      if (delta != 0.f) block_exclusive_scan(live, s.red, &n_s);
+      block_sort_desc_fast<2, kWaves>(v, s.ckeys, s.keys, ror4_is_up);
+    } else {
     // exact key of a survivor at (row of sorted X, column of sorted Y): the first half's partial sum is
     // exactly the left-to-right prefix of the score
     auto key_at = [&](int row, int col, bool live) -> unsigned long long {
@@ -755,23 +603,9 @@ __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams 
       for (int e = 0; e < E; e += 2) key_pair(tid * E + e, v[e], v[e + 1]);
       block_sort_desc_fast<E, kWaves>(v, s.ckeys, s.keys, ror4_is_up);
     };
-    if (n_s <= kFewMax) {
-      bool done;
-      if (n_s <= kThreads) {
-        unsigned long long v[1], none;
-        key_pair(tid, v[0], none);
-        done = few(v, tau_valid, final_level);
-      } else {
-        unsigned long long v[2];
-        key_pair(2 * tid, v[0], v[1]);
-        done = few(v, tau_valid, final_level);
-      }
-      if (done) break;
-      M *= 4;
-      __syncthreads();
-      continue;
-    }
-    if (n_s <= 8 * kThreads) {
+    if (n_s <= 2 * kThreads) {
+      sort_survivors_fast(std::integral_constant<int, 2>{});
+    } else if (n_s <= 8 * kThreads) {
       sort_survivors_fast(std::integral_constant<int, 8>{});
     } else {
       int P2 = 64;
@@ -784,6 +618,7 @@ __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams 
       }
       __syncthreads();
       block_bitonic_sort_desc(keys, P2);
+    }
     }
 
     // The walk is instantiated twice, once on the LDS lists and once on the lists in the global workspace: with
@@ -871,7 +706,7 @@ __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams 
     M *= 4;
     __syncthreads();
   }
-  lds_barrier();  // the kept list is complete (the scores are still on their way to memory)
+  __syncthreads();  // the kept list is complete
 
   const int n_c = n_d < beam ? n_d : beam;
   const int W = (max_nodes + 63) / 64;
@@ -897,121 +732,114 @@ __global__ __launch_bounds__(kThreads) void collapse_tree_kernel(CollapseParams 
     // table with an atomic max of (level, 127 - draft): per entry the current level's smallest draft
     // number wins and is read back as the creator of the draft's node on that level.  LDS operations
     // of one wavefront execute in order, so no barrier is needed between the levels.
-    auto tree = [&](auto u_tag) __attribute__((always_inline)) {
-      constexpr int U = decltype(u_tag)::value;
-      unsigned long long ck[U], creators[U] = {};  // byte d-1: creator of my node at depth d
-      int len[U], fprev[U] = {};
+    unsigned long long ck[2], creators[2] = {0ull, 0ull};  // byte d-1: creator of my node at depth d
+    int len[2], fprev[2] = {0, 0};
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int c = lane + 64 * u;
-        ck[u] = c < n_c ? s.kept_ck[c] : 0ull;
-        len[u] = c < n_c ? s.kept_len[c] : 0;
+    for (int u = 0; u < 2; ++u) {
+      const int c = lane + 64 * u;
+      ck[u] = c < n_c ? s.kept_ck[c] : 0ull;
+      len[u] = c < n_c ? s.kept_len[c] : 0;
+    }
+    for (int d = 1; d <= T; ++d) {
+      unsigned int key[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        key[u] = ((unsigned)fprev[u] << 6) | (unsigned)((ck[u] >> (7 * (d - 1))) & 0x3f);
+        if (d <= len[u]) atomicMax(&s.tree_table[key[u]], ((unsigned)d << 8) | (unsigned)(127 - (lane + 64 * u)));
       }
-      for (int d = 1; d <= T; ++d) {
-        unsigned int key[U];
+      // every lane's announcements must be issued before any lane reads a winner back: keep the
+      // compiler from moving the reads up (the hardware executes a wavefront's LDS operations in order)
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      __builtin_amdgcn_wave_barrier();
+      // both winners are read back in one round trip (the keys always lie inside the table, so the reads need no
+      // condition; a draft that has ended ignores what it reads)
+      unsigned int won[2];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          key[u] = ((unsigned)fprev[u] << 6) | (unsigned)((ck[u] >> (7 * (d - 1))) & 0x3f);
-          if (d <= len[u]) atomicMax(&s.tree_table[key[u]], ((unsigned)d << 8) | (unsigned)(127 - (lane + 64 * u)));
+      for (int u = 0; u < 2; ++u)
+        won[u] = __hip_atomic_load(&s.tree_table[key[u]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const bool on = d <= len[u];
+        fprev[u] = on ? 127 - (int)(won[u] & 0xffu) : fprev[u];
+        creators[u] |= on ? (unsigned long long)fprev[u] << (8 * (d - 1)) : 0ull;
+      }
+    }
+    // m = number of leading levels whose node another draft created; my tokens beyond m create nodes,
+    // node ids are handed out in (draft, depth) order
+    int m[2], excl[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int c = lane + 64 * u;
+      int mm = 0;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) mm += (d < len[u] && (int)((creators[u] >> (8 * d)) & 0xff) != c) ? 1 : 0;
+      m[u] = mm;
+    }
+    const int inc0 = wave_inclusive_scan_i32(len[0] - m[0]);
+    const int tot0 = __builtin_amdgcn_readlane(inc0, 63);
+    const int inc1 = wave_inclusive_scan_i32(len[1] - m[1]);
+    const int total_new = tot0 + __builtin_amdgcn_readlane(inc1, 63);
+    excl[0] = inc0 - (len[0] - m[0]);
+    excl[1] = tot0 + inc1 - (len[1] - m[1]);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int c = lane + 64 * u;
+      if (c < n_c) {
+        s.kept_m[c] = m[u];
+        s.kept_base[c] = 1 + excl[u];
+      }
+    }
+    const int n_nodes = (1 + total_new) < max_nodes ? (1 + total_new) : max_nodes;
+    if (lane == 0) {
+      s.n_nodes = n_nodes;
+      p.n_cand[b] = n_c;
+      p.n_nodes[b] = n_nodes;
+    }
+    // Every draft walks its path once: node id, token, ancestors of each level.  All LDS lookups of both drafts are
+    // requested up front and the walk is free of branches (node ids grow along a path, so "this level's node
+    // exists" already implies it for the levels above): as a loop with an early exit per level it waited for one
+    // LDS round trip per level.
+    int path_node[2][8], path_tok[2][8];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int d = 0; d < 8; ++d) {
+        const int f = d < len[u] ? (int)((creators[u] >> (8 * d)) & 0xff) : 0;
+        path_node[u][d] = s.kept_base[f] + (d - s.kept_m[f]);
+        path_tok[u][d] = s.ids[(int)((ck[u] >> (7 * d)) & 0x7f) & 63];
+      }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int c = lane + 64 * u;
+      int par = 0, leaf = 0;
+      bool whole = true;  // every level of the draft has its node (none cut by the node cap)
+      unsigned long long m0 = 1ull, m1 = 0ull;  // ancestors so far: the root
+#pragma unroll
+      for (int d = 0; d < 8; ++d) {
+        const int f = (int)((creators[u] >> (8 * d)) & 0xff);
+        const int node = path_node[u][d];
+        const bool level = c < n_c && d < len[u];
+        const bool exists = level && node < max_nodes;
+        whole = whole && (!level || exists);
+        // raw layout: a blank, or a token equal to the raw token right before it, is removed by the CTC transform -
+        // it sees its own prefix but nothing below it sees it
+        const int code = (int)((ck[u] >> (7 * d)) & 0x7f);
+        const bool removed = RAW && (code == s.blank_code || (d > 0 && code == (int)((ck[u] >> (7 * (d - 1))) & 0x7f)));
+        const unsigned long long b0 = node < 64 ? 1ull << (node & 63) : 0ull, b1 = node < 64 ? 0ull : 1ull << (node & 63);
+        if (exists && f == c) {
+          st_tok[node] = path_tok[u][d];
+          st_par[node] = par;
+          st_dep[node] = d + 1;
+          st_mask[2 * node] = m0 | b0;
+          st_mask[2 * node + 1] = m1 | b1;
+          if (RAW) st_rem[node] = removed ? 1 : 0;
         }
-        // every lane's announcements must be issued before any lane reads a winner back: keep the
-        // compiler from moving the reads up (the hardware executes a wavefront's LDS operations in order)
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_wave_barrier();
-        // both winners are read back in one round trip (the keys always lie inside the table, so the reads need no
-        // condition; a draft that has ended ignores what it reads)
-        unsigned int won[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          won[u] = __hip_atomic_load(&s.tree_table[key[u]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const bool on = d <= len[u];
-          fprev[u] = on ? 127 - (int)(won[u] & 0xffu) : fprev[u];
-          creators[u] |= on ? (unsigned long long)fprev[u] << (8 * (d - 1)) : 0ull;
-        }
+        if (exists && !removed) { m0 |= b0; m1 |= b1; }
+        par = exists ? node : par;
+        leaf = exists ? node : leaf;
       }
-      // m = number of leading levels whose node another draft created; my tokens beyond m create nodes,
-      // node ids are handed out in (draft, depth) order
-      int m[U], excl[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int c = lane + 64 * u;
-        int mm = 0;
-#pragma unroll
-        for (int d = 0; d < 8; ++d) mm += (d < len[u] && (int)((creators[u] >> (8 * d)) & 0xff) != c) ? 1 : 0;
-        m[u] = mm;
-      }
-      int total_new = 0;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int inc = wave_inclusive_scan_i32(len[u] - m[u]);
-        excl[u] = total_new + inc - (len[u] - m[u]);
-        total_new += __builtin_amdgcn_readlane(inc, 63);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int c = lane + 64 * u;
-        if (c < n_c) {
-          s.kept_m[c] = m[u];
-          s.kept_base[c] = 1 + excl[u];
-        }
-      }
-      const int n_nodes = (1 + total_new) < max_nodes ? (1 + total_new) : max_nodes;
-      if (lane == 0) {
-        s.n_nodes = n_nodes;
-        p.n_cand[b] = n_c;
-        p.n_nodes[b] = n_nodes;
-      }
-      // Every draft walks its path once: node id, token, ancestors of each level.  All LDS lookups of both drafts are
-      // requested up front and the walk is free of branches (node ids grow along a path, so "this level's node
-      // exists" already implies it for the levels above): as a loop with an early exit per level it waited for one
-      // LDS round trip per level.
-      int path_node[U][8], path_tok[U][8];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int d = 0; d < 8; ++d) {
-          const int f = d < len[u] ? (int)((creators[u] >> (8 * d)) & 0xff) : 0;
-          path_node[u][d] = s.kept_base[f] + (d - s.kept_m[f]);
-          path_tok[u][d] = s.ids[(int)((ck[u] >> (7 * d)) & 0x7f) & 63];
-        }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int c = lane + 64 * u;
-        int par = 0, leaf = 0;
-        bool whole = true;  // every level of the draft has its node (none cut by the node cap)
-        unsigned long long m0 = 1ull, m1 = 0ull;  // ancestors so far: the root
-#pragma unroll
-        for (int d = 0; d < 8; ++d) {
-          const int f = (int)((creators[u] >> (8 * d)) & 0xff);
-          const int node = path_node[u][d];
-          const bool level = c < n_c && d < len[u];
-          const bool exists = level && node < max_nodes;
-          whole = whole && (!level || exists);
-          // raw layout: a blank, or a token equal to the raw token right before it, is removed by the CTC transform -
-          // it sees its own prefix but nothing below it sees it
-          const int code = (int)((ck[u] >> (7 * d)) & 0x7f);
-          const bool removed = RAW && (code == s.blank_code || (d > 0 && code == (int)((ck[u] >> (7 * (d - 1))) & 0x7f)));
-          const unsigned long long b0 = node < 64 ? 1ull << (node & 63) : 0ull, b1 = node < 64 ? 0ull : 1ull << (node & 63);
-          if (exists && f == c) {
-            st_tok[node] = path_tok[u][d];
-            st_par[node] = par;
-            st_dep[node] = d + 1;
-            st_mask[2 * node] = m0 | b0;
-            st_mask[2 * node + 1] = m1 | b1;
-            if (RAW) st_rem[node] = removed ? 1 : 0;
-          }
-          if (exists && !removed) { m0 |= b0; m1 |= b1; }
-          par = exists ? node : par;
-          leaf = exists ? node : leaf;
-        }
-        if (c < n_c) p.cand_leaf[(size_t)b * beam + c] = (whole && len[u] > 0) ? leaf : -1;
-      }
-    };
-    // (half of the work where 64 lanes hold every draft)
-    if (n_c <= 64) tree(std::integral_constant<int, 1>{});
-    else tree(std::integral_constant<int, 2>{});
+      if (c < n_c) p.cand_leaf[(size_t)b * beam + c] = (whole && len[u] > 0) ? leaf : -1;
+    }
   } else {
     // ---- draft arrays, by the other wavefronts ----------------------------------------------------
     for (int i = tid - 64; i < beam * 8; i += kThreads - 64) {
@@ -1104,7 +932,7 @@ static int collapse_tree_call(ctcspec_ctx* ctx, const char* name, bool raw, cons
   CollapseParams p;
   p.topk_id = topk_id; p.topk_logp = topk_logp; p.root_token = root_token;
   p.T = T; p.k = k; p.blank_id = blank_id; p.beam = beam; p.max_nodes = max_nodes;
-  p.magic = (32768u + (unsigned)k - 1) / (unsigned)k;
+  p.magic = (unsigned int)((0x100000000ull + (unsigned)k - 1) / (unsigned)k);
   {
     unsigned long long n2 = 1;
     for (int t = 0; t < T / 2; ++t) n2 *= (unsigned)k;  // T2 = T - ceil(T/2) = floor(T/2)

@@ -52,19 +52,3 @@ def test_scores_not_a_number(pkg, T, k, slot):
     low[:, slot, k - 1] = -np.inf
     _run_stage3(pkg, ctx, ids, low, np.array([1, 2]), blank, beam, nodes)
     ctx.close()
-
-
-# Above 512 raw candidates: levels of up to 256, 257 to 512 and more survivors (by the beam), drafts of one score, repeats
-# and blanks that leave a level with too few drafts.
-@pytest.mark.parametrize("T,k", [(5, 4), (7, 3), (8, 4), (5, 8)])
-@pytest.mark.parametrize("quantum,p_blank", [(0.0, 0.1), (0.25, 0.1), (0.0, 0.7)])
-def test_collapse_by_levels(pkg, T, k, quantum, p_blank):
-    B, blank = 2, 40
-    ctx = _stage3_ctx(pkg, B, T, k)
-    for seed, vocab in ((1, k + 1), (2, 39)):
-        ids, logp = workloads.make_topk_case(100 * T + seed, B, T, k, blank, vocab=vocab, p_blank=p_blank, quantum=quantum)
-        logp -= np.float32(1.0)
-        for beam, nodes in ((3, 20), (60, 128), (100, 128), (128, 128)):
-            print(f"collapse T={T} k={k} quantum={quantum} p_blank={p_blank} vocab={vocab} beam={beam}", flush=True)
-            _run_stage3(pkg, ctx, ids, logp, np.array([1, 2]), blank, beam, nodes)
-    ctx.close()

@@ -28,9 +28,6 @@ constexpr size_t kCollapseWsBytesPerSeq = (size_t)kMaxAlign * 8 * 2 + (size_t)kM
 // ---- verifier head workspace geometry ---------------------------------------------------------
 constexpr int kVerifyCols = 128;  // columns (tree nodes) per pass over the base model's head weights
 
-// ---- attention workspace geometry --------------------------------------------------------------
-constexpr int kMaxKvSplits = 32;
-
 }  // namespace ctcspec
 
 struct ctcspec_ctx {

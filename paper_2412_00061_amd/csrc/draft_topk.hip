@@ -28,14 +28,6 @@
 namespace ctcspec {
 
 constexpr int kZStride = kRowsPerBlock + 4;  // floats per column in the LDS logit block
-// bytes per staged W row: 256 bf16 + pad.  The LDS serves a 16-byte access 16 lanes at a time - lanes l .. l+7 with
-// l+16 .. l+23 - so a fragment read (lane = row c, chunk g) is conflict-free when rows c .. c+7 at chunks g and g+1
-// fall on 16 different groups of 4 banks: pitch = 32 mod 64 bytes (with 16 bytes of pad the conflict counter read
-// 8200 cycles per workgroup)
-constexpr int kWRowStride = 512 + 32;
-constexpr int kWStageBytes = 16 * kWRowStride;  // per wave
-constexpr int kMfmaWaves = 8;
-
 struct LmHeadParams {
   const void* hidden;
   const void* w;
@@ -507,16 +499,6 @@ int flush_deferred(ctcspec_ctx* ctx) {
   return CTCSPEC_OK;
 }
 
-static int pick_kc(int BT, int D, int stages, int budget) {
-  const int unit = 256 * stages;
-  if (D % unit != 0) return 0;
-  for (int kc = D; kc >= unit; kc -= unit) {
-    if (D % kc != 0) continue;
-    if ((long long)BT * (2 * kc + 32) <= budget) return kc;
-  }
-  return 0;
-}
-
 // ev0/ev1, when given, are attached to the launch itself: they take the kernel's own begin and end timestamps (what a
 // kernel trace reports), without the dispatch work that a pair of events recorded around the launch also spans.
 template <int NT, int STAGES>
@@ -528,9 +510,6 @@ static hipError_t launch_mfma(const LmHeadParams& p, int lds_bytes, hipStream_t 
     hipLaunchKernelGGL(kern, dim3(p.n_blocks), dim3(64 * kMfmaWaves), lds_bytes, stream, p);
   return hipGetLastError();
 }
-
-// the streaming kernel's LDS need depends on the call's shape; its budget (see ctc_draft_topk) is the limit set here
-constexpr int kMfmaLdsLimit = 160 * 1024 - 64;
 
 template <int NT, int STAGES>
 static hipError_t allow_mfma_lds() {
@@ -660,13 +639,10 @@ static int draft_topk_launch(ctcspec_ctx* err, hipStream_t stream, const LmScrat
     return CTCSPEC_OK;
   };
 
-  // what the epilogues take: joining the wavefronts' k-lists; a column's workgroup pops k keys
   const bool f32 = dt == CTCSPEC_F32;
-  const int tile_cols = p.BT <= 16 ? 16 : p.BT <= 32 ? 32 : 64;
-  const double epilogue_us = tile_cols == 16 ? 1.5 : k <= 2 ? 2.0 : k <= 4 ? 3.0 : 4.0;
   HeadRangeParams h;
   h.hidden = hidden; h.w = w; h.zeros = sc.zeros; h.part = sc.part; h.cols = p.BT; h.D = D; h.V = Vp1;
-  if (plan_head(h, f32, head_whole_us(Vp1, p.BT, D, f32, kRowsPerBlock, tile_cols, epilogue_us), 1.5 + 0.2 * k, kDraftPartFloats)) {
+  if (plan_draft_head(h, f32, k)) {
     if (timing) CTCSPEC_HIP(err, hipEventRecord(ev0, stream));
     CTCSPEC_HIP(err, launch_head_ranges(h, f32, stream));
     if (timing) {
@@ -678,19 +654,10 @@ static int draft_topk_launch(ctcspec_ctx* err, hipStream_t stream, const LmScrat
     return CTCSPEC_OK;  // (nothing of it can be left to the collapse kernel)
   }
   if (dt == CTCSPEC_BF16) {
-    const int budget = kMfmaLdsLimit - kMfmaWaves * kWStageBytes;
-    // the streaming kernel needs the hidden states of all columns in LDS over the whole hidden dimension
-    // (4 register stages of prefetch; 2 when D is a multiple of 512 but not of 1024)
-    int stages = 4;
-    int kc = pick_kc(p.BT, D, stages, budget);
-    if (kc != D) {
-      stages = 2;
-      kc = pick_kc(p.BT, D, stages, budget);
-    }
-    if (kc == D) {
-      p.KC = kc;
-      p.hs_bytes = p.BT * (2 * kc + 32);
-      p.hs_magic = (unsigned int)((0x100000000ull + (unsigned)(kc / 8) - 1) / (unsigned)(kc / 8));
+    if (const int stages = draft_stream_stages(p.BT, D)) {
+      p.KC = D;
+      p.hs_bytes = p.BT * (2 * D + 32);
+      p.hs_magic = (unsigned int)((0x100000000ull + (unsigned)(D / 8) - 1) / (unsigned)(D / 8));
       int lds = p.hs_bytes + kMfmaWaves * kWStageBytes;
       int nt = (p.BT + 15) / 16;
       hipError_t e;

@@ -1,0 +1,105 @@
+// Which way a head takes (ctc_draft_topk, verify_head_argmax): its own kernel, or the product cut along the hidden dimension
+// (head_ranges.h).  Host code without HIP, so that a test can ask it.
+//
+// plan_head compares what both are made of.  A step of a tile takes what its LDS traffic takes (0.35 us for 16
+// columns to 1.1 for 128; float: the matrix rate, 0.45 to 3.5), or its share of the weights' stream.  Measured, a whole
+// call in a HIP graph before / with ranges, us:
+//   base head, bf16:  128 columns x 1565 rows of 3328  37.0 / 14.9     128 x 6189 of 4096 (2 sequences)  65.4 / 34.0
+//     64 x 3249 of 4072  34.1 / 24.0     512 x 1030 of 768 float  101.2 / 19.2     128 x 10407 of 2816  35.0 / 35.0 (not taken;
+//     with three ranges 37.4: 16 MB of partial sums)
+//   draft head, bf16:  40 columns x 2235 of 4096, k = 8  44.4 / 18.9     7 x 3801 of 4456  34.7 / 25.1     float:  30 x 2215 of
+//     512  33.9 / 14.6     a step of 128 rows and 8 slots, 3176 x 4833  152 / 91
+// 60 drawn calls each: draft head 1.29, base head 1.60 times as fast in the mean, the slowest 0.98 (within the scatter).
+#pragma once
+
+#include <stddef.h>
+
+namespace ctcspec {
+
+constexpr int kHeadRowBlock = 128;                           // vocabulary rows of a workgroup
+constexpr int kHeadColBlock = 128;                           // columns of the base head's own kernel
+constexpr int kHeadMaxSplits = 16;
+constexpr int kHeadColumnThreads = 512;                      // of the kernels that finish a column
+constexpr int kHeadMaxRows = kHeadColumnThreads * 4 * 8;     // vocabulary rows they hold
+// room for partial sums: the draft head's (the context's and the static scratch of the entry point that allocates nothing
+// alike, so that both take the same way) and the base head's
+constexpr size_t kDraftPartFloats = (size_t)2 << 20, kHeadPartFloats = (size_t)4 << 20;
+
+struct HeadPlan {
+  int cols, D, V;
+  int tile_cols;       // 16, 32, 64 or 128
+  int splits;
+  int row_blocks, col_blocks;
+};
+
+constexpr double kStartUs = 6.0, kFinishLaunchUs = 4.3;  // a workgroup's way to its first step; the second launch
+inline double step_us(int tile_cols, bool f32, long long groups) {
+  const int i = tile_cols <= 16 ? 0 : tile_cols <= 32 ? 1 : tile_cols <= 64 ? 2 : 3;
+  static const double lds[4] = {0.35, 0.4, 0.9, 1.1}, mfma[4] = {0.45, 0.9, 1.75, 3.5};
+  const double own = f32 ? mfma[i] : lds[i], stream = (double)(groups < 256 ? groups : 256) * 32768.0 / 5.9e6;
+  return own > stream ? own : stream;
+}
+inline double walk_us(long long groups, double steps, double step) {
+  return (double)((groups + 255) / 256) * (kStartUs + steps * step);
+}
+// the heads' own kernels: `rows` x `tile_cols` tiles over all steps, `finish_us` of epilogue
+inline double head_whole_us(int V, int cols, int D, bool f32, int rows, int tile_cols, double finish_us) {
+  const long long groups = (long long)((V + rows - 1) / rows) * ((cols + tile_cols - 1) / tile_cols);
+  const double steps = (double)D * (f32 ? 4 : 2) / 256.0;
+  return walk_us(groups, steps, step_us(tile_cols, f32, groups) * rows / 128.0) + kFinishLaunchUs + finish_us;
+}
+// whole_us: what the way without ranges takes, by head_whole_us.  Fills tile_cols and splits; false: not worth it.
+inline bool plan_head(HeadPlan& p, bool f32, double whole_us, double finish_us, size_t part_floats) {
+  if (p.V > kHeadMaxRows) return false;
+  p.row_blocks = (p.V + kHeadRowBlock - 1) / kHeadRowBlock;
+  const double steps = (double)p.D * (f32 ? 4 : 2) / 256.0;
+  const size_t sums = (size_t)p.cols * p.row_blocks * kHeadRowBlock;  // of one range
+  double least = 0.9 * whole_us;  // (the model is not better than that)
+  p.splits = 0;
+  for (int tile = 16; tile <= 128; tile *= 2) {
+    const long long groups = (long long)p.row_blocks * ((p.cols + tile - 1) / tile);
+    for (int S = 1; S <= kHeadMaxSplits && (S == 1 || S <= steps) && S * sums <= part_floats; ++S) {
+      const double us = walk_us(groups * S, steps / S, step_us(tile, f32, groups * S)) + (double)S * sums * 8.0 / 3e6 +
+                        kFinishLaunchUs + finish_us + ((p.cols + 255) / 256) * (double)S * p.V * 4.0 / 45e3;
+      if (us < least) {
+        least = us;
+        p.splits = S;
+        p.tile_cols = tile;
+      }
+    }
+    if (tile >= p.cols) break;
+  }
+  if (p.splits == 0) return false;
+  p.col_blocks = (p.cols + p.tile_cols - 1) / p.tile_cols;
+  return true;
+}
+
+inline int head_tile_cols(int cols) { return cols <= 16 ? 16 : cols <= 32 ? 32 : cols <= 64 ? 64 : 128; }
+// what the epilogues take: joining the wavefronts' k-lists; a column's workgroup pops k keys
+inline bool plan_draft_head(HeadPlan& p, bool f32, int k) {
+  const int tile_cols = head_tile_cols(p.cols);
+  const double epilogue_us = tile_cols == 16 ? 1.5 : k <= 2 ? 2.0 : k <= 4 ? 3.0 : 4.0;
+  return plan_head(p, f32, head_whole_us(p.V, p.cols, p.D, f32, kHeadRowBlock, tile_cols, epilogue_us), 1.5 + 0.2 * k, kDraftPartFloats);
+}
+inline bool plan_base_head(HeadPlan& p, bool f32) {
+  const int rows = p.cols > kHeadColBlock ? 256 : 128;
+  return plan_head(p, f32, head_whole_us(p.V, p.cols, p.D, f32, rows, head_tile_cols(p.cols), 1.0), 1.0, kHeadPartFloats);
+}
+
+// ---- the draft head's streaming kernel (bf16) -----------------------------------------------------------------------
+// bytes per staged W row: 256 bf16 + pad.  The LDS serves a 16-byte access 16 lanes at a time - lanes l .. l+7 with
+// l+16 .. l+23 - so a fragment read (lane = row c, chunk g) is conflict-free when rows c .. c+7 at chunks g and g+1
+// fall on 16 different groups of 4 banks: pitch = 32 mod 64 bytes (with 16 bytes of pad the conflict counter read
+// 8200 cycles per workgroup)
+constexpr int kWRowStride = 512 + 32;
+constexpr int kWStageBytes = 16 * kWRowStride;  // per wave
+constexpr int kMfmaWaves = 8;
+constexpr int kMfmaLdsLimit = 160 * 1024 - 64;                          // dynamic LDS that the kernel may ask for
+// Register stages of its prefetch, 0: not taken.  It needs the hidden states of all columns in LDS over the whole hidden
+// dimension (4 stages; 2 when D is a multiple of 512 but not of 1024).
+inline int draft_stream_stages(int cols, int D) {
+  if ((long long)cols * (2LL * D + 32) > kMfmaLdsLimit - kMfmaWaves * kWStageBytes) return 0;
+  return D % 1024 == 0 ? 4 : D % 512 == 0 ? 2 : 0;
+}
+
+}  // namespace ctcspec

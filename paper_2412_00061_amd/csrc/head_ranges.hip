@@ -1,4 +1,4 @@
-// The product of a head cut into ranges of the hidden dimension (head_ranges.h), and the rule that chooses it.
+// The product of a head cut into ranges of the hidden dimension (head_ranges.h; head_plan.h has the rule that chooses it).
 #include <type_traits>
 
 #include "gemm_tile.h"
@@ -43,47 +43,6 @@ __global__ __launch_bounds__(64 * kTileWaves) void head_range_kernel(HeadRangePa
     for (int rt = 0; rt < SH::RT; ++rt)
       __builtin_nontemporal_store(acc[rt][ct], (f32x4*)(out + (size_t)col * Vp + (wr * SH::RT + rt) * 16 + g * 4));
   }
-}
-
-// ---- the rule -------------------------------------------------------------------------------------------------------
-constexpr double kStartUs = 6.0, kFinishLaunchUs = 4.3;  // a workgroup's way to its first step; the second launch
-static double step_us(int tile_cols, bool f32, long long groups) {
-  const int i = tile_cols <= 16 ? 0 : tile_cols <= 32 ? 1 : tile_cols <= 64 ? 2 : 3;
-  static const double lds[4] = {0.35, 0.4, 0.9, 1.1}, mfma[4] = {0.45, 0.9, 1.75, 3.5};
-  const double own = f32 ? mfma[i] : lds[i], stream = (double)(groups < 256 ? groups : 256) * 32768.0 / 5.9e6;
-  return own > stream ? own : stream;
-}
-static double walk_us(long long groups, double steps, double step) {
-  return (double)((groups + 255) / 256) * (kStartUs + steps * step);
-}
-double head_whole_us(int V, int cols, int D, bool f32, int rows, int tile_cols, double finish_us) {
-  const long long groups = (long long)((V + rows - 1) / rows) * ((cols + tile_cols - 1) / tile_cols);
-  const double steps = (double)D * (f32 ? 4 : 2) / 256.0;
-  return walk_us(groups, steps, step_us(tile_cols, f32, groups) * rows / 128.0) + kFinishLaunchUs + finish_us;
-}
-bool plan_head(HeadRangeParams& p, bool f32, double whole_us, double finish_us, size_t part_floats) {
-  if (p.V > kHeadMaxRows) return false;
-  p.row_blocks = (p.V + kRowsPerBlock - 1) / kRowsPerBlock;
-  const double steps = (double)p.D * (f32 ? 4 : 2) / 256.0;
-  const size_t sums = (size_t)p.cols * p.row_blocks * kRowsPerBlock;  // of one range
-  double least = 0.9 * whole_us;  // (the model is not better than that)
-  p.splits = 0;
-  for (int tile = 16; tile <= 128; tile *= 2) {
-    const long long groups = (long long)p.row_blocks * ((p.cols + tile - 1) / tile);
-    for (int S = 1; S <= kHeadMaxSplits && (S == 1 || S <= steps) && S * sums <= part_floats; ++S) {
-      const double us = walk_us(groups * S, steps / S, step_us(tile, f32, groups * S)) + (double)S * sums * 8.0 / 3e6 +
-                        kFinishLaunchUs + finish_us + ((p.cols + 255) / 256) * (double)S * p.V * 4.0 / 45e3;
-      if (us < least) {
-        least = us;
-        p.splits = S;
-        p.tile_cols = tile;
-      }
-    }
-    if (tile >= p.cols) break;
-  }
-  if (p.splits == 0) return false;
-  p.col_blocks = (p.cols + p.tile_cols - 1) / p.tile_cols;
-  return true;
 }
 
 template <typename EL, bool ROWS16, typename F>

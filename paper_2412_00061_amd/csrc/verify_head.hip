@@ -313,9 +313,7 @@ extern "C" int verify_head_argmax(ctcspec_ctx* ctx, ctcspec_dtype dt, const void
   const bool f32 = dt == CTCSPEC_F32;
   HeadRangeParams r;
   r.hidden = node_hidden; r.w = w_base; r.zeros = ctx->zeros; r.part = ctx->vh_part; r.cols = p.cols_total; r.D = D; r.V = V;
-  const int tile_cols = p.cols_total <= 16 ? 16 : p.cols_total <= 32 ? 32 : p.cols_total <= 64 ? 64 : 128;
-  if (plan_head(r, f32, head_whole_us(V, p.cols_total, D, f32, p.cols_total > kVhCols ? 256 : 128, tile_cols, 1.0), 1.0,
-                kHeadPartFloats)) {
+  if (plan_base_head(r, f32)) {
     CTCSPEC_HIP(ctx, launch_head_ranges(r, f32, ctx->stream));
     const hipError_t e = launch_for_rows(V, [&](auto nv) {
       hipLaunchKernelGGL(verify_head_columns_kernel<decltype(nv)::value>, dim3((unsigned)cols_total), dim3(kHeadColumnThreads), 0,

@@ -1,0 +1,35 @@
+"""The launch rules, asked on the CPU (launch_plans.py): what they promise, and which kernels the GPU tests' sizes reach."""
+import pytest
+
+import launch_plans
+
+
+def test_range_sums_fit_their_scratch():
+    lines, rows_of = [], []
+    for cols in (1, 8, 17, 40, 64, 128, 200, 512):
+        for V in (1, 129, 1500, 5000, 9000, 16384, 16385):
+            for D in (64, 1031, 4096):
+                for f32 in (0, 1):
+                    for what in ("b", "d") if cols <= 64 else ("b",):
+                        lines.append((what, cols, D, V, f32, 4))
+                        rows_of.append((V + 127) // 128 * 128)
+    taken = 0
+    for line, rows, (way, tile, ranges) in zip(lines, rows_of, launch_plans.ask(lines)):
+        what, cols, D, V, f32, _ = line
+        if way == "ranges":
+            taken += 1
+            steps = D * (4 if f32 else 2) // 256
+            assert V <= 16384 and tile in (16, 32, 64, 128) and 1 <= ranges <= max(1, steps)
+            assert ranges * cols * rows <= (2 if what == "d" else 4) << 20
+    assert taken > 200
+
+
+@pytest.mark.parametrize("two_bf16", [0, 1])
+def test_attention_splits_fit_their_scratch(two_bf16):
+    lines = [("a", B, H, nodes, cap, dh, f32, two_bf16) for B in (1, 3, 8) for H in (1, 7, 32, 40) for nodes in (1, 16, 17, 64, 65, 128)
+             for cap in (0, 40, 300, 2048, 20000) for dh, f32 in ((128, 0), (128, 1), (64, 0), (16, 1)) if not (two_bf16 and f32)]
+    for (_, B, H, nodes, cap, dh, f32, _), (way, blocks, splits) in zip(lines, launch_plans.ask(lines)):
+        units = max(256, B * H)  # of 128 query rows
+        rows = 64 if way in ("any", "rows64") else 128
+        assert blocks * rows >= nodes or way == "few"
+        assert 1 <= splits <= 32 and (splits == 1 or B * H * blocks * splits * rows <= units * 128)

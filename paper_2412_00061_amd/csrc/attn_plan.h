@@ -20,24 +20,32 @@ inline bool attn_keys_by_wavefront(long long bh, int max_nodes, int kv_cap) {
 inline bool attn_rows64(AttnShape s, int max_nodes) { return s.QB == 2 || (max_nodes <= 64 && max_nodes > kFewRows); }
 
 // ---- launch shapes -------------------------------------------------------------------------------------------------
-// A call's time by what it is made of, in us; both kernels take the cheapest (query blocks, key splits).
+// A call's time by what it is made of, in us:
 //   workgroups a compute unit takes in turn x (start of one + iterations x time of one) + what splitting costs
-// Splitting costs the merge launch and the partial results, which go through memory.  Before, as many splits were taken as
-// fill the chip whatever the merge costs, at most 8, and two blocks of 64 rows as soon as the chip was full.  Measured in HIP
-// graphs, us a call before / with this choice:
+// Splitting costs the merge launch and the partial results, which go through memory.  Both kernels start from as many
+// splits as fill the chip (at most 8, a few tiles each; two blocks of 64 rows where they fill as much) and take the cheapest
+// (query blocks, key splits) of the model instead where it spares more than the model errs: 3 % (bf16, 128), 7 % (the others,
+// whose workgroups sit side by side).  Measured in HIP graphs, us a call as the chip is filled / with this choice:
 //   bf16, 128: 2 x 40 heads, 128 rows, 128 positions 17.1 (2 splits) / 10.0 (none, two blocks)    6 x 32 heads, 200: 22.3 / 16.8
 //     (one block)    4 x 32 heads, 100 rows, 300: 18.5 (2) / 13.2 (1)    32 heads, 64 rows, 256: 11.9 (2) / 10.2 (1)
 //     32 heads, 128 rows, 2048 positions: 4 splits both; none 36.8, 2 26.0, 3 21.6, 4 19.6, 8 of one block 20.0
-//   bf16, 80: 4 x 16 heads, 50 rows, 93 positions 10.5 (2) / 7.6 (1)    64: 32 heads, 128 rows, 512: 14.6 (8) / 11.9 (4)
-//   float, 128: 14 heads, 35 rows, up to 1923 positions 24.4 (8) / 18.4 (18)    float, 16: 4 heads, 128 rows, 32: 7.4 (3) / 4.0 (1, padded
+//   bf16, 80: 4 x 16 heads, 50 rows, 93 positions 10.5 (2) / 7.6 (1)
+//   float, 128: 14 heads, 35 rows, up to 1923 positions 24.0 (8) / 17.7 (16)    float, 16: 4 heads, 128 rows, 32: 7.4 (3) / 4.0 (1, padded
 //     to 16 instead of 32)
-// Over 400 shapes drawn from 1 to 8 sequences of 4 to 40 heads and 1 to 128 rows over 4 to 2048 positions: 7 % in the mean.
+// Every plan of 440 shapes drawn from 1 to 8 sequences of 4 to 40 heads and 1 to 128 rows over 4 to 2048 positions was timed: 4.4 %
+// (bf16, 128) and 6.5 % (the others) less time than as the chip is filled in the mean, one shape more than 4 % slower
+// (4.6).  Taking the model's plan whatever it spares: the same mean, 19 shapes more than 4 % slower (8 sequences x 14 float
+// heads of 32, 41 rows, up to 365 positions 12.0 -> 13.6).  That is 2.1 % above the best plan of each shape; with 2.2 us for the
+// merge - what such a launch takes behind an independent one - 3.1 %, with 4 to 4.3 us 2.0.
+constexpr int kFillSplits = 8;
+constexpr double kModelGain128 = 0.97, kModelGainAny = 0.93;
+constexpr double kMergeLaunchUs = 3.3;  // with the end of the kernel before it, whose stores it waits for
 // the merge launch, the partial results' way through memory, and a round trip of the merge for every eight splits more.  Rows as
 // two bf16 numbers are the merge's work otherwise: the 2 x 8 rows of a layer of 1024, 300 positions, 42.2 us with the layer's
 // attention in two splits, 44.0 in none.
 constexpr double kTwoBf16Us = 1.5;
 inline double split_us(long long bh, int S, int rows, int dh, bool two_bf16) {
-  return S == 1 ? (two_bf16 ? kTwoBf16Us : 0.0) : 3.3 + (double)bh * S * rows * dh * 4 * 0.25e-6 + (S - 1) / kMergeParts * 3.0;
+  return S == 1 ? (two_bf16 ? kTwoBf16Us : 0.0) : kMergeLaunchUs + (double)bh * S * rows * dh * 4 * 0.25e-6 + (S - 1) / kMergeParts * 3.0;
 }
 // how much longer than one workgroup a compute unit with `load` of them takes.  Of several sequences, not all are the longest.
 inline double taking_turns(double load, double next) { return load <= 1.0 ? 1.0 : 1.0 + (load - 1.0) * next; }
@@ -53,17 +61,31 @@ inline double iterations(int kv_cap, int max_nodes, int S, int per_iter) {
 // blocks of 128 one (0.88 us; 0.52 with a single live row group, whose partials are 16 rows).  slots: units of 128 rows that
 // the workspace holds.
 inline AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long long slots, bool two_bf16) {
-  AttnShape best = {1, 1};
   const long long bh = (long long)B * H;
-  double least = 1e30;
+  const int key_tiles = (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys;
+  auto fill = [&](int QB) {
+    long long S = 256 / (bh * QB);
+    S = S > key_tiles / 4 ? key_tiles / 4 : S;
+    S = S > kFillSplits ? kFillSplits : S;
+    while (S > 1 && bh * QB * S > slots) --S;
+    return S < 1 ? 1 : (int)S;
+  };
+  auto us_of = [&](AttnShape s) {
+    const bool rows64 = attn_rows64(s, max_nodes);
+    const double iter = rows64 ? (s.QB == 2 ? 1.1 : 0.9) : (max_nodes > kFewRows ? 0.88 : 0.52);
+    return taking_turns((double)(bh * s.QB * s.S) / 256.0, B > 1 ? 0.7 : 1.0) *
+               (4.8 + iterations(kv_cap, max_nodes, s.S, rows64 ? 2 : 1) * iter) +
+           split_us(bh, s.S, max_nodes, 128, two_bf16);
+  };
+  const int s128 = fill(1), s64 = fill(2);
+  AttnShape best = {1, s128};
+  if (max_nodes > 64 && (2 * s64 > s128 || (2 * s64 == s128 && s64 >= 4))) best = {2, s64};
+  double least = kModelGain128 * us_of(best);
   for (int QB = 1; QB <= (max_nodes > 64 ? 2 : 1); ++QB) {
-    const bool rows64 = max_nodes > 64 ? QB == 2 : max_nodes > kFewRows;
-    const double iter = rows64 ? (QB == 2 ? 1.1 : 0.9) : (max_nodes > kFewRows ? 0.88 : 0.52);
     for (int S = 1; S <= kMaxKvSplits; ++S) {
       const long long groups = bh * QB * S;
-      if (S > 1 && (groups > 256 || groups > slots || S * 4 > (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys)) break;
-      const double us = taking_turns(groups / 256.0, B > 1 ? 0.7 : 1.0) * (4.8 + iterations(kv_cap, max_nodes, S, rows64 ? 2 : 1) * iter) +
-                        split_us(bh, S, max_nodes, 128, two_bf16);
+      if (S > 1 && (groups > 256 || groups > slots || S * 4 > key_tiles)) break;
+      const double us = us_of({QB, S});
       if (us < least) {
         least = us;
         best = {QB, S};
@@ -75,16 +97,25 @@ inline AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long lon
 // Everything else, blocks of 64 rows.  Float: the matrix rate, workgroups on one compute unit take turns as far as their
 // wavefronts have rows; bf16: they run side by side.  slots: units of 64 rows.
 inline AttnShape plan_any(int B, int H, int max_nodes, int kv_cap, int dh, bool f32, long long slots, bool two_bf16) {
-  AttnShape best = {(max_nodes + 63) / 64, 1};
-  const long long bh = (long long)B * H, blocks = bh * best.QB;
-  const int live = max_nodes >= 64 ? 4 : (max_nodes + 15) / 16;
-  double least = 1e30;
-  for (int S = 1; S <= kMaxKvSplits; ++S) {
-    if (S > 1 && (blocks * S > slots || S * kTileKeys > kv_cap + max_nodes || bh > 65535)) break;  // (the merge's grid)
+  const int QB = (max_nodes + 63) / 64, live = max_nodes >= 64 ? 4 : (max_nodes + 15) / 16;
+  const long long bh = (long long)B * H, blocks = bh * QB;
+  if (bh > 65535) return {QB, 1};  // (the merge's grid)
+  auto us_of = [&](int S) {
     const long long groups = blocks * S;
-    const double turns = f32 && dh > 32 ? taking_turns((double)((groups * live + 1023) / 1024), B > 1 ? 0.5 : 1.0) : side_by_side(groups / 256.0);
+    const double turns = f32 && dh > 32 ? taking_turns((double)((groups * live + 1023) / 1024), B > 1 ? 0.5 : 1.0) : side_by_side((double)groups / 256.0);
     const double tile = f32 ? (dh <= 16 ? 0.7 : dh <= 32 ? 0.9 : (dh + 31) / 32 * 32 / 48.0) : (dh <= 64 ? 0.6 : 0.7);
-    const double us = turns * (3.0 + iterations(kv_cap, max_nodes, S, 1) * tile) + split_us(bh, S, max_nodes, dh, two_bf16);
+    return turns * (3.0 + iterations(kv_cap, max_nodes, S, 1) * tile) + split_us(bh, S, max_nodes, dh, two_bf16);
+  };
+  long long fill = 512 / blocks;  // two workgroups per compute unit, two tiles each
+  const int key_tiles = (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys;
+  fill = fill > key_tiles / 2 ? key_tiles / 2 : fill;
+  fill = fill > kFillSplits ? kFillSplits : fill;
+  while (fill > 1 && blocks * fill > slots) --fill;
+  AttnShape best = {QB, fill < 1 ? 1 : (int)fill};
+  double least = kModelGainAny * us_of(best.S);
+  for (int S = 1; S <= kMaxKvSplits; ++S) {
+    if (S > 1 && (blocks * S > slots || S * kTileKeys > kv_cap + max_nodes)) break;
+    const double us = us_of(S);
     if (us < least) {
       least = us;
       best.S = S;

@@ -1,15 +1,22 @@
 // Which way a head takes (ctc_draft_topk, verify_head_argmax): its own kernel, or the product cut along the hidden dimension
 // (head_ranges.h).  Host code without HIP, so that a test can ask it.
 //
-// plan_head compares what both are made of.  A step of a tile takes what its LDS traffic takes (0.35 us for 16
-// columns to 1.1 for 128; float: the matrix rate, 0.45 to 3.5), or its share of the weights' stream.  Measured, a whole
-// call in a HIP graph before / with ranges, us:
+// plan_head compares what both are made of; both take a second launch.  A step of a tile takes what its LDS traffic takes
+// (0.35 us for 16 columns to 1.1 for 128; float: the matrix rate, 0.45 to 3.5), or its share of the weights' stream.  The
+// kernel that finishes a column gets slower where a thread holds eight groups of rows: a draft head of 8193 to 16384 rows
+// takes 4 to 5 us longer so than with its own epilogue and merge, at the same product (up to 8192 rows 1.4, up to 4096 0.9 less), a
+// base head 4 (2.3, 1.7).  Measured, a whole call in a HIP graph before / with ranges, us:
 //   base head, bf16:  128 columns x 1565 rows of 3328  37.0 / 14.9     128 x 6189 of 4096 (2 sequences)  65.4 / 34.0
 //     64 x 3249 of 4072  34.1 / 24.0     512 x 1030 of 768 float  101.2 / 19.2     128 x 10407 of 2816  35.0 / 35.0 (not taken;
-//     with three ranges 37.4: 16 MB of partial sums)
+//     with three ranges 37.4: 16 MB of partial sums)     85 x 9043 of 2040  32.7 / 35.5 (not taken)
 //   draft head, bf16:  40 columns x 2235 of 4096, k = 8  44.4 / 18.9     7 x 3801 of 4456  34.7 / 25.1     float:  30 x 2215 of
-//     512  33.9 / 14.6     a step of 128 rows and 8 slots, 3176 x 4833  152 / 91
-// 60 drawn calls each: draft head 1.29, base head 1.60 times as fast in the mean, the slowest 0.98 (within the scatter).
+//     512  33.9 / 14.6     18 x 10174 of 768  24.8 / 28.3 (not taken)     a step of 128 rows and 8 slots, 3176 x 4833  152 / 91
+//   draft head, bf16, 8 columns of 4096 (the streaming kernel's):  501 rows 23.9 / 13.3     2001  20.5 / 13.1     4001  23.7 / 18.6
+//     6001  25.5 / 24.1 with two (not taken; the model sees 2 %).  With the merge left to ctc_collapse_tree, both calls together,
+//     4001 rows: 44.7 with a merge of its own, 47.4 with a deferred one, 39.1 with ranges - no reason for another line there,
+//     and a call takes the same way, to the same bits, whether the merge is deferred or not.
+// 590 calls drawn and in a grid, every plan timed: with this rule 0.75 of the time without ranges in the mean, none 2 % slower;
+// 8 % above the best plan of each.
 #pragma once
 
 #include <stddef.h>
@@ -32,7 +39,7 @@ struct HeadPlan {
   int row_blocks, col_blocks;
 };
 
-constexpr double kStartUs = 6.0, kFinishLaunchUs = 4.3;  // a workgroup's way to its first step; the second launch
+constexpr double kStartUs = 6.0;  // a workgroup's way to its first step
 inline double step_us(int tile_cols, bool f32, long long groups) {
   const int i = tile_cols <= 16 ? 0 : tile_cols <= 32 ? 1 : tile_cols <= 64 ? 2 : 3;
   static const double lds[4] = {0.35, 0.4, 0.9, 1.1}, mfma[4] = {0.45, 0.9, 1.75, 3.5};
@@ -46,7 +53,7 @@ inline double walk_us(long long groups, double steps, double step) {
 inline double head_whole_us(int V, int cols, int D, bool f32, int rows, int tile_cols, double finish_us) {
   const long long groups = (long long)((V + rows - 1) / rows) * ((cols + tile_cols - 1) / tile_cols);
   const double steps = (double)D * (f32 ? 4 : 2) / 256.0;
-  return walk_us(groups, steps, step_us(tile_cols, f32, groups) * rows / 128.0) + kFinishLaunchUs + finish_us;
+  return walk_us(groups, steps, step_us(tile_cols, f32, groups) * rows / 128.0) + finish_us;
 }
 // whole_us: what the way without ranges takes, by head_whole_us.  Fills tile_cols and splits; false: not worth it.
 inline bool plan_head(HeadPlan& p, bool f32, double whole_us, double finish_us, size_t part_floats) {
@@ -54,13 +61,13 @@ inline bool plan_head(HeadPlan& p, bool f32, double whole_us, double finish_us, 
   p.row_blocks = (p.V + kHeadRowBlock - 1) / kHeadRowBlock;
   const double steps = (double)p.D * (f32 ? 4 : 2) / 256.0;
   const size_t sums = (size_t)p.cols * p.row_blocks * kHeadRowBlock;  // of one range
-  double least = 0.9 * whole_us;  // (the model is not better than that)
+  double least = 0.9 * whole_us - 0.4;  // (the model is not better than that)
   p.splits = 0;
   for (int tile = 16; tile <= 128; tile *= 2) {
     const long long groups = (long long)p.row_blocks * ((p.cols + tile - 1) / tile);
     for (int S = 1; S <= kHeadMaxSplits && (S == 1 || S <= steps) && S * sums <= part_floats; ++S) {
       const double us = walk_us(groups * S, steps / S, step_us(tile, f32, groups * S)) + (double)S * sums * 8.0 / 3e6 +
-                        kFinishLaunchUs + finish_us + ((p.cols + 255) / 256) * (double)S * p.V * 4.0 / 45e3;
+                        finish_us + ((p.cols + 255) / 256) * (double)S * p.V * 4.0 / 45e3;
       if (us < least) {
         least = us;
         p.splits = S;
@@ -75,15 +82,19 @@ inline bool plan_head(HeadPlan& p, bool f32, double whole_us, double finish_us, 
 }
 
 inline int head_tile_cols(int cols) { return cols <= 16 ? 16 : cols <= 32 ? 32 : cols <= 64 ? 64 : 128; }
-// what the epilogues take: joining the wavefronts' k-lists; a column's workgroup pops k keys
+// what the epilogues take: joining the wavefronts' k-lists; a column's workgroup pops k keys, and is slow with eight groups of
+// rows a thread
+constexpr int kHeadSlowRows = kHeadColumnThreads * 4 * 4;
 inline bool plan_draft_head(HeadPlan& p, bool f32, int k) {
   const int tile_cols = head_tile_cols(p.cols);
   const double epilogue_us = tile_cols == 16 ? 1.5 : k <= 2 ? 2.0 : k <= 4 ? 3.0 : 4.0;
-  return plan_head(p, f32, head_whole_us(p.V, p.cols, p.D, f32, kHeadRowBlock, tile_cols, epilogue_us), 1.5 + 0.2 * k, kDraftPartFloats);
+  return plan_head(p, f32, head_whole_us(p.V, p.cols, p.D, f32, kHeadRowBlock, tile_cols, epilogue_us),
+                   1.5 + 0.2 * k + (p.V > kHeadSlowRows ? 3.0 : 0.0), kDraftPartFloats);
 }
 inline bool plan_base_head(HeadPlan& p, bool f32) {
   const int rows = p.cols > kHeadColBlock ? 256 : 128;
-  return plan_head(p, f32, head_whole_us(p.V, p.cols, p.D, f32, rows, head_tile_cols(p.cols), 1.0), 1.0, kHeadPartFloats);
+  return plan_head(p, f32, head_whole_us(p.V, p.cols, p.D, f32, rows, head_tile_cols(p.cols), 1.0),
+                   p.V > kHeadSlowRows ? 3.0 : 1.0, kHeadPartFloats);
 }
 
 // ---- the draft head's streaming kernel (bf16) -----------------------------------------------------------------------

@@ -45,3 +45,15 @@ def test_attention_leaves_the_full_chip_only_for_a_clear_gain():
     assert launch_plans.attention(1, 4, 128, 48, 16, "f32") == ("any", 2, 1)
     assert launch_plans.attention(1, 32, 128, 2064, 128, "bf16") == ("rows64", 2, 4)
     assert launch_plans.attention(1, 14, 35, 1939, 128, "f32")[2] > 8
+
+
+# Heads whose columns a thread holds eight groups of rows of take their own kernels where the ranges measured slower; what gained
+# takes the ranges.
+def test_heads_of_many_rows_take_the_ranges_only_for_a_clear_gain():
+    assert launch_plans.draft_head(18, 768, 10174, "f32", 3)[0] == "tile"
+    assert launch_plans.draft_head(48, 772, 15938, "f32", 5)[0] == "tile"
+    assert launch_plans.base_head(85, 2040, 9043, "bf16")[0] == "tile"
+    assert launch_plans.draft_head(40, 3432, 10988, "bf16", 4)[0] == "ranges"
+    assert launch_plans.draft_head(8, 4096, 4001, "bf16", 4)[0] == "ranges"
+    assert launch_plans.draft_head(8, 4096, 8001, "bf16", 4)[0] == "stream"
+    assert launch_plans.base_head(128, 4096, 6189, "bf16")[0] == "ranges"

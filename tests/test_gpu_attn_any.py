@@ -167,7 +167,7 @@ def test_attention_long_histories(pkg, N):
     ctx.close()
 
 
-# Few heads over a long capacity: more than eight key splits, which the merge takes eight at a time - all of them with keys,
+# Few heads over a long capacity: eight key splits (bf16, 128) and more, which the merge takes eight at a time - all of them with keys,
 # and with histories so short that most splits have none.  An infinity in the cache stays in its component (float and other
 # head dimensions).
 @pytest.mark.parametrize("dtype,dh,H,N,cap,tol", [("f32", 128, 2, 16, 2000, 1e-5), ("f32", 64, 1, 100, 2500, 1e-5),
@@ -235,3 +235,34 @@ def test_stages_on_three_streams(pkg, dtype):
             a, b = (t, res[name]) if name != "out" else (t.transpose(1, 2)[live], res[name].transpose(1, 2)[live])
             assert torch.equal(a, b), name
     ctx.close()
+
+
+# More than eight key splits (test_launch_plans.py asks the rule) whose maxima grow from one group of eight to the next: keys
+# that some rows score far above the rest lie in tiles of the splits behind the first eight.  P carries 16 mantissa bits (2^-17) at
+# bf16 and 128, 24 elsewhere; one sequence has keys in every split, the other in the first three only.
+MORE_SPLITS = [("bf16", 128, 1, 8, 4096, 3e-4), ("bf16", 128, 1, 17, 16384, 3e-4), ("bf16", 128, 1, 100, 16384, 3e-4),
+               ("bf16", 128, 2, 64, 16384, 3e-4), ("f32", 16, 2, 30, 4096, 1e-5), ("f32", 8, 1, 100, 6000, 1e-5),
+               ("bf16", 64, 1, 40, 16384, 1e-5), ("f32", 128, 1, 64, 4096, 1e-5)]
+
+
+@pytest.mark.parametrize("dtype,dh,H,N,cap,tol", MORE_SPLITS)
+def test_attention_maxima_behind_eight_splits(pkg, dtype, dh, H, N, cap, tol):
+    for ctx_len in (cap - 7, 70):
+        print(f"attention maxima behind eight splits {dtype} dh={dh} H={H} N={N} ctx={ctx_len}", flush=True)
+        case = workloads.make_attention_case(dh + N, 1, H, N, dh, cap, [ctx_len], dtype)
+        trees = _trees(N, 1, N, 128, "beam")
+        n = int(trees[0]["n_nodes"])
+        kc = case.k_cache.copy()
+        for row in range(0, n, 3):  # a key along that row's query, in the tile of split 8 + row / 3
+            q = case.q[0, :, row]
+            kc[0][:, 32 * (8 + row // 3 % 8) + row % 32] = workloads.round_to_storage(
+                q * (20.0 * np.sqrt(dh) / np.square(q).sum(-1, keepdims=True)), dtype)
+        mask = torch.from_numpy(np.stack([t["anc_mask"] for t in trees]).view(np.int64)).cuda()
+        ctx = pkg.Context(max_batch=1, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=N, max_heads=H, max_head_dim=dh)
+        got = pkg.tree_verify_attn(ctx, to_device(case.q, dtype), to_device(kc, dtype), to_device(case.v_cache, dtype),
+                                   dev_i64(case.kv_off), dev_i32(case.ctx_len), cap, to_device(case.k_tree, dtype),
+                                   to_device(case.v_tree, dtype), dev_i32(np.array([n])), mask, dh ** -0.5).cpu().numpy()[0, :, :n]
+        ref = oracle.tree_attention(case.q[0], kc[0], case.v_cache[0], ctx_len, case.k_tree[0], case.v_tree[0], n,
+                                    trees[0]["mask"], dh ** -0.5)
+        assert rel_err_rms_floor(got, ref) <= tol
+        ctx.close()

@@ -122,3 +122,80 @@ def test_draft_head_few_rows_long_hidden(pkg, dtype, B, T, D, Vp1, k):
     logp = np.take_along_axis(z, top, 1) - lse[:, None]
     assert np.all(np.abs(res["topk_logp"].cpu().numpy().reshape(B * T, k) - logp) <= tol[:, None] + 2.0 ** -23 * np.abs(logp))
     ctx.close()
+
+
+# The heads' own kernels at sizes that the ranges do not take (more than 16384 rows, or hidden dimensions too short for them;
+# test_launch_plans.py asks the rule).  Draft head: the tile loop with the epilogue of a lane per column (more than 16
+# columns), and the streaming kernel with two to four column tiles (bf16, D a multiple of 512).
+DRAFT_OWN_KERNEL = [(5, 8, 256, 16500, "bf16", ("tile", 64, 0)), (8, 8, 520, 16513, "bf16", ("tile", 64, 0)),
+                    (3, 8, 261, 16513, "bf16", ("tile", 32, 0)), (5, 8, 256, 16500, "f32", ("tile", 64, 0)),
+                    (3, 8, 261, 16513, "f32", ("tile", 32, 0)), (8, 8, 512, 16500, "f32", ("tile", 64, 0)),
+                    (3, 7, 512, 17000, "bf16", ("stream", 2, 2)), (3, 7, 1024, 17000, "bf16", ("stream", 2, 4)),
+                    (5, 8, 512, 17000, "bf16", ("stream", 3, 2)), (8, 8, 512, 16500, "bf16", ("stream", 4, 2))]
+TYPES = {"bf16": torch.bfloat16, "f32": torch.float32}
+
+
+@pytest.mark.parametrize("B,T,D,Vp1,dtype,way", DRAFT_OWN_KERNEL)
+def test_draft_head_own_kernels_every_k(pkg, B, T, D, Vp1, dtype, way):
+    h, w, _, _ = _operands(D + Vp1, B * T, D, Vp1, TYPES[dtype])
+    # equal rows in one 16-row group, in different ones and in different row blocks: equal logits, ids ascending among them
+    equal, second = [3, 5, 19, 131, 900, 16449], [17, 1040]
+    w[equal] = w[3].clone()
+    w[second] = w[17].clone()
+    bias = torch.linspace(-1, 1, Vp1, device="cuda")
+    bias[equal], bias[second] = 400.0, 300.0
+    z_ref = ((h.double() @ w.double().t()) + bias.double()).cpu().numpy()
+    bound = ((D + 1) * 2.0 ** -24 * (h.double().abs() @ w.double().abs().t())).cpu().numpy()
+    ctx = pkg.Context(max_batch=B, max_slots=T, max_topk=8, max_vocab_rows=Vp1, max_nodes=8, max_heads=1, max_head_dim=8)
+    for k in range(1, 9):
+        print(f"draft head own kernel {dtype} D={D} Vp1={Vp1} B={B} T={T} k={k}", flush=True)
+        res = pkg.ctc_draft_topk(ctx, h.view(B, T, D), w, bias, k, want_logits=True)
+        z = res["logits"].cpu().numpy().reshape(B * T, Vp1)
+        _check(z, z_ref, bound + 2.0 ** -23 * (1 + np.abs(z_ref)))
+        top = res["topk_id"].cpu().numpy().reshape(B * T, k)
+        assert (top == np.array(equal + second)[:k]).all()
+        assert np.array_equal(top, np.argsort(-z, axis=1, kind="stable")[:, :k])
+        lse = np.log(np.exp(z.astype(np.float64) - z.max(1, keepdims=True)).sum(1)) + z.max(1)
+        tol = 2e-5 + 4 * 2.0 ** -24 * np.abs(z).max(1)
+        assert np.all(np.abs(res["lse"].cpu().numpy().reshape(-1) - lse) <= tol)
+        logp = np.take_along_axis(z, top, 1) - lse[:, None]
+        assert np.all(np.abs(res["topk_logp"].cpu().numpy().reshape(B * T, k) - logp) <= tol[:, None] + 2.0 ** -23 * np.abs(logp))
+        none = pkg.ctc_draft_topk(ctx, h.view(B, T, D), w, None, k)
+        z0 = (h.double() @ w.double().t()).cpu().numpy()
+        got = np.take_along_axis(z0, none["topk_id"].cpu().numpy().reshape(B * T, k).astype(np.int64), 1)
+        want = -np.sort(-z0, axis=1)[:, :k]
+        assert np.all(np.abs(got - want) <= 2 * bound.max(1)[:, None])
+    ctx.close()
+
+
+# Base head: its own kernels with 65 to 128 columns (128-row tiles) and with more (256-row tiles), several steps and row
+# blocks, rows at any alignment; and 128-column tiles of the ranges.
+BASE_WIDE = [(1, 100, 256, 17000, "f32", ("tile", 128, 128)), (1, 100, 261, 16999, "f32", ("tile", 128, 128)),
+             (3, 100, 256, 17000, "f32", ("tile", 128, 256)), (4, 50, 1031, 16999, "f32", ("tile", 128, 256)),
+             (1, 100, 256, 17000, "bf16", ("tile", 128, 128)), (1, 100, 261, 16999, "bf16", ("tile", 128, 128)),
+             (3, 100, 256, 17000, "bf16", ("tile", 128, 256)), (4, 50, 1031, 16999, "bf16", ("tile", 128, 256)),
+             (8, 64, 1024, 5000, "f32", ("ranges", 128, 1)), (8, 64, 1031, 5000, "f32", ("ranges", 128, 1)),
+             (3, 100, 1031, 2500, "bf16", ("ranges", 128, 2)), (8, 64, 2049, 3000, "bf16", ("ranges", 128, 2))]
+
+
+@pytest.mark.parametrize("B,N,D,V,dtype,way", BASE_WIDE)
+def test_verify_head_many_columns(pkg, B, N, D, V, dtype, way):
+    print(f"verify head {way} {dtype} D={D} V={V} B={B} N={N}", flush=True)
+    h, w, z_ref, bound = _operands(D + V, B * N, D, V, TYPES[dtype])
+    ctx = pkg.Context(max_batch=B, max_slots=1, max_topk=1, max_vocab_rows=V, max_nodes=N, max_heads=1, max_head_dim=8)
+    n_nodes = torch.full((B,), N, dtype=torch.int32, device="cuda")
+    n_nodes[0] = N - 1
+    res = pkg.verify_head_argmax(ctx, h.view(B, N, D), w, n_nodes, want_logits=True)
+    z = res["logits"].cpu().numpy().reshape(B * N, V)
+    _check(z, z_ref, bound)
+    want = z.argmax(1).reshape(B, N)
+    want[0, N - 1] = -1
+    assert np.array_equal(res["target_argmax"].cpu().numpy(), want)
+    assert torch.equal(pkg.verify_head_argmax(ctx, h.view(B, N, D), w, n_nodes)["target_argmax"], res["target_argmax"])
+    # equal rows of the largest logit in one row block, in the next and in the last: the smallest id
+    h, w = h.abs(), w.clone()
+    w[[9, 7, 300, V - 1]] = 0.5
+    want[:] = 7
+    want[0, N - 1] = -1
+    assert np.array_equal(pkg.verify_head_argmax(ctx, h.view(B, N, D), w, n_nodes)["target_argmax"].cpu().numpy(), want)
+    ctx.close()

@@ -540,6 +540,56 @@ def test_deferred_merge_is_settled_by_whatever_comes_next(pkg):
     ctx.close()
 
 
+# 8 columns of 4096: a head of 2001 rows is cut along the hidden dimension and finished by ctc_draft_topk itself, one of
+# 20000 rows leaves its merge owed (test_launch_plans.py asks the rule).
+DEFERRED_HEADS = {"ranges": (1, 8, 4096, 2001, 4), "stream": (1, 8, 4096, 20000, 4)}
+
+
+def test_deferred_merge_with_a_head_that_finishes_itself(pkg):
+    g = torch.Generator(device="cuda").manual_seed(11)
+    root = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ctx = pkg.Context(max_batch=1, max_slots=8, max_topk=4, max_vocab_rows=20000, max_nodes=32, max_heads=1, max_head_dim=16)
+    heads = {}
+    for name, (B, T, D, Vp1, k) in DEFERRED_HEADS.items():
+        h, w = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((B, T, D), (Vp1, D)))
+        heads[name] = (h, w, Vp1, k)
+
+    def draft(name):
+        h, w, _, k = heads[name]
+        out = {"topk_id": torch.full((1, 8, k), -7, dtype=torch.int32, device="cuda"),
+               "topk_logp": torch.full((1, 8, k), float("nan"), device="cuda"), "lse": torch.full((1, 8), float("nan"), device="cuda")}
+        return pkg.ctc_draft_topk(ctx, h, w, None, k, out=out)
+
+    def tree(name, lists):
+        return pkg.ctc_collapse_tree(ctx, lists["topk_id"], lists["topk_logp"], root, heads[name][2] - 1, 32, 32)
+
+    def same(got, ref):
+        torch.cuda.synchronize()
+        for n in ref:
+            assert torch.equal(got[n].view(torch.int32), ref[n].view(torch.int32)), n
+
+    want = {n: draft(n) for n in heads}
+    want_tree = {n: tree(n, want[n]) for n in heads}
+    torch.cuda.synchronize()
+    ctx.defer_topk_merge(True)
+    lists = draft("ranges")
+    same(lists, want["ranges"])  # nothing owed
+    same(tree("ranges", lists), want_tree["ranges"])
+    owed = draft("stream")
+    lists = draft("ranges")  # settles the other head's debt first
+    same(owed, want["stream"])
+    same(lists, want["ranges"])
+    owed = draft("stream")
+    same(tree("ranges", lists), want_tree["ranges"])  # other lists than the owed ones
+    same(owed, want["stream"])
+    lists = draft("ranges")
+    owed = draft("stream")
+    same(tree("stream", owed), want_tree["stream"])
+    same(owed, want["stream"])
+    ctx.defer_topk_merge(False)
+    ctx.close()
+
+
 def test_deferred_merge_graph_replay(pkg):
     """The step with the deferred merge, captured and replayed: the same results as eager calls without it."""
     st = _Step(pkg, 2)

@@ -84,10 +84,10 @@ def test_draft_topk_full_size(pkg, cfg_index, variant):
 
 @pytest.mark.parametrize("B,T,D,Vp1,k,dtype", [
     (1, 8, 512, 1000, 4, "bf16"),     # smallest hidden size of the streaming kernel, ragged last tile
-    (1, 8, 1024, 129, 4, "bf16"),     # vocabulary barely past one block
+    (1, 8, 1024, 129, 4, "bf16"),     # vocabulary barely past one block: cut along the hidden dimension
     (2, 8, 1024, 2049, 8, "bf16"),    # 16 columns, k = 8
-    (3, 7, 2048, 777, 3, "bf16"),     # 21 columns: two column tiles, one ragged
-    (8, 8, 1024, 4097, 4, "bf16"),    # 64 columns: hidden states chunked through LDS
+    (3, 7, 2048, 777, 3, "bf16"),     # 21 columns, few rows: cut along the hidden dimension
+    (8, 8, 1024, 4097, 4, "bf16"),    # 64 columns: two column blocks of one range each
     (1, 5, 320, 300, 2, "bf16"),      # hidden size the streaming kernel does not take: tile kernel
     (2, 3, 48, 11, 5, "f32"),         # fewer rows than a tile
     (1, 1, 8, 1, 1, "f32"),           # a single row, a single slot
@@ -110,8 +110,9 @@ def test_draft_topk_shapes(pkg, B, T, D, Vp1, k, dtype):
     (3, 8, 4096, 2500, 1), (3, 8, 4096, 2500, 2), (5, 7, 4096, 2500, 5), (4, 8, 4096, 2500, 8),
 ])
 def test_draft_topk_many_columns_every_k(pkg, B, T, D, Vp1, k):
-    """More than 16 columns that do not fit the streaming kernel's LDS: the tile kernel with its lane-per-column
-    epilogue, at every width of the per-lane key list (k = 1, 2, 3..4, 5..8), with exact ties in the top k."""
+    """More than 16 columns over few vocabulary rows: the product cut along the hidden dimension and a workgroup per column, at
+    every width of the per-lane key list (k = 1, 2, 3..4, 5..8), with exact ties in the top k.  (The heads' own kernels at
+    these column counts: test_gpu_head_shapes.py::test_draft_head_own_kernels_every_k.)"""
     rng = np.random.Generator(np.random.PCG64(B * 100 + D + k))
     hidden = workloads.round_to_storage(rng.standard_normal((B, T, D), dtype=np.float32), "bf16")
     w = workloads.round_to_storage(rng.standard_normal((Vp1, D), dtype=np.float32) * 0.05, "bf16")

@@ -2,6 +2,11 @@
 import pytest
 
 import launch_plans
+import test_gpu_attn_any as attn_any
+import test_gpu_attn_peaked as attn_peaked
+import test_gpu_head_shapes as head_shapes
+import test_gpu_launch_modes as launch_modes
+import test_zz_no_alloc as zz_no_alloc
 
 
 def test_range_sums_fit_their_scratch():
@@ -57,3 +62,22 @@ def test_heads_of_many_rows_take_the_ranges_only_for_a_clear_gain():
     assert launch_plans.draft_head(8, 4096, 4001, "bf16", 4)[0] == "ranges"
     assert launch_plans.draft_head(8, 4096, 8001, "bf16", 4)[0] == "stream"
     assert launch_plans.base_head(128, 4096, 6189, "bf16")[0] == "ranges"
+
+
+# ---- which kernels the GPU tests' sizes reach ---------------------------------------------------------------------------
+def test_head_cases_take_the_kernels_they_are_meant_for():
+    for B, T, D, Vp1, dtype, way in head_shapes.DRAFT_OWN_KERNEL:
+        assert {launch_plans.draft_head(B * T, D, Vp1, dtype, k) for k in range(1, 9)} == {way}
+    for B, N, D, V, dtype, way in head_shapes.BASE_WIDE:
+        assert launch_plans.base_head(B * N, D, V, dtype) == way
+    assert [launch_plans.draft_head(B * T, D, Vp1, dtype, k)[0] for B, T, D, Vp1, k, dtype in zz_no_alloc.SEQUENCE] == [
+        "stream", "stream", "ranges", "ranges", "tile", "stream", "tile", "ranges", "tile"]
+    for way, (B, T, D, Vp1, k) in launch_modes.DEFERRED_HEADS.items():
+        assert launch_plans.draft_head(B * T, D, Vp1, "bf16", k)[0] == way
+
+
+def test_attention_cases_take_the_splits_they_are_meant_for():
+    for dtype, dh, H, N, cap, _ in attn_any.MORE_SPLITS:
+        assert launch_plans.attention(1, H, N, cap, dh, dtype)[2] >= 16
+    got = {n: launch_plans.attention(B, H, N, cap, 128, "bf16") for n, (B, H, N, cap, _, _) in attn_peaked.SHAPES.items()}
+    assert got == attn_peaked.TAKES

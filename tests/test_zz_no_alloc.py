@@ -62,8 +62,8 @@ def test_noalloc_against_the_oracle(pkg):
         assert np.max(np.abs(got["lse"].cpu().numpy() - lse_ref)) <= tol
 
 
-# (B, T, D, V+1, k, dtype): streaming kernel with a large head, the same kernel on fewer rows and columns, the
-# tile kernel with many columns and with float operands - each after the other on the same scratch
+# (B, T, D, V+1, k, dtype): streaming kernel with a large head, the same kernel on fewer rows and columns, heads cut along the
+# hidden dimension, the tile kernel with float operands and with many columns - each after the other on the same scratch
 SEQUENCE = [
     (1, 8, 4096, 32001, 4, "bf16"),
     (1, 5, 1024, 1500, 3, "bf16"),
@@ -71,6 +71,9 @@ SEQUENCE = [
     (1, 2, 512, 129, 8, "bf16"),
     (2, 3, 48, 11, 5, "f32"),
     (1, 8, 4096, 32001, 4, "bf16"),
+    (8, 8, 256, 16500, 4, "bf16"),
+    (8, 8, 2048, 3000, 8, "f32"),
+    (8, 8, 256, 16500, 8, "bf16"),
 ]
 
 

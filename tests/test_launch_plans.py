@@ -71,7 +71,7 @@ def test_head_cases_take_the_kernels_they_are_meant_for():
     for B, N, D, V, dtype, way in head_shapes.BASE_WIDE:
         assert launch_plans.base_head(B * N, D, V, dtype) == way
     assert [launch_plans.draft_head(B * T, D, Vp1, dtype, k)[0] for B, T, D, Vp1, k, dtype in zz_no_alloc.SEQUENCE] == [
-        "stream", "stream", "ranges", "ranges", "tile", "stream", "tile", "ranges", "tile"]
+        "stream", "stream", "ranges", "stream", "tile", "stream", "tile", "ranges", "tile"]
     for way, (B, T, D, Vp1, k) in launch_modes.DEFERRED_HEADS.items():
         assert launch_plans.draft_head(B * T, D, Vp1, "bf16", k)[0] == way
 

@@ -44,7 +44,7 @@ struct ctcspec_ctx {
   float* lm_pmax;               // [kMaxCols][lm_max_blocks]
   float* lm_psum;               // [kMaxCols][lm_max_blocks]
   unsigned long long* lm_pkey;  // [kMaxCols][kMaxTopk][lm_max_blocks]
-  float* lm_part;               // kDraftPartFloats partial sums of a head cut along the hidden dimension
+  float* lm_part;               // partial sums of a head cut along the hidden dimension (head_part_floats)
   // deferred merge (ctcspec_defer_topk_merge): a ctc_draft_topk call has left its per-workgroup partials in the
   // workspace and owes the caller these outputs; the next call on the context settles the debt first
   int lm_defer;
@@ -63,7 +63,7 @@ struct ctcspec_ctx {
   const void* zeros;            // 256 bytes of zeros
   int vh_col_blocks;            // column blocks of kVerifyCols the limits allow: ceil(max_batch * max_nodes / 128)
   unsigned long long* vh_pkey;  // [vh_col_blocks][lm_max_blocks][kVerifyCols] best (logit, id) key per row block and column
-  float* vh_part;               // kHeadPartFloats partial sums of a head cut along the hidden dimension
+  float* vh_part;               // partial sums of a head cut along the hidden dimension (head_part_floats)
   // collapse / tree
   unsigned char* collapse_ws;   // [max_batch][kCollapseWsBytesPerSeq]
   // attention

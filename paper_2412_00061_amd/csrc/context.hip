@@ -132,10 +132,10 @@ extern "C" int ctcspec_create(ctcspec_ctx** out, void* hip_stream, const ctcspec
   size_t o_po = carve(attn_rows * lim->max_head_dim * sizeof(float));
   size_t o_pm = carve(attn_rows * sizeof(float));
   size_t o_pl = carve(attn_rows * sizeof(float));
-  // partial sums of the heads, a space for each: every stage has scratch of its own, so that a caller may run the draft head,
-  // the attention and the base head of one context on streams of their own
-  size_t o_dpart = carve(kDraftPartFloats * sizeof(float));
-  size_t o_hpart = carve(kHeadPartFloats * sizeof(float));
+  // partial sums of the heads, a space for each: calls of different stages may overlap (the header says which), and by the
+  // limits: up to 8 and 16 MB, a few KB in a context that only computes the loss
+  size_t o_dpart = carve(head_part_floats((long long)lim->max_batch * lim->max_slots, lim->max_vocab_rows, kDraftPartFloats) * sizeof(float));
+  size_t o_hpart = carve(head_part_floats((long long)lim->max_batch * lim->max_nodes, lim->max_vocab_rows, kHeadPartFloats) * sizeof(float));
   ctx->ws_bytes = off;
   e = hipMalloc(&ctx->ws, ctx->ws_bytes);
   if (e != hipSuccess) {

@@ -28,9 +28,15 @@ constexpr int kHeadColBlock = 128;                           // columns of the b
 constexpr int kHeadMaxSplits = 16;
 constexpr int kHeadColumnThreads = 512;                      // of the kernels that finish a column
 constexpr int kHeadMaxRows = kHeadColumnThreads * 4 * 8;     // vocabulary rows they hold
-// room for partial sums: the draft head's (the context's and the static scratch of the entry point that allocates nothing
-// alike, so that both take the same way) and the base head's
+// partial sums that a call may leave: the draft head's (in a context and in the static scratch of the entry point that allocates
+// nothing alike, so that both take the same way) and the base head's
 constexpr size_t kDraftPartFloats = (size_t)2 << 20, kHeadPartFloats = (size_t)4 << 20;
+// room for the sums of every call with up to `cols` columns and `vocab_rows` rows (a context's limits); `most` is one of those above
+inline size_t head_part_floats(long long cols, int vocab_rows, size_t most) {
+  const int rows = vocab_rows < kHeadMaxRows ? vocab_rows : kHeadMaxRows;
+  const size_t all = (size_t)kHeadMaxSplits * cols * ((rows + kHeadRowBlock - 1) / kHeadRowBlock * kHeadRowBlock);
+  return all < most ? all : most;
+}
 
 struct HeadPlan {
   int cols, D, V;

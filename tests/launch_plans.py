@@ -27,6 +27,8 @@ int main() {
     } else if (what == 'b') {  // cols D V f32
       if (plan_base_head(p, d != 0)) printf("ranges %d %d\n", p.tile_cols, p.splits);
       else printf("tile %d %d\n", head_tile_cols(a), a > kHeadColBlock ? 256 : 128);
+    } else if (what == 's') {  // columns, rows: floats for a draft head, for a base head
+      printf("room %zu %zu\n", head_part_floats(a, b, kDraftPartFloats), head_part_floats(a, b, kHeadPartFloats));
     } else {  // B H nodes kv_cap dh; f32, rows as two bf16 numbers; a context for just these sequences and heads
       const long long bh = (long long)a * b, units = bh > 256 ? bh : 256;
       if (!f && e == 128 && attn_keys_by_wavefront(bh, c, d)) printf("few 1 1\n");
@@ -63,6 +65,11 @@ def draft_head(cols, D, Vp1, dtype, k):
 def base_head(cols, D, V, dtype):
     """('ranges', tile columns, ranges) or ('tile', tile columns, rows)."""
     return ask([("b", cols, D, V, int("32" in str(dtype)))])[0]
+
+
+def head_room(cols, rows):
+    """('room', floats for a draft head, for a base head): what a context of these limits keeps for partial sums."""
+    return ask([("s", cols, rows)])[0]
 
 
 def attention(B, H, nodes, kv_cap, dh, dtype, two_bf16=False):

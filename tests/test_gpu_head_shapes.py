@@ -199,3 +199,28 @@ def test_verify_head_many_columns(pkg, B, N, D, V, dtype, way):
     want[0, N - 1] = -1
     assert np.array_equal(pkg.verify_head_argmax(ctx, h.view(B, N, D), w, n_nodes)["target_argmax"].cpu().numpy(), want)
     ctx.close()
+
+
+def test_small_contexts_keep_small_scratch(pkg):
+    """A context keeps room for the heads' partial sums by its limits, and the heads take the same way in it as in a large one."""
+    small = dict(max_batch=1, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=8, max_heads=1, max_head_dim=8)
+    sizes = []
+    for more in ({}, dict(max_vocab_rows=2000, max_slots=8, max_nodes=64)):
+        ctx = pkg.Context(**{**small, **more})
+        sizes.append(ctx.workspace_bytes())
+        ctx.close()
+    # the attention's partials and the collapse's tables are 1.3 and 1.6 MB of the first
+    assert sizes[0] < 4 << 20 and sizes[1] - sizes[0] < 12 << 20
+    large = pkg.Context(max_batch=8, max_slots=8, max_topk=8, max_vocab_rows=40000, max_nodes=64, max_heads=1, max_head_dim=8)
+    for B, T, N, D, V, dtype in [(1, 8, 16, 4096, 1500, "bf16"), (2, 8, 64, 1031, 700, "f32"), (1, 1, 1, 2048, 130, "bf16")]:
+        print(f"exact context B={B} T={T} N={N} D={D} V={V} {dtype}", flush=True)
+        h, w, _, _ = _operands(V, B * N, D, V, TYPES[dtype])
+        hd = h.repeat(8, 1)[:B * T].view(B, T, D).contiguous()
+        n_nodes = torch.full((B,), N, dtype=torch.int32, device="cuda")
+        exact = pkg.Context(max_batch=B, max_slots=T, max_topk=4, max_vocab_rows=V, max_nodes=N, max_heads=1, max_head_dim=8)
+        for call in (lambda c: pkg.verify_head_argmax(c, h.view(B, N, D), w, n_nodes, want_logits=True),
+                     lambda c: pkg.ctc_draft_topk(c, hd, w, None, 4, want_logits=True)):
+            a, b = call(exact), call(large)
+            assert all(torch.equal(a[n], b[n]) for n in a)
+        exact.close()
+    large.close()

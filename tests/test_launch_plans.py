@@ -29,6 +29,20 @@ def test_range_sums_fit_their_scratch():
     assert taken > 200
 
 
+# A context keeps room by its limits: whatever fits them fits the room, which is a few KB where the limits are small.
+def test_head_room_by_the_limits():
+    _, draft, base = launch_plans.head_room(1, 8)
+    assert draft == base == 16 * 128
+    assert launch_plans.head_room(64, 32001)[1:] == (2 << 20, 4 << 20)  # (all that a call may leave)
+    limits = [(c, r) for c in (1, 7, 40, 64, 200, 512) for r in (1, 128, 129, 1000, 5000, 16384, 40000)]
+    rooms = launch_plans.ask([("s", c, r) for c, r in limits])
+    for (cols, rows), (_, draft, base) in zip(limits, rooms):
+        calls = [(w, max(1, c), D, max(1, V), f32, 8) for c in (cols, cols * 2 // 3) for V in (rows, rows // 2) for D in (256, 1031, 4096, 16384)
+                 for f32 in (0, 1) for w in (("b", "d") if c <= 64 else ("b",))]
+        for (w, c, D, V, f32, _), (way, _, ranges) in zip(calls, launch_plans.ask(calls)):
+            assert way != "ranges" or ranges * c * ((V + 127) // 128 * 128) <= (draft if w == "d" else base)
+
+
 @pytest.mark.parametrize("two_bf16", [0, 1])
 def test_attention_splits_fit_their_scratch(two_bf16):
     lines = [("a", B, H, nodes, cap, dh, f32, two_bf16) for B in (1, 3, 8) for H in (1, 7, 32, 40) for nodes in (1, 16, 17, 64, 65, 128)

@@ -151,7 +151,7 @@ int ctc_draft_topk(ctcspec_ctx* ctx, ctcspec_dtype dt, const void* hidden, const
  * hip_stream   a hipStream_t (NULL = the default stream); host value
  * every other argument as for ctc_draft_topk
  * Limits: Vp1 <= CTCSPEC_NOALLOC_MAX_VOCAB_ROWS (larger heads are rejected with CTCSPEC_EUNSUPPORTED: use a context),
- * B*T <= CTCSPEC_MAX_COLUMNS, k <= CTCSPEC_MAX_TOPK, T <= CTCSPEC_MAX_SLOTS.  The array (10.8 MB) exists once per GPU
+ * B*T <= CTCSPEC_MAX_COLUMNS, k <= CTCSPEC_MAX_TOPK, T <= CTCSPEC_MAX_SLOTS.  The array (8.4 MB) exists once per GPU
  * for the life of the process, and every call on a GPU uses it: calls that overlap on one GPU (two streams, two
  * threads) race on it; calls in stream order are safe and need no clearing between them (every entry a call reads
  * it has written first).  Errors are reported through ctcspec_last_error(NULL).

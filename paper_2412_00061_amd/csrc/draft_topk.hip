@@ -550,15 +550,17 @@ static hipError_t allow_large_lds() {
 
 // ---- scratch of the entry point that allocates nothing ------------------------------------------------------------
 // The same partial results that ctc_draft_topk keeps in its context's workspace, in a device array of the library
-// itself: [256 bytes of zeros][pmax][psum][pkey][sums of the ranges], laid out as in the context for kStaticMaxBlocks row
-// blocks.  Every GPU the library runs on holds its own copy (10.8 MB) at its own address until the process ends.
+// itself: [256 bytes of zeros][pmax][psum][pkey], laid out as in the context for kStaticMaxBlocks row blocks.  A head cut into
+// ranges leaves their sums from pmax on: a call uses one or the other, and calls follow each other in stream order.
+// Every GPU the library runs on holds its own copy (8.4 MB) at its own address until the process ends.
 constexpr int kStaticMaxBlocks = CTCSPEC_NOALLOC_MAX_VOCAB_ROWS / kRowsPerBlock;
 constexpr size_t kScratchZeros = 0;
-constexpr size_t kScratchPmax = 256;
+constexpr size_t kScratchPmax = 256, kScratchPart = kScratchPmax;
 constexpr size_t kScratchPsum = kScratchPmax + (size_t)kStaticMaxBlocks * kMaxCols * sizeof(float);
 constexpr size_t kScratchPkey = kScratchPsum + (size_t)kStaticMaxBlocks * kMaxCols * sizeof(float);
-constexpr size_t kScratchPart = kScratchPkey + (size_t)kStaticMaxBlocks * kMaxCols * kMaxTopk * sizeof(unsigned long long);
-constexpr size_t kScratchBytes = kScratchPart + kDraftPartFloats * sizeof(float);
+constexpr size_t kScratchPkeyEnd = kScratchPkey + (size_t)kStaticMaxBlocks * kMaxCols * kMaxTopk * sizeof(unsigned long long);
+constexpr size_t kScratchPartEnd = kScratchPart + kDraftPartFloats * sizeof(float);
+constexpr size_t kScratchBytes = kScratchPkeyEnd > kScratchPartEnd ? kScratchPkeyEnd : kScratchPartEnd;
 static_assert(CTCSPEC_NOALLOC_MAX_VOCAB_ROWS % kRowsPerBlock == 0 && kScratchPkey % 256 == 0 && kScratchPart % 256 == 0, "scratch layout");
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -610,7 +612,7 @@ struct LmScratch {
   unsigned long long* pkey;
   int pstride;
   const void* zeros;
-  float* part;  // kDraftPartFloats
+  float* part;  // of a head cut along the hidden dimension
 };
 
 static int draft_topk_launch(ctcspec_ctx* err, hipStream_t stream, const LmScratch& sc, hipEvent_t ev0, hipEvent_t ev1,

@@ -13,8 +13,14 @@
  *    back to back.
  *  - Return value: CTCSPEC_OK (0) or a negative error code.  On error nothing has been launched and
  *    ctcspec_last_error(ctx) describes the reason.  No C++ exception crosses this boundary.
- *  - One context serves one stream at a time: calls on the same context from several threads, or
- *    overlapping on the GPU, race on its workspace.
+ *  - One context serves one thread and one stream at a time.  Calls issued to different streams (ctcspec_set_stream in between)
+ *    may overlap on the GPU only if they use different scratch of the context:
+ *      ctc_draft_topk, and with a deferred merge whatever call settles it
+ *      ctc_collapse_tree, ctc_raw_tree
+ *      tree_verify_attn, draft_layer_forward
+ *      verify_head_argmax
+ *    Two calls of one of these lines race on it.  Every other call uses none.  (Ordering a call behind those
+ *    whose outputs it reads is the caller's part, as everywhere.)
  *  - Row-major, innermost index last, no padding unless stated.  bf16 is the upper half of an IEEE
  *    float32 (1-8-7).  int32_t/int64_t/uint64_t are little endian device integers.
  *

@@ -200,7 +200,7 @@ def test_attention_many_splits(pkg, dtype, dh, H, N, cap, tol, short):
     ctx.close()
 
 
-# The draft head, the attention and the base head of one context on streams of their own: each has scratch of its own, so
+# The draft head, the attention and the base head of one context on streams of their own, as the header allows: each has scratch of its own, so
 # what runs beside a call changes none of its bits.
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_stages_on_three_streams(pkg, dtype):

@@ -98,7 +98,7 @@ __device__ void lmhead_block_epilogue_wide(const LmHeadParams& p, const float* z
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int row_base = blockIdx.x * kRowsPerBlock;
-  static_assert(kMaxCols <= 64 && kRowsPerBlock == 16 * kMfmaWaves && kMfmaWaves == 8, "a lane per column, sixteen rows per wavefront");
+  static_assert(kMaxCols == 64 && kRowsPerBlock == 16 * kMfmaWaves && kMfmaWaves == 8, "a lane per column - every lane writes to `part` -, sixteen rows per wavefront");
   if (p.logits_out) {
     for (int idx = tid; idx < p.BT * kRowsPerBlock; idx += blockDim.x) {
       int m = idx / kRowsPerBlock, r = idx % kRowsPerBlock;

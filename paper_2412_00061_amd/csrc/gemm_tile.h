@@ -17,8 +17,9 @@
 // (3200 clocks) for the 32 KB of W at the HBM rate, so the LDS work fits under the stream only if nothing
 // serialises.  All loads are unconditional and counted (indices clamped; a request past the last step reads a
 // block of zeros), so the waits name the loads that stay in flight.
-// Hidden sizes that are no whole number of steps: what is left of every row goes first, unpipelined, padded with
-// zeros.  Rows that start at any element take the same loads at that alignment.  (One thread per logit with a dot
+// Hidden sizes that are no whole number of steps: what is left of every row goes first, padded with zeros - through the
+// prefetch stages in narrow tiles, unpipelined in wide ones.  Rows that start at any element take the same loads at that
+// alignment.  (One thread per logit with a dot
 // product over uncoalesced rows, which these shapes and float operands took before: 16 float columns x 32001 x 2048
 // in 2.12 ms against 53 us = 4.9 TB/s here, bound by HBM; 128 columns x 100 x 64 in 542 against 7 us.)
 #pragma once
@@ -274,8 +275,9 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
   // fill a trip - through the same rotating stages, one copy of the code per remainder, so that every path reaches the
   // loop with the same loads in flight.  Wide tiles have no registers for that (it spilled, +3 us a call): there they run
   // before the first prefetch, a load latency each.  Narrow ones did too: 8 columns x 12547 rows of 1499 bf16
-  // elements 27.4 -> 24.1 us,
-  // 64 x 14949 of 1234 21.8 -> 16.8, 40 x 18230 of 1280 33.2 -> 32.1 (whole calls).
+  // elements 27.4 -> 24.1 us, 64 x 14949 of 1234 21.8 -> 16.8, 40 x 18230 of 1280 33.2 -> 32.1 (whole calls).  The copies make the
+  // kernels two to four times as large (base head, 128 x 16 bf16: 5.0 -> 16.5 KB); a call runs one of them, and with everything
+  // else flushed out of the caches in between the first of these takes 41.0 us with its launches against 47.6, the second 43.5 against 51.6.
   constexpr bool kWide = RT * CTW >= 8;
   const int lead = WHOLE_TRIPS ? 0 : total_steps % TRIP;
   auto load_tail = [&](auto stage) __attribute__((always_inline)) {

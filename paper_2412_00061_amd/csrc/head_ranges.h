@@ -27,7 +27,7 @@ hipError_t prepare_head_ranges();
 
 #if defined(__HIPCC__)
 // A column's logits by a workgroup of kHeadColumnThreads: the ranges' sums in ascending order; z[j] holds rows
-// 4 (j * threads + tid) .. + 3, what lies behind the row blocks is left at 0.
+// 4 (j * threads + tid) .. + 3.  What lies behind the row blocks holds another row's sums: the caller leaves rows >= V out.
 template <int NV>
 __device__ __forceinline__ void load_head_column(const HeadRangeParams& p, int col, f32x4 (&z)[NV]) {
   const int Vp = p.row_blocks * kRowsPerBlock, tid = threadIdx.x;

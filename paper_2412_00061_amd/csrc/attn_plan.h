@@ -58,8 +58,10 @@ inline double iterations(int kv_cap, int max_nodes, int S, int per_iter) {
   return n > 1.0 ? n : 1.0;
 }
 // bf16, head dimension 128.  Blocks of 64 rows take two tiles an iteration (0.9 us; 1.1 when two blocks share the keys),
-// blocks of 128 one (0.88 us; 0.52 with a single live row group, whose partials are 16 rows).  slots: units of 128 rows that
-// the workspace holds.
+// blocks of 128 one (0.88 us; 0.52 with a single live row group, whose partials are 16 rows).  Of the 155 drawn shapes that come
+// here, 0.78 to 0.95 us make no difference in the mean (0.1 %) and none is 4 % slower than the filled chip with 0.78 to 0.88;
+// the larger value serves equal histories, where two blocks are ahead (64 heads, 128 rows, 684 positions: 18.8 against 19.5).
+// slots: units of 128 rows that the workspace holds.
 inline AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long long slots, bool two_bf16) {
   const long long bh = (long long)B * H;
   const int key_tiles = (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys;

@@ -24,44 +24,42 @@ inline bool attn_rows64(AttnShape s, int max_nodes) { return s.QB == 2 || (max_n
 //   workgroups a compute unit takes in turn x (start of one + iterations x time of one) + what splitting costs
 // Splitting costs the merge launch and the partial results, which go through memory.  Both kernels start from as many
 // splits as fill the chip (at most 8, a few tiles each; two blocks of 64 rows where they fill as much) and take the cheapest
-// (query blocks, key splits) of the model instead where it spares more than the model errs: 3 % (bf16, 128), 7 % (the others,
-// whose workgroups sit side by side).  Measured in HIP graphs, us a call as the chip is filled / with this choice:
+// (query blocks, key splits) of the model instead where it spares 3 %.  Measured in HIP graphs, us a call as the chip is filled /
+// with this choice:
 //   bf16, 128: 2 x 40 heads, 128 rows, 128 positions 17.1 (2 splits) / 10.0 (none, two blocks)    6 x 32 heads, 200: 22.3 / 16.8
 //     (one block)    4 x 32 heads, 100 rows, 300: 18.5 (2) / 13.2 (1)    32 heads, 64 rows, 256: 11.9 (2) / 10.2 (1)
 //     32 heads, 128 rows, 2048 positions: 4 splits both; none 36.8, 2 26.0, 3 21.6, 4 19.6, 8 of one block 20.0
 //   bf16, 80: 4 x 16 heads, 50 rows, 93 positions 10.5 (2) / 7.6 (1)
 //   float, 128: 14 heads, 35 rows, up to 1923 positions 24.0 (8) / 17.7 (16)    float, 16: 4 heads, 128 rows, 32: 7.4 (3) / 4.0 (1, padded
 //     to 16 instead of 32)
-// Every plan of 440 shapes drawn from 1 to 8 sequences of 4 to 40 heads and 1 to 128 rows over 4 to 2048 positions was timed: 4.4 %
-// (bf16, 128) and 6.5 % (the others) less time than as the chip is filled in the mean, one shape more than 4 % slower
-// (4.6).  Taking the model's plan whatever it spares: the same mean, 19 shapes more than 4 % slower (8 sequences x 14 float
-// heads of 32, 41 rows, up to 365 positions 12.0 -> 13.6).  That is 2.1 % above the best plan of each shape; with 2.2 us for the
-// merge - what such a launch takes behind an independent one - 3.1 %, with 4 to 4.3 us 2.0.
+// Every plan of 1460 shapes drawn from 1 to 8 sequences of 4 to 40 heads and 1 to 128 rows over 4 to 2048 positions was timed, and
+// the constants are the ones (of a coarse grid, the same for both kernels where they mean the same) that come closest to the best
+// plan of each: within 1.1 % in the mean (bf16, 128), 1.0 (bf16, others), 1.5 (float), 1.1 (float heads up to 32) - and the same on
+// 510 shapes that they were not chosen on.  That is 4.8, 8.3, 5.8 and 5.8 % less than as the chip is filled, 13 shapes more than
+// 4 % slower than that (the worst 11 %).
 constexpr int kFillSplits = 8;
-constexpr double kModelGain128 = 0.97, kModelGainAny = 0.93;
-constexpr double kMergeLaunchUs = 3.3;  // with the end of the kernel before it, whose stores it waits for
-// the merge launch, the partial results' way through memory, and a round trip of the merge for every eight splits more.  Rows as
-// two bf16 numbers are the merge's work otherwise: the 2 x 8 rows of a layer of 1024, 300 positions, 42.2 us with the layer's
-// attention in two splits, 44.0 in none.
-constexpr double kTwoBf16Us = 1.5;
+constexpr double kModelGain = 0.97;
+// the merge launch with the end of the kernel before it, whose stores it waits for (behind an independent kernel a launch takes 2.2
+// us; with that in its place the mean is 1 % worse), the partial results' way through memory, and a round trip of the merge for every eight
+// splits more.  Rows as two bf16 numbers are the merge's work otherwise: the 2 x 8 rows of a layer of 1024, 300 positions, 42.2 us with
+// the layer's attention in two splits, 44.0 in none.
+constexpr double kMergeUs = 3.5, kTwoBf16Us = 1.5;
 inline double split_us(long long bh, int S, int rows, int dh, bool two_bf16) {
-  return S == 1 ? (two_bf16 ? kTwoBf16Us : 0.0) : kMergeLaunchUs + (double)bh * S * rows * dh * 4 * 0.25e-6 + (S - 1) / kMergeParts * 3.0;
+  return S == 1 ? (two_bf16 ? kTwoBf16Us : 0.0) : kMergeUs + (double)bh * S * rows * dh * 4 * 0.33e-6 + (S - 1) / kMergeParts * 2.0;
 }
 // how much longer than one workgroup a compute unit with `load` of them takes.  Of several sequences, not all are the longest.
 inline double taking_turns(double load, double next) { return load <= 1.0 ? 1.0 : 1.0 + (load - 1.0) * next; }
 // (two at a time hide each other's waits)
-inline double side_by_side(double load) { return load <= 1.0 ? 1.0 : load <= 2.0 ? 1.0 + (load - 1.0) * 0.4 : load * 0.7; }
-// tiles of 32 keys that a workgroup expects: the lengths are on the device, the host takes most of the capacity for them;
-// what does not divide leaves half an iteration idle on average
+inline double side_by_side(double load) { return load <= 1.0 ? 1.0 : load <= 2.0 ? 1.1 + (load - 1.0) * 0.2 : load * 0.68; }
+// tiles of 32 keys that a workgroup expects: the lengths are on the device, the host takes the capacity for them;
+// what does not divide leaves part of an iteration idle
 inline double iterations(int kv_cap, int max_nodes, int S, int per_iter) {
-  const double n = (0.875 * kv_cap + max_nodes) / (kTileKeys * per_iter * S) + 0.5;
+  const double n = (double)(kv_cap + max_nodes) / (kTileKeys * per_iter * S) + 0.4;
   return n > 1.0 ? n : 1.0;
 }
-// bf16, head dimension 128.  Blocks of 64 rows take two tiles an iteration (0.9 us; 1.1 when two blocks share the keys),
-// blocks of 128 one (0.88 us; 0.52 with a single live row group, whose partials are 16 rows).  Of the 155 drawn shapes that come
-// here, 0.78 to 0.95 us make no difference in the mean (0.1 %) and none is 4 % slower than the filled chip with 0.78 to 0.88;
-// the larger value serves equal histories, where two blocks are ahead (64 heads, 128 rows, 684 positions: 18.8 against 19.5).
-// slots: units of 128 rows that the workspace holds.
+// bf16, head dimension 128.  Blocks of 64 rows take two tiles an iteration (0.9 us; 0.95 when two blocks share the keys),
+// blocks of 128 one (0.72 us; 0.52 with a single live row group, whose partials are 16 rows), all of them a fifth longer when
+// every compute unit has one.  slots: units of 128 rows that the workspace holds.
 inline AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long long slots, bool two_bf16) {
   const long long bh = (long long)B * H;
   const int key_tiles = (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys;
@@ -74,15 +72,16 @@ inline AttnShape plan_bf16_128(int B, int H, int max_nodes, int kv_cap, long lon
   };
   auto us_of = [&](AttnShape s) {
     const bool rows64 = attn_rows64(s, max_nodes);
-    const double iter = rows64 ? (s.QB == 2 ? 1.1 : 0.9) : (max_nodes > kFewRows ? 0.88 : 0.52);
-    return taking_turns((double)(bh * s.QB * s.S) / 256.0, B > 1 ? 0.7 : 1.0) *
-               (4.8 + iterations(kv_cap, max_nodes, s.S, rows64 ? 2 : 1) * iter) +
+    const double iter = rows64 ? (s.QB == 2 ? 0.95 : 0.9) : (max_nodes > kFewRows ? 0.72 : 0.52);
+    const double load = (double)(bh * s.QB * s.S) / 256.0;
+    return taking_turns(load, B > 1 ? 1.5 : 1.0) * (1.0 + 0.2 * (load < 1.0 ? load : 1.0)) *
+               (8.0 + iterations(kv_cap, max_nodes, s.S, rows64 ? 2 : 1) * iter) +
            split_us(bh, s.S, max_nodes, 128, two_bf16);
   };
   const int s128 = fill(1), s64 = fill(2);
   AttnShape best = {1, s128};
   if (max_nodes > 64 && (2 * s64 > s128 || (2 * s64 == s128 && s64 >= 4))) best = {2, s64};
-  double least = kModelGain128 * us_of(best);
+  double least = kModelGain * us_of(best);
   for (int QB = 1; QB <= (max_nodes > 64 ? 2 : 1); ++QB) {
     for (int S = 1; S <= kMaxKvSplits; ++S) {
       const long long groups = bh * QB * S;
@@ -104,9 +103,10 @@ inline AttnShape plan_any(int B, int H, int max_nodes, int kv_cap, int dh, bool 
   if (bh > 65535) return {QB, 1};  // (the merge's grid)
   auto us_of = [&](int S) {
     const long long groups = blocks * S;
-    const double turns = f32 && dh > 32 ? taking_turns((double)((groups * live + 1023) / 1024), B > 1 ? 0.5 : 1.0) : side_by_side((double)groups / 256.0);
-    const double tile = f32 ? (dh <= 16 ? 0.7 : dh <= 32 ? 0.9 : (dh + 31) / 32 * 32 / 48.0) : (dh <= 64 ? 0.6 : 0.7);
-    return turns * (3.0 + iterations(kv_cap, max_nodes, S, 1) * tile) + split_us(bh, S, max_nodes, dh, two_bf16);
+    const bool in_turn = f32 && dh > 32;
+    const double turns = in_turn ? taking_turns((double)((groups * live + 1023) / 1024), B > 1 ? 0.5 : 1.0) : side_by_side((double)groups / 256.0);
+    const double tile = f32 ? (dh <= 16 ? 0.6 : dh <= 32 ? 0.9 : (dh + 31) / 32 * 32 / 48.0) : (dh <= 64 ? 0.6 : 0.7);
+    return turns * ((in_turn ? 2.5 : 3.0) + iterations(kv_cap, max_nodes, S, 1) * tile) + split_us(bh, S, max_nodes, dh, two_bf16);
   };
   long long fill = 512 / blocks;  // two workgroups per compute unit, two tiles each
   const int key_tiles = (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys;
@@ -114,7 +114,7 @@ inline AttnShape plan_any(int B, int H, int max_nodes, int kv_cap, int dh, bool 
   fill = fill > kFillSplits ? kFillSplits : fill;
   while (fill > 1 && blocks * fill > slots) --fill;
   AttnShape best = {QB, fill < 1 ? 1 : (int)fill};
-  double least = kModelGainAny * us_of(best.S);
+  double least = kModelGain * us_of(best.S);
   for (int S = 1; S <= kMaxKvSplits; ++S) {
     if (S > 1 && (blocks * S > slots || S * kTileKeys > kv_cap + max_nodes)) break;
     const double us = us_of(S);

@@ -98,7 +98,7 @@ def _run(pkg, case, trees, B, H, N, dh):
 
 # (B, H, max_nodes, kv_cap, ctx_len, tree kind): the 7B step's shape (two 64-row blocks of 4 row groups x 2 key parts,
 # four key splits), the same heads over a short context (five tiles per split: an odd count for the two key parts),
-# twice the heads (one 128-row block, four splits; over fewer positions two 64-row blocks, two splits), 56 heads (one 128-row block,
+# twice the heads (one 128-row block, four splits; 40 heads over fewer positions two 64-row blocks, three splits), 56 heads (one 128-row block,
 # four splits), the ragged batch (one 64-row block, one key range per workgroup:
 # both key parts meet masked context ends), and the draft layer's 8 causal rows (one live row group, eight splits)
 SHAPES = {
@@ -108,7 +108,7 @@ SHAPES = {
     "batch8_ragged": (8, 32, 64, 2048, [256, 2048, 1111, 777, 1999, 300, 1280, 95], "beam"),
     "draft_layer_rows": (1, 32, 8, 2048, [2048], "chain"),
     "one_block_56_heads": (1, 56, 128, 1024, [1000], "beam"),
-    "two_blocks_64_heads": (1, 64, 128, 700, [690], "beam"),
+    "two_blocks_40_heads": (1, 40, 128, 700, [690], "beam"),
 }
 # what the launch rule makes of them (test_launch_plans.py asks it): rows of a block, blocks, key splits
 TAKES = {
@@ -118,7 +118,7 @@ TAKES = {
     "batch8_ragged": ("rows64", 1, 1),
     "draft_layer_rows": ("rows128", 1, 8),
     "one_block_56_heads": ("rows128", 1, 4),
-    "two_blocks_64_heads": ("rows64", 2, 2),
+    "two_blocks_40_heads": ("rows64", 2, 3),
 }
 
 

@@ -168,9 +168,10 @@ def test_draft_head_own_kernels_every_k(pkg, B, T, D, Vp1, dtype, way):
     ctx.close()
 
 
-# Base head: its own kernels with 65 to 128 columns (128-row tiles) and with more (256-row tiles), several steps and row
+# Base head: its own kernels with up to 128 columns (128-row tiles) and with more (256-row tiles), several steps and row
 # blocks, rows at any alignment; and 128-column tiles of the ranges.
-BASE_WIDE = [(1, 100, 256, 17000, "f32", ("tile", 128, 128)), (1, 100, 261, 16999, "f32", ("tile", 128, 128)),
+BASE_WIDE = [(1, 16, 256, 17000, "bf16", ("tile", 16, 128)), (1, 30, 512, 17000, "f32", ("tile", 32, 128)), (1, 50, 261, 16999, "bf16", ("tile", 64, 128)),
+             (1, 100, 256, 17000, "f32", ("tile", 128, 128)), (1, 100, 261, 16999, "f32", ("tile", 128, 128)),
              (3, 100, 256, 17000, "f32", ("tile", 128, 256)), (4, 50, 1031, 16999, "f32", ("tile", 128, 256)),
              (1, 100, 256, 17000, "bf16", ("tile", 128, 128)), (1, 100, 261, 16999, "bf16", ("tile", 128, 128)),
              (3, 100, 256, 17000, "bf16", ("tile", 128, 256)), (4, 50, 1031, 16999, "bf16", ("tile", 128, 256)),

@@ -67,7 +67,7 @@ inline bool plan_head(HeadPlan& p, bool f32, double whole_us, double finish_us, 
   p.row_blocks = (p.V + kHeadRowBlock - 1) / kHeadRowBlock;
   const double steps = (double)p.D * (f32 ? 4 : 2) / 256.0;
   const size_t sums = (size_t)p.cols * p.row_blocks * kHeadRowBlock;  // of one range
-  double least = 0.9 * whole_us - 0.4;  // (the model is not better than that)
+  double least = 0.9 * whole_us - 0.43;  // (the model is not better than that)
   p.splits = 0;
   for (int tile = 16; tile <= 128; tile *= 2) {
     const long long groups = (long long)p.row_blocks * ((p.cols + tile - 1) / tile);

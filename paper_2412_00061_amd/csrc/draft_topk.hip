@@ -92,7 +92,7 @@ __device__ void lmhead_block_epilogue(const LmHeadParams& p, const float* zbuf) 
 // wavefronts handing theirs to the other half.  `part` is LDS behind zbuf: 4 x kMaxCols x (2 floats + KMAX keys).
 // Bound: instruction issue of single wavefronts.  With sorted insertion of every key and the first wavefront joining all
 // eight lists that way: 40 columns x 41675 rows of 3840, k = 6, 107 us a call,
-// 88.5 so; 64 columns x 32001 of 4096, k = 4, 64.9 / 60.6.
+// 88.5 so; 64 columns x 32001 of 4096, k = 4, 64.9 to 65.3 / 60.6 to 63.6 (by card and placement).
 template <int KMAX>
 __device__ void lmhead_block_epilogue_wide(const LmHeadParams& p, const float* zbuf, unsigned char* part) {
   const int tid = threadIdx.x, lane = tid & 63;

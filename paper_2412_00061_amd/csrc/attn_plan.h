@@ -30,13 +30,13 @@ inline bool attn_rows64(AttnShape s, int max_nodes) { return s.QB == 2 || (max_n
 //     (one block)    4 x 32 heads, 100 rows, 300: 18.5 (2) / 13.2 (1)    32 heads, 64 rows, 256: 11.9 (2) / 10.2 (1)
 //     32 heads, 128 rows, 2048 positions: 4 splits both; none 36.8, 2 26.0, 3 21.6, 4 19.6, 8 of one block 20.0
 //   bf16, 80: 4 x 16 heads, 50 rows, 93 positions 10.5 (2) / 7.6 (1)
-//   float, 128: 14 heads, 35 rows, up to 1923 positions 24.0 (8) / 17.7 (16)    float, 16: 4 heads, 128 rows, 32: 7.4 (3) / 4.0 (1, padded
+//   float, 128: 14 heads, 35 rows, up to 1923 positions 24.0 (8) / 18.4 (24)    float, 16: 4 heads, 128 rows, 32: 7.4 (3) / 4.0 (1, padded
 //     to 16 instead of 32)
 // Every plan of 1460 shapes drawn from 1 to 8 sequences of 4 to 40 heads and 1 to 128 rows over 4 to 2048 positions was timed, and
-// the constants are the ones (of a coarse grid, the same for both kernels where they mean the same) that come closest to the best
-// plan of each: within 1.1 % in the mean (bf16, 128), 1.0 (bf16, others), 1.5 (float), 1.1 (float heads up to 32) - and the same on
-// 510 shapes that they were not chosen on.  That is 4.8, 8.3, 5.8 and 5.8 % less than as the chip is filled, 13 shapes more than
-// 4 % slower than that (the worst 11 %).
+// the constants are the ones of a coarse grid (the same for both kernels where they mean the same) that come closest to the best
+// plan of each: within 1.1 % in the mean (bf16, 128), 1.0 (bf16, others), 1.5 (float) and 1.1 (float heads up to 32); on 510 further
+// shapes 0.9, 0.7, 1.1 and 3.2 %.  That is 4.8, 8.3, 5.8 and 5.8 % less than as the chip is filled (further shapes: 4.2, 8.0,
+// 5.2 and 7.5); 18 of the 1970 take more than 4 % longer than that, the worst 11 %.
 constexpr int kFillSplits = 8;
 constexpr double kModelGain = 0.97;
 // the merge launch with the end of the kernel before it, whose stores it waits for (behind an independent kernel a launch takes 2.2
@@ -103,10 +103,9 @@ inline AttnShape plan_any(int B, int H, int max_nodes, int kv_cap, int dh, bool 
   if (bh > 65535) return {QB, 1};  // (the merge's grid)
   auto us_of = [&](int S) {
     const long long groups = blocks * S;
-    const bool in_turn = f32 && dh > 32;
-    const double turns = in_turn ? taking_turns((double)((groups * live + 1023) / 1024), B > 1 ? 0.5 : 1.0) : side_by_side((double)groups / 256.0);
+    const double turns = f32 && dh > 32 ? taking_turns((double)((groups * live + 1023) / 1024), B > 1 ? 0.35 : 1.0) : side_by_side((double)groups / 256.0);
     const double tile = f32 ? (dh <= 16 ? 0.6 : dh <= 32 ? 0.9 : (dh + 31) / 32 * 32 / 48.0) : (dh <= 64 ? 0.6 : 0.7);
-    return turns * ((in_turn ? 2.5 : 3.0) + iterations(kv_cap, max_nodes, S, 1) * tile) + split_us(bh, S, max_nodes, dh, two_bf16);
+    return turns * (3.0 + iterations(kv_cap, max_nodes, S, 1) * tile) + split_us(bh, S, max_nodes, dh, two_bf16);
   };
   long long fill = 512 / blocks;  // two workgroups per compute unit, two tiles each
   const int key_tiles = (kv_cap + max_nodes + kTileKeys - 1) / kTileKeys;

@@ -100,6 +100,18 @@ typedef __attribute__((address_space(1))) u32x4 GlobalU32x4;  // a pointer made 
 // 16-byte loads, declared with the element's alignment, and 64-bit offsets.
 inline bool tile_rows16(int D, int elem) { return ((long long)D * elem) % 16 == 0 && (long long)D * elem * 256 < (1LL << 32); }
 
+// Rows that lie a multiple of 4096 bytes apart, all workgroups at about the same place of their rows: what is in flight then
+// falls on a part of the memory channels.  Successive steps are therefore taken 2048 bytes apart, so that the
+// prefetched ones are spread.  A stream of 128 rows a workgroup alone, 32000 rows in all, steps of 256 bytes, us in order / 512 /
+// 1024 / 2048 / 4096 bytes apart: pitch 4096 27.5 / 26.2 / 24.3 / 21.8 / -, 8192 53.0 / 48.0 / 44.5 / 40.7 / 56.6, 12288
+// 79.6 / 72.1 / 64.3 / 59.2 / 84.5, 16384 116 / 102 / 90 / 89 / 117; at 2048, 5120, 6144, 10240 and 14336 all the same within 2 %,
+// at 22016 3 % slower 512 apart.  Another place to start from in every workgroup reaches 38 to 41 at 8192, but gives equal
+// rows of different blocks different sums.  Whole calls, in order / so: draft head 64 columns x 32001 rows of 4096 bf16 63.1 / 53.0 us,
+// 16 x 32001 of 2048 float 52.8 / 51.3, base head 128 x 32000 of 4096 with logits 71.6 / 68.4, the draft layer 113 / 105.6.
+__host__ __device__ __forceinline__ int step_segment(size_t pitch, int step_bytes) {
+  return pitch % 4096 == 0 ? 2048 / step_bytes : 1;
+}
+
 // acc[rt][ct][i]: row row_base + 16 (RT wr + rt) + 4 (lane >> 4) + i, column 16 CTW wc + 16 ct + (lane & 15),
 // wr = wave / WC, wc = wave % WC.
 // Every wavefront of the workgroup (8) must call it; it ends with a barrier after the last read of LDS.
@@ -154,12 +166,18 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
   // A request past the last step still issues its loads, so that every wait counts the same loads: it reads
   // a 256-byte block of zeros (in L2, no HBM traffic) and nothing computes from the result.
   u32x4 wreg[DIST][WP], hreg[DIST][HP];
+  // The steps' place in the row, in the order they are requested: 0, seg, 2 seg, ... then 1, seg + 1, ... (step_segment).
+  // Every row of the product takes the same order, so equal weight rows have equal sums wherever they lie.
+  const int seg = step_segment(pitch, STEPB);
+  int place = 0, lap = 0;
   auto request_step = [&](int step, auto stage, auto there_tag) __attribute__((always_inline)) {
     constexpr int S = decltype(stage)::value;
     // address arithmetic in integers: a select between pointers would become a branch around each load
     const bool valid = decltype(there_tag)::value || step < total_steps;
     const Offset mask = valid ? ~(Offset)0 : (Offset)0;
-    const Offset st = ((Offset)step * (Offset)STEPB) & mask;
+    const Offset st = ((Offset)place * (Offset)STEPB) & mask;
+    place += seg;
+    if (place >= total_steps) place = ++lap;
     const uintptr_t hb = (valid ? h_addr : z_addr) + st, wb = (valid ? w_addr : z_addr) + st;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

@@ -9,7 +9,8 @@
 #include <type_traits>
 #include <utility>
 
-#include "gemm_tile.h"
+#include "dma_tile.h"
+#include "head_plan.h"
 #include "layer_plan.h"
 
 namespace ctcspec {
@@ -38,19 +39,20 @@ struct LayerTileParams {
   const void* zeros;
   float* part;        // [splits][cols][N]
   int N, K, cols, plane_cols, col0, row_blocks, splits;
+  bool streamed;      // streamed_weights (head_plan.h), by the whole layer
   int trips, more;    // k trips of a split; the first `more` splits have one more
 };
 struct LayerColumns {
   int cols, plane_cols;
-  __device__ __forceinline__ int operator()(int r) const {
+  __device__ __forceinline__ int row_or_none(int r) const {
     const int col = (r >> 5) * 16 + (r & 15);
-    return ((r >> 4) & 1) * plane_cols + (col < cols ? col : cols - 1);
+    return col < cols ? ((r >> 4) & 1) * plane_cols + col : -1;
   }
 };
 template <typename SH>
 __global__ __launch_bounds__(64 * kTileWaves) void layer_tile_kernel(LayerTileParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  static_assert(SH::STEPB == 128 && SH::CTW % 2 == 0, "steps of 64 elements, column tiles in high / low pairs");
+  static_assert(kLtTripK * 2 % SH::STEPB == 0 && SH::CTW % 2 == 0, "whole steps, column tiles in high / low pairs");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wave / SH::WC, wc = wave % SH::WC;
@@ -61,9 +63,9 @@ __global__ __launch_bounds__(64 * kTileWaves) void layer_tile_kernel(LayerTilePa
   GemmTileArgs t;
   t.w = (const unsigned char*)p.w + (size_t)t0 * kLtTripK * 2;
   t.hidden = (const unsigned char*)p.x + (size_t)p.col0 * p.K * 2 + (size_t)t0 * kLtTripK * 2;
-  t.zeros = p.zeros; t.D = (t1 - t0) * kLtTripK; t.pitch = p.K; t.V = p.N; t.row_base = rb * SH::ROWS;
+  t.zeros = p.zeros; t.D = (t1 - t0) * kLtTripK; t.pitch = p.K; t.V = p.N; t.row_base = rb * SH::ROWS; t.streamed = p.streamed;
   f32x4 acc[SH::RT][SH::CTW];
-  gemm_tile<4, SH, TileBf16, true, true>(t, LayerColumns{p.cols, p.plane_cols}, smem, acc);
+  dma_tile<SH, TileBf16>(t, LayerColumns{p.cols, p.plane_cols}, smem, acc);
   float* out = p.part + (size_t)split * p.cols * p.N;
 #pragma unroll
   for (int ct = 0; ct < SH::CTW; ct += 2) {
@@ -259,14 +261,14 @@ static int device_cus() {
 }
 
 // rows x 16, 32 or 64 columns (twice as many tile columns); which one: layer_plan.h
-using LayerTile128x16 = TileShape<8, 2, 128, 1>;
-using LayerTile256x16 = TileShape<8, 2, 128, 2>;
-using LayerTile128x32 = TileShape<4, 2, 128, 2>;
-using LayerTile192x32 = TileShape<4, 2, 128, 3>;
-using LayerTile256x32 = TileShape<4, 2, 128, 4>;
-using LayerTile128x64 = TileShape<4, 4, 128, 2>;
-using LayerTile192x64 = TileShape<4, 4, 128, 3>;
-using LayerTile256x64 = TileShape<4, 4, 128, 4>;
+using LayerTile128x16 = DmaShape<8, 1, 2, 256, 4, 3>;
+using LayerTile256x16 = DmaShape<8, 2, 2, 128, 4, 4>;
+using LayerTile128x32 = DmaShape<4, 2, 2, 256, 3, 3>;
+using LayerTile192x32 = DmaShape<4, 3, 2, 128, 4, 4>;
+using LayerTile256x32 = DmaShape<4, 4, 2, 128, 4, 4>;
+using LayerTile128x64 = DmaShape<4, 2, 4, 256, 3, 2>;
+using LayerTile192x64 = DmaShape<4, 3, 4, 128, 4, 4>;
+using LayerTile256x64 = DmaShape<4, 4, 4, 128, 3, 3>;
 template <typename SH>
 static hipError_t launch_shape(const LayerTileParams& tp, hipStream_t stream) {
   hipLaunchKernelGGL(layer_tile_kernel<SH>, dim3((unsigned)tp.row_blocks, (unsigned)tp.splits), dim3(64 * kTileWaves), SH::LDS_BYTES,
@@ -364,6 +366,7 @@ extern "C" int draft_layer_forward(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
       CTCSPEC_REQUIRE(ctx, make_plan(plan, N, K, p.cols, BT, cus), CTCSPEC_EUNSUPPORTED,
                       "draft_layer_forward: a %d x %d matrix does not fit the tile kernel", N, K);
       LayerTileParams tp;
+      tp.streamed = streamed_weights(2LL * (4LL * D * D + 3LL * D * F), 2LL * K);
       tp.w = wmat; tp.x = xin; tp.zeros = ctx->zeros; tp.part = (float*)(ws + lw.part);
       tp.N = N; tp.K = K; tp.cols = p.cols; tp.plane_cols = BT; tp.col0 = col0; tp.splits = plan.splits;
       CTCSPEC_HIP(ctx, launch_pass(tp, plan.rows, st));

@@ -21,7 +21,7 @@
 
 #include <hip/hip_ext.h>
 
-#include "gemm_tile.h"
+#include "dma_tile.h"
 #include "head_ranges.h"
 #include "topk_merge.h"
 
@@ -46,6 +46,7 @@ struct LmHeadParams {
   float* topk_logp;
   float* lse;
   float* logits_out;
+  bool streamed;      // streamed_weights (dma_tile.h)
 };
 
 // Epilogue shared by both producers.  zbuf holds the block's logits column-major:
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(64 * kMfmaWaves) void lmhead_bf16_mfma_kernel(LmHea
       if (hs_dst[u] >= 0) *(u32x4*)(hs + hs_dst[u]) = hreg[u];
   };
 
-  // the order of the steps (step_segment in gemm_tile.h): 8 columns of 4096 x 32001 rows take 3.3 us less so than in order
+  // the order of the steps (step_segment in dma_tile.h): 8 columns of 4096 x 32001 rows take 3.3 us less so than in order
   struct Order {
     int seg, steps, place = 0, lap = 0;
     __device__ __forceinline__ int next() {
@@ -428,24 +429,25 @@ __global__ __launch_bounds__(64 * kMfmaWaves) void lmhead_bf16_mfma_kernel(LmHea
 // ---- tile producer: any hidden size and type --------------------------------------------------------------------
 // The tile loop shared with the base-model head, 128 rows x 16, 32 or 64 columns: both operands staged through LDS
 // step by step, the weights still read exactly once.  Then the same block epilogue as the other producer.
-constexpr int kLmTileDist = 4;
-template <typename SH, typename EL, bool ROWS16>
+template <typename SH, typename EL>
 __global__ __launch_bounds__(64 * kTileWaves) void lmhead_tile_kernel(LmHeadParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  static_assert(SH::CTW == 1 && SH::ROWS == kRowsPerBlock, "one column tile per wavefront");
+  static_assert(SH::ROWS == kRowsPerBlock, "the epilogue's block");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wave / SH::WC, wc = wave % SH::WC;
   const int c = lane & 15, g = lane >> 4;
   const int row_base = blockIdx.x * kRowsPerBlock;
   GemmTileArgs t;
-  t.w = p.w; t.hidden = p.hidden; t.zeros = p.zeros; t.D = t.pitch = p.D; t.V = p.Vp1; t.row_base = row_base;
-  f32x4 acc[SH::RT][1];
-  gemm_tile<kLmTileDist, SH, EL, ROWS16>(t, TileColumns{p.BT}, smem, acc);
+  t.w = p.w; t.hidden = p.hidden; t.zeros = p.zeros; t.D = t.pitch = p.D; t.V = p.Vp1; t.row_base = row_base; t.streamed = p.streamed;
+  f32x4 acc[SH::RT][SH::CTW];
+  tile_product<SH, EL>(t, TileColumns{p.BT}, smem, acc);
   // (the loop's last barrier has every wavefront done with the LDS tiles)
   float* zbuf = (float*)smem;
-  const int col = wc * 16 + c;
-  if (col < p.BT) {
+#pragma unroll
+  for (int ct = 0; ct < SH::CTW; ++ct) {
+    const int col = (wc * SH::CTW + ct) * 16 + c;
+    if (col >= p.BT) continue;
 #pragma unroll
     for (int rt = 0; rt < SH::RT; ++rt) {
       f32x4 z;
@@ -453,7 +455,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void lmhead_tile_kernel(LmHeadPara
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = row_base + r0 + i;
-        z[i] = row < p.Vp1 ? acc[rt][0][i] + (p.bias ? p.bias[row] : 0.f) : -INFINITY;
+        z[i] = row < p.Vp1 ? acc[rt][ct][i] + (p.bias ? p.bias[row] : 0.f) : -INFINITY;
       }
       *(f32x4*)(zbuf + col * kZStride + r0) = z;
     }
@@ -471,25 +473,23 @@ __global__ __launch_bounds__(64 * kTileWaves) void lmhead_tile_kernel(LmHeadPara
 }
 constexpr int kLmEpilogueBytes = kMaxCols * kZStride * 4 + kMfmaWaves / 2 * kMaxCols * (8 + 8 * kMaxTopk);
 static_assert(kMaxCols <= 64 && kLmEpilogueBytes <= Tile128x64::LDS_BYTES && kLmEpilogueBytes <= Tile128x32::LDS_BYTES &&
-                  16 * kZStride * 4 <= Tile128x16::LDS_BYTES,
+                  16 * kZStride * 4 <= Tile128x16::LDS_BYTES && kLmEpilogueBytes <= Dma128x64::LDS_BYTES &&
+                  kLmEpilogueBytes <= Dma128x32::LDS_BYTES && 16 * kZStride * 4 <= Dma128x16::LDS_BYTES,
               "one tile holds every column and the epilogue's partials");
 
-template <typename SH, typename EL, bool ROWS16>
+template <typename SH, typename EL>
 static hipError_t launch_tile_shape(const LmHeadParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL((lmhead_tile_kernel<SH, EL, ROWS16>), dim3(p.n_blocks), dim3(64 * kTileWaves), SH::LDS_BYTES, stream, p);
+  hipLaunchKernelGGL((lmhead_tile_kernel<SH, EL>), dim3(p.n_blocks), dim3(64 * kTileWaves), SH::LDS_BYTES, stream, p);
   return hipGetLastError();
-}
-template <typename EL, bool ROWS16>
-static hipError_t launch_tile_rows(const LmHeadParams& p, hipStream_t stream) {
-  // the narrowest tile that holds the columns: a wavefront without live columns would contract for nothing, which
-  // float operands (a sixteenth of the bf16 matrix rate) cannot afford
-  if (p.BT <= 16) return launch_tile_shape<Tile128x16, EL, ROWS16>(p, stream);
-  if (p.BT <= 32) return launch_tile_shape<Tile128x32, EL, ROWS16>(p, stream);
-  return launch_tile_shape<Tile128x64, EL, ROWS16>(p, stream);
 }
 template <typename EL>
 static hipError_t launch_tile(const LmHeadParams& p, hipStream_t stream) {
-  return tile_rows16(p.D, EL::ELEM) ? launch_tile_rows<EL, true>(p, stream) : launch_tile_rows<EL, false>(p, stream);
+  // the narrowest tile that holds the columns: a wavefront without live columns would contract for nothing, which
+  // float operands (a sixteenth of the bf16 matrix rate) cannot afford
+  const bool dma = dma_rows(p.Vp1, p.D, EL::ELEM);
+  if (p.BT <= 16) return dma ? launch_tile_shape<Dma128x16, EL>(p, stream) : launch_tile_shape<Tile128x16, EL>(p, stream);
+  if (p.BT <= 32) return dma ? launch_tile_shape<Dma128x32, EL>(p, stream) : launch_tile_shape<Tile128x32, EL>(p, stream);
+  return dma ? launch_tile_shape<Dma128x64, EL>(p, stream) : launch_tile_shape<Tile128x64, EL>(p, stream);
 }
 
 static void launch_merge(const LmHeadParams& p, hipStream_t stream) {
@@ -529,17 +529,18 @@ static hipError_t allow_mfma_lds() {
                              hipFuncAttributeMaxDynamicSharedMemorySize, kMfmaLdsLimit);
 }
 
-template <typename EL, bool ROWS16>
+template <typename EL, typename... SH>
 static hipError_t allow_tile_lds() {
-  hipError_t e = hipFuncSetAttribute((const void*)lmhead_tile_kernel<Tile128x16, EL, ROWS16>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, Tile128x16::LDS_BYTES);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)lmhead_tile_kernel<Tile128x32, EL, ROWS16>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, Tile128x32::LDS_BYTES);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)lmhead_tile_kernel<Tile128x64, EL, ROWS16>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, Tile128x64::LDS_BYTES);
+  hipError_t e = hipSuccess;
+  ((e = e == hipSuccess ? hipFuncSetAttribute((const void*)lmhead_tile_kernel<SH, EL>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                              SH::LDS_BYTES)
+                        : e),
+   ...);
   return e;
+}
+template <typename EL>
+static hipError_t allow_tile_lds_all() {
+  return allow_tile_lds<EL, Tile128x16, Tile128x32, Tile128x64, Dma128x16, Dma128x32, Dma128x64>();
 }
 
 // dynamic LDS limits of this file's kernels, on the current device
@@ -552,10 +553,8 @@ static hipError_t allow_large_lds() {
   if (e == hipSuccess) e = allow_mfma_lds<2, 2>();
   if (e == hipSuccess) e = allow_mfma_lds<3, 2>();
   if (e == hipSuccess) e = allow_mfma_lds<4, 2>();
-  if (e == hipSuccess) e = allow_tile_lds<TileBf16, true>();
-  if (e == hipSuccess) e = allow_tile_lds<TileBf16, false>();
-  if (e == hipSuccess) e = allow_tile_lds<TileF32, true>();
-  if (e == hipSuccess) e = allow_tile_lds<TileF32, false>();
+  if (e == hipSuccess) e = allow_tile_lds_all<TileBf16>();
+  if (e == hipSuccess) e = allow_tile_lds_all<TileF32>();
   if (e == hipSuccess) e = prepare_head_ranges();
   return e;
 }
@@ -638,6 +637,8 @@ static int draft_topk_launch(ctcspec_ctx* err, hipStream_t stream, const LmScrat
   p.n_blocks = (Vp1 + kRowsPerBlock - 1) / kRowsPerBlock;
   p.pmax = sc.pmax; p.psum = sc.psum; p.pkey = sc.pkey; p.pstride = sc.pstride;
   p.topk_id = topk_id; p.topk_logp = topk_logp; p.lse = lse; p.logits_out = logits_out;
+  const long long row_bytes = (long long)D * (dt == CTCSPEC_BF16 ? 2 : 4);
+  p.streamed = streamed_weights(Vp1 * row_bytes, row_bytes);
   const bool timing = ev0 && ev1;
   // defer: leave the partials and record what is owed (err is the context then); the collapse/tree kernel or
   // flush_deferred does the merge
@@ -655,7 +656,7 @@ static int draft_topk_launch(ctcspec_ctx* err, hipStream_t stream, const LmScrat
 
   const bool f32 = dt == CTCSPEC_F32;
   HeadRangeParams h;
-  h.hidden = hidden; h.w = w; h.zeros = sc.zeros; h.part = sc.part; h.cols = p.BT; h.D = D; h.V = Vp1;
+  h.hidden = hidden; h.w = w; h.zeros = sc.zeros; h.part = sc.part; h.cols = p.BT; h.D = D; h.V = Vp1; h.streamed = p.streamed;
   if (plan_draft_head(h, f32, k)) {
     if (timing) CTCSPEC_HIP(err, hipEventRecord(ev0, stream));
     CTCSPEC_HIP(err, launch_head_ranges(h, f32, stream));

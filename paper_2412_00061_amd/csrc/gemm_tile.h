@@ -1,15 +1,14 @@
-// A tile of a [V, D] x [cols, D]^T product, bf16 or float operands, fp32 accumulators: the main loop shared by the
-// base-model head (verify_head_argmax), the draft head and the draft layer's passes.
+// A tile of a [V, D] x [cols, D]^T product, bf16 or float operands, fp32 accumulators, whose rows start at any element
+// (hidden sizes that are no multiple of 16 bytes): what the heads take there, and for the smallest calls.  Others: dma_tile.h.
 //
 // 8 wavefronts in a WR x WC grid (WR * WC = 8): wavefront (wr, wc) owns weight rows [16 RT wr, +16 RT) x columns
-// [16 CTW wc, +16 CTW) - RT x CTW MFMA tiles.  Shapes in use (rows x columns, bytes of a row per step).  The heads: 128 x 16,
+// [16 CTW wc, +16 CTW) - RT x CTW MFMA tiles.  Shapes in use (rows x columns, bytes of a row per step): 128 x 16,
 // x 32, x 64 and x 128 with steps of 256 bytes, and 256 x 128 with steps of 128 (4 x 2 wavefronts, 64 x 64 per
 // wavefront) for products with several column blocks: per flop it reads two thirds of the fragments from LDS and
-// fetches half of the hidden-state tiles from L2.  The draft layer: 128, 192 or 256 rows x 32, 64 or 128 tile columns (but
-// 192 x 32) with steps of 128 bytes - its columns come twice, high and low parts - of a range of k (pitch > D).
-// Per step both operands go through LDS: the W tile (nontemporal, the A operand) and the hidden states of the step
-// (the B operand) are fetched by all threads together with coalesced 16-byte loads, DIST steps ahead, into
-// rotating register stages (the VGPR file, 512 KB per compute unit, is the deep staging buffer), and written to
+// fetches half of the hidden-state tiles from L2.
+// Per step both operands go through LDS: the W tile (the A operand) and the hidden states of the step
+// (the B operand) are fetched by all threads together with 16-byte loads declared with an element's alignment, DIST steps
+// ahead, into rotating register stages, and written to
 // one of two LDS buffers while the other one is computed from: one barrier per step.  Within a step the fragment
 // reads of the next k-block and the tile writes are issued in front of the MFMAs of the current one and run under them.
 // What bounds it (measured, one compute unit): b128 fragment reads at 128 B per clock, b128 writes at 79 B per
@@ -18,10 +17,7 @@
 // serialises.  All loads are unconditional and counted (indices clamped; a request past the last step reads a
 // block of zeros), so the waits name the loads that stay in flight.
 // Hidden sizes that are no whole number of steps: what is left of every row goes first, padded with zeros - through the
-// prefetch stages in narrow tiles, unpipelined in wide ones.  Rows that start at any element take the same loads at that
-// alignment.  (One thread per logit with a dot
-// product over uncoalesced rows, which these shapes and float operands took before: 16 float columns x 32001 x 2048
-// in 2.12 ms against 53 us = 4.9 TB/s here, bound by HBM; 128 columns x 100 x 64 in 542 against 7 us.)
+// prefetch stages in narrow tiles, unpipelined in wide ones.
 #pragma once
 
 #include <type_traits>
@@ -37,6 +33,7 @@ __device__ __forceinline__ int clamp_int(int v, int lo, int hi) { return v < lo 
 
 template <int WR_, int CTW_, int STEPB_, int RT_ = 4>
 struct TileShape {
+  static constexpr bool DMA = false;
   static constexpr int WR = WR_, WC = kTileWaves / WR_;  // wavefront grid
   static constexpr int CTW = CTW_, RT = RT_;             // 16-column and 16-row MFMA tiles per wavefront
   static constexpr int STEPB = STEPB_;                   // bytes of a row per step
@@ -86,44 +83,27 @@ struct GemmTileArgs {
   int D, V;            // contracted elements, weight rows
   int pitch;           // elements from row to row, of both operands
   int row_base;        // first weight row of the tile
+  bool streamed = false;  // dma_tile.h: the weights by nontemporal loads
 };
-// which row of the hidden states a column of the tile is: columns past the end repeat the last one (never read back)
+// which row of the hidden states a column of the tile is: columns past the end repeat the last one (never read back), or have none
 struct TileColumns {
   int cols;
   __device__ __forceinline__ int operator()(int r) const { return r < cols ? r : cols - 1; }
+  __device__ __forceinline__ int row_or_none(int r) const { return r < cols ? r : -1; }
 };
 
 typedef __attribute__((address_space(1))) u32x4 GlobalU32x4;  // a pointer made from an integer is generic otherwise
 
-// How rows are read.  ROWS16: rows start at multiples of 16 bytes (the row size is one) and the rows of a tile lie
-// within 4 GB of the first, so a thread's place is a 32-bit offset.  Otherwise rows start at any element: the same
-// 16-byte loads, declared with the element's alignment, and 64-bit offsets.
-inline bool tile_rows16(int D, int elem) { return ((long long)D * elem) % 16 == 0 && (long long)D * elem * 256 < (1LL << 32); }
-
-// Rows that lie a multiple of 4096 bytes apart, all workgroups at about the same place of their rows: what is in flight then
-// falls on a part of the memory channels.  Successive steps are therefore taken 2048 bytes apart, so that the
-// prefetched ones are spread.  A stream of 128 rows a workgroup alone, 32000 rows in all, steps of 256 bytes, us in order / 512 /
-// 1024 / 2048 / 4096 bytes apart: pitch 4096 27.5 / 26.2 / 24.3 / 21.8 / -, 8192 53.0 / 48.0 / 44.5 / 40.7 / 56.6, 12288
-// 79.6 / 72.1 / 64.3 / 59.2 / 84.5, 16384 116 / 102 / 90 / 89 / 117; at 2048, 5120, 6144, 10240 and 14336 all the same within 2 %,
-// at 22016 3 % slower 512 apart.  Another place to start from in every workgroup reaches 38 to 41 at 8192, but gives equal
-// rows of different blocks different sums.  Whole calls, in order / so: draft head 64 columns x 32001 rows of 4096 bf16 63.1 / 53.0 us,
-// 16 x 32001 of 2048 float 52.8 / 51.3, base head 128 x 32000 of 4096 with logits 71.6 / 68.4, the draft layer 113 / 105.6.
-__host__ __device__ __forceinline__ int step_segment(size_t pitch, int step_bytes) {
-  return pitch % 4096 == 0 ? 2048 / step_bytes : 1;
-}
-
 // acc[rt][ct][i]: row row_base + 16 (RT wr + rt) + 4 (lane >> 4) + i, column 16 CTW wc + 16 ct + (lane & 15),
 // wr = wave / WC, wc = wave % WC.
 // Every wavefront of the workgroup (8) must call it; it ends with a barrier after the last read of LDS.
-// WHOLE_TRIPS: D is known to be a multiple of DIST steps.
-template <int DIST, typename SH, typename EL, bool ROWS16, bool WHOLE_TRIPS = false, typename COLUMNS>
+template <int DIST, typename SH, typename EL, typename COLUMNS>
 __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& columns, unsigned char* smem,
                                           f32x4 (&acc)[SH::RT][SH::CTW]) {
   constexpr int CTW = SH::CTW, RT = SH::RT, STEPB = SH::STEPB, PITCH = SH::PITCH, CPR = SH::CPR, RPP = SH::RPP;
   constexpr int WP = SH::WP, HP = SH::HP, KK = SH::KK;
   constexpr int WPK = (WP + KK - 1) / KK, HPK = (HP + KK - 1) / KK;  // pieces written to LDS per k-block of the step before
   constexpr int HS_BYTES = SH::HS_BYTES, BUF_BYTES = SH::BUF_BYTES;
-  using Offset = std::conditional_t<ROWS16, unsigned int, size_t>;
   struct Packed16 { u32x4 v; } __attribute__((packed, aligned(EL::ELEM)));  // 16 bytes at an element's alignment
   typedef __attribute__((address_space(1))) Packed16 GlobalPacked16;
   constexpr int TRIP = DIST;    // steps per loop trip: stage and buffer static
@@ -154,78 +134,64 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
   const unsigned int lane_off = pchunk * 16;
   const uintptr_t w_addr = (uintptr_t)t.w + (size_t)row_base * pitch, h_addr = (uintptr_t)t.hidden;
   const uintptr_t z_addr = (uintptr_t)t.zeros;
-  Offset woff[WP], hoff[HP];
+  size_t woff[WP], hoff[HP];
   const int dst0 = prow * PITCH + pchunk * 16;
 #pragma unroll
   for (int u = 0; u < WP; ++u) {
     const int r = prow + RPP * u, last = t.V - 1 - row_base;
-    woff[u] = (Offset)(r < last ? r : last) * (Offset)pitch;  // the ragged last block re-reads the last row
+    woff[u] = (size_t)(r < last ? r : last) * (size_t)pitch;  // the ragged last block re-reads the last row
   }
 #pragma unroll
-  for (int u = 0; u < HP; ++u) hoff[u] = (Offset)columns(prow + RPP * u) * (Offset)pitch;
+  for (int u = 0; u < HP; ++u) hoff[u] = (size_t)columns(prow + RPP * u) * (size_t)pitch;
   // A request past the last step still issues its loads, so that every wait counts the same loads: it reads
   // a 256-byte block of zeros (in L2, no HBM traffic) and nothing computes from the result.
   u32x4 wreg[DIST][WP], hreg[DIST][HP];
-  // The steps' place in the row, in the order they are requested: 0, seg, 2 seg, ... then 1, seg + 1, ... (step_segment).
-  // Every row of the product takes the same order, so equal weight rows have equal sums wherever they lie.
-  const int seg = step_segment(pitch, STEPB);
-  int place = 0, lap = 0;
-  auto request_step = [&](int step, auto stage, auto there_tag) __attribute__((always_inline)) {
+  auto request = [&](int step, auto stage) __attribute__((always_inline)) {
     constexpr int S = decltype(stage)::value;
     // address arithmetic in integers: a select between pointers would become a branch around each load
-    const bool valid = decltype(there_tag)::value || step < total_steps;
-    const Offset mask = valid ? ~(Offset)0 : (Offset)0;
-    const Offset st = ((Offset)place * (Offset)STEPB) & mask;
-    place += seg;
-    if (place >= total_steps) place = ++lap;
+    const bool valid = step < total_steps;
+    const size_t mask = valid ? ~(size_t)0 : (size_t)0;
+    const size_t st = ((size_t)step * (size_t)STEPB) & mask;
     const uintptr_t hb = (valid ? h_addr : z_addr) + st, wb = (valid ? w_addr : z_addr) + st;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < HP; ++u) {
       const uintptr_t a = hb + ((hoff[u] & mask) + lane_off);
-      if constexpr (ROWS16) hreg[S][u] = *(const GlobalU32x4*)a;
-      else hreg[S][u] = ((const GlobalPacked16*)a)->v;
+      hreg[S][u] = ((const GlobalPacked16*)a)->v;
     }
 #pragma unroll
     for (int u = 0; u < WP; ++u) {
       const uintptr_t a = wb + ((woff[u] & mask) + lane_off);
-      if constexpr (ROWS16) wreg[S][u] = __builtin_nontemporal_load((const GlobalU32x4*)a);
-      else wreg[S][u] = ((const GlobalPacked16*)a)->v;
+      wreg[S][u] = ((const GlobalPacked16*)a)->v;
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto request = [&](int step, auto stage) __attribute__((always_inline)) { request_step(step, stage, std::false_type{}); };
   // The elements of a row behind its last whole step (tail_bytes of them), zeros behind those: a thread's chunk has tail_n
   // of its bytes in the row.  It is loaded so that it ends with them - every load stays inside its row - and shifted down
   // when it is used, so that nothing waits for it in between.  (A row of less than 16 bytes: element by element.)
   const int tail_bytes = (int)(row_bytes - (size_t)total_steps * STEPB);
   const int tail_n = clamp_int(tail_bytes - pchunk * 16, 0, 16);
   auto tail_load = [&](uintptr_t row) __attribute__((always_inline)) -> u32x4 {
-    if constexpr (ROWS16) {  // whole chunks
-      return *(const GlobalU32x4*)(row + row_bytes - tail_bytes + (tail_n ? pchunk * 16 : 0));
-    } else {
-      if (row_bytes >= 16) return ((const GlobalPacked16*)(row + (tail_n ? row_bytes - tail_bytes + pchunk * 16 + tail_n - 16 : 0)))->v;
-      using E = std::conditional_t<EL::ELEM == 2, unsigned short, unsigned int>;
-      constexpr int PER = 4 / EL::ELEM;  // elements per word
-      typedef __attribute__((address_space(1))) E GlobalE;
-      u32x4 v = {0u, 0u, 0u, 0u};
-      for (int e = 0; e < 4 * PER; ++e) {
-        const unsigned int x = e * EL::ELEM < tail_n ? *(const GlobalE*)(row + e * EL::ELEM) : 0u;
+    if (row_bytes >= 16) return ((const GlobalPacked16*)(row + (tail_n ? row_bytes - tail_bytes + pchunk * 16 + tail_n - 16 : 0)))->v;
+    using E = std::conditional_t<EL::ELEM == 2, unsigned short, unsigned int>;
+    constexpr int PER = 4 / EL::ELEM;  // elements per word
+    typedef __attribute__((address_space(1))) E GlobalE;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    for (int e = 0; e < 4 * PER; ++e) {
+      const unsigned int x = e * EL::ELEM < tail_n ? *(const GlobalE*)(row + e * EL::ELEM) : 0u;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] |= e / PER == q ? x << (8 * EL::ELEM * (e % PER)) : 0u;
-      }
-      return v;
+      for (int q = 0; q < 4; ++q) v[q] |= e / PER == q ? x << (8 * EL::ELEM * (e % PER)) : 0u;
     }
+    return v;
   };
   auto tail_use = [&](u32x4 v) __attribute__((always_inline)) -> u32x4 {
-    if constexpr (!ROWS16)
-      if (row_bytes >= 16 && tail_n > 0 && tail_n < 16) {
-        unsigned long long lo = ((unsigned long long)v[1] << 32) | v[0], hi = ((unsigned long long)v[3] << 32) | v[2];
-        const int bits = 8 * (16 - tail_n);
-        lo = bits >= 64 ? hi >> (bits & 63) : (lo >> bits) | (hi << (64 - bits));
-        hi = bits >= 64 ? 0ull : hi >> bits;
-        v = u32x4{(unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32)};
-      }
+    if (row_bytes >= 16 && tail_n > 0 && tail_n < 16) {
+      unsigned long long lo = ((unsigned long long)v[1] << 32) | v[0], hi = ((unsigned long long)v[3] << 32) | v[2];
+      const int bits = 8 * (16 - tail_n);
+      lo = bits >= 64 ? hi >> (bits & 63) : (lo >> bits) | (hi << (64 - bits));
+      hi = bits >= 64 ? 0ull : hi >> bits;
+      v = u32x4{(unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32)};
+    }
     return tail_n ? v : u32x4{0u, 0u, 0u, 0u};
   };
   auto commit = [&](auto stage, auto buffer) __attribute__((always_inline)) {
@@ -297,7 +263,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
   // kernels two to four times as large (base head, 128 x 16 bf16: 5.0 -> 16.5 KB); a call runs one of them, and with everything
   // else flushed out of the caches in between the first of these takes 41.0 us with its launches against 47.6, the second 43.5 against 51.6.
   constexpr bool kWide = RT * CTW >= 8;
-  const int lead = WHOLE_TRIPS ? 0 : total_steps % TRIP;
+  const int lead = total_steps % TRIP;
   auto load_tail = [&](auto stage) __attribute__((always_inline)) {
     constexpr int S = decltype(stage)::value;
 #pragma unroll
@@ -324,7 +290,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
     const int step0 = lead - L;
     if constexpr (TAIL) load_tail(CTCSPEC_TILE_STAGE(DIST - 1));
     [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {
-      (request_step(step0 + U, CTCSPEC_TILE_STAGE(U), std::bool_constant<WHOLE_TRIPS>{}), ...);
+      (request(step0 + U, CTCSPEC_TILE_STAGE(U)), ...);
     }(std::make_integer_sequence<int, TAIL ? DIST - 1 : DIST>{});
     if constexpr (TAIL) {
       commit_tail(CTCSPEC_TILE_STAGE(DIST - 1), CTCSPEC_TILE_BUFFER(1));
@@ -343,9 +309,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
 #undef CTCSPEC_TILE_STAGE
 #undef CTCSPEC_TILE_BUFFER
   };
-  if constexpr (WHOLE_TRIPS) {
-    enter(I0{}, std::false_type{});
-  } else if (kWide || total_steps < 2) {  // (nothing to prefetch either)
+  if (kWide || total_steps < 2) {  // (nothing to prefetch either)
     bool used = false;  // LDS has been computed from
     if (tail_bytes > 0) {
       load_tail(I0{});

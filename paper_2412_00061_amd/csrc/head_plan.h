@@ -38,6 +38,16 @@ inline size_t head_part_floats(long long cols, int vocab_rows, size_t most) {
   return all < most ? all : most;
 }
 
+// Whether `bytes` of weights are read by nontemporal loads (dma_tile.h): rows of whole cache lines, unless a program that small may
+// find them in the 256 MB last-level cache.  32000 rows, us plain / nontemporal, first when the same weights come again and
+// again, then when others went through in between:
+//   16 columns:  33 MB 9.5 / 11.5, 12.6 / 11.8     49 MB 12.6 / 13.2, 14.7 / 13.8     66 MB 15.6 / 15.4, 16.9 / 16.1
+//     131 MB 23.6 / 25.3, 29.6 / 26.6     262 MB 42.3 / 44.5, 51.8 / 45.5     328 MB 57.2 / 52.1, 58.8 / 52.6
+//   8 columns of 4096, 8001 rows (66 MB): 23.9 / 28.8, 30.1 / 28.3     128 columns, 262 MB: 51.5 / 52.0, 58.0 / 52.2
+// Other rows share lines with their neighbours and with the next step, and nontemporal loads fetch those again: rows of 4104
+// elements, 16 columns 41.7 / 53.9, 50.2 / 55.0; 128 columns 56.8 / 65.6, 64.2 / 66.2.
+inline bool streamed_weights(long long bytes, long long row_bytes) { return row_bytes % 128 == 0 && bytes > (48LL << 20); }
+
 struct HeadPlan {
   int cols, D, V;
   int tile_cols;       // 16, 32, 64 or 128
@@ -87,6 +97,13 @@ inline bool plan_head(HeadPlan& p, bool f32, double whole_us, double finish_us, 
   return true;
 }
 
+// Base head, more than 128 columns, rows on 16-byte boundaries: 256-row tiles of 256 columns (a step 1.7 times that of 128 columns:
+// 103 us against 60 for a round over the compute units at 4096) or of 128, by the rounds that they take.
+inline int head_wide_columns(int V, int cols) {
+  const long long rows = (V + 255) / 256;
+  const long long rounds256 = (rows * ((cols + 255) / 256) + 255) / 256, rounds128 = (rows * ((cols + 127) / 128) + 255) / 256;
+  return 17 * rounds256 <= 10 * rounds128 ? 256 : 128;
+}
 inline int head_tile_cols(int cols) { return cols <= 16 ? 16 : cols <= 32 ? 32 : cols <= 64 ? 64 : 128; }
 // what the epilogues take: joining the wavefronts' k-lists; a column's workgroup pops k keys, and is slow with eight groups of
 // rows a thread

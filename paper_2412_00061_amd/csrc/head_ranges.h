@@ -20,6 +20,7 @@ struct HeadRangeParams : HeadPlan {
   const void* w;       // [V][D]
   const void* zeros;   // 256 bytes of zeros
   float* part;         // [splits][cols][row_blocks * 128]
+  bool streamed;       // streamed_weights
 };
 
 hipError_t launch_head_ranges(const HeadRangeParams& p, bool f32, hipStream_t stream);

@@ -1,14 +1,14 @@
 // The product of a head cut into ranges of the hidden dimension (head_ranges.h; head_plan.h has the rule that chooses it).
 #include <type_traits>
 
-#include "gemm_tile.h"
+#include "dma_tile.h"
 #include "head_ranges.h"
 
 namespace ctcspec {
 
 // Bound: start-up (a workgroup's first tile is in LDS after about 6 us) and then LDS traffic per step, as in gemm_tile.h; the
 // partial sums go out in 64-byte pieces, nontemporal (read once, by another kernel).
-template <typename SH, typename EL, bool ROWS16>
+template <typename SH, typename EL>
 __global__ __launch_bounds__(64 * kTileWaves) void head_range_kernel(HeadRangeParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   static_assert(SH::ROWS == kRowsPerBlock, "row blocks of 128");
@@ -30,9 +30,9 @@ __global__ __launch_bounds__(64 * kTileWaves) void head_range_kernel(HeadRangePa
   GemmTileArgs t;
   t.w = (const unsigned char*)p.w + from;
   t.hidden = (const unsigned char*)p.hidden + (size_t)col0 * row_bytes + from;
-  t.zeros = p.zeros; t.D = (int)((to - from) / EL::ELEM); t.pitch = p.D; t.V = p.V; t.row_base = rb * SH::ROWS;
+  t.zeros = p.zeros; t.D = (int)((to - from) / EL::ELEM); t.pitch = p.D; t.V = p.V; t.row_base = rb * SH::ROWS; t.streamed = p.streamed;
   f32x4 acc[SH::RT][SH::CTW];
-  gemm_tile<4, SH, EL, ROWS16>(t, TileColumns{cols}, smem, acc);
+  tile_product<SH, EL>(t, TileColumns{cols}, smem, acc);
   const int Vp = p.row_blocks * SH::ROWS;
   float* out = p.part + ((size_t)split * p.cols + col0) * Vp + t.row_base;
 #pragma unroll
@@ -45,45 +45,41 @@ __global__ __launch_bounds__(64 * kTileWaves) void head_range_kernel(HeadRangePa
   }
 }
 
-template <typename EL, bool ROWS16, typename F>
-static hipError_t each_shape(F&& f) {
-  hipError_t e = f(Tile128x16{});
-  if (e == hipSuccess) e = f(Tile128x32{});
-  if (e == hipSuccess) e = f(Tile128x64{});
-  if (e == hipSuccess) e = f(Tile128x128{});
+template <typename F>
+static hipError_t each_shape(bool dma, F&& f) {
+  hipError_t e = dma ? f(Dma128x16{}) : f(Tile128x16{});
+  if (e == hipSuccess) e = dma ? f(Dma128x32{}) : f(Tile128x32{});
+  if (e == hipSuccess) e = dma ? f(Dma128x64{}) : f(Tile128x64{});
+  if (e == hipSuccess) e = dma ? f(Dma128x128{}) : f(Tile128x128{});
   return e;
-}
-template <typename EL, bool ROWS16>
-static hipError_t launch_rows(const HeadRangeParams& p, hipStream_t stream) {
-  return each_shape<EL, ROWS16>([&](auto shape) {
-    using SH = decltype(shape);
-    if (SH::COLS != p.tile_cols) return hipSuccess;
-    const long long units = (long long)p.row_blocks * p.splits, grid = (units + 7) / 8 * 8 * p.col_blocks;
-    hipLaunchKernelGGL((head_range_kernel<SH, EL, ROWS16>), dim3((unsigned)grid), dim3(64 * kTileWaves), SH::LDS_BYTES, stream, p);
-    return hipGetLastError();
-  });
 }
 template <typename EL>
 static hipError_t launch_type(const HeadRangeParams& p, hipStream_t stream) {
-  return tile_rows16(p.D, EL::ELEM) ? launch_rows<EL, true>(p, stream) : launch_rows<EL, false>(p, stream);
+  return each_shape(dma_rows(p.V, p.D, EL::ELEM), [&](auto shape) {
+    using SH = decltype(shape);
+    if (SH::COLS != p.tile_cols) return hipSuccess;
+    const long long units = (long long)p.row_blocks * p.splits, grid = (units + 7) / 8 * 8 * p.col_blocks;
+    hipLaunchKernelGGL((head_range_kernel<SH, EL>), dim3((unsigned)grid), dim3(64 * kTileWaves), SH::LDS_BYTES, stream, p);
+    return hipGetLastError();
+  });
 }
 hipError_t launch_head_ranges(const HeadRangeParams& p, bool f32, hipStream_t stream) {
   return f32 ? launch_type<TileF32>(p, stream) : launch_type<TileBf16>(p, stream);
 }
 
-template <typename EL, bool ROWS16>
-static hipError_t allow_lds() {
-  return each_shape<EL, ROWS16>([](auto shape) {
+template <typename EL>
+static hipError_t allow_lds(bool dma) {
+  return each_shape(dma, [](auto shape) {
     using SH = decltype(shape);
-    return hipFuncSetAttribute((const void*)head_range_kernel<SH, EL, ROWS16>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               SH::LDS_BYTES);
+    return hipFuncSetAttribute((const void*)head_range_kernel<SH, EL>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
   });
 }
 hipError_t prepare_head_ranges() {
-  hipError_t e = allow_lds<TileBf16, true>();
-  if (e == hipSuccess) e = allow_lds<TileBf16, false>();
-  if (e == hipSuccess) e = allow_lds<TileF32, true>();
-  if (e == hipSuccess) e = allow_lds<TileF32, false>();
+  hipError_t e = hipSuccess;
+  for (const bool dma : {false, true}) {
+    if (e == hipSuccess) e = allow_lds<TileBf16>(dma);
+    if (e == hipSuccess) e = allow_lds<TileF32>(dma);
+  }
   return e;
 }
 

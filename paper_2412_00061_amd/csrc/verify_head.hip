@@ -3,8 +3,8 @@
 //
 // The head is the same stream over a [V, D] weight matrix as the draft head, but with up to 128 columns
 // (one per tree node) instead of 8, and all that is kept of a column is its best (logit, id) key:
-//   * verify_head_kernel         - the tile loop of gemm_tile.h: 128 vocabulary rows x 16 to 128 columns per
-//                                  workgroup (256 x 128 when there are several column blocks); all column blocks
+//   * verify_head_kernel         - the tile loop of dma_tile.h (gemm_tile.h): 128 vocabulary rows x 16 to 128 columns per
+//                                  workgroup (256 x 128 or 256 x 256 with more columns); all column blocks
 //                                  in one launch, those of a row block side by side on one XCD (the weights come
 //                                  from HBM once)
 //   * verify_head_merge_kernel   - best key over the row blocks -> token id, -1 for rows without a node
@@ -12,40 +12,41 @@
 //                                  -> its token id
 #include <type_traits>
 
-#include "gemm_tile.h"
+#include "dma_tile.h"
 #include "head_ranges.h"
 
 namespace ctcspec {
 
 constexpr int kVhCols = kVerifyCols;            // columns (tree nodes) per pass over the weights
 constexpr int kVhWaves = kTileWaves;
-constexpr int kVhDist = 4;                      // prefetch distance in steps = register stages per operand
-// dynamic LDS of a tile shape: the staging buffers, or the logit block (column-major, 4 floats of pad per column)
-// when the caller asks for logits - whichever is larger
+// dynamic LDS of a tile shape: the staging buffers, or the logit block (column-major, 4 floats of pad per column, at most
+// kVhCols columns at a time) when the caller asks for logits - whichever is larger
 template <typename SH>
 constexpr int vh_lds_bytes() {
-  return SH::LDS_BYTES > SH::COLS * (SH::ROWS + 4) * 4 ? SH::LDS_BYTES : SH::COLS * (SH::ROWS + 4) * 4;
+  constexpr int block = (SH::COLS < kVhCols ? SH::COLS : kVhCols) * (SH::ROWS + 4) * 4;
+  return SH::LDS_BYTES > block ? SH::LDS_BYTES : block;
 }
-static_assert(kVhCols == 128 && Tile128x128::COLS == kVhCols && Tile256x128::COLS == kVhCols, "tile shape");
-static_assert(vh_lds_bytes<Tile256x128>() <= 160 * 1024, "fits the compute unit's LDS");
+static_assert(kVhCols == 128 && Tile128x128::COLS == kVhCols && Tile256x128::COLS == kVhCols && Dma256x256::COLS == 2 * kVhCols, "tile shape");
+static_assert(vh_lds_bytes<Tile256x128>() <= 160 * 1024 && vh_lds_bytes<Dma256x256>() <= 160 * 1024, "fits the compute unit's LDS");
 
 struct VerifyHeadParams {
   const void* hidden;   // [cols_total][D]
   const void* w;        // [V][D]
   int cols_total;       // all columns of the call, covered in one launch, block by block
-  int col_blocks;       // ceil(cols_total / kVhCols)
+  int col_blocks;       // of the tile shape's columns
   int D, V;
   int n_blocks;         // row blocks (of the tile shape's rows: 128 or 256)
-  unsigned long long* pkey;  // [col_blocks][n_blocks][kVhCols] best key per (column block, row block, column)
+  unsigned long long* pkey;  // [blocks of kVhCols columns][n_blocks][kVhCols] best key per (column block, row block, column)
   float* logits_out;    // [cols_total][V] or null
   const void* zeros;    // 256 bytes of zeros
   const int32_t* n_nodes;  // [B]
   int max_nodes;
   int32_t* target;      // [cols_total]
+  bool streamed;        // streamed_weights (dma_tile.h)
 };
 
 // ---- the shared tile loop, then the best (logit, id) key per column ----------------------------------------------
-template <typename SH, typename EL, bool ROWS16>
+template <typename SH, typename EL>
 __global__ __launch_bounds__(64 * kVhWaves) void verify_head_kernel(VerifyHeadParams p) {
   constexpr int ROWS = SH::ROWS, CTW = SH::CTW, WR = SH::WR, RT = SH::RT;
   constexpr int ZSTRIDE = ROWS + 4;  // floats per column of the logit block
@@ -63,14 +64,14 @@ __global__ __launch_bounds__(64 * kVhWaves) void verify_head_kernel(VerifyHeadPa
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int cb = slot % p.col_blocks, rb = (slot / p.col_blocks) * 8 + xcd;
   if (rb >= p.n_blocks) return;
-  const int col0 = cb * kVhCols;
-  const int cols = p.cols_total - col0 < kVhCols ? p.cols_total - col0 : kVhCols;
+  const int col0 = cb * SH::COLS;
+  const int cols = p.cols_total - col0 < SH::COLS ? p.cols_total - col0 : SH::COLS;
   const int row_base = rb * ROWS;
   GemmTileArgs t;
   t.w = p.w; t.hidden = (const unsigned char*)p.hidden + (size_t)col0 * p.D * EL::ELEM; t.zeros = p.zeros;
-  t.D = t.pitch = p.D; t.V = p.V; t.row_base = row_base;
+  t.D = t.pitch = p.D; t.V = p.V; t.row_base = row_base; t.streamed = p.streamed;
   f32x4 acc[RT][CTW];
-  gemm_tile<kVhDist, SH, EL, ROWS16>(t, TileColumns{cols}, smem, acc);
+  tile_product<SH, EL>(t, TileColumns{cols}, smem, acc);
 
   // ---- best (logit, id) key per column ---------------------------------------------------------------------
   // (the loop's last barrier has every wavefront done with the LDS tiles)
@@ -78,20 +79,26 @@ __global__ __launch_bounds__(64 * kVhWaves) void verify_head_kernel(VerifyHeadPa
     // the logit block goes through LDS so that it leaves in rows of the output
     float* zbuf = (float*)smem;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+    for (int first = 0; first < SH::COLS; first += kVhCols) {
+      const int wcol = wc * 16 * CTW - first;  // this wavefront's columns in the part of kVhCols
+      if (wcol >= 0 && wcol < kVhCols)
 #pragma unroll
-      for (int ct = 0; ct < CTW; ++ct)
-        *(f32x4*)(zbuf + (wc * 16 * CTW + ct * 16 + c) * ZSTRIDE + (wr * RT + rt) * 16 + g * 4) = acc[rt][ct];
-    __syncthreads();
-    for (int idx = tid; idx < cols * ROWS; idx += NTHREADS) {
-      const int m = idx / ROWS, r = idx % ROWS;
-      if (row_base + r < p.V) p.logits_out[(size_t)(col0 + m) * p.V + row_base + r] = zbuf[m * ZSTRIDE + r];
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int ct = 0; ct < CTW; ++ct)
+            *(f32x4*)(zbuf + (wcol + ct * 16 + c) * ZSTRIDE + (wr * RT + rt) * 16 + g * 4) = acc[rt][ct];
+      __syncthreads();
+      const int here = cols - first < kVhCols ? cols - first : kVhCols;
+      for (int idx = tid; idx < here * ROWS; idx += NTHREADS) {
+        const int m = idx / ROWS, r = idx % ROWS;
+        if (row_base + r < p.V) p.logits_out[(size_t)(col0 + first + m) * p.V + row_base + r] = zbuf[m * ZSTRIDE + r];
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
   // a lane holds 4 RT rows of CTW columns: best of those, then over the 4 lane groups (16 RT rows), then over the
   // WR wavefronts that share the columns
-  unsigned long long* kbuf = (unsigned long long*)smem;  // [WR][128]
+  unsigned long long* kbuf = (unsigned long long*)smem;  // [WR][COLS]
 #pragma unroll
   for (int ct = 0; ct < CTW; ++ct) {
     unsigned long long best = 0ull;
@@ -107,17 +114,18 @@ __global__ __launch_bounds__(64 * kVhWaves) void verify_head_kernel(VerifyHeadPa
     best = o > best ? o : best;
     o = __shfl_xor(best, 32);
     best = o > best ? o : best;
-    if (g == 0) kbuf[wr * kVhCols + wc * 16 * CTW + ct * 16 + c] = best;
+    if (g == 0) kbuf[wr * SH::COLS + wc * 16 * CTW + ct * 16 + c] = best;
   }
   __syncthreads();
   if (tid < cols) {
     unsigned long long best = kbuf[tid];
 #pragma unroll
     for (int r = 1; r < WR; ++r) {
-      const unsigned long long o = kbuf[r * kVhCols + tid];
+      const unsigned long long o = kbuf[r * SH::COLS + tid];
       best = o > best ? o : best;
     }
-    p.pkey[((size_t)cb * p.n_blocks + rb) * kVhCols + tid] = best;
+    const int col = col0 + tid;
+    p.pkey[((size_t)(col / kVhCols) * p.n_blocks + rb) * kVhCols + col % kVhCols] = best;
   }
 }
 
@@ -231,55 +239,47 @@ __global__ __launch_bounds__(256) void kv_commit_kernel(KvCommitParams p) {
   }
 }
 
-template <typename F>
-static hipError_t each_tile_shape(F&& f) {
-  hipError_t e = f(Tile128x16{});
-  if (e == hipSuccess) e = f(Tile128x32{});
-  if (e == hipSuccess) e = f(Tile128x64{});
-  if (e == hipSuccess) e = f(Tile128x128{});
-  if (e == hipSuccess) e = f(Tile256x128{});
+// The tile shapes: those of dma_tile.h where dma_rows says so, else those of gemm_tile.h.
+template <typename... SH, typename F>
+static hipError_t for_shapes(F&& f) {
+  hipError_t e = hipSuccess;
+  ((e = e == hipSuccess ? f(SH{}) : e), ...);
   return e;
 }
-template <typename EL, bool ROWS16>
+template <typename EL>
 static hipError_t allow_lds() {
-  return each_tile_shape([](auto shape) {
+  return for_shapes<Tile128x16, Tile128x32, Tile128x64, Tile128x128, Tile256x128, Dma128x16, Dma128x32, Dma128x64, Dma128x128,
+                    Dma256x128, Dma256x256>([](auto shape) {
     using SH = decltype(shape);
-    return hipFuncSetAttribute((const void*)verify_head_kernel<SH, EL, ROWS16>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute((const void*)verify_head_kernel<SH, EL>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                vh_lds_bytes<SH>());
   });
 }
 hipError_t prepare_verify_head() {
-  hipError_t e = allow_lds<TileBf16, true>();
-  if (e == hipSuccess) e = allow_lds<TileBf16, false>();
-  if (e == hipSuccess) e = allow_lds<TileF32, true>();
-  if (e == hipSuccess) e = allow_lds<TileF32, false>();
-  return e;
+  const hipError_t e = allow_lds<TileBf16>();
+  return e == hipSuccess ? allow_lds<TileF32>() : e;
 }
 
-template <typename SH, typename EL, bool ROWS16>
+template <typename SH, typename EL>
 static hipError_t launch_shape(VerifyHeadParams& p, hipStream_t stream) {
   p.n_blocks = (p.V + SH::ROWS - 1) / SH::ROWS;
+  p.col_blocks = (p.cols_total + SH::COLS - 1) / SH::COLS;
   const long long grid = (long long)((p.n_blocks + 7) / 8) * 8 * p.col_blocks;  // the caller has checked the range
-  hipLaunchKernelGGL((verify_head_kernel<SH, EL, ROWS16>), dim3((unsigned)grid), dim3(64 * kVhWaves), vh_lds_bytes<SH>(),
-                     stream, p);
+  hipLaunchKernelGGL((verify_head_kernel<SH, EL>), dim3((unsigned)grid), dim3(64 * kVhWaves), vh_lds_bytes<SH>(), stream, p);
   return hipGetLastError();
 }
 // One launch for every column block (the kernel's workgroup numbering keeps a row block's column blocks on one XCD).
-// One column block: 128-row tiles as narrow as the columns allow - a workgroup per compute unit, the stream from HBM
-// sets the pace, and no matrix instruction is spent on dead columns.  Several: 256-row tiles - the workgroups of a
-// row block share the weight tile through L2 and the loop's own LDS traffic sets the pace, which the larger tile
-// halves per flop.
-template <typename EL, bool ROWS16>
-static hipError_t launch_rows(VerifyHeadParams& p, hipStream_t stream) {
-  if (p.col_blocks > 1) return launch_shape<Tile256x128, EL, ROWS16>(p, stream);
-  if (p.cols_total <= 16) return launch_shape<Tile128x16, EL, ROWS16>(p, stream);
-  if (p.cols_total <= 32) return launch_shape<Tile128x32, EL, ROWS16>(p, stream);
-  if (p.cols_total <= 64) return launch_shape<Tile128x64, EL, ROWS16>(p, stream);
-  return launch_shape<Tile128x128, EL, ROWS16>(p, stream);
-}
+// Up to 128 columns: 128-row tiles as narrow as the columns allow - a workgroup per compute unit, the stream from HBM
+// sets the pace, and no matrix instruction is spent on dead columns.  More: head_wide_columns in head_plan.h.
 template <typename EL>
 static hipError_t launch_head(VerifyHeadParams& p, hipStream_t stream) {
-  return tile_rows16(p.D, EL::ELEM) ? launch_rows<EL, true>(p, stream) : launch_rows<EL, false>(p, stream);
+  const bool dma = dma_rows(p.V, p.D, EL::ELEM);
+  if (p.cols_total <= 16) return dma ? launch_shape<Dma128x16, EL>(p, stream) : launch_shape<Tile128x16, EL>(p, stream);
+  if (p.cols_total <= 32) return dma ? launch_shape<Dma128x32, EL>(p, stream) : launch_shape<Tile128x32, EL>(p, stream);
+  if (p.cols_total <= 64) return dma ? launch_shape<Dma128x64, EL>(p, stream) : launch_shape<Tile128x64, EL>(p, stream);
+  if (p.cols_total <= kVhCols) return dma ? launch_shape<Dma128x128, EL>(p, stream) : launch_shape<Tile128x128, EL>(p, stream);
+  if (!dma) return launch_shape<Tile256x128, EL>(p, stream);
+  return head_wide_columns(p.V, p.cols_total) == 256 ? launch_shape<Dma256x256, EL>(p, stream) : launch_shape<Dma256x128, EL>(p, stream);
 }
 
 }  // namespace ctcspec
@@ -300,10 +300,11 @@ extern "C" int verify_head_argmax(ctcspec_ctx* ctx, ctcspec_dtype dt, const void
                   "verify_head_argmax: node_hidden and w_base must be 16-byte aligned");
   CTCSPEC_REQUIRE(ctx, B <= ctx->lim.max_batch && max_nodes <= ctx->lim.max_nodes && V <= ctx->lim.max_vocab_rows,
                   CTCSPEC_EUNSUPPORTED, "verify_head_argmax: shape exceeds the context's limits");
+  const long long row_bytes = (long long)D * (dt == CTCSPEC_BF16 ? 2 : 4);
   VerifyHeadParams p;
   p.hidden = node_hidden; p.w = w_base; p.D = D; p.V = V;
   p.zeros = ctx->zeros; p.pkey = ctx->vh_pkey; p.logits_out = logits_out; p.n_nodes = n_nodes; p.max_nodes = max_nodes;
-  p.target = target_argmax;
+  p.target = target_argmax; p.streamed = streamed_weights((long long)V * row_bytes, row_bytes);
   const long long cols_total = (long long)B * max_nodes;
   CTCSPEC_REQUIRE(ctx, (cols_total + kVhCols - 1) / kVhCols <= ctx->vh_col_blocks, CTCSPEC_EUNSUPPORTED,
                   "verify_head_argmax: %lld columns exceed the context's workspace", cols_total);
@@ -312,7 +313,7 @@ extern "C" int verify_head_argmax(ctcspec_ctx* ctx, ctcspec_dtype dt, const void
   p.cols_total = (int)cols_total;
   const bool f32 = dt == CTCSPEC_F32;
   HeadRangeParams r;
-  r.hidden = node_hidden; r.w = w_base; r.zeros = ctx->zeros; r.part = ctx->vh_part; r.cols = p.cols_total; r.D = D; r.V = V;
+  r.hidden = node_hidden; r.w = w_base; r.zeros = ctx->zeros; r.part = ctx->vh_part; r.cols = p.cols_total; r.D = D; r.V = V; r.streamed = p.streamed;
   if (plan_base_head(r, f32)) {
     CTCSPEC_HIP(ctx, launch_head_ranges(r, f32, ctx->stream));
     const hipError_t e = launch_for_rows(V, [&](auto nv) {
@@ -323,7 +324,6 @@ extern "C" int verify_head_argmax(ctcspec_ctx* ctx, ctcspec_dtype dt, const void
     CTCSPEC_HIP(ctx, e);
     return CTCSPEC_OK;
   }
-  p.col_blocks = (int)((cols_total + kVhCols - 1) / kVhCols);
   CTCSPEC_HIP(ctx, dt == CTCSPEC_BF16 ? launch_head<TileBf16>(p, ctx->stream) : launch_head<TileF32>(p, ctx->stream));
   hipLaunchKernelGGL(verify_head_merge_kernel, dim3((unsigned)cols_total), dim3(64), 0, ctx->stream, p);
   CTCSPEC_HIP(ctx, hipGetLastError());

@@ -14,7 +14,7 @@
 // hold up the products behind them (256 x 256: 112 us in bursts, 103 spread).
 //
 // What lies behind the rows, the columns or a row's end has an offset that the hardware's bounds check answers with zeros
-// without reading, so every wavefront has the same number of requests per step and the waits count them.  Large tiles
+// without reading, so every wavefront has the same number of requests per step and the waits count them.  The heads' large tiles
 // (UNIFORM) make the requests behind the last step as well, of a buffer without records, and take plain loads only: branches among
 // 32 products a block cost 4 to 8 % there (512 columns x 32000 rows of 4096), and nontemporal loads spare nothing (122 us
 // both ways when the weights come from memory, 107 against 117 when they are cached).
@@ -28,12 +28,12 @@
 
 namespace ctcspec {
 
-template <int WR_, int RT_, int CTW_, int STEPB_, int NA_, int NB_>
+template <int WR_, int RT_, int CTW_, int STEPB_, int NA_, int NB_, bool UNIFORM_ = false>
 struct DmaShape {
   static constexpr bool DMA = true;
   static constexpr int WR = WR_, WC = kTileWaves / WR_, RT = RT_, CTW = CTW_, STEPB = STEPB_, NA = NA_, NB = NB_;
   static constexpr int ROWS = 16 * RT * WR, COLS = 16 * CTW * WC, KK = STEPB / 64;
-  static constexpr bool UNIFORM = RT * CTW >= 16;
+  static constexpr bool UNIFORM = UNIFORM_;
   static constexpr int CPR = STEPB / 16, RPI = 64 / CPR;  // chunks of a row, rows that one request of a wavefront covers
   static constexpr int AI = ROWS / RPI / kTileWaves;      // requests of a wavefront per step: weights, hidden states
   static constexpr int BI = (COLS / RPI + kTileWaves - 1) / kTileWaves;
@@ -47,8 +47,8 @@ using Dma128x16 = DmaShape<8, 1, 1, 256, 4, 3>;
 using Dma128x32 = DmaShape<4, 2, 1, 256, 4, 3>;
 using Dma128x64 = DmaShape<4, 2, 2, 256, 3, 3>;
 using Dma128x128 = DmaShape<2, 4, 2, 256, 3, 2>;
-using Dma256x128 = DmaShape<4, 4, 4, 128, 3, 3>;
-using Dma256x256 = DmaShape<2, 8, 4, 128, 3, 2>;
+using Dma256x128 = DmaShape<4, 4, 4, 128, 3, 3, true>;
+using Dma256x256 = DmaShape<2, 8, 4, 128, 3, 2, true>;
 
 // Rows that lie a multiple of 4096 bytes apart, all workgroups at about the same place of their rows: what is in flight then
 // falls on a part of the memory channels.  Successive steps are therefore taken 2048 bytes apart, so that the

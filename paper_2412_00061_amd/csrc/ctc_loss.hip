@@ -25,6 +25,7 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 constexpr int kCtcMaxLabels = 2047;  // with the blank 2048 positions: 2 per thread of ctc_row_kernel's 1024, 4 of its 512
 constexpr int kCtcMaxRow = 16 * 1024 * 4;  // 65536 symbols: 16 16-byte loads per thread of a 1024-thread workgroup
 constexpr int kCtcFixThreads = 256;
+constexpr float kDpNarrow = -60.f;  // the recursion in doubles takes log2 p from here on (and p = 0)
 
 struct CtcParams {
   const float* logits;      // [B][T][Vp1]
@@ -41,7 +42,7 @@ struct CtcParams {
   int blocks;     // blocks of pairs
   // the pipelined recursions (null otherwise)
   unsigned long long* edge;  // [B][2][T][blocks]: what a block hands to the next one, 0: not there yet
-  int* wide;      // [B][T]: 1 when a log-probability of the frame is too low for the pipelined recursion
+  int* wide;      // [B][T]: a log-probability of the frame is too low for the recursion in doubles (1), in mantissas and exponents (2)
   int* ticket;
   float wide_below;
   double* logp;   // [B]: log2 P(Y | X)
@@ -169,7 +170,8 @@ __global__ __launch_bounds__(THREADS) void ctc_row_kernel(CtcParams p) {
     const float l = (zy[r] - lse) * kLog2e;
     if (j < L) out[j] = l;
     else if (j == L) out[p.Lmax] = l;  // this thread's spare slot fetched the blank
-    if (p.edge && j <= L && l < p.wide_below && l > -INFINITY) p.wide[(size_t)b * p.T + t] = 1;  // cleared above
+    if (p.edge && j <= L && !(l >= kDpNarrow) && l != -INFINITY)  // cleared above
+      atomicOr(p.wide + (size_t)b * p.T + t, l < p.wide_below ? 3 : 1);
   }
   if (g) {
     const float inv = 1.f / sum;
@@ -407,15 +409,22 @@ __device__ void ctc_links(const CtcParams& p, int b, int part, int parts, int32_
 //   wavefront 0 runs the recursion over kDpFrames frames, neighbours by a lane shift, no barrier between frames;
 //   wavefront 1 fetches and converts the next frames' probabilities and waits for the values that the block before hands over
 //               (the label state of its last pair, frame by frame);
-//   wavefronts 2 and 3 hand over this block's, convert the frames before to what ctc_fix_kernel reads and write them
-//               (half of the frames each: that is as many instructions a frame as the recursion itself).
+//   the others  hand over this block's, convert the frames before to what ctc_fix_kernel reads and write them, four or
+//               eight frames each (that is more instructions a frame than the recursion itself).
 // One barrier per kDpFrames frames.  A value handed over is one 64-bit word (never 0) stored and loaded with relaxed
 // device-scope atomics: nothing has to be fenced.  Blocks take their number from a ticket in dependence order, so the
 // block that a workgroup waits for has always been started before it.
 //
-// The values are linear, as mantissa and exponent (m in [0.5, 1), value m * 2^e): three ldexp and a sum take the place of
-// three exp2 and a log2, the relative error of a step is 2^-24 whatever the length of the sequence, and no frame maximum has
-// to be known.  An impossible state has e = kDpFloor; everything below kDpImpossible counts as impossible.
+// The values are linear: doubles against a power of two of the lane's own, which stays for the kDpFrames frames of a step.  A frame is
+// two sums and two products then, and a factor - the scale of the lane before against this lane's - on what comes from there.
+// The scale is the exponent of the larger of the lane's two values, or that of the lane before less 60 where that is more: with
+// log2 p >= -60 (kDpNarrow) values neither overflow in sixteen frames (at most 2^(60 * 16) * 3^16 flows in) nor fall out of a
+// double's range (2^-960); what a lane loses at the start of a step is 2^-1000 of what its neighbour sends it.
+//
+// Sequences with a lower log-probability, or one that is not a number, hold mantissa and exponent (m in [0.5, 1), value m * 2^e):
+// three ldexp and a sum take the place of three exp2 and a log2, the relative error of a step is 2^-24 whatever the length of
+// the sequence, and no frame maximum has to be known.  An impossible state has e = kDpFloor; everything below kDpImpossible counts as
+// impossible.
 //
 // Sequences with a finite log-probability so low that exponents could get there (wide_below: about -32768, a token that
 // is masked out by a large finite number) run the same pipeline in the log domain (LOG): a block holds its values
@@ -425,15 +434,19 @@ __device__ void ctc_links(const CtcParams& p, int b, int part, int parts, int32_
 //
 // The backward recursion is the forward one over the mirrored sequence (last frame and last state first).
 //
-// Bound: instruction issue of wavefront 0, about 40 instructions a frame (0.1 us).  Measured, 4 sequences of 2048 frames
-// with up to 1024 labels: 217 us.  One workgroup of 1024 threads per sequence and direction, log domain, a barrier and a
+// Bound: instruction issue of wavefront 0.  Measured, 4 sequences of 2048 frames
+// with up to 1024 labels: 186 us - 1.1 us a step of sixteen frames, and three steps that each block runs behind the one before; in mantissas
+// and exponents, about 40 instructions a frame, 217.  One workgroup of 1024 threads per sequence and direction, log domain, a barrier and a
 // frame maximum per frame took 1221 us, and its gradient was five times as far from the float64 one (5e-6 against 9e-7).
 // In the log domain a frame takes about 0.25 us: 4 x 2048 frames of 1001 symbols, 1024 labels, the blank masked with -1e9,
 // 585 us a call; 8 x 512 frames, 100 labels 123 us.  One workgroup per sequence and direction, a barrier and a frame
 // maximum per frame: 1794 and 258 us with 1024 threads, 2400 and 223 us with 256 and the pairs in registers.
 constexpr int kDpFrames = 16;
 constexpr int kDpPairs = 64;
-constexpr int kDpThreads = 256;
+constexpr int dp_threads(int writers) { return 64 * (2 + writers); }  // writers: wavefronts that convert and write the rows
+constexpr int kDpDecay = 60;               // exponents by which a lane's scale may lie below that of the lane before
+enum DpForm { kDpDouble, kDpMantissa, kDpLog };
+static_assert(kDpDecay >= -kDpNarrow && kDpFrames * (kDpDecay + 2) < 1022, "values stay within a double's range over a step");
 constexpr int kDpFloor = -(1 << 30);
 constexpr int kDpZeroP = -(1 << 29);       // exponent of a probability that is 0
 constexpr int kDpImpossible = -(1 << 28);
@@ -444,6 +457,10 @@ struct DpShared {
   u32x2 in[2][kDpFrames][64];   // label probability (m, e) per lane
   u32x4 uni[2][kDpFrames];      // blank probability (m, e), handed-over value (m, e) of the frame before
   u32x4 out[2][kDpFrames][64];  // blank (m, e), label (m, e) after the frame
+  // kDpDouble: `in` and the first half of `uni` are doubles, `out` two of them, and
+  int scale[2][64];             // the lanes' exponents
+  int highest[2];               // largest exponent handed over
+  double edge[kDpFrames];       // the handed-over values against lane 0's exponent
 };
 
 __device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
@@ -486,10 +503,35 @@ __device__ __forceinline__ DpValue dp_scaled(float sum, int e, float pm, int pe)
   return v;
 }
 
-// One block of states of one sequence and direction, by a workgroup.  LOG: in the log domain (see above).
-template <bool LOG>
+// a double as mantissa and exponent, against 2^scale; zero has no exponent
+__device__ __forceinline__ DpValue dp_value(double v, int scale) {
+  DpValue r;
+  r.m = v == 0.0 ? 0.5f : (float)__builtin_amdgcn_frexp_mant(v);
+  r.e = v == 0.0 ? kDpFloor : __builtin_amdgcn_frexp_exp(v) + scale;
+  return r;
+}
+__device__ __forceinline__ double lane_shift_up(double v, double first) {
+  const unsigned long long x = (unsigned long long)__double_as_longlong(v), y = (unsigned long long)__double_as_longlong(first);
+  return as_double(lane_shift_up((unsigned)x, (unsigned)y), lane_shift_up((unsigned)(x >> 32), (unsigned)(y >> 32)));
+}
+// the largest of the lanes up to and with this one
+__device__ __forceinline__ int wave_prefix_max(int v) {
+#define CTCSPEC_PREFIX(CTRL, ROWS) v = imax(v, __builtin_amdgcn_update_dpp(kDpFloor, v, CTRL, ROWS, 0xf, false));
+  CTCSPEC_PREFIX(0x111, 0xf)  // row_shr:1, 2, 4, 8
+  CTCSPEC_PREFIX(0x112, 0xf)
+  CTCSPEC_PREFIX(0x114, 0xf)
+  CTCSPEC_PREFIX(0x118, 0xf)
+  CTCSPEC_PREFIX(0x142, 0xa)  // row_bcast:15 into rows 1 and 3
+  CTCSPEC_PREFIX(0x143, 0xc)  // row_bcast:31 into rows 2 and 3
+#undef CTCSPEC_PREFIX
+  return v;
+}
+
+// One block of states of one sequence and direction, by a workgroup.  FORM: what holds the values (see above).
+template <int FORM, int WRITERS>
 __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int directions, int block, int b, bool backward,
                                           int L, int Tb) {
+  constexpr bool LOG = FORM == kDpLog, DOUBLE = FORM == kDpDouble;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool last_block = (block + 1) * kDpPairs > L;
@@ -528,14 +570,57 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
     // LOG: the two states against off, the largest of the block against off
     float bl = q == 0 ? 0.f : -INFINITY, ll = -INFINITY, top = block == 0 ? 0.f : -INFINITY;
     double off = 0.0;
+    // DOUBLE: the two states against 2^scale
+    double db = q == 0 ? 1.0 : 0.0, dl = 0.0;
+    int scale = 0;
     lds_barrier();  // LDS only: loads and stores of memory stay in flight
     auto frames_of = [&](int ch, auto partial) __attribute__((always_inline)) {
       const int buf = ch & 1;
+      double from_before = 0.0, from_label = 0.0;  // factors of the label before's value, into the blank and into the label
+      double pl[kDpFrames], pb[kDpFrames], edge_in[kDpFrames];
+      if constexpr (DOUBLE) {
+        // all of the step's probabilities are asked for first: an LDS read takes as long as a frame
+#pragma unroll
+        for (int f = 0; f < kDpFrames; ++f) {
+          pl[f] = *(const double*)&sh.in[buf][f][lane];
+          pb[f] = *(const double*)&sh.uni[buf][f];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        int e = imax(dp_value(db, scale).e, dp_value(dl, scale).e);
+        e = lane == 0 ? imax(e, sh.highest[buf] - kDpDecay) : e;
+        const int next = wave_prefix_max(e + kDpDecay * lane) - kDpDecay * lane;
+        db = __builtin_amdgcn_ldexp(db, scale - next);
+        dl = __builtin_amdgcn_ldexp(dl, scale - next);
+        scale = next;
+        sh.scale[buf][lane] = scale;
+        const int before = (int)lane_shift_up((unsigned)scale, (unsigned)scale);  // lane 0: `edge` is against its own
+        from_before = __builtin_amdgcn_ldexp(1.0, before - scale);
+        from_label = skip ? from_before : 0.0;
+        if (lane < kDpFrames) {
+          const u32x4 un = sh.uni[buf][lane];
+          const int e = (int)un[3];
+          sh.edge[lane] = e < kDpImpossible ? 0.0 : __builtin_amdgcn_ldexp((double)__uint_as_float(un[2]), e - (int)readlane_u32((unsigned)scale, 0));
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int f = 0; f < kDpFrames; ++f) edge_in[f] = sh.edge[f];
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int f = 0; f < kDpFrames; ++f) {
         const u32x2 pr = sh.in[buf][f][lane];
         const u32x4 un = sh.uni[buf][f];
         const bool run = !decltype(partial)::value || ch * kDpFrames + f < Tb;  // frames past the end change nothing
+        if constexpr (DOUBLE) {
+          const double x = lane_shift_up(dl, edge_in[f]);
+          const double nb = __builtin_fma(from_before, x, db) * pb[f];
+          const double nl = __builtin_fma(from_label, x, dl + db) * pl[f];
+          db = run ? nb : db;
+          dl = run ? nl : dl;
+          const unsigned long long vb = (unsigned long long)__double_as_longlong(db), vl = (unsigned long long)__double_as_longlong(dl);
+          sh.out[buf][f][lane] = u32x4{(unsigned)vb, (unsigned)(vb >> 32), (unsigned)vl, (unsigned)(vl >> 32)};
+          continue;
+        }
         if constexpr (LOG) {
           const double h = as_double(un[2], un[3]);
           double ref = fmax(off + (double)top, h);
@@ -577,6 +662,10 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
       else if (ch < chunks) frames_of(ch, std::true_type{});
       lds_barrier();
     }
+    if constexpr (DOUBLE) {
+      const DpValue vb = dp_value(db, scale), vl = dp_value(dl, scale);
+      bm = vb.m; be = vb.e; lm = vl.m; le = vl.e;
+    }
     if (!backward && last_block) {
       // P = the last blank + the label before it
       unsigned long long v = kNothing;
@@ -603,41 +692,69 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
     }
   } else if (wave == 1) {
     const int col = has_label ? j : p.Lmax;
-    float lp[kDpFrames], lb = 0.f;
+    // log-probabilities come two chunks ahead, handed-over values one: a chunk takes less than a load from memory
+    float lp[2][kDpFrames], lb[2] = {0.f, 0.f};
     unsigned long long early = 0ull;
-    auto fetch = [&](int ch) {
-      if (lane < kDpFrames) early = look(ch * kDpFrames + lane - 1);
+    auto fetch = [&](int ch, auto set) __attribute__((always_inline)) {
+      constexpr int S = decltype(set)::value;
 #pragma unroll
       for (int f = 0; f < kDpFrames; ++f) {
         const int i = ch * kDpFrames + f;
-        lp[f] = lpc[(size_t)frame(i < Tb ? i : Tb - 1) * LP + col];
+        lp[S][f] = lpc[(size_t)frame(i < Tb ? i : Tb - 1) * LP + col];
       }
       const int i = ch * kDpFrames + (lane & (kDpFrames - 1));
-      lb = lpc[(size_t)frame(i < Tb ? i : Tb - 1) * LP + p.Lmax];
+      lb[S] = lpc[(size_t)frame(i < Tb ? i : Tb - 1) * LP + p.Lmax];
     };
-    auto prepare = [&](int ch) {  // chunk ch, whose log-probabilities are in lp / lb; fetches the next one's
+    auto look_early = [&](int ch) __attribute__((always_inline)) {
+      if (lane < kDpFrames) early = look(ch * kDpFrames + lane - 1);
+    };
+    // chunk ch, whose log-probabilities are in set S; asks for the handed-over values of the next and fills the set again
+    auto prepare = [&](int ch, auto set) __attribute__((always_inline)) {
+      constexpr int S = decltype(set)::value;
       const int buf = ch & 1;
 #pragma unroll
       for (int f = 0; f < kDpFrames; ++f) {
         if constexpr (LOG) {
-          sh.in[buf][f][lane] = u32x2{__float_as_uint(has_label ? lp[f] : -INFINITY), 0u};
+          sh.in[buf][f][lane] = u32x2{__float_as_uint(has_label ? lp[S][f] : -INFINITY), 0u};
+        } else if constexpr (DOUBLE) {
+          const unsigned long long v = (unsigned long long)__double_as_longlong(has_label ? (double)__builtin_amdgcn_exp2f(lp[S][f]) : 0.0);
+          sh.in[buf][f][lane] = u32x2{(unsigned)v, (unsigned)(v >> 32)};
         } else {
-          const DpValue v = dp_probability(lp[f]);
+          const DpValue v = dp_probability(lp[S][f]);
           sh.in[buf][f][lane] = u32x2{__float_as_uint(v.m), has_label ? (unsigned)v.e : (unsigned)kDpZeroP};
         }
       }
-      const DpValue vb = LOG ? DpValue{lb, 0} : dp_probability(lb);
+      const DpValue vb = LOG ? DpValue{lb[S], 0} : dp_probability(lb[S]);
       if (lane < kDpFrames) {
         const unsigned long long h = wait_for(ch * kDpFrames + lane - 1, early);
-        sh.uni[buf][lane] = u32x4{__float_as_uint(vb.m), (unsigned)vb.e, (unsigned)h, (unsigned)(h >> 32)};
+        if constexpr (DOUBLE) {
+          const unsigned long long v = (unsigned long long)__double_as_longlong((double)__builtin_amdgcn_exp2f(lb[S]));
+          sh.uni[buf][lane] = u32x4{(unsigned)v, (unsigned)(v >> 32), (unsigned)h, (unsigned)(h >> 32)};
+          int e = (int)(h >> 32);
+          e = imax(e, (int)dpp_row_ror<1>((unsigned)e));
+          e = imax(e, (int)dpp_row_ror<2>((unsigned)e));
+          e = imax(e, (int)dpp_row_ror<4>((unsigned)e));
+          e = imax(e, (int)dpp_row_ror<8>((unsigned)e));
+          if (lane == 0) sh.highest[buf] = e;
+        } else {
+          sh.uni[buf][lane] = u32x4{__float_as_uint(vb.m), (unsigned)vb.e, (unsigned)h, (unsigned)(h >> 32)};
+        }
       }
-      if (ch + 1 < chunks) fetch(ch + 1);
+      if (ch + 1 < chunks) look_early(ch + 1);
+      if (ch + 2 < chunks) fetch(ch + 2, set);
     };
-    fetch(0);
-    prepare(0);
+    using Even = std::integral_constant<int, 0>;
+    using Odd = std::integral_constant<int, 1>;
+    fetch(0, Even{});
+    look_early(0);
+    if (chunks > 1) fetch(1, Odd{});
+    prepare(0, Even{});
     lds_barrier();
-    for (int ch = 0; ch <= chunks; ++ch) {
-      if (ch + 1 < chunks) prepare(ch + 1);
+    for (int ch = 0; ch <= chunks; ch += 2) {
+      if (ch + 1 < chunks) prepare(ch + 1, Odd{});
+      lds_barrier();
+      if (ch + 1 > chunks) break;
+      if (ch + 2 < chunks) prepare(ch + 2, Even{});
       lds_barrier();
     }
   } else {
@@ -654,17 +771,28 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
             word = (unsigned long long)__double_as_longlong(as_double(v[2], v[3]) + (double)__uint_as_float(v[1]));
             word = word ? word : 1ull << 63;  // -0.0
           }
+          if constexpr (DOUBLE) {
+            const DpValue l = dp_value(as_double(v[2], v[3]), sh.scale[buf][63]);
+            word = ((unsigned long long)(unsigned)l.e << 32) | __float_as_uint(l.m);
+          }
           __hip_atomic_store(edge + (size_t)frame(i0 + lane) * p.blocks + block, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if (directions == 2) {  // (the loss alone needs no rows)
           constexpr int kGroup = 4;  // frames side by side: the chain of a frame is long and narrow
 #pragma unroll
-          for (int f0 = 0; f0 < kDpFrames / 2; f0 += kGroup) {
-            const int first = (wave - 2) * (kDpFrames / 2) + f0;
+          for (int f0 = 0; f0 < kDpFrames / WRITERS; f0 += kGroup) {
+            const int first = (wave - 2) * (kDpFrames / WRITERS) + f0;
             u32x4 v[kGroup];
             int ref[kGroup];
 #pragma unroll
-            for (int u = 0; u < kGroup; ++u) v[u] = sh.out[buf][first + u][lane];
+            for (int u = 0; u < kGroup; ++u) {
+              v[u] = sh.out[buf][first + u][lane];
+              if constexpr (DOUBLE) {
+                const DpValue vb = dp_value(as_double(v[u][0], v[u][1]), sh.scale[buf][lane]);
+                const DpValue vl = dp_value(as_double(v[u][2], v[u][3]), sh.scale[buf][lane]);
+                v[u] = u32x4{__float_as_uint(vb.m), (unsigned)vb.e, __float_as_uint(vl.m), (unsigned)vl.e};
+              }
+            }
 #pragma unroll
             for (int u = 0; u < kGroup; ++u) ref[u] = q <= L ? imax((int)v[u][1], (int)v[u][3]) : kDpFloor;
             if constexpr (!LOG) wave_max_i32(ref);
@@ -688,7 +816,8 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
 }
 
 // Workgroups beyond the recursions' `jobs` build the links of the labels meanwhile.
-__global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, int directions, int jobs) {
+template <int WRITERS>
+__global__ __launch_bounds__(dp_threads(WRITERS)) void ctc_dp_pipe_kernel(CtcParams p, int directions, int jobs) {
   __shared__ DpShared sh;
   __shared__ int job_id;
   const int tid = threadIdx.x;
@@ -714,10 +843,11 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
     }
     return;
   }
-  int too_low = 0;
-  for (int t = tid; t < Tb; t += kDpThreads) too_low |= p.wide[(size_t)b * p.T + t];
-  if (__syncthreads_or(too_low)) ctc_block<true>(p, sh, directions, block, b, backward, L, Tb);
-  else ctc_block<false>(p, sh, directions, block, b, backward, L, Tb);
+  int wide = 0;
+  for (int t = tid; t < Tb; t += dp_threads(WRITERS)) wide |= p.wide[(size_t)b * p.T + t];
+  if (__syncthreads_or(wide & 2)) ctc_block<kDpLog, WRITERS>(p, sh, directions, block, b, backward, L, Tb);
+  else if (WRITERS == 2 || __syncthreads_or(wide)) ctc_block<kDpMantissa, WRITERS>(p, sh, directions, block, b, backward, L, Tb);
+  else if constexpr (WRITERS == 4) ctc_block<kDpDouble, WRITERS>(p, sh, directions, block, b, backward, L, Tb);
 }
 
 // One wavefront per frame: the occupancies gamma_t(s) = alpha_t(s) beta_t(s) / (p_t(z_s) P) of the label's tokens
@@ -728,7 +858,9 @@ __global__ __launch_bounds__(kDpThreads) void ctc_dp_pipe_kernel(CtcParams p, in
 __global__ __launch_bounds__(kCtcFixThreads) void ctc_fix_kernel(CtcParams p) {
   extern __shared__ float occupancies[];  // [wavefront][Lmax]
   const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * (kCtcFixThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), b = blockIdx.y;
+  // the rows written last come first: part of them is still in the last-level cache (4 x 2048 rows of 32001: 193 -> 190 us)
+  const int t = (gridDim.x - 1 - blockIdx.x) * (kCtcFixThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = gridDim.y - 1 - blockIdx.y;
   const int Tb = clampi(p.frame_len[b], 0, p.T);
   if (t >= Tb) return;  // rows past the sequence were written as zeros
   float* __restrict__ g = p.grad + ((size_t)b * p.T + t) * p.Vp1;
@@ -822,6 +954,11 @@ static bool ctc_pipelined(int B, int T, int Lmax) {
   if (T >= kShortFrames) return Lmax >= kDpPairs || B <= 768;
   return T >= kPipeFrames && B <= 8 * T - 64;
 }
+// Doubles and four writers, whose workgroups take more registers, while there is a compute unit for each; beyond that the chip's
+// throughput counts, and mantissas with two writers are the faster form.  us in doubles with four writers / in mantissas with two, 64
+// frames, 20 labels: 128 sequences (256 workgroups) 27.3 / 28.1, 256 44.0 / 42.2, 300 51.3 / 46.2; 512 frames, 200 labels: 32 (256) 93.6 /
+// 110.9, 100 253 / 246.
+static bool ctc_doubles(long long jobs) { return jobs <= 256; }
 static CtcWorkspace ctc_workspace(int B, int T, int Lmax) {
   CtcWorkspace w;
   size_t off = 0;
@@ -925,7 +1062,10 @@ extern "C" int ctc_loss(ctcspec_ctx* ctx, const float* logits, const int32_t* la
     CTCSPEC_HIP(ctx, hipGetLastError());
     return CTCSPEC_OK;
   }
-  hipLaunchKernelGGL(ctc_dp_pipe_kernel, dim3((unsigned)groups), dim3(kDpThreads), 0, st, p, directions, (int)jobs);
+  if (ctc_doubles(jobs))
+    hipLaunchKernelGGL(ctc_dp_pipe_kernel<4>, dim3((unsigned)groups), dim3(dp_threads(4)), 0, st, p, directions, (int)jobs);
+  else
+    hipLaunchKernelGGL(ctc_dp_pipe_kernel<2>, dim3((unsigned)groups), dim3(dp_threads(2)), 0, st, p, directions, (int)jobs);
   CTCSPEC_HIP(ctx, hipGetLastError());
   if (grad) {
     const int per = kCtcFixThreads / 64;

@@ -55,6 +55,7 @@ struct HeadPlan {
   int row_blocks, col_blocks;
 };
 
+constexpr double kHeadMergeUs = 2.0;  // the second launch, which a single row block does not take
 constexpr double kStartUs = 6.0;  // a workgroup's way to its first step
 inline double step_us(int tile_cols, bool f32, long long groups) {
   const int i = tile_cols <= 16 ? 0 : tile_cols <= 32 ? 1 : tile_cols <= 64 ? 2 : 3;
@@ -111,12 +112,16 @@ constexpr int kHeadSlowRows = kHeadColumnThreads * 4 * 4;
 inline bool plan_draft_head(HeadPlan& p, bool f32, int k) {
   const int tile_cols = head_tile_cols(p.cols);
   const double epilogue_us = tile_cols == 16 ? 1.5 : k <= 2 ? 2.0 : k <= 4 ? 3.0 : 4.0;
-  return plan_head(p, f32, head_whole_us(p.V, p.cols, p.D, f32, kHeadRowBlock, tile_cols, epilogue_us),
+  // (the epilogue of a lane per column takes as long as the launch that it saves)
+  const double merge_us = p.V <= kHeadRowBlock && tile_cols == 16 ? -0.5 * kHeadMergeUs : 0.0;
+  return plan_head(p, f32, head_whole_us(p.V, p.cols, p.D, f32, kHeadRowBlock, tile_cols, epilogue_us) + merge_us,
                    1.5 + 0.2 * k + (p.V > kHeadSlowRows ? 3.0 : 0.0), kDraftPartFloats);
 }
 inline bool plan_base_head(HeadPlan& p, bool f32) {
   const int rows = p.cols > kHeadColBlock ? 256 : 128;
-  return plan_head(p, f32, head_whole_us(p.V, p.cols, p.D, f32, rows, head_tile_cols(p.cols), 1.0),
+  const double whole_us = p.V <= kHeadRowBlock ? head_whole_us(p.V, p.cols, p.D, f32, kHeadRowBlock, 16, 1.0) - kHeadMergeUs
+                                               : head_whole_us(p.V, p.cols, p.D, f32, rows, head_tile_cols(p.cols), 1.0);
+  return plan_head(p, f32, whole_us,
                    p.V > kHeadSlowRows ? 3.0 : 1.0, kHeadPartFloats);
 }
 

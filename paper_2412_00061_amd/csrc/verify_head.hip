@@ -45,6 +45,14 @@ struct VerifyHeadParams {
   bool streamed;        // streamed_weights (dma_tile.h)
 };
 
+// the token of a column's best key; rows of the node table without a node get -1
+__device__ __forceinline__ void store_target(const VerifyHeadParams& p, int col, unsigned long long best) {
+  const int b = col / p.max_nodes, i = col - b * p.max_nodes;
+  int n = p.n_nodes[b];
+  n = n < 0 ? 0 : (n > p.max_nodes ? p.max_nodes : n);
+  p.target[col] = i < n ? (int32_t)rank_key_index(best) : -1;
+}
+
 // ---- the shared tile loop, then the best (logit, id) key per column ----------------------------------------------
 template <typename SH, typename EL>
 __global__ __launch_bounds__(64 * kVhWaves) void verify_head_kernel(VerifyHeadParams p) {
@@ -62,7 +70,8 @@ __global__ __launch_bounds__(64 * kVhWaves) void verify_head_kernel(VerifyHeadPa
   // first of them pulls from HBM serves the others from that L2 - one pass over the weights in HBM for any number
   // of columns.  (One column block: row block = workgroup number.)
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int cb = slot % p.col_blocks, rb = (slot / p.col_blocks) * 8 + xcd;
+  const bool alone = p.n_blocks == 1;  // a single row block: its column blocks over all XCDs, nothing to merge
+  const int cb = alone ? blockIdx.x : slot % p.col_blocks, rb = alone ? 0 : (slot / p.col_blocks) * 8 + xcd;
   if (rb >= p.n_blocks) return;
   const int col0 = cb * SH::COLS;
   const int cols = p.cols_total - col0 < SH::COLS ? p.cols_total - col0 : SH::COLS;
@@ -125,6 +134,10 @@ __global__ __launch_bounds__(64 * kVhWaves) void verify_head_kernel(VerifyHeadPa
       best = o > best ? o : best;
     }
     const int col = col0 + tid;
+    if (alone) {
+      store_target(p, col, best);
+      return;
+    }
     p.pkey[((size_t)(col / kVhCols) * p.n_blocks + rb) * kVhCols + col % kVhCols] = best;
   }
 }
@@ -146,12 +159,7 @@ __global__ __launch_bounds__(64) void verify_head_merge_kernel(VerifyHeadParams 
     for (int u = 0; u < 4; ++u) best = x[u] > best ? x[u] : best;
   }
   best = wave_max_u64(best);
-  if (lane == 0) {
-    const int b = col / p.max_nodes, i = col - b * p.max_nodes;
-    int n = p.n_nodes[b];
-    n = n < 0 ? 0 : (n > p.max_nodes ? p.max_nodes : n);
-    p.target[col] = i < n ? (int32_t)rank_key_index(best) : -1;
-  }
+  if (lane == 0) store_target(p, col, best);
 }
 
 // one workgroup per column: the ranges' sums, the logits' row, the best key
@@ -264,16 +272,18 @@ template <typename SH, typename EL>
 static hipError_t launch_shape(VerifyHeadParams& p, hipStream_t stream) {
   p.n_blocks = (p.V + SH::ROWS - 1) / SH::ROWS;
   p.col_blocks = (p.cols_total + SH::COLS - 1) / SH::COLS;
-  const long long grid = (long long)((p.n_blocks + 7) / 8) * 8 * p.col_blocks;  // the caller has checked the range
+  const long long grid = p.n_blocks == 1 ? p.col_blocks : (long long)((p.n_blocks + 7) / 8) * 8 * p.col_blocks;  // the caller has checked the range
   hipLaunchKernelGGL((verify_head_kernel<SH, EL>), dim3((unsigned)grid), dim3(64 * kVhWaves), vh_lds_bytes<SH>(), stream, p);
   return hipGetLastError();
 }
 // One launch for every column block (the kernel's workgroup numbering keeps a row block's column blocks on one XCD).
 // Up to 128 columns: 128-row tiles as narrow as the columns allow - a workgroup per compute unit, the stream from HBM
-// sets the pace, and no matrix instruction is spent on dead columns.  More: head_wide_columns in head_plan.h.
+// sets the pace, and no matrix instruction is spent on dead columns.  More: head_wide_columns in head_plan.h.  A single row
+// block (dma_rows says no there) is cut into blocks of 16 columns and finishes itself: 100 rows of 64 float, 128 columns 6.2 -> 4.4 us.
 template <typename EL>
 static hipError_t launch_head(VerifyHeadParams& p, hipStream_t stream) {
   const bool dma = dma_rows(p.V, p.D, EL::ELEM);
+  if (p.V <= kRowsPerBlock) return launch_shape<Tile128x16, EL>(p, stream);  // as many workgroups as the columns give
   if (p.cols_total <= 16) return dma ? launch_shape<Dma128x16, EL>(p, stream) : launch_shape<Tile128x16, EL>(p, stream);
   if (p.cols_total <= 32) return dma ? launch_shape<Dma128x32, EL>(p, stream) : launch_shape<Tile128x32, EL>(p, stream);
   if (p.cols_total <= 64) return dma ? launch_shape<Dma128x64, EL>(p, stream) : launch_shape<Tile128x64, EL>(p, stream);
@@ -325,8 +335,10 @@ extern "C" int verify_head_argmax(ctcspec_ctx* ctx, ctcspec_dtype dt, const void
     return CTCSPEC_OK;
   }
   CTCSPEC_HIP(ctx, dt == CTCSPEC_BF16 ? launch_head<TileBf16>(p, ctx->stream) : launch_head<TileF32>(p, ctx->stream));
-  hipLaunchKernelGGL(verify_head_merge_kernel, dim3((unsigned)cols_total), dim3(64), 0, ctx->stream, p);
-  CTCSPEC_HIP(ctx, hipGetLastError());
+  if (p.n_blocks > 1) {
+    hipLaunchKernelGGL(verify_head_merge_kernel, dim3((unsigned)cols_total), dim3(64), 0, ctx->stream, p);
+    CTCSPEC_HIP(ctx, hipGetLastError());
+  }
   return CTCSPEC_OK;
 }
 

@@ -12,7 +12,8 @@
 //                                streams 16 rows, the hidden states of all columns sit in LDS (up to 11
 //                                columns at D = 4096)
 //   * lmhead_tile_kernel       - everything else (more columns, other hidden sizes, float operands): the tile
-//                                loop of gemm_tile.h, both operands stepping through LDS
+//                                loop of dma_tile.h (rows that start anywhere, single steps and single row
+//                                blocks: gemm_tile.h), both operands stepping through LDS
 // Both hand the block over in LDS to the same epilogue.  Vocabularies that do not fill the chip are cut along the hidden
 // dimension as well (head_ranges.h); lmhead_columns_kernel then finishes a column.
 #include <mutex>
@@ -49,7 +50,7 @@ struct LmHeadParams {
   bool streamed;      // streamed_weights (dma_tile.h)
 };
 
-// What a vocabulary of a single row block leaves itself, to the bits of the merge kernel: 101 rows of 64 float, 4 columns 7.2 -> 4.9 us
+// What a vocabulary of a single row block leaves itself, to the bits of the merge kernel: 101 rows of 64 float, 4 columns 6.6 -> 4.1 us
 // a call.
 __device__ __forceinline__ float block_lse(float mx, float s) { return (mx > -INFINITY ? mx : -INFINITY) + __logf(s); }
 __device__ __forceinline__ void store_ranked(const LmHeadParams& p, int col, int r, unsigned long long key, float lse) {
@@ -691,7 +692,8 @@ static int draft_topk_launch(ctcspec_ctx* err, hipStream_t stream, const LmScrat
                      : k <= 4 ? launch_columns<4>(h, p, stream) : launch_columns<8>(h, p, stream));
     return CTCSPEC_OK;  // (nothing of it can be left to the collapse kernel)
   }
-  if (dt == CTCSPEC_BF16 && p.n_blocks > 1) {  // (a stream of one workgroup is none: 64 columns x 100 rows of 512 15.9 us, 7.0 as a tile)
+  if (dt == CTCSPEC_BF16 && p.n_blocks > 1) {  // (a stream of one workgroup is none: 64 columns x 100 rows of 512 15.9 us, 12.8 as a tile,
+    // 7.7 in the ranges it gets)
     if (const int stages = draft_stream_stages(p.BT, D)) {
       p.KC = D;
       p.hs_bytes = p.BT * (2 * D + 32);

@@ -6,7 +6,7 @@
 
 namespace ctcspec {
 
-// Bound: start-up (a workgroup's first tile is in LDS after about 6 us) and then LDS traffic per step, as in gemm_tile.h; the
+// Bound: start-up (a workgroup's first tile is in LDS after about 6 us) and then a step's way from HBM or L2 into LDS (dma_tile.h); the
 // partial sums go out in 64-byte pieces, nontemporal (read once, by another kernel).
 template <typename SH, typename EL>
 __global__ __launch_bounds__(64 * kTileWaves) void head_range_kernel(HeadRangeParams p) {

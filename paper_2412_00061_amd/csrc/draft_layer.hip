@@ -29,8 +29,8 @@ __device__ __forceinline__ unsigned short float_to_bf16_bits(float f) {
 // Why this split: a pass is bound by what a compute unit takes in per step - its weight rows from HBM and all
 // columns' activations from L2, about 45 GB/s together - so the rows of a workgroup and the number of splits are chosen
 // to fill the 256 compute units in as few rounds as possible (layer_plan.h), not by the matrix alone.
-// Measured at the 7B shape (passes over 101, 34, 180 and 90 MB), all four passes together: 8 columns 80 us = 5.1 TB/s,
-// 64 columns 108 us.  Before, wavefronts streamed 16-row units past activations held in LDS, 16 columns at a time: 107 us
+// Measured at the 7B shape (passes over 101, 34, 180 and 90 MB), all four passes together: 8 columns 75 us = 5.4 TB/s,
+// 64 columns 106 us (through registers, steps in order: 84 to 88 and 117).  Before that, wavefronts streamed 16-row units past activations held in LDS, 16 columns at a time: 107 us
 // for 8 columns (three accumulators per wavefront for ranges that cross row tiles, 6 MB of partial tiles per pass),
 // 16 passes of 28 to 32 us for 64.
 struct LayerTileParams {

@@ -21,8 +21,9 @@ inline int tile_columns(int cols) { return cols <= 16 ? 32 : (cols <= 32 ? 64 : 
 // Rows of a workgroup and k splits of an [N][K] pass: fewest microseconds by the model
 //   rounds over the compute units x (steps x time of a step + 6 us until the first tile is in LDS)
 //   + the partial sums written and read back at 5 TB/s,
-// a step taking what the compute unit needs for its bytes: 45 GB/s for weights and activations together (the base
-// head's 1.39 us per 64 KB step), 25 GB/s for the weights alone (its share of HBM).
+// a step taking what the compute unit needs for its bytes: 45 GB/s for weights and activations together (1.39 us
+// per 64 KB step), 25 GB/s for the weights alone (its share of HBM).  Taken from a tile loop through registers; with the loads straight into
+// LDS the choice is still within 1.5 % of the best of all (rows, splits) at the 7B shape.
 inline bool make_plan(LayerPlan& pl, int N, int K, int cols, int plane_cols, int cus) {
   if (K % kLtTripK != 0 || N % 16 != 0 || cols < 1 || cols > kLtMaxCols) return false;
   if ((long long)K * 2 * 256 >= (1LL << 32) || (long long)K * 4 * plane_cols >= (1LL << 32)) return false;  // 32-bit offsets

@@ -21,11 +21,12 @@
 namespace ctcspec {
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) int i32x2;
 
 constexpr int kCtcMaxLabels = 2047;  // with the blank 2048 positions: 2 per thread of ctc_row_kernel's 1024, 4 of its 512
 constexpr int kCtcMaxRow = 16 * 1024 * 4;  // 65536 symbols: 16 16-byte loads per thread of a 1024-thread workgroup
 constexpr int kCtcFixThreads = 256;
-constexpr float kDpNarrow = -60.f;  // the recursion in doubles takes log2 p from here on (and p = 0)
+constexpr float kDpNarrow = -40.f;  // the recursion in doubles takes log2 p from here on (and p = 0)
 
 struct CtcParams {
   const float* logits;      // [B][T][Vp1]
@@ -405,7 +406,7 @@ __device__ void ctc_links(const CtcParams& p, int b, int part, int parts, int32_
 // ---- the recursions, pipelined over blocks of states ---------------------------------------------------------------
 // A state depends on itself and on the two states before it, in the frame before: dependences run one way through the
 // states, so the states are cut into blocks of 64 pairs (a lane per pair) and a block may run as far behind the one before
-// it as it likes.  A workgroup of four wavefronts owns a block of one sequence and direction:
+// it as it likes.  A workgroup of four or six wavefronts owns a block of one sequence and direction:
 //   wavefront 0 runs the recursion over kDpFrames frames, neighbours by a lane shift, no barrier between frames;
 //   wavefront 1 fetches and converts the next frames' probabilities and waits for the values that the block before hands over
 //               (the label state of its last pair, frame by frame);
@@ -415,13 +416,18 @@ __device__ void ctc_links(const CtcParams& p, int b, int part, int parts, int32_
 // device-scope atomics: nothing has to be fenced.  Blocks take their number from a ticket in dependence order, so the
 // block that a workgroup waits for has always been started before it.
 //
-// The values are linear: doubles against a power of two of the lane's own, which stays for the kDpFrames frames of a step.  A frame is
-// two sums and two products then, and a factor - the scale of the lane before against this lane's - on what comes from there.
-// The scale is the exponent of the larger of the lane's two values, or that of the lane before less 60 where that is more: with
-// log2 p >= -60 (kDpNarrow) values neither overflow in sixteen frames (at most 2^(60 * 16) * 3^16 flows in) nor fall out of a
-// double's range (2^-960); what a lane loses at the start of a step is 2^-1000 of what its neighbour sends it.
+// The values are linear: doubles against a power of two of the state's own, which stays for the kDpFrames frames of a step.  A frame
+// is three sums and two products then, with a factor - the scale of the state before against this one's - on what comes from there.
+// A state's scale is its value's exponent, or the scale of a state before it less kDpDecay where that is more, so that what arrives
+// within the step does not overflow (a factor of 2^40 and three terms a frame: 2^660).  With log2 p >= kDpNarrow a value that
+// is at most kDpRoom below its scale keeps all of its bits in sixteen frames.  One that lies further below would be lost, and may be the one
+// that counts in the end: a path that is ahead may be the only one that still reaches the last state in time, and one that waits
+// may be the one whose token comes again.  Nor may a factor be rounded to 0 unless what it stands for is below 2^-60 of what is there
+// (kDpLeast).  Where the values before a step do not allow for it, the block takes the step in mantissas and exponents (below): one
+// step in a hundred where each token is certain in one frame and at 2^-35 elsewhere, none with random logits.  (Scales of the lane, for
+// both of its states, and no such look: losses off by up to a third, and infinite ones.)
 //
-// Sequences with a lower log-probability, or one that is not a number, hold mantissa and exponent (m in [0.5, 1), value m * 2^e):
+// Sequences with a lower log-probability, or one that is not a number, take all steps so.  They hold mantissa and exponent (m in [0.5, 1), value m * 2^e):
 // three ldexp and a sum take the place of three exp2 and a log2, the relative error of a step is 2^-24 whatever the length of
 // the sequence, and no frame maximum has to be known.  An impossible state has e = kDpFloor; everything below kDpImpossible counts as
 // impossible.
@@ -435,8 +441,8 @@ __device__ void ctc_links(const CtcParams& p, int b, int part, int parts, int32_
 // The backward recursion is the forward one over the mirrored sequence (last frame and last state first).
 //
 // Bound: instruction issue of wavefront 0.  Measured, 4 sequences of 2048 frames
-// with up to 1024 labels: 186 us - 1.1 us a step of sixteen frames, and three steps that each block runs behind the one before; in mantissas
-// and exponents, about 40 instructions a frame, 217.  One workgroup of 1024 threads per sequence and direction, log domain, a barrier and a
+// with up to 1024 labels: 192 us - 1.1 us a step of sixteen frames, and three steps that each block runs behind the one before; in mantissas
+// and exponents, about 40 instructions a frame, 227.  One workgroup of 1024 threads per sequence and direction, log domain, a barrier and a
 // frame maximum per frame took 1221 us, and its gradient was five times as far from the float64 one (5e-6 against 9e-7).
 // In the log domain a frame takes about 0.25 us: 4 x 2048 frames of 1001 symbols, 1024 labels, the blank masked with -1e9,
 // 585 us a call; 8 x 512 frames, 100 labels 123 us.  One workgroup per sequence and direction, a barrier and a frame
@@ -444,9 +450,11 @@ __device__ void ctc_links(const CtcParams& p, int b, int part, int parts, int32_
 constexpr int kDpFrames = 16;
 constexpr int kDpPairs = 64;
 constexpr int dp_threads(int writers) { return 64 * (2 + writers); }  // writers: wavefronts that convert and write the rows
-constexpr int kDpDecay = 60;               // exponents by which a lane's scale may lie below that of the lane before
+constexpr int kDpDecay = 40;               // exponents by which a state's scale may lie below that of a state before it
+constexpr int kDpRoom = 1010 - kDpFrames * kDpDecay;             // ... a value below its scale
+constexpr int kDpLeast = kDpFrames * (2 * kDpDecay + 2) + 60;    // a scale so far above that of a state before: nothing of it arrives
 enum DpForm { kDpDouble, kDpMantissa, kDpLog };
-static_assert(kDpDecay >= -kDpNarrow && kDpFrames * (kDpDecay + 2) < 1022, "values stay within a double's range over a step");
+static_assert(kDpDecay >= -kDpNarrow && kDpFrames * (kDpDecay + 2) < 1022 && kDpRoom > 0, "values stay within a double's range over a step");
 constexpr int kDpFloor = -(1 << 30);
 constexpr int kDpZeroP = -(1 << 29);       // exponent of a probability that is 0
 constexpr int kDpImpossible = -(1 << 28);
@@ -458,9 +466,10 @@ struct DpShared {
   u32x4 uni[2][kDpFrames];      // blank probability (m, e), handed-over value (m, e) of the frame before
   u32x4 out[2][kDpFrames][64];  // blank (m, e), label (m, e) after the frame
   // kDpDouble: `in` and the first half of `uni` are doubles, `out` two of them, and
-  int scale[2][64];             // the lanes' exponents
+  i32x2 scale[2][64];           // the states' exponents
   int highest[2];               // largest exponent handed over
-  double edge[kDpFrames];       // the handed-over values against lane 0's exponent
+  int mantissas[2];             // the step was taken in mantissas: `out` holds them
+  double edge[kDpFrames];       // the handed-over values against the largest exponent
 };
 
 __device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
@@ -504,19 +513,21 @@ __device__ __forceinline__ DpValue dp_scaled(float sum, int e, float pm, int pe)
 }
 
 // a double as mantissa and exponent, against 2^scale; zero has no exponent
+__device__ __forceinline__ int dp_exponent(double v, int scale) { return v == 0.0 ? kDpFloor : __builtin_amdgcn_frexp_exp(v) + scale; }
 __device__ __forceinline__ DpValue dp_value(double v, int scale) {
   DpValue r;
   r.m = v == 0.0 ? 0.5f : (float)__builtin_amdgcn_frexp_mant(v);
-  r.e = v == 0.0 ? kDpFloor : __builtin_amdgcn_frexp_exp(v) + scale;
+  r.e = dp_exponent(v, scale);
   return r;
 }
 __device__ __forceinline__ double lane_shift_up(double v, double first) {
   const unsigned long long x = (unsigned long long)__double_as_longlong(v), y = (unsigned long long)__double_as_longlong(first);
   return as_double(lane_shift_up((unsigned)x, (unsigned)y), lane_shift_up((unsigned)(x >> 32), (unsigned)(y >> 32)));
 }
-// the largest of the lanes up to and with this one
-__device__ __forceinline__ int wave_prefix_max(int v) {
-#define CTCSPEC_PREFIX(CTRL, ROWS) v = imax(v, __builtin_amdgcn_update_dpp(kDpFloor, v, CTRL, ROWS, 0xf, false));
+// join over the lanes up to and with this one
+template <typename F>
+__device__ __forceinline__ int wave_prefix(int v, int nothing, F&& join) {
+#define CTCSPEC_PREFIX(CTRL, ROWS) v = join(v, __builtin_amdgcn_update_dpp(nothing, v, CTRL, ROWS, 0xf, false));
   CTCSPEC_PREFIX(0x111, 0xf)  // row_shr:1, 2, 4, 8
   CTCSPEC_PREFIX(0x112, 0xf)
   CTCSPEC_PREFIX(0x114, 0xf)
@@ -570,56 +581,85 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
     // LOG: the two states against off, the largest of the block against off
     float bl = q == 0 ? 0.f : -INFINITY, ll = -INFINITY, top = block == 0 ? 0.f : -INFINITY;
     double off = 0.0;
-    // DOUBLE: the two states against 2^scale
+    // DOUBLE: the two states against 2^bscale and 2^lscale
     double db = q == 0 ? 1.0 : 0.0, dl = 0.0;
-    int scale = 0;
+    int bscale = 0, lscale = 0;
+    // the decay from the label handed over to this lane's
+    const int decay = wave_prefix(skip ? kDpDecay : 2 * kDpDecay, 0, [](int x, int y) { return x + y; });
     lds_barrier();  // LDS only: loads and stores of memory stay in flight
+    // a step in doubles; false, and nothing has changed: the values do not allow for it
+    auto double_frames = [&](int ch, auto partial) __attribute__((always_inline)) -> bool {
+      const int buf = ch & 1;
+      double pl[kDpFrames], pb[kDpFrames], edge_in[kDpFrames];
+      // all of the step's probabilities are asked for first, behind what the scales need: an LDS read takes as long as a frame
+      const int highest = sh.highest[buf];
+      const u32x4 un = sh.uni[buf][lane & (kDpFrames - 1)];  // (four lanes a frame)
+      const int handed = (int)un[3];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int f = 0; f < kDpFrames; ++f) {
+        pl[f] = *(const double*)&sh.in[buf][f][lane];
+        pb[f] = *(const double*)&sh.uni[buf][f];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      const int be = dp_exponent(db, bscale), le = dp_exponent(dl, lscale);
+      int top = imax(le, be - kDpDecay) + decay;
+      top = lane == 0 ? imax(top, highest) : top;
+      const int lnext = wave_prefix(top, kDpFloor, imax) - decay;
+      const int before = (int)lane_shift_up((unsigned)lnext, (unsigned)highest);
+      const int bnext = imax(be, before - kDpDecay);
+      // scales as far apart as the factor may neither be held nor left out
+      auto between = [](int above) { return (unsigned)(above - 1022) < (unsigned)(kDpLeast - 1022); };
+      auto below = [](int scale, int e) { return (unsigned)(scale - e - kDpRoom) < (unsigned)(-kDpImpossible); };  // (a state of value 0 is further down)
+      // (without branches)
+      const int no = (int)below(highest, handed) | (int)below(bnext, be) | (int)below(lnext, le) | (int)between(bnext - before) | (int)between(lnext - bnext) |
+                     ((int)skip & (int)between(lnext - before));
+      const bool fits = __builtin_amdgcn_ballot_w64(no != 0) == 0ull;
+      if (lane == 0) sh.mantissas[buf] = fits ? 0 : 1;
+      if (!fits) return false;
+      db = __builtin_amdgcn_ldexp(db, bscale - bnext);
+      dl = __builtin_amdgcn_ldexp(dl, lscale - lnext);
+      bscale = bnext;
+      lscale = lnext;
+      sh.scale[buf][lane] = i32x2{bscale, lscale};
+      // factors: the label before into the blank and into the label, the blank into the label
+      const double from_before = __builtin_amdgcn_ldexp(1.0, before - bscale), from_blank = __builtin_amdgcn_ldexp(1.0, bscale - lscale);
+      const double from_label = skip ? __builtin_amdgcn_ldexp(1.0, before - lscale) : 0.0;
+      if (lane < kDpFrames) sh.edge[lane] = handed < kDpImpossible ? 0.0 : __builtin_amdgcn_ldexp((double)__uint_as_float(un[2]), handed - highest);
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int f = 0; f < kDpFrames; ++f) edge_in[f] = sh.edge[f];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int f = 0; f < kDpFrames; ++f) {
+        const bool run = !decltype(partial)::value || ch * kDpFrames + f < Tb;  // frames past the end change nothing
+        const double x = lane_shift_up(dl, edge_in[f]);
+        const double nb = __builtin_fma(from_before, x, db) * pb[f];
+        const double nl = __builtin_fma(from_label, x, __builtin_fma(from_blank, db, dl)) * pl[f];
+        db = run ? nb : db;
+        dl = run ? nl : dl;
+        const unsigned long long vb = (unsigned long long)__double_as_longlong(db), vl = (unsigned long long)__double_as_longlong(dl);
+        sh.out[buf][f][lane] = u32x4{(unsigned)vb, (unsigned)(vb >> 32), (unsigned)vl, (unsigned)(vl >> 32)};
+      }
+      return true;
+    };
     auto frames_of = [&](int ch, auto partial) __attribute__((always_inline)) {
       const int buf = ch & 1;
-      double from_before = 0.0, from_label = 0.0;  // factors of the label before's value, into the blank and into the label
-      double pl[kDpFrames], pb[kDpFrames], edge_in[kDpFrames];
       if constexpr (DOUBLE) {
-        // all of the step's probabilities are asked for first: an LDS read takes as long as a frame
-#pragma unroll
-        for (int f = 0; f < kDpFrames; ++f) {
-          pl[f] = *(const double*)&sh.in[buf][f][lane];
-          pb[f] = *(const double*)&sh.uni[buf][f];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        int e = imax(dp_value(db, scale).e, dp_value(dl, scale).e);
-        e = lane == 0 ? imax(e, sh.highest[buf] - kDpDecay) : e;
-        const int next = wave_prefix_max(e + kDpDecay * lane) - kDpDecay * lane;
-        db = __builtin_amdgcn_ldexp(db, scale - next);
-        dl = __builtin_amdgcn_ldexp(dl, scale - next);
-        scale = next;
-        sh.scale[buf][lane] = scale;
-        const int before = (int)lane_shift_up((unsigned)scale, (unsigned)scale);  // lane 0: `edge` is against its own
-        from_before = __builtin_amdgcn_ldexp(1.0, before - scale);
-        from_label = skip ? from_before : 0.0;
-        if (lane < kDpFrames) {
-          const u32x4 un = sh.uni[buf][lane];
-          const int e = (int)un[3];
-          sh.edge[lane] = e < kDpImpossible ? 0.0 : __builtin_amdgcn_ldexp((double)__uint_as_float(un[2]), e - (int)readlane_u32((unsigned)scale, 0));
-        }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int f = 0; f < kDpFrames; ++f) edge_in[f] = sh.edge[f];
-        __builtin_amdgcn_sched_barrier(0);
+        if (double_frames(ch, partial)) return;
+        const DpValue vb = dp_value(db, bscale), vl = dp_value(dl, lscale);
+        bm = vb.m; be = vb.e; lm = vl.m; le = vl.e;
       }
 #pragma unroll
       for (int f = 0; f < kDpFrames; ++f) {
-        const u32x2 pr = sh.in[buf][f][lane];
-        const u32x4 un = sh.uni[buf][f];
+        u32x2 pr = sh.in[buf][f][lane];
+        u32x4 un = sh.uni[buf][f];
         const bool run = !decltype(partial)::value || ch * kDpFrames + f < Tb;  // frames past the end change nothing
-        if constexpr (DOUBLE) {
-          const double x = lane_shift_up(dl, edge_in[f]);
-          const double nb = __builtin_fma(from_before, x, db) * pb[f];
-          const double nl = __builtin_fma(from_label, x, dl + db) * pl[f];
-          db = run ? nb : db;
-          dl = run ? nl : dl;
-          const unsigned long long vb = (unsigned long long)__double_as_longlong(db), vl = (unsigned long long)__double_as_longlong(dl);
-          sh.out[buf][f][lane] = u32x4{(unsigned)vb, (unsigned)(vb >> 32), (unsigned)vl, (unsigned)(vl >> 32)};
-          continue;
+        if constexpr (DOUBLE) {  // doubles of 2^kDpNarrow and above, or 0
+          const float pl = (float)as_double(pr[0], pr[1]), pb = (float)as_double(un[0], un[1]);
+          pr = u32x2{__float_as_uint(pl == 0.f ? 0.5f : pl), pl == 0.f ? (unsigned)kDpZeroP : 0u};
+          un[0] = __float_as_uint(pb == 0.f ? 0.5f : pb);
+          un[1] = pb == 0.f ? (unsigned)kDpZeroP : 0u;
         }
         if constexpr (LOG) {
           const double h = as_double(un[2], un[3]);
@@ -656,6 +696,12 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
         le = run ? nl.e : le;
         sh.out[buf][f][lane] = u32x4{__float_as_uint(bm), (unsigned)be, __float_as_uint(lm), (unsigned)le};
       }
+      if constexpr (DOUBLE) {
+        db = be < kDpImpossible ? 0.0 : (double)bm;
+        dl = le < kDpImpossible ? 0.0 : (double)lm;
+        bscale = be;
+        lscale = le;
+      }
     };
     for (int ch = 0; ch <= chunks; ++ch) {
       if ((ch + 1) * kDpFrames <= Tb) frames_of(ch, std::false_type{});
@@ -663,7 +709,7 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
       lds_barrier();
     }
     if constexpr (DOUBLE) {
-      const DpValue vb = dp_value(db, scale), vl = dp_value(dl, scale);
+      const DpValue vb = dp_value(db, bscale), vl = dp_value(dl, lscale);
       bm = vb.m; be = vb.e; lm = vl.m; le = vl.e;
     }
     if (!backward && last_block) {
@@ -764,6 +810,7 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
     for (int ch = 0; ch <= chunks; ++ch) {
       if (ch > 0) {
         const int buf = (ch - 1) & 1, i0 = (ch - 1) * kDpFrames;
+        const bool doubles = DOUBLE && !__builtin_amdgcn_readfirstlane(sh.mantissas[buf]);
         if (wave == 2 && !last_block && lane < kDpFrames && i0 + lane < Tb) {
           const u32x4 v = sh.out[buf][lane][63];
           unsigned long long word = ((unsigned long long)v[3] << 32) | v[2];
@@ -771,8 +818,8 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
             word = (unsigned long long)__double_as_longlong(as_double(v[2], v[3]) + (double)__uint_as_float(v[1]));
             word = word ? word : 1ull << 63;  // -0.0
           }
-          if constexpr (DOUBLE) {
-            const DpValue l = dp_value(as_double(v[2], v[3]), sh.scale[buf][63]);
+          if (doubles) {
+            const DpValue l = dp_value(as_double(v[2], v[3]), sh.scale[buf][63][1]);
             word = ((unsigned long long)(unsigned)l.e << 32) | __float_as_uint(l.m);
           }
           __hip_atomic_store(edge + (size_t)frame(i0 + lane) * p.blocks + block, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -785,11 +832,12 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
             u32x4 v[kGroup];
             int ref[kGroup];
 #pragma unroll
-            for (int u = 0; u < kGroup; ++u) {
-              v[u] = sh.out[buf][first + u][lane];
-              if constexpr (DOUBLE) {
-                const DpValue vb = dp_value(as_double(v[u][0], v[u][1]), sh.scale[buf][lane]);
-                const DpValue vl = dp_value(as_double(v[u][2], v[u][3]), sh.scale[buf][lane]);
+            for (int u = 0; u < kGroup; ++u) v[u] = sh.out[buf][first + u][lane];
+            if (doubles) {
+              const i32x2 scale = sh.scale[buf][lane];
+#pragma unroll
+              for (int u = 0; u < kGroup; ++u) {
+                const DpValue vb = dp_value(as_double(v[u][0], v[u][1]), scale[0]), vl = dp_value(as_double(v[u][2], v[u][3]), scale[1]);
                 v[u] = u32x4{__float_as_uint(vb.m), (unsigned)vb.e, __float_as_uint(vl.m), (unsigned)vl.e};
               }
             }

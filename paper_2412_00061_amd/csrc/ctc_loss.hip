@@ -26,7 +26,7 @@ typedef __attribute__((ext_vector_type(2))) int i32x2;
 constexpr int kCtcMaxLabels = 2047;  // with the blank 2048 positions: 2 per thread of ctc_row_kernel's 1024, 4 of its 512
 constexpr int kCtcMaxRow = 16 * 1024 * 4;  // 65536 symbols: 16 16-byte loads per thread of a 1024-thread workgroup
 constexpr int kCtcFixThreads = 256;
-constexpr float kDpNarrow = -40.f;  // the recursion in doubles takes log2 p from here on (and p = 0)
+constexpr float kDpNarrow = -40.f;  // the recursion in doubles takes log2 p from here on
 
 struct CtcParams {
   const float* logits;      // [B][T][Vp1]
@@ -43,7 +43,7 @@ struct CtcParams {
   int blocks;     // blocks of pairs
   // the pipelined recursions (null otherwise)
   unsigned long long* edge;  // [B][2][T][blocks]: what a block hands to the next one, 0: not there yet
-  int* wide;      // [B][T]: a log-probability of the frame is too low for the recursion in doubles (1), in mantissas and exponents (2)
+  int* wide;      // [B][T]: a log-probability of the frame is not for the recursion in doubles (1), in mantissas and exponents (2)
   int* ticket;
   float wide_below;
   double* logp;   // [B]: log2 P(Y | X)
@@ -171,8 +171,8 @@ __global__ __launch_bounds__(THREADS) void ctc_row_kernel(CtcParams p) {
     const float l = (zy[r] - lse) * kLog2e;
     if (j < L) out[j] = l;
     else if (j == L) out[p.Lmax] = l;  // this thread's spare slot fetched the blank
-    if (p.edge && j <= L && !(l >= kDpNarrow) && l != -INFINITY)  // cleared above
-      atomicOr(p.wide + (size_t)b * p.T + t, l < p.wide_below ? 3 : 1);
+    if (p.edge && j <= L && !(l >= kDpNarrow))  // cleared above
+      atomicOr(p.wide + (size_t)b * p.T + t, l < p.wide_below && l > -INFINITY ? 3 : 1);
   }
   if (g) {
     const float inv = 1.f / sum;
@@ -427,7 +427,8 @@ __device__ void ctc_links(const CtcParams& p, int b, int part, int parts, int32_
 // step in a hundred where each token is certain in one frame and at 2^-35 elsewhere, none with random logits.  (Scales of the lane, for
 // both of its states, and no such look: losses off by up to a third, and infinite ones.)
 //
-// Sequences with a lower log-probability, or one that is not a number, take all steps so.  They hold mantissa and exponent (m in [0.5, 1), value m * 2^e):
+// Sequences with a lower log-probability, one that is not a number or a probability of 0 - which may end, within a step, the larger value
+// beside which another one was left out - take all steps so.  They hold mantissa and exponent (m in [0.5, 1), value m * 2^e):
 // three ldexp and a sum take the place of three exp2 and a log2, the relative error of a step is 2^-24 whatever the length of
 // the sequence, and no frame maximum has to be known.  An impossible state has e = kDpFloor; everything below kDpImpossible counts as
 // impossible.
@@ -655,11 +656,11 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
         u32x2 pr = sh.in[buf][f][lane];
         u32x4 un = sh.uni[buf][f];
         const bool run = !decltype(partial)::value || ch * kDpFrames + f < Tb;  // frames past the end change nothing
-        if constexpr (DOUBLE) {  // doubles of 2^kDpNarrow and above, or 0
-          const float pl = (float)as_double(pr[0], pr[1]), pb = (float)as_double(un[0], un[1]);
-          pr = u32x2{__float_as_uint(pl == 0.f ? 0.5f : pl), pl == 0.f ? (unsigned)kDpZeroP : 0u};
-          un[0] = __float_as_uint(pb == 0.f ? 0.5f : pb);
-          un[1] = pb == 0.f ? (unsigned)kDpZeroP : 0u;
+        if constexpr (DOUBLE) {  // doubles of 2^kDpNarrow and above, 0 where there is no label
+          const float pl = (float)as_double(pr[0], pr[1]);
+          pr = u32x2{__float_as_uint(has_label ? pl : 0.5f), has_label ? 0u : (unsigned)kDpZeroP};
+          un[0] = __float_as_uint((float)as_double(un[0], un[1]));
+          un[1] = 0u;
         }
         if constexpr (LOG) {
           const double h = as_double(un[2], un[3]);
@@ -1004,8 +1005,8 @@ static bool ctc_pipelined(int B, int T, int Lmax) {
 }
 // Doubles and four writers, whose workgroups take more registers, while there is a compute unit for each; beyond that the chip's
 // throughput counts, and mantissas with two writers are the faster form.  us in doubles with four writers / in mantissas with two, 64
-// frames, 20 labels: 128 sequences (256 workgroups) 27.3 / 28.1, 256 44.0 / 42.2, 300 51.3 / 46.2; 512 frames, 200 labels: 32 (256) 93.6 /
-// 110.9, 100 253 / 246.
+// frames, 20 labels: 128 sequences (256 workgroups) 27.8 / 28.5, 256 44.0 / 42.2, 300 51.3 / 46.2; 512 frames, 200 labels: 32 (256) 95.5 /
+// 112.2, 100 253 / 246.
 static bool ctc_doubles(long long jobs) { return jobs <= 256; }
 static CtcWorkspace ctc_workspace(int B, int T, int Lmax) {
   CtcWorkspace w;

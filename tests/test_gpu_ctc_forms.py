@@ -110,3 +110,46 @@ def test_piecewise_constant(pkg, seed):  # noqa: F811
             t += n
     labels = rng.integers(0, C - 1, (B, L)).astype(np.int32)
     _far(pkg, logits, labels, 1, C - 1)
+
+
+# ---- probabilities of exactly 0: what is lost beside a larger value matters once that one is masked out ------------------------
+@pytest.mark.parametrize("copies", [1, 130])
+@pytest.mark.parametrize("mask", [17, 31, 32, 40, 54, 63, 64, 90])  # within a step of sixteen frames, at its ends
+def test_masked_behind_an_improbable_stretch(pkg, mask, copies):  # noqa: F811
+    print(f"ctc_loss masked at {mask} x {copies}", flush=True)
+    T, low = mask + 24, -27.0  # log2 p = -39, where doubles are taken
+    logits = np.full((1, T, 4), np.float32(low))  # tokens 0 and 1 are the label, 2 is another one, 3 the blank
+    logits[0, 0, 0] = 0.0
+    logits[0, 1:mask, 1] = 0.0
+    logits[0, mask] = [0.0, -np.inf, low, -np.inf]
+    logits[0, mask + 1:, 1] = 0.0
+    _far(pkg, logits, np.array([[0, 1]], dtype=np.int32), copies, 3)
+
+
+@pytest.mark.parametrize("seed", range(16))
+def test_piecewise_constant_with_masks(pkg, seed):  # noqa: F811
+    """Segments with tokens masked out that an alignment of the label does not need there; every sequence stays reachable."""
+    rng = np.random.Generator(np.random.PCG64(100 + seed))
+    B, T, C = 3, int(rng.integers(64, 400)), int(rng.integers(3, 8))
+    L = int(rng.integers(1, min(150, T // 3)))
+    low = float(rng.uniform(5, 26))
+    print(f"ctc_loss masks {seed} T={T} L={L} C={C} low={low}", flush=True)
+    labels = rng.integers(0, C - 1, (B, L)).astype(np.int32)
+    logits = np.empty((B, T, C), dtype=np.float32)
+    for b in range(B):
+        # the alignment that stays: a frame for every token, blanks in between
+        needed = np.full(T, C - 1)
+        at = np.sort(rng.choice(T // 2, L, replace=False)) * 2
+        needed[at] = labels[b]
+        t = 0
+        while t < T:
+            n = int(rng.integers(4, 60))
+            logits[b, t:t + n] = rng.uniform(-low, 0.0, C)
+            logits[b, t:t + n, rng.integers(C)] = 0.0
+            masked = rng.random(C) < 0.3
+            for u in range(t, min(T, t + n)):
+                for c in np.flatnonzero(masked):
+                    if c != needed[u]:
+                        logits[b, u, c] = -np.inf
+            t += n
+    _far(pkg, logits, labels, 1, C - 1)

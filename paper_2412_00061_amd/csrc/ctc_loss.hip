@@ -1007,7 +1007,8 @@ static bool ctc_pipelined(int B, int T, int Lmax) {
 // throughput counts, and mantissas with two writers are the faster form.  us in doubles with four writers / in mantissas with two, 64
 // frames, 20 labels: 128 sequences (256 workgroups) 27.8 / 28.5, 256 44.0 / 42.2, 300 51.3 / 46.2; 512 frames, 200 labels: 32 (256) 95.5 /
 // 112.2, 100 253 / 246.
-static bool ctc_doubles(long long jobs) { return jobs <= 256; }
+// Both directions count also where the loss alone is asked for, so that it has the same bits with and without its gradient.
+static bool ctc_doubles(int B, int blocks) { return 2LL * B * blocks <= 256; }
 static CtcWorkspace ctc_workspace(int B, int T, int Lmax) {
   CtcWorkspace w;
   size_t off = 0;
@@ -1111,7 +1112,7 @@ extern "C" int ctc_loss(ctcspec_ctx* ctx, const float* logits, const int32_t* la
     CTCSPEC_HIP(ctx, hipGetLastError());
     return CTCSPEC_OK;
   }
-  if (ctc_doubles(jobs))
+  if (ctc_doubles(B, p.blocks))
     hipLaunchKernelGGL(ctc_dp_pipe_kernel<4>, dim3((unsigned)groups), dim3(dp_threads(4)), 0, st, p, directions, (int)jobs);
   else
     hipLaunchKernelGGL(ctc_dp_pipe_kernel<2>, dim3((unsigned)groups), dim3(dp_threads(2)), 0, st, p, directions, (int)jobs);

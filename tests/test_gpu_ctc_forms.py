@@ -6,9 +6,11 @@ import math
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from test_gpu_ctc_pipeline import _check, pkg  # noqa: F401
+from workloads.device import dev_f32, dev_i32
 
 pytestmark = pytest.mark.gpu
 
@@ -153,3 +155,16 @@ def test_piecewise_constant_with_masks(pkg, seed):  # noqa: F811
                         logits[b, u, c] = -np.inf
             t += n
     _far(pkg, logits, labels, 1, C - 1)
+
+
+@pytest.mark.parametrize("B,T,L", [(128, 90, 30), (129, 90, 30), (200, 120, 40), (256, 90, 30), (257, 90, 30), (43, 200, 130), (80, 200, 130)])
+def test_loss_alone_has_the_same_bits(pkg, B, T, L):  # noqa: F811
+    """One direction or two, on both sides of the line between the forms (256 blocks of both directions)."""
+    print(f"ctc_loss alone B={B} T={T} L={L}", flush=True)
+    rng = np.random.Generator(np.random.PCG64(B))
+    C = 50
+    args = (dev_f32(rng.standard_normal((B, T, C), dtype=np.float32) * np.float32(2)), dev_i32(rng.integers(0, C - 1, (B, L))),
+            dev_i32(rng.integers(L // 2, L + 1, B)), dev_i32(rng.integers(3 * T // 4, T + 1, B)), C - 1)
+    ctx = pkg.Context(max_batch=1, max_slots=1, max_topk=1, max_vocab_rows=8, max_nodes=1, max_heads=1, max_head_dim=8)
+    assert torch.equal(pkg.ctc_loss(ctx, *args)["loss"], pkg.ctc_loss(ctx, *args, want_grad=False)["loss"])
+    ctx.close()

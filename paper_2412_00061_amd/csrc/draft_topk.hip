@@ -61,7 +61,7 @@ __device__ __forceinline__ void store_ranked(const LmHeadParams& p, int col, int
 // Epilogue shared by both producers.  zbuf holds the block's logits column-major:
 // zbuf[col * kZStride + r] = z of row (blockIdx.x*128 + r), -inf for rows >= Vp1.
 // Whole wavefronts must call this (the reductions use every lane).
-__device__ void lmhead_block_epilogue(const LmHeadParams& p, const float* zbuf) {
+__device__ __forceinline__ void lmhead_block_epilogue(const LmHeadParams& p, const float* zbuf) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nwaves = blockDim.x >> 6;
   const int row_base = blockIdx.x * kRowsPerBlock;
@@ -112,7 +112,7 @@ __device__ void lmhead_block_epilogue(const LmHeadParams& p, const float* zbuf) 
 // eight lists that way: 40 columns x 41675 rows of 3840, k = 6, 107 us a call,
 // 88.5 so; 64 columns x 32001 of 4096, k = 4, 64.9 to 65.3 / 60.6 to 63.6 (by card and placement).
 template <int KMAX>
-__device__ void lmhead_block_epilogue_wide(const LmHeadParams& p, const float* zbuf, unsigned char* part) {
+__device__ __forceinline__ void lmhead_block_epilogue_wide(const LmHeadParams& p, const float* zbuf, unsigned char* part) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int row_base = blockIdx.x * kRowsPerBlock;

@@ -44,10 +44,11 @@ struct LayerTileParams {
 };
 struct LayerColumns {
   int cols, plane_cols;
-  __device__ __forceinline__ int row_or_none(int r) const {
+  __device__ __forceinline__ int operator()(int r) const {
     const int col = (r >> 5) * 16 + (r & 15);
-    return col < cols ? ((r >> 4) & 1) * plane_cols + col : -1;
+    return ((r >> 4) & 1) * plane_cols + (col < cols ? col : cols - 1);
   }
+  __device__ __forceinline__ int row_or_none(int r) const { return (r >> 5) * 16 + (r & 15) < cols ? (*this)(r) : -1; }
 };
 template <typename SH>
 __global__ __launch_bounds__(64 * kTileWaves) void layer_tile_kernel(LayerTileParams p) {
@@ -65,7 +66,8 @@ __global__ __launch_bounds__(64 * kTileWaves) void layer_tile_kernel(LayerTilePa
   t.hidden = (const unsigned char*)p.x + (size_t)p.col0 * p.K * 2 + (size_t)t0 * kLtTripK * 2;
   t.zeros = p.zeros; t.D = (t1 - t0) * kLtTripK; t.pitch = p.K; t.V = p.N; t.row_base = rb * SH::ROWS; t.streamed = p.streamed;
   f32x4 acc[SH::RT][SH::CTW];
-  dma_tile<SH, TileBf16>(t, LayerColumns{p.cols, p.plane_cols}, smem, acc);
+  if constexpr (SH::DMA) dma_tile<SH, TileBf16>(t, LayerColumns{p.cols, p.plane_cols}, smem, acc);
+  else gemm_tile<4, SH, TileBf16, true>(t, LayerColumns{p.cols, p.plane_cols}, smem, acc);
   float* out = p.part + (size_t)split * p.cols * p.N;
 #pragma unroll
   for (int ct = 0; ct < SH::CTW; ct += 2) {
@@ -262,6 +264,7 @@ static int device_cus() {
 
 // rows x 16, 32 or 64 columns (twice as many tile columns); which one: layer_plan.h
 using LayerTile128x16 = DmaShape<8, 1, 2, 256, 4, 3>;
+using LayerTileShort = TileShape<8, 2, 128, 1>;  // through registers (layer_plan.h: through_registers)
 using LayerTile256x16 = DmaShape<8, 2, 2, 128, 4, 4>;
 using LayerTile128x32 = DmaShape<4, 2, 2, 256, 3, 3>;
 using LayerTile192x32 = DmaShape<4, 3, 2, 128, 4, 4>;
@@ -275,10 +278,12 @@ static hipError_t launch_shape(const LayerTileParams& tp, hipStream_t stream) {
                      stream, tp);
   return hipGetLastError();
 }
-static hipError_t launch_pass(LayerTileParams& tp, int rows, hipStream_t stream) {
+static hipError_t launch_pass(LayerTileParams& tp, const LayerPlan& plan, hipStream_t stream) {
+  const int rows = plan.rows;
   tp.row_blocks = (tp.N + rows - 1) / rows;
   tp.trips = tp.K / kLtTripK / tp.splits;
   tp.more = tp.K / kLtTripK % tp.splits;
+  if (through_registers(plan, tp.streamed)) return launch_shape<LayerTileShort>(tp, stream);
   switch (tile_columns(tp.cols)) {
     case 32: return rows == 128 ? launch_shape<LayerTile128x16>(tp, stream) : launch_shape<LayerTile256x16>(tp, stream);
     case 64:
@@ -300,7 +305,7 @@ static hipError_t allow_lds() {
   return e;
 }
 hipError_t prepare_draft_layer() {
-  return allow_lds<LayerTile128x16, LayerTile256x16, LayerTile128x32, LayerTile192x32, LayerTile256x32, LayerTile128x64,
+  return allow_lds<LayerTileShort, LayerTile128x16, LayerTile256x16, LayerTile128x32, LayerTile192x32, LayerTile256x32, LayerTile128x64,
                    LayerTile192x64, LayerTile256x64>();
 }
 
@@ -369,7 +374,7 @@ extern "C" int draft_layer_forward(ctcspec_ctx* ctx, ctcspec_dtype dt, const voi
       tp.streamed = streamed_weights(2LL * (4LL * D * D + 3LL * D * F), 2LL * K);
       tp.w = wmat; tp.x = xin; tp.zeros = ctx->zeros; tp.part = (float*)(ws + lw.part);
       tp.N = N; tp.K = K; tp.cols = p.cols; tp.plane_cols = BT; tp.col0 = col0; tp.splits = plan.splits;
-      CTCSPEC_HIP(ctx, launch_pass(tp, plan.rows, st));
+      CTCSPEC_HIP(ctx, launch_pass(tp, plan, st));
       finish(plan);
       CTCSPEC_HIP(ctx, hipGetLastError());
     }

@@ -1,5 +1,6 @@
 // A tile of a [V, D] x [cols, D]^T product, bf16 or float operands, fp32 accumulators, whose rows start at any element
-// (hidden sizes that are no multiple of 16 bytes): what the heads take there, and for the smallest calls.  Others: dma_tile.h.
+// (hidden sizes that are no multiple of 16 bytes): what the heads take there, and for the smallest calls, and the draft layer for
+// its shortest ranges but one.  Others: dma_tile.h.
 //
 // 8 wavefronts in a WR x WC grid (WR * WC = 8): wavefront (wr, wc) owns weight rows [16 RT wr, +16 RT) x columns
 // [16 CTW wc, +16 CTW) - RT x CTW MFMA tiles.  Shapes in use (rows x columns, bytes of a row per step): 128 x 16,
@@ -97,7 +98,8 @@ typedef __attribute__((address_space(1))) u32x4 GlobalU32x4;  // a pointer made 
 // acc[rt][ct][i]: row row_base + 16 (RT wr + rt) + 4 (lane >> 4) + i, column 16 CTW wc + 16 ct + (lane & 15),
 // wr = wave / WC, wc = wave % WC.
 // Every wavefront of the workgroup (8) must call it; it ends with a barrier after the last read of LDS.
-template <int DIST, typename SH, typename EL, typename COLUMNS>
+// STREAMED: rows on 16-byte boundaries, the weights by nontemporal loads.
+template <int DIST, typename SH, typename EL, bool STREAMED = false, typename COLUMNS>
 __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& columns, unsigned char* smem,
                                           f32x4 (&acc)[SH::RT][SH::CTW]) {
   constexpr int CTW = SH::CTW, RT = SH::RT, STEPB = SH::STEPB, PITCH = SH::PITCH, CPR = SH::CPR, RPP = SH::RPP;
@@ -162,7 +164,8 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
 #pragma unroll
     for (int u = 0; u < WP; ++u) {
       const uintptr_t a = wb + ((woff[u] & mask) + lane_off);
-      wreg[S][u] = ((const GlobalPacked16*)a)->v;
+      if constexpr (STREAMED) wreg[S][u] = __builtin_nontemporal_load((const GlobalU32x4*)a);
+      else wreg[S][u] = ((const GlobalPacked16*)a)->v;
     }
     __builtin_amdgcn_sched_barrier(0);
   };

@@ -47,6 +47,16 @@ inline bool make_plan(LayerPlan& pl, int N, int K, int cols, int plane_cols, int
   return true;
 }
 
+// Ranges of two trips, up to 16 columns, weights that are streamed: the tile goes through registers (gemm_tile.h).  All of such a range
+// is requested at once by the loop that loads straight into LDS, and it takes longer than the other loop, whose loads follow one
+// another.  A pass over an [N][K] matrix through registers / straight into LDS, us: 6144 x 2048 in 4 ranges 7.3 / 7.9, 8192 x 2048 in 4 8.6 to
+// 8.9 / 9.4, 2048 x 5632 in 11 7.3 / 7.6, 4096 x 4096 and 4096 x 11008 in 8 together 26.6 / 27.0.  Ranges of one trip: 2048 x 2048 in 8 5.2 / 5.0,
+// 3072 x 1024 in 4 (not streamed) 5.1 / 4.3; of more: 11264 x 2048 in 2 11.0 / 11.0, 12288 x 4096 in 2 20.4 / 18.7, 15360 x 5120 in 2 26.4 / 25.5.
+inline bool through_registers(const LayerPlan& pl, bool streamed) {
+  const int trips = pl.K / kLtTripK;
+  return streamed && pl.rows == 128 && tile_columns(pl.cols) == 32 && (trips + pl.splits - 1) / pl.splits == 2;
+}
+
 struct LayerWorkspace {
   size_t q, arows, h1, xn2, act, n_rows, causal, ss1, ss2, part, total;
 };

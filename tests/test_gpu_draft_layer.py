@@ -158,3 +158,13 @@ WIDE_CASES = [
 @pytest.mark.parametrize("seed,B,T,D,H,F,ctx_len,cap", WIDE_CASES)
 def test_draft_layer_wide_workgroups(pkg, seed, B, T, D, H, F, ctx_len, cap):
     _check(pkg, seed, B, T, D, H, F, ctx_len, cap)
+
+
+# Ranges of two trips over weights that are streamed go through registers (one column, sixteen, two ranges of unequal length);
+# tests/test_layer_plan.py asks the plan.
+SHORT_RANGE_CASES = [(40, 1, 1, 2048, 16, 5632, [70], 96), (41, 2, 8, 2048, 16, 4096, [5, 300], 320), (42, 1, 5, 2048, 16, 4864, [0], 32)]
+
+
+@pytest.mark.parametrize("seed,B,T,D,H,F,ctx_len,cap", SHORT_RANGE_CASES)
+def test_draft_layer_short_ranges(pkg, seed, B, T, D, H, F, ctx_len, cap):
+    _check(pkg, seed, B, T, D, H, F, ctx_len, cap)

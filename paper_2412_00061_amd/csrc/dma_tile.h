@@ -25,6 +25,7 @@
 #pragma once
 
 #include "gemm_tile.h"
+#include "head_plan.h"
 
 namespace ctcspec {
 
@@ -205,15 +206,6 @@ __device__ __forceinline__ void dma_tile(const GemmTileArgs& t, const COLUMNS& c
   if constexpr (SH::UNIFORM) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   lds_barrier();
 #endif
-}
-
-// Which loop a head takes.  Here: rows that start at multiples of 16 bytes (the row size is one), 256 of them within 32-bit
-// offsets.  With a single step (rows of up to 256 bytes) or a single row block there is nothing to pipeline, and the way through
-// registers is 0.3 us shorter: 100 rows of 64 float, 64 and 128 columns 6.3 us here, 6.7 through LDS alone; rows of 256 bf16, 2000 of them, 7 to
-// 10 % faster so.
-inline bool dma_rows(long long V, int D, int elem) {
-  const long long row = (long long)D * elem;
-  return row % 16 == 0 && row * 256 < (1LL << 32) && row > 256 && V > 128;
 }
 
 template <typename SH, typename EL, typename COLUMNS>

@@ -48,6 +48,16 @@ inline size_t head_part_floats(long long cols, int vocab_rows, size_t most) {
 // elements, 16 columns 41.7 / 53.9, 50.2 / 55.0; 128 columns 56.8 / 65.6, 64.2 / 66.2.
 inline bool streamed_weights(long long bytes, long long row_bytes) { return row_bytes % 128 == 0 && bytes > (48LL << 20); }
 
+// Which loop a head's tiles take, in `splits` ranges of its hidden dimension: the one that loads straight into LDS (dma_tile.h), or the one
+// through registers (gemm_tile.h).  The former takes rows that start at multiples of 16 bytes (the row size is one), 256 of them within
+// 32-bit offsets.  With a single step of 256 bytes, whole rows or ranges, or a single row block there is nothing to pipeline, and the way
+// through registers is 0.3 to 0.5 us shorter: 100 rows of 64 float, 64 and 128 columns 6.3 us so, 6.7 straight into LDS alone; rows of 256
+// bf16, 2000 of them, 7 to 10 % faster so; 975 rows of 256 float in four ranges, 20 columns 6.7 and 7.1, 465 rows, 32 columns 10.9 and 11.4.
+inline bool dma_rows(long long V, int D, int elem, int splits = 1) {
+  const long long row = (long long)D * elem;
+  return row % 16 == 0 && row * 256 < (1LL << 32) && row > 256LL * splits && V > kHeadRowBlock;
+}
+
 struct HeadPlan {
   int cols, D, V;
   int tile_cols;       // 16, 32, 64 or 128

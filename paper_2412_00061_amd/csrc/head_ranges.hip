@@ -55,7 +55,7 @@ static hipError_t each_shape(bool dma, F&& f) {
 }
 template <typename EL>
 static hipError_t launch_type(const HeadRangeParams& p, hipStream_t stream) {
-  return each_shape(dma_rows(p.V, p.D, EL::ELEM), [&](auto shape) {
+  return each_shape(dma_rows(p.V, p.D, EL::ELEM, p.splits), [&](auto shape) {
     using SH = decltype(shape);
     if (SH::COLS != p.tile_cols) return hipSuccess;
     const long long units = (long long)p.row_blocks * p.splits, grid = (units + 7) / 8 * 8 * p.col_blocks;

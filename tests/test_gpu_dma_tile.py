@@ -17,7 +17,8 @@ def _case(pkg, dtype, cols, D, V):  # noqa: F811
     B = {200: 2, 520: 8, 732: 6}.get(cols, 1)
     N = cols // B
     h, w, _, _ = _operands(D + cols, cols, D, V, TYPES[dtype])
-    w[[9, 700, V - 1]] = w[9].clone()
+    same = 700 if V > 700 else V // 2
+    w[[9, same, V - 1]] = w[9].clone()
     z_ref = (h.double() @ w.double().t()).cpu().numpy()
     bound = ((D + 1) * 2.0 ** -24 * (h.double().abs() @ w.double().abs().t())).cpu().numpy()
     ctx = pkg.Context(max_batch=B, max_slots=1, max_topk=1, max_vocab_rows=V, max_nodes=N, max_heads=1, max_head_dim=8)
@@ -26,7 +27,7 @@ def _case(pkg, dtype, cols, D, V):  # noqa: F811
     res = pkg.verify_head_argmax(ctx, h.view(B, N, D), w, n_nodes, want_logits=True)
     z = res["logits"].cpu().numpy().reshape(cols, V)
     _check(z, z_ref, bound)
-    assert np.array_equal(z[:, 9], z[:, 700]) and np.array_equal(z[:, 9], z[:, V - 1])
+    assert np.array_equal(z[:, 9], z[:, same]) and np.array_equal(z[:, 9], z[:, V - 1])
     want = z.argmax(1).reshape(B, N)
     want[0, int(n_nodes[0]):] = -1
     assert np.array_equal(res["target_argmax"].cpu().numpy(), want)
@@ -66,3 +67,14 @@ def test_draft_head_shapes(pkg, dtype, elem, row):  # noqa: F811
         assert np.array_equal(z[:, 9], z[:, 700]) and np.array_equal(z[:, 9], z[:, Vp1 - 1])
         assert np.array_equal(res["topk_id"].cpu().numpy().reshape(B * T, k), np.argsort(-z, axis=1, kind="stable")[:, :k])
         ctx.close()
+
+
+# Ranges of the hidden dimension of a single step each go through registers, rows on 16-byte boundaries or not (test_launch_plans.py
+# asks the rule): columns, hidden size, vocabulary rows
+SINGLE_STEPS = [("f32", 20, 256, 975), ("f32", 20, 192, 465), ("f32", 7, 320, 129), ("bf16", 50, 384, 465), ("bf16", 128, 512, 129),
+                ("f32", 200, 128, 465)]
+
+
+@pytest.mark.parametrize("dtype,cols,D,V", SINGLE_STEPS)
+def test_ranges_of_a_single_step(pkg, dtype, cols, D, V):  # noqa: F811
+    _case(pkg, dtype, cols, D, V)

@@ -4,6 +4,7 @@ import pytest
 import launch_plans
 import test_gpu_attn_any as attn_any
 import test_gpu_attn_peaked as attn_peaked
+import test_gpu_dma_tile as dma_tile
 import test_gpu_head_shapes as head_shapes
 import test_gpu_launch_modes as launch_modes
 import test_zz_no_alloc as zz_no_alloc
@@ -90,6 +91,12 @@ def test_head_cases_take_the_kernels_they_are_meant_for():
         "stream", "stream", "ranges", "stream", "tile", "stream", "tile", "ranges", "tile"]
     for way, (B, T, D, Vp1, k) in launch_modes.DEFERRED_HEADS.items():
         assert launch_plans.draft_head(B * T, D, Vp1, "bf16", k)[0] == way
+
+
+def test_cases_of_single_steps_have_them():
+    for dtype, cols, D, V in dma_tile.SINGLE_STEPS:
+        way, _, ranges = launch_plans.base_head(cols, D, V, dtype)
+        assert way == "ranges" and ranges * 256 >= D * (4 if dtype == "f32" else 2)
 
 
 def test_attention_cases_take_the_splits_they_are_meant_for():

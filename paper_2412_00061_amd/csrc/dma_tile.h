@@ -173,11 +173,14 @@ __device__ __forceinline__ void dma_tile(const GemmTileArgs& t, const COLUMNS& c
     if (j < CTW) b[f][j < CTW ? j : 0] = *(const u32x4*)(smem + bslot * SH::B_BYTES + (boff ^ (kk * 64)) + j * 16 * STEPB);
     else if (j < CTW + RT) a[f][j - CTW < RT ? j - CTW : 0] = *(const u32x4*)(smem + aslot * SH::A_BYTES + (aoff ^ (kk * 64)) + (j - CTW) * 16 * STEPB);
   };
-  constexpr int kReads = (CTW + RT + RT - 1) / RT, kRequests = (AI + BI + RT - 1) / RT;  // per row of tiles
+  // Rows of tiles that are taken together: with a single tile a row, its products (of float four, one after the other) would stand alone.
+  // 13106 rows of 1536 float, 32 columns 36.5 -> 35.6 us, bf16 tiles of 32 columns 1.5 % in the mean.
+  constexpr int kRows = CTW == 1 ? RT : 1, kGroups = RT / kRows;
+  constexpr int kReads = (CTW + RT + kGroups - 1) / kGroups, kRequests = (AI + BI + kGroups - 1) / kGroups;  // per group of rows of tiles
   // the products of the fragments in slot f, the reads of block kk for the other slot and, at the end of a step, the requests
   auto block = [&](int f, int kk, auto last) __attribute__((always_inline)) {
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
+    for (int rt = 0; rt < kGroups; ++rt) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int j = rt * kReads; j < (rt + 1) * kReads; ++j) read_fragment(f ^ 1, kk, j);
@@ -185,7 +188,9 @@ __device__ __forceinline__ void dma_tile(const GemmTileArgs& t, const COLUMNS& c
         requests(rt * kRequests < BI + AI ? rt * kRequests : BI + AI, (rt + 1) * kRequests < BI + AI ? (rt + 1) * kRequests : BI + AI);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int ct = 0; ct < CTW; ++ct) acc[rt][ct] = EL::mma(a[f][rt], b[f][ct], acc[rt][ct]);
+      for (int r = 0; r < kRows; ++r)
+#pragma unroll
+        for (int ct = 0; ct < CTW; ++ct) acc[rt * kRows + r][ct] = EL::mma(a[f][rt * kRows + r], b[f][ct], acc[rt * kRows + r][ct]);
     }
     __builtin_amdgcn_sched_barrier(0);
   };

@@ -186,7 +186,8 @@ __device__ __forceinline__ void dma_tile(const GemmTileArgs& t, const COLUMNS& c
       for (int j = rt * kReads; j < (rt + 1) * kReads; ++j) read_fragment(f ^ 1, kk, j);
       if constexpr (decltype(last)::value)
         requests(rt * kRequests < BI + AI ? rt * kRequests : BI + AI, (rt + 1) * kRequests < BI + AI ? (rt + 1) * kRequests : BI + AI);
-      __builtin_amdgcn_sched_barrier(0);
+      // (no fence where four products of float follow one another: requests stand between them, 16 columns x 7367 rows of 2048 30.4 -> 30.1 us)
+      if constexpr (!(CTW == 1 && EL::ELEM == 4)) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int r = 0; r < kRows; ++r)
 #pragma unroll

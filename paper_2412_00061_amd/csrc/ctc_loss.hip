@@ -422,8 +422,8 @@ __device__ void ctc_links(const CtcParams& p, int b, int part, int parts, int32_
 // within the step does not overflow (a factor of 2^40 and three terms a frame: 2^660).  With log2 p >= kDpNarrow a value that
 // is at most kDpRoom below its scale keeps all of its bits in sixteen frames.  One that lies further below would be lost, and may be the one
 // that counts in the end: a path that is ahead may be the only one that still reaches the last state in time, and one that waits
-// may be the one whose token comes again.  Nor may a factor be rounded to 0 unless what it stands for is below 2^-60 of what is there
-// (kDpLeast).  Where the values before a step do not allow for it, the block takes the step in mantissas and exponents (below): one
+// may be the one whose token comes again.  A factor below 2^-1022 would lose bits too.
+// Where the values before a step do not allow for it, the block takes the step in mantissas and exponents (below): one
 // step in a hundred where each token is certain in one frame and at 2^-35 elsewhere, none with random logits.  (Scales of the lane, for
 // both of its states, and no such look: losses off by up to a third, and infinite ones.)
 //
@@ -453,10 +453,10 @@ constexpr int kDpPairs = 64;
 constexpr int dp_threads(int writers) { return 64 * (2 + writers); }  // writers: wavefronts that convert and write the rows
 constexpr int kDpDecay = 40;               // exponents by which a state's scale may lie below that of a state before it
 constexpr int kDpRoom = 1010 - kDpFrames * kDpDecay;             // ... a value below its scale
-constexpr int kDpLeast = kDpFrames * (2 * kDpDecay + 2) + 60;    // a scale so far above that of a state before: nothing of it arrives
 enum DpForm { kDpDouble, kDpMantissa, kDpLog };
 static_assert(kDpDecay >= -kDpNarrow && kDpFrames * (kDpDecay + 2) < 1022 && kDpRoom > 0, "values stay within a double's range over a step");
 constexpr int kDpFloor = -(1 << 30);
+constexpr int kDpMantissas = 1 << 30;      // no exponent
 constexpr int kDpZeroP = -(1 << 29);       // exponent of a probability that is 0
 constexpr int kDpImpossible = -(1 << 28);
 constexpr int kDpMaxPolls = 1 << 20;       // about a second; a wait is over long before
@@ -467,9 +467,8 @@ struct DpShared {
   u32x4 uni[2][kDpFrames];      // blank probability (m, e), handed-over value (m, e) of the frame before
   u32x4 out[2][kDpFrames][64];  // blank (m, e), label (m, e) after the frame
   // kDpDouble: `in` and the first half of `uni` are doubles, `out` two of them, and
-  i32x2 scale[2][64];           // the states' exponents
+  i32x2 scale[2][64];           // the states' exponents; kDpMantissas: the step was taken in mantissas
   int highest[2];               // largest exponent handed over
-  int mantissas[2];             // the step was taken in mantissas: `out` holds them
   double edge[kDpFrames];       // the handed-over values against the largest exponent
 };
 
@@ -587,6 +586,7 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
     int bscale = 0, lscale = 0;
     // the decay from the label handed over to this lane's
     const int decay = wave_prefix(skip ? kDpDecay : 2 * kDpDecay, 0, [](int x, int y) { return x + y; });
+    const int skip_room = skip ? 1022 : 1 << 30;
     lds_barrier();  // LDS only: loads and stores of memory stay in flight
     // a step in doubles; false, and nothing has changed: the values do not allow for it
     auto double_frames = [&](int ch, auto partial) __attribute__((always_inline)) -> bool {
@@ -609,15 +609,16 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
       const int lnext = wave_prefix(top, kDpFloor, imax) - decay;
       const int before = (int)lane_shift_up((unsigned)lnext, (unsigned)highest);
       const int bnext = imax(be, before - kDpDecay);
-      // scales as far apart as the factor may neither be held nor left out
-      auto between = [](int above) { return (unsigned)(above - 1022) < (unsigned)(kDpLeast - 1022); };
-      auto below = [](int scale, int e) { return (unsigned)(scale - e - kDpRoom) < (unsigned)(-kDpImpossible); };  // (a state of value 0 is further down)
-      // (without branches)
-      const int no = (int)below(highest, handed) | (int)below(bnext, be) | (int)below(lnext, le) | (int)between(bnext - before) | (int)between(lnext - bnext) |
-                     ((int)skip & (int)between(lnext - before));
-      const bool fits = __builtin_amdgcn_ballot_w64(no != 0) == 0ull;
-      if (lane == 0) sh.mantissas[buf] = fits ? 0 : 1;
-      if (!fits) return false;
+      // by how much one is more than `room` above the other, as a number from 0 on; more than any such where it is not, or the other is a
+      // value of 0 (kDpFloor)
+      auto above = [](int a, int b, int room) { return (unsigned)(a - b - room); };
+      auto least = [](unsigned a, unsigned b) { return a < b ? a : b; };
+      const unsigned excess = least(least(above(highest, handed, kDpRoom), least(above(bnext, be, kDpRoom), above(lnext, le, kDpRoom))),
+                                    least(above(bnext, before, 1022), least(above(lnext, bnext, 1022), above(lnext, before, skip_room))));
+      if (__builtin_amdgcn_ballot_w64(excess < (unsigned)-kDpImpossible) != 0ull) {
+        sh.scale[buf][lane] = i32x2{kDpMantissas, kDpMantissas};
+        return false;
+      }
       db = __builtin_amdgcn_ldexp(db, bscale - bnext);
       dl = __builtin_amdgcn_ldexp(dl, lscale - lnext);
       bscale = bnext;
@@ -811,7 +812,6 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
     for (int ch = 0; ch <= chunks; ++ch) {
       if (ch > 0) {
         const int buf = (ch - 1) & 1, i0 = (ch - 1) * kDpFrames;
-        const bool doubles = DOUBLE && !__builtin_amdgcn_readfirstlane(sh.mantissas[buf]);
         if (wave == 2 && !last_block && lane < kDpFrames && i0 + lane < Tb) {
           const u32x4 v = sh.out[buf][lane][63];
           unsigned long long word = ((unsigned long long)v[3] << 32) | v[2];
@@ -819,9 +819,10 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
             word = (unsigned long long)__double_as_longlong(as_double(v[2], v[3]) + (double)__uint_as_float(v[1]));
             word = word ? word : 1ull << 63;  // -0.0
           }
-          if (doubles) {
-            const DpValue l = dp_value(as_double(v[2], v[3]), sh.scale[buf][63][1]);
-            word = ((unsigned long long)(unsigned)l.e << 32) | __float_as_uint(l.m);
+          if constexpr (DOUBLE) {
+            const int scale = sh.scale[buf][63][1];
+            const DpValue l = dp_value(as_double(v[2], v[3]), scale);
+            word = scale != kDpMantissas ? ((unsigned long long)(unsigned)l.e << 32) | __float_as_uint(l.m) : word;
           }
           __hip_atomic_store(edge + (size_t)frame(i0 + lane) * p.blocks + block, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -834,8 +835,9 @@ __device__ __forceinline__ void ctc_block(const CtcParams& p, DpShared& sh, int 
             int ref[kGroup];
 #pragma unroll
             for (int u = 0; u < kGroup; ++u) v[u] = sh.out[buf][first + u][lane];
-            if (doubles) {
-              const i32x2 scale = sh.scale[buf][lane];
+            i32x2 scale = {0, 0};
+            if constexpr (DOUBLE) scale = sh.scale[buf][lane];
+            if (DOUBLE && __builtin_amdgcn_readfirstlane(scale[0]) != kDpMantissas) {
 #pragma unroll
               for (int u = 0; u < kGroup; ++u) {
                 const DpValue vb = dp_value(as_double(v[u][0], v[u][1]), scale[0]), vl = dp_value(as_double(v[u][2], v[u][3]), scale[1]);

@@ -47,7 +47,7 @@ struct LmHeadParams {
   float* topk_logp;
   float* lse;
   float* logits_out;
-  bool streamed;      // streamed_weights (dma_tile.h)
+  bool streamed;      // streamed_weights (head_plan.h)
 };
 
 // What a vocabulary of a single row block leaves itself, to the bits of the merge kernel: 101 rows of 64 float, 4 columns 6.6 -> 4.1 us
@@ -696,9 +696,8 @@ static int draft_topk_launch(ctcspec_ctx* err, hipStream_t stream, const LmScrat
                      : k <= 4 ? launch_columns<4>(h, p, stream) : launch_columns<8>(h, p, stream));
     return CTCSPEC_OK;  // (nothing of it can be left to the collapse kernel)
   }
-  if (dt == CTCSPEC_BF16 && p.n_blocks > 1) {  // (a stream of one workgroup is none: 64 columns x 100 rows of 512 15.9 us, 12.8 as a tile,
-    // 7.7 in the ranges it gets)
-    if (const int stages = draft_stream_stages(p.BT, D)) {
+  if (dt == CTCSPEC_BF16) {
+    if (const int stages = draft_stream_stages(p.BT, D, Vp1)) {
       p.KC = D;
       p.hs_bytes = p.BT * (2 * D + 32);
       p.hs_magic = (unsigned int)((0x100000000ull + (unsigned)(D / 8) - 1) / (unsigned)(D / 8));

@@ -42,7 +42,7 @@ struct VerifyHeadParams {
   const int32_t* n_nodes;  // [B]
   int max_nodes;
   int32_t* target;      // [cols_total]
-  bool streamed;        // streamed_weights (dma_tile.h)
+  bool streamed;        // streamed_weights (head_plan.h)
 };
 
 // the token of a column's best key; rows of the node table without a node get -1

@@ -22,11 +22,14 @@ int main() {
     AttnShape s = {0, 0};
     if (what == 'd') {  // cols D V f32 k
       if (plan_draft_head(p, d != 0, e)) printf("ranges %d %d\n", p.tile_cols, p.splits);
-      else if (!d && draft_stream_stages(a, b)) printf("stream %d %d\n", (a + 15) / 16, draft_stream_stages(a, b));
+      else if (!d && draft_stream_stages(a, b, c)) printf("stream %d %d\n", (a + 15) / 16, draft_stream_stages(a, b, c));
       else printf("tile %d 0\n", head_tile_cols(a) > 64 ? 64 : head_tile_cols(a));
     } else if (what == 'b') {  // cols D V f32
       if (plan_base_head(p, d != 0)) printf("ranges %d %d\n", p.tile_cols, p.splits);
       else printf("tile %d %d\n", head_tile_cols(a), a > kHeadColBlock ? 256 : 128);
+    } else if (what == 'l') {  // cols D V f32 ranges
+      const bool dma = dma_rows(c, b, d ? 4 : 2, e);
+      printf("%s %d 0\n", dma ? "dma" : "registers", a <= kHeadColBlock ? head_tile_cols(a) : dma ? head_wide_columns(c, a) : 128);
     } else if (what == 's') {  // columns, rows: floats for a draft head, for a base head
       printf("room %zu %zu\n", head_part_floats(a, b, kDraftPartFloats), head_part_floats(a, b, kHeadPartFloats));
     } else {  // B H nodes kv_cap dh; f32, rows as two bf16 numbers; a context for just these sequences and heads
@@ -65,6 +68,11 @@ def draft_head(cols, D, Vp1, dtype, k):
 def base_head(cols, D, V, dtype):
     """('ranges', tile columns, ranges) or ('tile', tile columns, rows)."""
     return ask([("b", cols, D, V, int("32" in str(dtype)))])[0]
+
+
+def head_loop(cols, D, V, dtype, ranges=1):
+    """('dma' or 'registers', columns of the base head's own tiles, 0): the tile loop that a head's tiles take."""
+    return ask([("l", cols, D, V, int("32" in str(dtype)), ranges)])[0]
 
 
 def head_room(cols, rows):

@@ -93,9 +93,25 @@ def test_head_cases_take_the_kernels_they_are_meant_for():
         assert launch_plans.draft_head(B * T, D, Vp1, "bf16", k)[0] == way
 
 
+def test_head_cases_take_the_loops_they_are_meant_for():
+    for elem, dtype in ((2, "bf16"), (4, "f32")):
+        for row in dma_tile.ROW_BYTES:
+            for cols in (7, 32, 50, 128):
+                assert launch_plans.base_head(cols, row // elem, 16500, dtype)[0] == "tile"
+                assert launch_plans.head_loop(cols, row // elem, 16500, dtype)[0] == "dma"
+            assert launch_plans.head_loop(200, row // elem, 16500, dtype)[:2] == ("dma", 128)
+            assert {launch_plans.head_loop(cols, row // elem, 16500, dtype)[:2] for cols in (520, 732)} == {("dma", 256)}
+            assert launch_plans.draft_head(21, row // elem, 16500, dtype, 4)[0] in ("tile", "stream")
+    assert launch_plans.head_loop(200, 65, 16500, "bf16")[:2] == ("registers", 128)  # rows that start anywhere
+    assert launch_plans.head_loop(50, 128, 16500, "bf16")[0] == "registers"  # rows of one step
+    assert launch_plans.head_loop(50, 512, 128, "bf16")[0] == "registers"  # a single row block
+    assert launch_plans.draft_head(64, 512, 128, "bf16", 4)[0] != "stream"
+
+
 def test_cases_of_single_steps_have_them():
     for dtype, cols, D, V in dma_tile.SINGLE_STEPS:
         way, _, ranges = launch_plans.base_head(cols, D, V, dtype)
+        assert launch_plans.head_loop(cols, D, V, dtype, ranges)[0] == "registers"
         assert way == "ranges" and ranges * 256 >= D * (4 if dtype == "f32" else 2)
 
 

@@ -43,7 +43,7 @@ struct CtcParams {
   int blocks;     // blocks of pairs
   // the pipelined recursions (null otherwise)
   unsigned long long* edge;  // [B][2][T][blocks]: what a block hands to the next one, 0: not there yet
-  int* wide;      // [B][T]: a log-probability of the frame is not for the recursion in doubles (1), in mantissas and exponents (2)
+  int* wide;      // [B][T]: byte 0: a log-probability of the frame is not for the recursion in doubles, byte 1: nor in mantissas and exponents
   int* ticket;
   float wide_below;
   double* logp;   // [B]: log2 P(Y | X)
@@ -171,8 +171,11 @@ __global__ __launch_bounds__(THREADS) void ctc_row_kernel(CtcParams p) {
     const float l = (zy[r] - lse) * kLog2e;
     if (j < L) out[j] = l;
     else if (j == L) out[p.Lmax] = l;  // this thread's spare slot fetched the blank
-    if (p.edge && j <= L && !(l >= kDpNarrow))  // cleared above
-      atomicOr(p.wide + (size_t)b * p.T + t, l < p.wide_below && l > -INFINITY ? 3 : 1);
+    if (p.edge && j <= L && !(l >= kDpNarrow)) {  // cleared above; by bytes, so that no thread's mark undoes another's
+      unsigned char* marks = (unsigned char*)(p.wide + (size_t)b * p.T + t);
+      marks[0] = 1;
+      if (l < p.wide_below && l > -INFINITY) marks[1] = 1;
+    }
   }
   if (g) {
     const float inv = 1.f / sum;
@@ -896,7 +899,7 @@ __global__ __launch_bounds__(dp_threads(WRITERS)) void ctc_dp_pipe_kernel(CtcPar
   }
   int wide = 0;
   for (int t = tid; t < Tb; t += dp_threads(WRITERS)) wide |= p.wide[(size_t)b * p.T + t];
-  if (__syncthreads_or(wide & 2)) ctc_block<kDpLog, WRITERS>(p, sh, directions, block, b, backward, L, Tb);
+  if (__syncthreads_or(wide & 0xff00)) ctc_block<kDpLog, WRITERS>(p, sh, directions, block, b, backward, L, Tb);
   else if (WRITERS == 2 || __syncthreads_or(wide)) ctc_block<kDpMantissa, WRITERS>(p, sh, directions, block, b, backward, L, Tb);
   else if constexpr (WRITERS == 4) ctc_block<kDpDouble, WRITERS>(p, sh, directions, block, b, backward, L, Tb);
 }

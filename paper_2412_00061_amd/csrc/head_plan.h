@@ -15,8 +15,9 @@
 //     6001  25.5 / 24.1 with two (not taken; the model sees 2 %).  With the merge left to ctc_collapse_tree, both calls together,
 //     4001 rows: 44.7 with a merge of its own, 47.4 with a deferred one, 39.1 with ranges - no reason for another line there,
 //     and a call takes the same way, to the same bits, whether the merge is deferred or not.
-// 590 calls drawn and in a grid, every plan timed: with this rule 0.75 of the time without ranges in the mean, none 2 % slower;
-// 8 % above the best plan of each.
+// The steps' times are those of the loop through registers (gemm_tile.h).  4098 calls drawn, every plan timed with the loops that run now:
+// with this rule 0.72 of the time without ranges in the mean, 18 more than 2 % slower than without (the worst 288 columns x 10360 rows of
+// 3328, 61.7 us against 45.4), 8.5 % above the best plan of each.
 #pragma once
 
 #include <stddef.h>
@@ -46,6 +47,8 @@ inline size_t head_part_floats(long long cols, int vocab_rows, size_t most) {
 //   8 columns of 4096, 8001 rows (66 MB): 23.9 / 28.8, 30.1 / 28.3     128 columns, 262 MB: 51.5 / 52.0, 58.0 / 52.2
 // Other rows share lines with their neighbours and with the next step, and nontemporal loads fetch those again: rows of 4104
 // elements, 16 columns 41.7 / 53.9, 50.2 / 55.0; 128 columns 56.8 / 65.6, 64.2 / 66.2.
+// 48 MB is a middle: where all else goes through in between, nontemporal loads are up to 7 % faster below it as well; 600 calls drawn, three
+// states in turn, are 0.9 to 3.6 % slower with them in the mean, up to 27 %.
 inline bool streamed_weights(long long bytes, long long row_bytes) { return row_bytes % 128 == 0 && bytes > (48LL << 20); }
 
 // Which loop a head's tiles take, in `splits` ranges of its hidden dimension: the one that loads straight into LDS (dma_tile.h), or the one

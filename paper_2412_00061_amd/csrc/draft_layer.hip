@@ -67,7 +67,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void layer_tile_kernel(LayerTilePa
   t.zeros = p.zeros; t.D = (t1 - t0) * kLtTripK; t.pitch = p.K; t.V = p.N; t.row_base = rb * SH::ROWS; t.streamed = p.streamed;
   f32x4 acc[SH::RT][SH::CTW];
   if constexpr (SH::DMA) dma_tile<SH, TileBf16>(t, LayerColumns{p.cols, p.plane_cols}, smem, acc);
-  else gemm_tile<4, SH, TileBf16, true>(t, LayerColumns{p.cols, p.plane_cols}, smem, acc);
+  else gemm_tile<4, SH, TileBf16>(t, LayerColumns{p.cols, p.plane_cols}, smem, acc);
   float* out = p.part + (size_t)split * p.cols * p.N;
 #pragma unroll
   for (int ct = 0; ct < SH::CTW; ct += 2) {
@@ -264,7 +264,7 @@ static int device_cus() {
 
 // rows x 16, 32 or 64 columns (twice as many tile columns); which one: layer_plan.h
 using LayerTile128x16 = DmaShape<8, 1, 2, 256, 4, 3>;
-using LayerTileShort = TileShape<8, 2, 128, 1>;  // through registers (layer_plan.h: through_registers)
+using LayerTileShort = TileShape<8, 2, 128, 1, true, true>;  // through registers (layer_plan.h: through_registers)
 using LayerTile256x16 = DmaShape<8, 2, 2, 128, 4, 4>;
 using LayerTile128x32 = DmaShape<4, 2, 2, 256, 3, 3>;
 using LayerTile192x32 = DmaShape<4, 3, 2, 128, 4, 4>;

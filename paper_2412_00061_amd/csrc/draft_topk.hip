@@ -513,10 +513,13 @@ template <typename EL>
 static hipError_t launch_tile(const LmHeadParams& p, hipStream_t stream) {
   // the narrowest tile that holds the columns: a wavefront without live columns would contract for nothing, which
   // float operands (a sixteenth of the bf16 matrix rate) cannot afford
-  const bool dma = dma_rows(p.Vp1, p.D, EL::ELEM);
-  if (p.BT <= 16) return dma ? launch_tile_shape<Dma128x16, EL>(p, stream) : launch_tile_shape<Tile128x16, EL>(p, stream);
-  if (p.BT <= 32) return dma ? launch_tile_shape<Dma128x32, EL>(p, stream) : launch_tile_shape<Tile128x32, EL>(p, stream);
-  return dma ? launch_tile_shape<Dma128x64, EL>(p, stream) : launch_tile_shape<Tile128x64, EL>(p, stream);
+  auto launch = [&](auto straight, auto tile) {
+    if (dma_rows(p.Vp1, p.D, EL::ELEM)) return launch_tile_shape<decltype(straight), EL>(p, stream);
+    return rows16(p.D, EL::ELEM) ? launch_tile_shape<Rows16<decltype(tile)>, EL>(p, stream) : launch_tile_shape<decltype(tile), EL>(p, stream);
+  };
+  if (p.BT <= 16) return launch(Dma128x16{}, Tile128x16{});
+  if (p.BT <= 32) return launch(Dma128x32{}, Tile128x32{});
+  return launch(Dma128x64{}, Tile128x64{});
 }
 
 static void launch_merge(const LmHeadParams& p, hipStream_t stream) {
@@ -567,7 +570,8 @@ static hipError_t allow_tile_lds() {
 }
 template <typename EL>
 static hipError_t allow_tile_lds_all() {
-  return allow_tile_lds<EL, Tile128x16, Tile128x32, Tile128x64, Dma128x16, Dma128x32, Dma128x64>();
+  return allow_tile_lds<EL, Tile128x16, Tile128x32, Tile128x64, Rows16<Tile128x16>, Rows16<Tile128x32>, Rows16<Tile128x64>, Dma128x16,
+                        Dma128x32, Dma128x64>();
 }
 
 // dynamic LDS limits of this file's kernels, on the current device

@@ -32,9 +32,12 @@ constexpr int kTileWaves = 8;
 
 __device__ __forceinline__ int clamp_int(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-template <int WR_, int CTW_, int STEPB_, int RT_ = 4>
+// ROWS16: rows start at multiples of 16 bytes, 256 of them within 32-bit offsets (rows16 in head_plan.h).  Otherwise they start at any element: the
+// same 16-byte loads, declared with the element's alignment, 64-bit offsets, and a row's end that has to be shifted into place.  119 rows of
+// 632 float cut into ranges 5.0 us so, 6.1 as rows that start anywhere.  STREAMED: of those, the weights by nontemporal loads.
+template <int WR_, int CTW_, int STEPB_, int RT_ = 4, bool ROWS16_ = false, bool STREAMED_ = false>
 struct TileShape {
-  static constexpr bool DMA = false;
+  static constexpr bool DMA = false, ROWS16 = ROWS16_, STREAMED = STREAMED_;
   static constexpr int WR = WR_, WC = kTileWaves / WR_;  // wavefront grid
   static constexpr int CTW = CTW_, RT = RT_;             // 16-column and 16-row MFMA tiles per wavefront
   static constexpr int STEPB = STEPB_;                   // bytes of a row per step
@@ -50,8 +53,10 @@ struct TileShape {
   static constexpr int KK = STEPB / 64;                  // k-blocks of 64 bytes per step
   static constexpr int HS_BYTES = HP * RPP * PITCH, BUF_BYTES = HS_BYTES + ROWS * PITCH;
   static constexpr int LDS_BYTES = 2 * BUF_BYTES;
-  static_assert(WR * WC == kTileWaves && ROWS % RPP == 0, "tile shape");
+  static_assert(WR * WC == kTileWaves && ROWS % RPP == 0 && (ROWS16 || !STREAMED), "tile shape");
 };
+template <typename SH>
+using Rows16 = TileShape<SH::WR, SH::CTW, SH::STEPB, SH::RT, true>;
 using Tile128x16 = TileShape<8, 1, 256, 1>;
 using Tile128x32 = TileShape<4, 1, 256, 2>;
 using Tile128x64 = TileShape<2, 1, 256>;
@@ -98,14 +103,15 @@ typedef __attribute__((address_space(1))) u32x4 GlobalU32x4;  // a pointer made 
 // acc[rt][ct][i]: row row_base + 16 (RT wr + rt) + 4 (lane >> 4) + i, column 16 CTW wc + 16 ct + (lane & 15),
 // wr = wave / WC, wc = wave % WC.
 // Every wavefront of the workgroup (8) must call it; it ends with a barrier after the last read of LDS.
-// STREAMED: rows on 16-byte boundaries, the weights by nontemporal loads.
-template <int DIST, typename SH, typename EL, bool STREAMED = false, typename COLUMNS>
+template <int DIST, typename SH, typename EL, typename COLUMNS>
 __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& columns, unsigned char* smem,
                                           f32x4 (&acc)[SH::RT][SH::CTW]) {
   constexpr int CTW = SH::CTW, RT = SH::RT, STEPB = SH::STEPB, PITCH = SH::PITCH, CPR = SH::CPR, RPP = SH::RPP;
   constexpr int WP = SH::WP, HP = SH::HP, KK = SH::KK;
   constexpr int WPK = (WP + KK - 1) / KK, HPK = (HP + KK - 1) / KK;  // pieces written to LDS per k-block of the step before
   constexpr int HS_BYTES = SH::HS_BYTES, BUF_BYTES = SH::BUF_BYTES;
+  constexpr bool ROWS16 = SH::ROWS16;
+  using Offset = std::conditional_t<ROWS16, unsigned int, size_t>;
   struct Packed16 { u32x4 v; } __attribute__((packed, aligned(EL::ELEM)));  // 16 bytes at an element's alignment
   typedef __attribute__((address_space(1))) Packed16 GlobalPacked16;
   constexpr int TRIP = DIST;    // steps per loop trip: stage and buffer static
@@ -136,15 +142,15 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
   const unsigned int lane_off = pchunk * 16;
   const uintptr_t w_addr = (uintptr_t)t.w + (size_t)row_base * pitch, h_addr = (uintptr_t)t.hidden;
   const uintptr_t z_addr = (uintptr_t)t.zeros;
-  size_t woff[WP], hoff[HP];
+  Offset woff[WP], hoff[HP];
   const int dst0 = prow * PITCH + pchunk * 16;
 #pragma unroll
   for (int u = 0; u < WP; ++u) {
     const int r = prow + RPP * u, last = t.V - 1 - row_base;
-    woff[u] = (size_t)(r < last ? r : last) * (size_t)pitch;  // the ragged last block re-reads the last row
+    woff[u] = (Offset)(r < last ? r : last) * (Offset)pitch;  // the ragged last block re-reads the last row
   }
 #pragma unroll
-  for (int u = 0; u < HP; ++u) hoff[u] = (size_t)columns(prow + RPP * u) * (size_t)pitch;
+  for (int u = 0; u < HP; ++u) hoff[u] = (Offset)columns(prow + RPP * u) * (Offset)pitch;
   // A request past the last step still issues its loads, so that every wait counts the same loads: it reads
   // a 256-byte block of zeros (in L2, no HBM traffic) and nothing computes from the result.
   u32x4 wreg[DIST][WP], hreg[DIST][HP];
@@ -152,19 +158,21 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
     constexpr int S = decltype(stage)::value;
     // address arithmetic in integers: a select between pointers would become a branch around each load
     const bool valid = step < total_steps;
-    const size_t mask = valid ? ~(size_t)0 : (size_t)0;
-    const size_t st = ((size_t)step * (size_t)STEPB) & mask;
+    const Offset mask = valid ? ~(Offset)0 : (Offset)0;
+    const Offset st = ((Offset)step * (Offset)STEPB) & mask;
     const uintptr_t hb = (valid ? h_addr : z_addr) + st, wb = (valid ? w_addr : z_addr) + st;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < HP; ++u) {
       const uintptr_t a = hb + ((hoff[u] & mask) + lane_off);
-      hreg[S][u] = ((const GlobalPacked16*)a)->v;
+      if constexpr (ROWS16) hreg[S][u] = *(const GlobalU32x4*)a;
+      else hreg[S][u] = ((const GlobalPacked16*)a)->v;
     }
 #pragma unroll
     for (int u = 0; u < WP; ++u) {
       const uintptr_t a = wb + ((woff[u] & mask) + lane_off);
-      if constexpr (STREAMED) wreg[S][u] = __builtin_nontemporal_load((const GlobalU32x4*)a);
+      if constexpr (SH::STREAMED) wreg[S][u] = __builtin_nontemporal_load((const GlobalU32x4*)a);
+      else if constexpr (ROWS16) wreg[S][u] = *(const GlobalU32x4*)a;
       else wreg[S][u] = ((const GlobalPacked16*)a)->v;
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -175,6 +183,8 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
   const int tail_bytes = (int)(row_bytes - (size_t)total_steps * STEPB);
   const int tail_n = clamp_int(tail_bytes - pchunk * 16, 0, 16);
   auto tail_load = [&](uintptr_t row) __attribute__((always_inline)) -> u32x4 {
+    if constexpr (ROWS16)  // whole chunks
+      return *(const GlobalU32x4*)(row + row_bytes - tail_bytes + (tail_n ? pchunk * 16 : 0));
     if (row_bytes >= 16) return ((const GlobalPacked16*)(row + (tail_n ? row_bytes - tail_bytes + pchunk * 16 + tail_n - 16 : 0)))->v;
     using E = std::conditional_t<EL::ELEM == 2, unsigned short, unsigned int>;
     constexpr int PER = 4 / EL::ELEM;  // elements per word
@@ -188,7 +198,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTileArgs& t, const COLUMNS& 
     return v;
   };
   auto tail_use = [&](u32x4 v) __attribute__((always_inline)) -> u32x4 {
-    if (row_bytes >= 16 && tail_n > 0 && tail_n < 16) {
+    if (!ROWS16 && row_bytes >= 16 && tail_n > 0 && tail_n < 16) {
       unsigned long long lo = ((unsigned long long)v[1] << 32) | v[0], hi = ((unsigned long long)v[3] << 32) | v[2];
       const int bits = 8 * (16 - tail_n);
       lo = bits >= 64 ? hi >> (bits & 63) : (lo >> bits) | (hi << (64 - bits));

@@ -56,9 +56,9 @@ inline bool streamed_weights(long long bytes, long long row_bytes) { return row_
 // 32-bit offsets.  With a single step of 256 bytes, whole rows or ranges, or a single row block there is nothing to pipeline, and the way
 // through registers is 0.3 to 0.5 us shorter: 100 rows of 64 float, 64 and 128 columns 6.3 us so, 6.7 straight into LDS alone; rows of 256
 // bf16, 2000 of them, 7 to 10 % faster so; 975 rows of 256 float in four ranges, 20 columns 6.7 and 7.1, 465 rows, 32 columns 10.9 and 11.4.
+inline bool rows16(int D, int elem) { return ((long long)D * elem) % 16 == 0 && (long long)D * elem * 256 < (1LL << 32); }
 inline bool dma_rows(long long V, int D, int elem, int splits = 1) {
-  const long long row = (long long)D * elem;
-  return row % 16 == 0 && row * 256 < (1LL << 32) && row > 256LL * splits && V > kHeadRowBlock;
+  return rows16(D, elem) && (long long)D * elem > 256LL * splits && V > kHeadRowBlock;
 }
 
 struct HeadPlan {

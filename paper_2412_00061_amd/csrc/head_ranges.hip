@@ -46,16 +46,17 @@ __global__ __launch_bounds__(64 * kTileWaves) void head_range_kernel(HeadRangePa
 }
 
 template <typename F>
-static hipError_t each_shape(bool dma, F&& f) {
-  hipError_t e = dma ? f(Dma128x16{}) : f(Tile128x16{});
-  if (e == hipSuccess) e = dma ? f(Dma128x32{}) : f(Tile128x32{});
-  if (e == hipSuccess) e = dma ? f(Dma128x64{}) : f(Tile128x64{});
-  if (e == hipSuccess) e = dma ? f(Dma128x128{}) : f(Tile128x128{});
+static hipError_t each_shape(bool dma, bool aligned, F&& f) {
+  auto one = [&](auto straight, auto tile) { return dma ? f(straight) : aligned ? f(Rows16<decltype(tile)>{}) : f(tile); };
+  hipError_t e = one(Dma128x16{}, Tile128x16{});
+  if (e == hipSuccess) e = one(Dma128x32{}, Tile128x32{});
+  if (e == hipSuccess) e = one(Dma128x64{}, Tile128x64{});
+  if (e == hipSuccess) e = one(Dma128x128{}, Tile128x128{});
   return e;
 }
 template <typename EL>
 static hipError_t launch_type(const HeadRangeParams& p, hipStream_t stream) {
-  return each_shape(dma_rows(p.V, p.D, EL::ELEM, p.splits), [&](auto shape) {
+  return each_shape(dma_rows(p.V, p.D, EL::ELEM, p.splits), rows16(p.D, EL::ELEM), [&](auto shape) {
     using SH = decltype(shape);
     if (SH::COLS != p.tile_cols) return hipSuccess;
     const long long units = (long long)p.row_blocks * p.splits, grid = (units + 7) / 8 * 8 * p.col_blocks;
@@ -68,17 +69,17 @@ hipError_t launch_head_ranges(const HeadRangeParams& p, bool f32, hipStream_t st
 }
 
 template <typename EL>
-static hipError_t allow_lds(bool dma) {
-  return each_shape(dma, [](auto shape) {
+static hipError_t allow_lds(bool dma, bool aligned) {
+  return each_shape(dma, aligned, [](auto shape) {
     using SH = decltype(shape);
     return hipFuncSetAttribute((const void*)head_range_kernel<SH, EL>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
   });
 }
 hipError_t prepare_head_ranges() {
   hipError_t e = hipSuccess;
-  for (const bool dma : {false, true}) {
-    if (e == hipSuccess) e = allow_lds<TileBf16>(dma);
-    if (e == hipSuccess) e = allow_lds<TileF32>(dma);
+  for (const int way : {0, 1, 2}) {
+    if (e == hipSuccess) e = allow_lds<TileBf16>(way == 2, way == 1);
+    if (e == hipSuccess) e = allow_lds<TileF32>(way == 2, way == 1);
   }
   return e;
 }

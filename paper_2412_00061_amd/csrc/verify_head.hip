@@ -256,7 +256,8 @@ static hipError_t for_shapes(F&& f) {
 }
 template <typename EL>
 static hipError_t allow_lds() {
-  return for_shapes<Tile128x16, Tile128x32, Tile128x64, Tile128x128, Tile256x128, Dma128x16, Dma128x32, Dma128x64, Dma128x128,
+  return for_shapes<Tile128x16, Tile128x32, Tile128x64, Tile128x128, Tile256x128, Rows16<Tile128x16>, Rows16<Tile128x32>,
+                    Rows16<Tile128x64>, Rows16<Tile128x128>, Rows16<Tile256x128>, Dma128x16, Dma128x32, Dma128x64, Dma128x128,
                     Dma256x128, Dma256x256>([](auto shape) {
     using SH = decltype(shape);
     return hipFuncSetAttribute((const void*)verify_head_kernel<SH, EL>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -283,13 +284,16 @@ static hipError_t launch_shape(VerifyHeadParams& p, hipStream_t stream) {
 template <typename EL>
 static hipError_t launch_head(VerifyHeadParams& p, hipStream_t stream) {
   const bool dma = dma_rows(p.V, p.D, EL::ELEM);
-  if (p.V <= kRowsPerBlock) return launch_shape<Tile128x16, EL>(p, stream);  // as many workgroups as the columns give
-  if (p.cols_total <= 16) return dma ? launch_shape<Dma128x16, EL>(p, stream) : launch_shape<Tile128x16, EL>(p, stream);
-  if (p.cols_total <= 32) return dma ? launch_shape<Dma128x32, EL>(p, stream) : launch_shape<Tile128x32, EL>(p, stream);
-  if (p.cols_total <= 64) return dma ? launch_shape<Dma128x64, EL>(p, stream) : launch_shape<Tile128x64, EL>(p, stream);
-  if (p.cols_total <= kVhCols) return dma ? launch_shape<Dma128x128, EL>(p, stream) : launch_shape<Tile128x128, EL>(p, stream);
-  if (!dma) return launch_shape<Tile256x128, EL>(p, stream);
-  return head_wide_columns(p.V, p.cols_total) == 256 ? launch_shape<Dma256x256, EL>(p, stream) : launch_shape<Dma256x128, EL>(p, stream);
+  auto launch = [&](auto straight, auto tile) {
+    if (dma) return launch_shape<decltype(straight), EL>(p, stream);
+    return rows16(p.D, EL::ELEM) ? launch_shape<Rows16<decltype(tile)>, EL>(p, stream) : launch_shape<decltype(tile), EL>(p, stream);
+  };
+  if (p.V <= kRowsPerBlock || p.cols_total <= 16) return launch(Dma128x16{}, Tile128x16{});  // (a single block: as many workgroups as the columns give)
+  if (p.cols_total <= 32) return launch(Dma128x32{}, Tile128x32{});
+  if (p.cols_total <= 64) return launch(Dma128x64{}, Tile128x64{});
+  if (p.cols_total <= kVhCols) return launch(Dma128x128{}, Tile128x128{});
+  if (dma && head_wide_columns(p.V, p.cols_total) == 256) return launch_shape<Dma256x256, EL>(p, stream);
+  return launch(Dma256x128{}, Tile256x128{});
 }
 
 }  // namespace ctcspec

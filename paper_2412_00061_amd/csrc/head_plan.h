@@ -134,8 +134,10 @@ inline bool plan_draft_head(HeadPlan& p, bool f32, int k) {
 }
 inline bool plan_base_head(HeadPlan& p, bool f32) {
   const int rows = p.cols > kHeadColBlock ? 256 : 128;
-  const double whole_us = p.V <= kHeadRowBlock ? head_whole_us(p.V, p.cols, p.D, f32, kHeadRowBlock, 16, 1.0) - kHeadMergeUs
-                                               : head_whole_us(p.V, p.cols, p.D, f32, rows, head_tile_cols(p.cols), 1.0);
+  // a single row block, one workgroup for 16 columns, is slower a step than many: float, 6 steps 8.2 us, 8.5 9.7, 16 14.0, 32 23.9 (in eight ranges
+  // 8.2, 8.7, 10.5, 10.9; by the others' step it was not cut at 8.5)
+  const double alone_us = f32 ? 5.3 + 0.61 * ((double)p.D * 4 / 256.0) : head_whole_us(p.V, p.cols, p.D, f32, kHeadRowBlock, 16, 1.0) - kHeadMergeUs;
+  const double whole_us = p.V <= kHeadRowBlock ? alone_us : head_whole_us(p.V, p.cols, p.D, f32, rows, head_tile_cols(p.cols), 1.0);
   return plan_head(p, f32, whole_us,
                    p.V > kHeadSlowRows ? 3.0 : 1.0, kHeadPartFloats);
 }

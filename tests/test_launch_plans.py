@@ -79,6 +79,8 @@ def test_heads_of_many_rows_take_the_ranges_only_for_a_clear_gain():
     assert launch_plans.draft_head(8, 4096, 4001, "bf16", 4)[0] == "ranges"
     assert launch_plans.draft_head(8, 4096, 8001, "bf16", 4)[0] == "stream"
     assert launch_plans.base_head(128, 4096, 6189, "bf16")[0] == "ranges"
+    assert {launch_plans.base_head(c, 544, 68, "f32")[0] for c in (6, 32, 120, 256)} == {"ranges"}  # a lone float row block
+    assert {launch_plans.base_head(c, 256, 68, "f32")[0] for c in (6, 32, 120, 512)} == {"tile"}
 
 
 # ---- which kernels the GPU tests' sizes reach ---------------------------------------------------------------------------
